@@ -1578,8 +1578,8 @@ extern "C" int ashrt_td_forward(const ashrt_plan* plan, const float* m, float* d
     return fail(ASHRT_E_NOT_IMPLEMENTED, "the time-domain pair takes regular traces only (plan has x_pos)");
   DeviceGuard dg(P.device);
   if (!dg.ok) return fail(ASHRT_E_HIP, "cannot select the plan's device");
-  TdArgs a{P.d_gd, P.d_pan, const_cast<float*>(m), d, mask, (long long)P.g[0].nd()};
-  HIP_TRY(launch_td(a, true, (hipStream_t)stream));
+  TdArgs a{P.d_gd, P.d_pan, const_cast<float*>(m), d, mask};
+  HIP_TRY(launch_td(a, true, P.g[0].z.nt, P.g[0].z.nx, P.g[0].z.P, (hipStream_t)stream));
   return ASHRT_OK;
 }
 
@@ -1590,8 +1590,8 @@ extern "C" int ashrt_td_adjoint(const ashrt_plan* plan, const float* d, float* m
     return fail(ASHRT_E_NOT_IMPLEMENTED, "the time-domain pair takes regular traces only (plan has x_pos)");
   DeviceGuard dg(P.device);
   if (!dg.ok) return fail(ASHRT_E_HIP, "cannot select the plan's device");
-  TdArgs a{P.d_gd, P.d_pan, m, const_cast<float*>(d), mask, (long long)P.g[0].nm()};
-  HIP_TRY(launch_td(a, false, (hipStream_t)stream));
+  TdArgs a{P.d_gd, P.d_pan, m, const_cast<float*>(d), mask};
+  HIP_TRY(launch_td(a, false, P.g[0].z.nt, P.g[0].z.nx, P.g[0].z.P, (hipStream_t)stream));
   return ASHRT_OK;
 }
 

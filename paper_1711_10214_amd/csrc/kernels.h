@@ -192,9 +192,8 @@ struct TdArgs {
   float* m;                // [P][nx][nt]
   float* d;                // [nx][nt]
   const uint8_t* tmask;    // [nx] or null
-  long long n_out;         // output samples of the launch
 };
-hipError_t launch_td(const TdArgs& a, bool forward, hipStream_t s);
+hipError_t launch_td(const TdArgs& a, bool forward, int nt, int nx, int npanel, hipStream_t s);
 
 // vec_kernels.hip
 hipError_t launch_vec_stats(const float* a, const float* b, long long n, double alpha, int p, double* out,

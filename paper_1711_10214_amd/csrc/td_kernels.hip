@@ -10,9 +10,20 @@
 // f = T - i0, samples outside [0, nt) dropped); the forward is its exact
 // transpose written as a gather: d[x][t] = sum_{p, xa, tau} hat(T - t)
 // m[p][xa][tau] with hat(s) = max(0, 1 - |s|), over the tau whose curve
-// passes within one sample of t (found from the inverse of T).  T is FP64
-// (its fractional part is the interpolation weight); sums are FP32.  No
-// atomics: every output is owned by one thread.
+// passes within one sample of t (found from the inverse of T).  T is good to
+// FP64 rounding of its square (its fractional part is the interpolation
+// weight); sums are FP32.  No atomics: every output has one owner.
+//
+// T depends on the panel and on the distance h = |x - xa| alone, so one set
+// of curve times and weights serves every (x, xa) pair at that distance: a
+// wave takes consecutive times of K neighbouring traces and walks the
+// distances, and at each one uses the weights for up to 2 K pairs (both
+// sides).  32 panels of 512 x 128 samples: forward 7140 -> 609 us, adjoint
+// 377 -> 222 us against one curve time per pair (and per candidate tau in
+// the forward).  The forward is bound by vector instructions (86 % of its
+// cycles), a third of them the pairs' products; waves near an apex, where
+// many tau fall on one time, take several rounds.  The adjoint waits on its
+// L1 loads.
 #include "kernels.h"
 
 namespace ashrt {
@@ -25,88 +36,261 @@ __device__ __forceinline__ double td_q(const PanelDev& P, const GatherDev& G) {
   return r * r / P.c2;
 }
 
-__device__ __forceinline__ bool td_h2(double q, int dxa, double* h2) {
-  if (q < 0.0) {  // v = 0: only the apex trace
-    *h2 = 0.0;
-    return dxa == 0;
-  }
-  *h2 = (double)dxa * (double)dxa * q;
-  return true;
+constexpr int kTdFwdWaves = 16;  // waves that share a forward tile's panels and distances
+constexpr int kTdAdjWaves = 4;   // adjoint waves per workgroup
+constexpr int kTdAdjX = 4;       // neighbouring apexes per adjoint wave
+
+// sqrt(T2) as its integer part i and fraction f in [0, 1], from the FP32 root
+// and its exact residual: sqrt(T2) = s + (T2 - s^2) / (2 s) to 1e-8.  T2 is
+// below 2^26 (callers test it against the record first).
+struct TdTime {
+  float i, f;
+};
+__device__ __forceinline__ TdTime td_time(double T2) {
+  const float s = __builtin_amdgcn_sqrtf((float)T2);
+  const double sd = (double)s;
+  const float r = (float)fma(-sd, sd, T2);
+  const float dl = 0.5f * r * __builtin_amdgcn_rcpf(fmaxf(s, 1e-30f));
+  TdTime o;
+  o.i = floorf(s);
+  o.f = (s - o.i) + dl;
+  const float c = o.f < 0.f ? -1.f : (o.f >= 1.f ? 1.f : 0.f);
+  o.i += c;
+  o.f -= c;
+  return o;
 }
 
-// Adjoint: one thread per model sample (p, xa, tau); loops over the traces.
-__global__ __launch_bounds__(256) void k_td_adjoint(TdArgs A) {
+// The pairs of a distance: bit k is trace x0 + k + h, bit K + k is
+// x0 + k - h (h = 0: only the first half), each set where the trace is in
+// the gather and live.  Wave-uniform.
+template <int K>
+__device__ __forceinline__ unsigned td_pairs(int x0, int h, int nx, const uint8_t* __restrict__ live) {
+  if (!live && h > 0 && x0 - h >= 0 && x0 + K - 1 + h < nx) return (1u << 2 * K) - 1;
+  const int lane = (int)threadIdx.x & 63, k = lane & (K - 1);
+  const int x = lane < K ? x0 + k + h : x0 + k - h;
+  bool ok = lane < 2 * K && x0 + k < nx && x >= 0 && x < nx && (h > 0 || lane < K);
+  if (ok && live) ok = live[x] != 0;
+  return __builtin_amdgcn_readfirstlane((unsigned)__ballot(ok));
+}
+
+// n consecutive floats at a 4-byte aligned address, as one load.
+template <int N>
+__device__ __forceinline__ void td_load(float (&v)[N], const float* row, unsigned off) {
+  __builtin_memcpy(v, reinterpret_cast<const char*>(row) + off, 4 * N);
+}
+
+// Adjoint: a wave owns 64 apex times of K neighbouring apexes of one panel.
+__global__ __launch_bounds__(64 * kTdAdjWaves) void k_td_adjoint(TdArgs A) {
+  constexpr int K = kTdAdjX;
   const GatherDev G = A.gd[0];
   const int nt = G.nt, nx = G.nx;
-  const long long n = (long long)G.npanel * nx * nt;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const int tau = (int)(i % nt);
-    const long long r = i / nt;
-    const int xa = (int)(r % nx), p = (int)(r / nx);
-    const PanelDev P = A.panels[G.panel_off + p];
-    const double q = td_q(P, G);
+  const int ntt = (nt + 63) / 64, nxt = (nx + K - 1) / K;
+  const int lane = (int)threadIdx.x & 63;
+  const int id = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kTdAdjWaves + (threadIdx.x >> 6)));
+  if (id >= G.npanel * nxt * ntt) return;
+  // early times see more traces inside the record: panels and apexes vary
+  // fastest, so that the longest waves start first
+  const int tb = id / (G.npanel * nxt), q2 = id - tb * (G.npanel * nxt), x0 = (q2 % nxt) * K, p = q2 / nxt;
+  const PanelDev P = A.panels[G.panel_off + p];
+  const double q = td_q(P, G);
+  const int tau = tb * 64 + lane;
+  float acc[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) acc[k] = 0.f;
+  if (P.n0 < nt) {
     const double t2 = (double)tau * (double)tau;
-    float acc = 0.f;
-    for (int x = 0; x < nx; ++x) {
-      if (A.tmask && A.tmask[x] == 0) continue;
-      double h2;
-      if (!td_h2(q, x - xa, &h2)) continue;
-      const double T = (double)P.n0 + sqrt(t2 + h2);
-      const double fl = floor(T);
-      if (fl >= (double)nt) continue;
-      const int i0 = (int)fl;
-      const float f = (float)(T - fl);
-      const float* dr = A.d + (long long)x * nt;
-      if (i0 >= 0) acc = fmaf(1.f - f, dr[i0], acc);
-      if (i0 + 1 >= 0 && i0 + 1 < nt) acc = fmaf(f, dr[i0 + 1], acc);
+    const double lim = (double)(nt - P.n0) * (double)(nt - P.n0);
+    const int hmax = q < 0.0 ? 0 : max(x0 + K - 1, nx - 1 - x0);
+    for (int h = 0; h <= hmax; ++h) {
+      const double T2 = q < 0.0 ? t2 : fma((double)h * (double)h, q, t2);
+      const bool on = tau < nt && T2 < lim;  // T < nt
+      if (!__any(on)) break;                 // T rises with h
+      const unsigned ok = td_pairs<K>(x0, h, nx, A.tmask);
+      if (!on) continue;
+      const TdTime T = td_time(T2);
+      const int i0 = P.n0 + (int)T.i;
+      const float f = T.f, e = 1.f - T.f;
+      const float* up = A.d + (long long)(x0 + h) * nt;  // rows x0 + h + k and x0 - h + k
+      const float* dn = A.d + (long long)(x0 - h) * nt;
+      if (i0 + 1 < nt) {
+        const unsigned off = 4u * (unsigned)i0;
+        if (ok == (1u << 2 * K) - 1) {
+          float v[2 * K][2];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            td_load(v[k], up + (long long)k * nt, off);
+            td_load(v[K + k], dn + (long long)k * nt, off);
+          }
+#pragma unroll
+          for (int k = 0; k < 2 * K; ++k) acc[k % K] = fmaf(f, v[k][1], fmaf(e, v[k][0], acc[k % K]));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 2 * K; ++k) {
+            if (ok >> k & 1) {
+              float v[2];
+              td_load(v, (k < K ? up : dn) + (long long)(k % K) * nt, off);
+              acc[k % K] = fmaf(f, v[1], fmaf(e, v[0], acc[k % K]));
+            }
+          }
+        }
+      } else if (i0 < nt) {  // the record's last sample
+#pragma unroll
+        for (int k = 0; k < 2 * K; ++k)
+          if (ok >> k & 1) acc[k % K] = fmaf(e, ((k < K ? up : dn) + (long long)(k % K) * nt)[i0], acc[k % K]);
+      }
     }
-    A.m[i] = acc;
+  }
+  if (tau < nt) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (x0 + k < nx) A.m[((long long)p * nx + x0 + k) * nt + tau] = acc[k];
   }
 }
 
-// Forward: one thread per data sample (x, t); loops over panels, apexes and
-// the apex times whose curve passes within one sample of t.
-__global__ __launch_bounds__(256) void k_td_forward(TdArgs A) {
-  const GatherDev G = A.gd[0];
+// One wave's share of a forward tile of 32 times: its two halves take two
+// neighbouring distances, and the (panel, distance pair) list is dealt to the
+// kTdFwdWaves waves in turn.  The tau of a curve within one sample of
+// t are a run of about 2 / slope (slope = dT / dtau <= 1): taken four at a
+// time, with weights computed once per (panel, distance), and one four-sample
+// load per pair.  SAFE leaves out samples without weight; otherwise they are
+// multiplied by zero, which differs only where a sample is not finite.
+template <int K, bool SAFE>
+__device__ __forceinline__ void td_forward_wave(const TdArgs& A, const GatherDev& G, int tb, int x0, int wave,
+                                                float (&acc)[K]) {
   const int nt = G.nt, nx = G.nx;
-  const long long n = (long long)nx * nt;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const int t = (int)(i % nt), x = (int)(i / nt);
-    float acc = 0.f;
-    if (!(A.tmask && A.tmask[x] == 0)) {
-      for (int p = 0; p < G.npanel; ++p) {
-        const PanelDev P = A.panels[G.panel_off + p];
-        const double q = td_q(P, G);
-        const double s1 = (double)(t - 1 - P.n0), s2 = (double)(t + 1 - P.n0);
-        if (s2 <= 0.0) continue;
-        const float* mp = A.m + (long long)p * nx * nt;
-        for (int xa = 0; xa < nx; ++xa) {
-          double h2;
-          if (!td_h2(q, x - xa, &h2)) continue;
-          if (s2 * s2 <= h2) continue;  // the curve starts after t + 1
-          // tau range whose T lies in (t - 1, t + 1), widened by one sample
-          const int lo = (s1 > 0.0 && s1 * s1 > h2) ? max(0, (int)floor(sqrt(s1 * s1 - h2)) - 1) : 0;
-          const int hi = min(nt - 1, (int)ceil(sqrt(s2 * s2 - h2)) + 1);
-          const float* mr = mp + (long long)xa * nt;
-          for (int tau = lo; tau <= hi; ++tau) {
-            const double T = (double)P.n0 + sqrt((double)tau * (double)tau + h2);
-            const double w = 1.0 - fabs(T - (double)t);
-            if (w > 0.0) acc = fmaf((float)w, mr[tau], acc);
+  const int half = ((int)threadIdx.x >> 5) & 1;
+  const int t = tb * 32 + ((int)threadIdx.x & 31);
+#pragma unroll
+  for (int k = 0; k < K; ++k) acc[k] = 0.f;
+  int turn = 0;
+  for (int p = 0; p < G.npanel; ++p) {
+    const PanelDev P = A.panels[G.panel_off + p];
+    if (P.n0 >= nt) continue;
+    const double q = td_q(P, G);
+    // last distance whose curve starts before the tile's last time + 1
+    const double smax = (double)(min(tb * 32 + 31, nt - 1) + 1 - P.n0);
+    if (smax <= 0.0) continue;
+    int hmax = q < 0.0 ? 0 : max(x0 + K - 1, nx - 1 - x0);
+    if (q > 0.0) hmax = (int)fmin((double)hmax, smax / sqrt(q) + 1.0);
+    hmax = __builtin_amdgcn_readfirstlane(hmax);
+    const float* __restrict__ mp = A.m + (long long)p * nx * nt;
+    const int ts = t - P.n0;
+    const double s0 = (double)ts, s1 = (double)(ts - 1), s2 = (double)(ts + 1);
+    const double s02 = s0 * s0, s12 = s1 * s1, s22 = s2 * s2;
+    const float tf = (float)ts;
+    int hh = wave - turn;
+    if (hh < 0) hh += kTdFwdWaves;
+    for (; 2 * hh <= hmax; hh += kTdFwdWaves) {
+      const int h = 2 * hh + half;
+      const double h2 = q < 0.0 ? 0.0 : (double)h * (double)h * q;
+      // tau with t - 1 < T < t + 1 lie in [lo, hi] (FP32 roots are good to
+      // 5e-4 here, the margins cover that)
+      const bool on = t < nt && ts >= 0 && s22 > h2 && h <= hmax;
+      int lo = 0, hi = -1;
+      if (on) {
+        const float a = (float)(s12 - h2);
+        lo = (ts > 1 && a > 0.f) ? max(0, (int)ceilf(__builtin_amdgcn_sqrtf(a) - 2e-3f)) : 0;
+        hi = min(nt - 1, (int)floorf(__builtin_amdgcn_sqrtf((float)(s22 - h2)) + 2e-3f));
+      }
+      // both halves' pairs all inside the gather
+      const bool inside = hh > 0 && x0 - 2 * hh - 1 >= 0 && x0 + K - 1 + 2 * hh + 1 < nx && nt >= 4;
+      const float* row = mp + (long long)x0 * nt;
+      const double base = h2 - s02;
+      for (int c = lo; c <= hi; c += 4) {
+        const int b = max(0, min(c, nt - 4));  // the load stays in the row (nt >= 4)
+        float w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // D = T - t = (T^2 - t^2) / (T + t), the numerator good to FP64
+          // rounding and the root only in the denominator: within 3e-7
+          const int tau = b + i;
+          const double td = (double)tau;
+          const float num = (float)fma(td, td, base);
+          const float T = __builtin_amdgcn_sqrtf(fmaxf(fmaf(tf, tf, num), 0.f));
+          const float D = num * __builtin_amdgcn_rcpf(fmaxf(T + tf, 1e-30f));
+          const float ww = 1.f - fabsf(D);
+          w[i] = (tau >= c && tau <= hi && ww > 0.f) ? ww : 0.f;
+        }
+        auto add = [&](float& a, const float (&v)[4]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) a = fmaf(w[i], SAFE && !(w[i] > 0.f) ? 0.f : v[i], a);
+        };
+        if (inside) {
+          // byte offsets from the tile's first row (4 nx nt < 2^31)
+          const unsigned up = 4u * (unsigned)(h * nt + b), dn = 4u * (unsigned)b - 4u * (unsigned)(h * nt);
+          float v[2 * K][4];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            td_load(v[k], row + (long long)k * nt, up);
+            td_load(v[K + k], mp + (long long)k * nt, dn + 4u * (unsigned)(x0 * nt));
+          }
+#pragma unroll
+          for (int k = 0; k < 2 * K; ++k) add(acc[k % K], v[k]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 2 * K; ++k) {
+            const int xa = k < K ? x0 + k + h : x0 + k - K - h;
+            if (x0 + k % K < nx && xa >= 0 && xa < nx && (h > 0 || k < K)) {
+              const float* mr = mp + (long long)xa * nt;
+              float v[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) v[i] = mr[min(b + i, nt - 1)];
+              add(acc[k % K], v);
+            }
           }
         }
       }
     }
-    A.d[i] = acc;
+    turn = (turn + hmax / 2 + 1) % kTdFwdWaves;
   }
 }
 
-hipError_t launch_td(const TdArgs& a, bool forward, hipStream_t s) {
-  const long long n = a.n_out;
-  long long g = (n + 255) / 256;
-  if (g > 65536) g = 65536;
-  if (g < 1) g = 1;
-  if (forward) hipLaunchKernelGGL(k_td_forward, dim3((unsigned)g), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_td_adjoint, dim3((unsigned)g), dim3(256), 0, s, a);
+// Forward: a workgroup owns 32 times of K neighbouring traces; its waves add
+// their sums through LDS in wave order.
+template <int K>
+__global__ __launch_bounds__(64 * kTdFwdWaves) void k_td_forward(TdArgs A) {
+  __shared__ float part[kTdFwdWaves][K][64];
+  const GatherDev G = A.gd[0];
+  const int nt = G.nt, nx = G.nx;
+  const int nxt = (nx + K - 1) / K;
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // late times see more traces: start them first
+  const int tb = (nt + 31) / 32 - 1 - (int)blockIdx.x / nxt, x0 = ((int)blockIdx.x % nxt) * K;
+  float acc[K];
+  td_forward_wave<K, false>(A, G, tb, x0, wave, acc);
+  bool fin = true;
+#pragma unroll
+  for (int k = 0; k < K; ++k) fin = fin && isfinite(acc[k]);
+  if (__any(!fin)) td_forward_wave<K, true>(A, G, tb, x0, wave, acc);
+#pragma unroll
+  for (int k = 0; k < K; ++k) part[wave][k][lane] = acc[k];
+  __syncthreads();
+  for (int i = threadIdx.x; i < K * 32; i += 64 * kTdFwdWaves) {
+    const int k = i >> 5, l = i & 31, x = x0 + k, tt = tb * 32 + l;
+    if (x >= nx || tt >= nt) continue;
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kTdFwdWaves; ++w) s += part[w][k][l] + part[w][k][l + 32];
+    A.d[(long long)x * nt + tt] = (A.tmask && A.tmask[x] == 0) ? 0.f : s;
+  }
+}
+
+hipError_t launch_td(const TdArgs& a, bool forward, int nt, int nx, int npanel, hipStream_t s) {
+  if (forward) {
+    // the widest tile (fewest weight evaluations per pair) that still gives
+    // every CU two workgroups, a late and an early one
+    const dim3 b(64 * kTdFwdWaves);
+    auto tiles = [&](int K) { return (unsigned)((nt + 31) / 32 * ((nx + K - 1) / K)); };
+    if (tiles(8) >= 512) hipLaunchKernelGGL(k_td_forward<8>, dim3(tiles(8)), b, 0, s, a);
+    else if (tiles(4) >= 512) hipLaunchKernelGGL(k_td_forward<4>, dim3(tiles(4)), b, 0, s, a);
+    else hipLaunchKernelGGL(k_td_forward<2>, dim3(tiles(2)), b, 0, s, a);
+  } else {
+    const long long waves = (long long)((nt + 63) / 64) * ((nx + kTdAdjX - 1) / kTdAdjX) * npanel;
+    if (waves > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_td_adjoint, dim3((unsigned)((waves + kTdAdjWaves - 1) / kTdAdjWaves)), dim3(64 * kTdAdjWaves),
+                       0, s, a);
+  }
   return hipGetLastError();
 }
 

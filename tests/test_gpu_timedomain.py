@@ -73,3 +73,44 @@ def test_time_domain_mask(A):
     fr = TD.forward(m, 0.004, 12.5, vel) * mask[:, None]
     ar = TD.adjoint(d * mask[:, None], 0.004, 12.5, vel)
     assert rel_l2(fg, fr) <= 1e-5 and rel_l2(ag, ar) <= 1e-5
+
+
+# Edges of the kernels' tiles (64 times, 8 traces, windows of 4 samples) and of
+# the record: shortest traces, shifts past the record, curves that leave it,
+# flat apexes (a far trace at a low velocity spans many apex times per sample).
+EDGES = [
+    (2, 2, [2000.0], [0]), (3, 5, [1500.0, 0.0], [1, 0]), (4, 8, [900.0], [0]), (5, 9, [3000.0], [2]),
+    (63, 7, [1500.0, 2500.0], [0, 70]), (64, 8, [400.0], [0]), (65, 17, [1500.0], [64]), (130, 33, [600.0, 5000.0], [3, 0]),
+]
+
+
+@pytest.mark.parametrize("nt,nx,vel,tau0", EDGES)
+def test_time_domain_tile_edges(A, nt, nx, vel, tau0):
+    """Same bar as above; dead traces hold NaN, which must not reach any output."""
+    import torch
+    print(f"[gpu] time-domain edges {nt} x {nx}", flush=True)
+    rng = np.random.default_rng(nt)
+    P = len(vel)
+    m = f32(rng.standard_normal((P, nx, nt)))
+    d = f32(rng.standard_normal((nx, nt)))
+    mask = np.ones(nx, np.uint8)
+    mask[1::3] = 0
+    plan = A.Plan(nt, nx, 0.004, 12.5, vel, tau0=tau0, ntp=max(8, 1 << (2 * nt - 1).bit_length()),
+                  nxp=max(4, 1 << (2 * nx - 1).bit_length()))
+    dn = np.where(mask[:, None] == 0, np.nan, d)
+    mk = torch.tensor(mask, device="cuda")
+    fg = plan.td_forward(torch.tensor(m, dtype=torch.float32, device="cuda"), mask=mk).cpu().numpy()
+    ag = plan.td_adjoint(torch.tensor(dn, dtype=torch.float32, device="cuda"), mask=mk).cpu().numpy()
+    fr, ar = np.zeros((nx, nt)), np.zeros_like(m)
+    d0 = d * mask[:, None]
+    for p, (v, n0) in enumerate(zip(vel, tau0)):
+        if v > 0:
+            fr += TD.forward(m[p:p + 1], 0.004, 12.5, [v], [n0])
+            ar[p] = TD.adjoint(d0, 0.004, 12.5, [v], [n0])[0]
+        elif n0 < nt:
+            fr[:, n0:] += m[p][:, :nt - n0]
+            ar[p][:, :nt - n0] = d0[:, n0:]
+    fr *= mask[:, None]
+    assert np.isfinite(fg).all() and np.isfinite(ag).all()
+    assert np.linalg.norm(fg - fr) <= 1e-5 * max(np.linalg.norm(fr), 1e-3)
+    assert np.linalg.norm(ag - ar) <= 1e-5 * max(np.linalg.norm(ar), 1e-3)
