@@ -311,7 +311,7 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost*
       while (rl < gh->nrows && c * c * (double)rl * (double)rl <= lim) ++rl;
     }
     gh->panels[p].rlive = rl;
-    gh->panels[p].pad_ = 0;
+    gh->panels[p].n0m = gh->panels[p].n0 % z.ntp;
   }
   gh->xpos.clear();
   if (d->x_pos) {

@@ -72,7 +72,7 @@ struct PanelDev {
   int n0;        // asymptote shift in samples
   int rlive;     // rows r < rlive can reach the band (c2 r^2 <= jhi^2); rows at and above it have
                  // no in-cone bin, so their x-spectra are neither written nor read
-  int pad_;
+  int n0m;       // n0 mod ntp: the phase ramp's step through the twiddle table
 };
 
 // Work item: gather g plus up to three stage-specific indices.

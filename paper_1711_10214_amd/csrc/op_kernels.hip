@@ -232,13 +232,20 @@ __device__ __forceinline__ Taps taps_of(int j, double a2, int Rrt) {
 }
 
 // Per data bin j of panel p: W_j s_p exp(-2 pi i j n0 / ntp), from the exact
-// FFT twiddle table in global memory (the ramp index is reduced with integer
-// arithmetic).
+// FFT twiddle table in global memory.  The ramp index is reduced with
+// integers: j and n0 mod ntp are below 2^12, so their product fits 32 bits,
+// and ntp is a compile-time constant where N > 0 (a mask or one mul_hi; the
+// 64-bit remainder by a runtime ntp was half of the bin loop's instructions
+// on shifted panels).
+template <int N>
 __device__ __forceinline__ float2 bin_factor(const GatherDev& G, const PanelDev& P,
                                              const float2* __restrict__ tw,
                                              const float* __restrict__ wav, int j) {
   float2 e = make_float2(1.0f, 0.0f);
-  if (P.n0 != 0) e = tw[G.tw_t_off + (int)(((long long)j * P.n0) % G.ntp)];
+  if (P.n0m != 0) {
+    const unsigned i = (unsigned)j * (unsigned)P.n0m;
+    e = tw[G.tw_t_off + (int)(N > 0 ? i % (unsigned)(N > 0 ? N : 1) : i % (unsigned)G.ntp)];
+  }
   float s = P.scale;
   if (G.wav_off >= 0) s *= wav[G.wav_off + j];
   return cscale(e, s);
@@ -1102,7 +1109,7 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
       if (r >= PD.rlive) continue;
       row_spectrum<N, NT>(buf, xrow + p * pstride, r, nt, ntp, twl);
     }
-    const bool plain = (PD.n0 == 0) && (G.wav_off < 0);
+    const bool plain = (PD.n0m == 0) && (G.wav_off < 0);
     // rows >= 1 map only bins inside the cone (the rest add zero); row 0's
     // l = 0 half covers the whole band
     const int jstart = (r != 0) ? max(jlo, cone_first_bin(PD.c2 * lup2)) : jlo;
@@ -1111,14 +1118,16 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
       const RowA2 aup = split_a2(PD.c2 * lup2);
       const RowA2 alo = split_a2(PD.c2 * llo2);
       const int jcone_lo = (r == 0) ? cone_first_bin(PD.c2 * llo2) : 0;
-      auto put = [&](int j, float2 au, float2 al) {
+      // (the factor is fetched before the taps are computed, so its load is
+      // in flight meanwhile)
+      auto factor = [&](int j) { return plain ? make_float2(0.f, 0.f) : bin_factor<N>(G, PD, A.tw, A.wav, j); };
+      auto put = [&](int j, float2 cj, float2 au, float2 al) {
         float2* du = acc + (j - jlo);
         float2* dl = acc + nband + (j - jlo);
         if (plain) {
           *du = cfma(PD.scale, au, *du);
           *dl = cfma(PD.scale, al, *dl);
         } else {
-          const float2 cj = bin_factor(G, PD, A.tw, A.wav, j);
           *du = cadd(*du, cmul(cj, au));
           *dl = cadd(*dl, cmul(cj, al));
         }
@@ -1130,6 +1139,7 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
 #pragma unroll 1
         for (int j = jstart + (int)threadIdx.x; j <= jhi; j += NT) {
           float2 au = make_float2(0.f, 0.f), al = make_float2(0.f, 0.f);
+          const float2 cj = factor(j);
           const Taps4 tu = taps4(j, aup);
           const float4* qu = P4 + (tu.k0 - 3);
 #pragma unroll
@@ -1138,12 +1148,13 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
             au = cfma(tu.w[t], make_float2(q.x, q.y), au);
             al = cfma(tu.w[t], make_float2(q.z, -q.w), al);
           }
-          put(j, au, al);
+          put(j, cj, au, al);
         }
       } else {
 #pragma unroll 1
         for (int j = jstart + (int)threadIdx.x; j <= jhi; j += NT) {
           float2 au = make_float2(0.f, 0.f), al = make_float2(0.f, 0.f);
+          const float2 cj = factor(j);
           const Taps4 tu = taps4(j, aup);
           const float4* qu = P4 + (tu.k0 - 3);
 #pragma unroll
@@ -1160,7 +1171,7 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
               al = cfma(tl.w[t], make_float2(q.z, -q.w), al);
             }
           }
-          put(j, au, al);
+          put(j, cj, au, al);
         }
       }
       __syncthreads();
@@ -1213,7 +1224,7 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
         *du = cfma(PD.scale, au, *du);
         *dl = cfma(PD.scale, al, *dl);
       } else {
-        const float2 cj = bin_factor(G, PD, A.tw, A.wav, j);
+        const float2 cj = bin_factor<N>(G, PD, A.tw, A.wav, j);
         *du = cadd(*du, cmul(cj, au));
         *dl = cadd(*dl, cmul(cj, al));
       }
@@ -1394,7 +1405,7 @@ struct ScatterBin {
   float2 e1, e2;
 };
 
-template <int RC>
+template <int N, int RC>
 __device__ __forceinline__ ScatterBin scatter_bin(const RowsArgs& A, const GatherDev& G, const PanelDev& PD,
                                                   bool plain, const float2* bufD, int r, int pass, double a2, int R,
                                                   int j, int jmax) {
@@ -1415,7 +1426,7 @@ __device__ __forceinline__ ScatterBin scatter_bin(const RowsArgs& A, const Gathe
     du = cscale(du, PD.scale);
     dl = cscale(dl, PD.scale);
   } else {
-    const float2 c = bin_factor(G, PD, A.tw, A.wav, j);
+    const float2 c = bin_factor<N>(G, PD, A.tw, A.wav, j);
     du = cmulconj(du, c);
     dl = cmulconj(dl, c);
   }
@@ -1442,7 +1453,7 @@ struct ScatterBin4 {
 // MODE 0: a row r >= 1; 1: row 0's l = 0 half (pass 0); 2: its Nyquist half
 // (pass 1).  A compile-time mode keeps the per-bin selection of the two
 // scattered values out of the bin loop.
-template <int MODE>
+template <int N, int MODE>
 __device__ __forceinline__ ScatterBin4 scatter_bin4(const RowsArgs& A, const GatherDev& G, const PanelDev& PD,
                                                     bool plain, const float2* bufD, RowA2 a, int j, int jmax) {
   ScatterBin4 b;
@@ -1451,6 +1462,8 @@ __device__ __forceinline__ ScatterBin4 scatter_bin4(const RowsArgs& A, const Gat
 #pragma unroll
   for (int t = 0; t < 8; ++t) b.w[t] = 0.f;
   if (j > jmax) return b;
+  // (fetched before the taps are computed, so its load is in flight meanwhile)
+  const float2 c = plain ? make_float2(0.f, 0.f) : bin_factor<N>(G, PD, A.tw, A.wav, j);
   const Taps4 T = taps4(j, a);
   b.k0 = T.k0;
 #pragma unroll
@@ -1462,7 +1475,6 @@ __device__ __forceinline__ ScatterBin4 scatter_bin4(const RowsArgs& A, const Gat
     du = cscale(du, PD.scale);
     dl = cscale(dl, PD.scale);
   } else {
-    const float2 c = bin_factor(G, PD, A.tw, A.wav, j);
     du = cmulconj(du, c);
     dl = cmulconj(dl, c);
   }
@@ -1515,7 +1527,7 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
   for (int p = chunk; p < P; p += G.nchunk) {
     const PanelDev PD = A.panels[G.panel_off + p];
     if (r >= PD.rlive) continue;
-    const bool plain = (PD.n0 == 0) && (G.wav_off < 0);
+    const bool plain = (PD.n0m == 0) && (G.wav_off < 0);
     for (int k = threadIdx.x; k < ntp / 2; k += NT) reinterpret_cast<float4*>(bufM)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     for (int pass = 0; pass < npass; ++pass) {
@@ -1551,11 +1563,11 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
               // read after its transform), taps past N/2-1 in bufM's own
               // padding (overwritten by its transform), and pair 0 is never
               // read by the inverse transform
-              const ScatterBin4 sa = scatter_bin4<MODE>(A, G, PD, plain, bufD, a, jb + sg * 64 + lane, jhi);
+              const ScatterBin4 sa = scatter_bin4<N, MODE>(A, G, PD, plain, bufD, a, jb + sg * 64 + lane, jhi);
               float4* qa = sa.k0 != kNoTap ? reinterpret_cast<float4*>(bufM) + (sa.k0 - 3) : sink;
               const int sg2 = sg + 2 * NW;
               if (sg2 < nseg) {
-                const ScatterBin4 sb = scatter_bin4<MODE>(A, G, PD, plain, bufD, a, jb + sg2 * 64 + lane, jhi);
+                const ScatterBin4 sb = scatter_bin4<N, MODE>(A, G, PD, plain, bufD, a, jb + sg2 * 64 + lane, jhi);
                 float4* qb = sb.k0 != kNoTap ? reinterpret_cast<float4*>(bufM) + (sb.k0 - 3) : sink;
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
@@ -1585,7 +1597,7 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
       for (int ph = 0; ph < 2; ++ph) {
 #pragma unroll 1
         for (int sg = 2 * wave + ph; sg < nseg; sg += 2 * NW) {
-          const ScatterBin sb = scatter_bin<RC>(A, G, PD, plain, bufD, r, pass, a2, R, jb + sg * 64 + lane, jhi);
+          const ScatterBin sb = scatter_bin<N, RC>(A, G, PD, plain, bufD, r, pass, a2, R, jb + sg * 64 + lane, jhi);
           if (sb.k0 != kNoTap) {
 #pragma unroll
             for (int t = -R + 1; t <= R; ++t) {
