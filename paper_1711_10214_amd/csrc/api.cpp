@@ -438,9 +438,9 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       const double a = -2.0 * M_PI * (double)m / (double)N;
       tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
     }
-    // pass table of the compile-time FFT: per pass (radix R, span Ns) the
-    // base twiddles exp(-2 pi i jm / (Ns R)), jm = 0..Ns-1 (the kernels take
-    // the powers r = 2..R-1 by recurrence)
+    // pass table of the compile-time FFT (layout in fft_tpl.h): (cos, tan) of
+    // the stage twiddles of every pass but the first
+    if (tw.size() & 1) tw.push_back(make_float2(0.f, 0.f));  // 16-byte records
     twp_off[i] = (int)tw.size();
     const int want = fft_tpl_twsize(N);
     if (want > 0) {
@@ -455,12 +455,33 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       for (int k = 0; k < L2 / 3; ++k) radices.push_back(8);
       if (L2 % 3 == 1) radices.push_back(2);
       if (L2 % 3 == 2) radices.push_back(4);
-      int Ns = 1;
+      int Ns = radices[0];
       const size_t start = tw.size();
-      for (int R : radices) {
-        for (int jm = 0; jm < Ns; ++jm) {
-          const double a = -2.0 * M_PI * (double)jm / ((double)Ns * (double)R);
-          tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
+      // exp(-2 pi i turns) as (cos, tan), the cosine kept off zero
+      auto put = [&](double turns) {
+        const double a = -2.0 * M_PI * turns;
+        double c = std::cos(a);
+        const double sn = std::sin(a);
+        if (std::fabs(c) < kTwMinCos) c = c < 0.0 ? -kTwMinCos : kTwMinCos;
+        tw.push_back(make_float2((float)c, (float)(sn / c)));
+      };
+      for (size_t k = 1; k < radices.size(); ++k) {
+        const int R = radices[k];
+        const double f = 1.0 / ((double)Ns * (double)R);  // w = exp(-2 pi i jm f)
+        if (R == 8) {
+          for (int jm = 0; jm < Ns; ++jm) {
+            put(4.0 * jm * f);
+            put(2.0 * jm * f);
+          }
+          for (int jm = 0; jm < Ns; ++jm) {
+            put(jm * f);
+            put(jm * f + 0.125);
+          }
+        } else {
+          for (int jm = 0; jm < Ns; ++jm) {
+            if (R == 4) put(2.0 * jm * f);
+            put(jm * f);
+          }
         }
         Ns *= R;
       }

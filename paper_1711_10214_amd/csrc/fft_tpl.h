@@ -8,11 +8,24 @@
 // Elements live at padded LDS positions fft_pad(i) = i + i/16 (one 8-byte
 // gap every 128 bytes), which makes the strided writes of the first passes
 // hit distinct banks; a padded transform occupies fft_padlen(N) slots.
-// Its twiddles w^(r jm), r = 1..R-1, jm = 0..Ns-1, come from one tabulated
-// w^jm per butterfly (FftPlan<N>::twoff(i) + jm in a per-length "pass
-// table" built in FP64 on the host) by complex multiplication.  Each pass
-// reads its butterflies into registers, waits at a barrier, and writes the
-// outputs in place.
+// Each pass reads its butterflies into registers, waits at a barrier, and
+// writes the outputs in place.
+//
+// Twiddles.  A radix-8 butterfly of v_r w^r is three radix-2 stages whose
+// twiddles are w^4, then w^2, then w and w e^(-i pi/4), up to a factor -i
+// that only swaps components.  Each is stored as (c, t) = (cos, tan) of its
+// angle, so a + w b and a - w b take six FMAs: u = b.x - t b.y, v = b.y + t b.x,
+// then a +- c (u, v).  That is 72 instructions per twiddled radix-8 butterfly
+// where multiplying the inputs by w .. w^7 formed by recurrence took 112, with
+// fewer roundings on the way (no powers, one FMA where a multiply and an add
+// were).  On the 1024 x 256, 32-panel gather the forward row kernel went from
+// 21.8 to 18.2 M vector instructions and from 48.3 to 45.4 us, the model x
+// kernels from 28.3 to 27.1 and 31.2 to 30.1 us, and the operator's error
+// against FP64 from 3.7e-7 to 2.2e-7.  Only the quarter turn has cos = 0; its cosine is stored as 2^-28
+// (kTwMinCos), 4e-9 off.  A per-length "pass table" built in FP64 on the host
+// holds, for pass i and jm = 0..Ns-1,
+//   radix 8: (w^4, w^2)[Ns], (w, w e^(-i pi/4))[Ns];  radix 4: (w^2, w)[Ns];
+//   radix 2: w[Ns]          (16-byte records, w = exp(-2 pi i jm / (Ns R))).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -83,17 +96,22 @@ struct FftPlan {
     for (int k = 0; k < i; ++k) s *= radix(k);
     return s;
   }
+  // float2 entries of pass i's twiddles (pass 0 has none) and their offset
+  static constexpr int twlen(int i) { return i == 0 ? 0 : ns(i) * (radix(i) / 2); }
   static constexpr int twoff(int i) {
     int o = 0;
-    for (int k = 0; k < i; ++k) o += ns(k);
+    for (int k = 0; k < i; ++k) o += twlen(k);
     return o;
   }
   static constexpr int twsize() { return twoff(npass); }
 };
 
-// LDS slots of the staged twiddles in front of an FFT buffer: the pass
-// table rounded up to an even count (what follows stays 16-byte aligned), or
-// the plain n-entry table of the generic runtime FFT (key 0).
+constexpr double kTwMinCos = 1.0 / 268435456.0;
+
+// LDS slots of the staged twiddles in front of an FFT buffer, an even count
+// (what follows stays 16-byte aligned): the pass table without its last pass
+// (whose twiddles depend on the thread alone and stay in registers), or the
+// plain n-entry table of the generic runtime FFT (key 0).
 inline __host__ __device__ int fft_tw_slots(int key, int n);
 
 // Host and device: pass-table length for a runtime N of a supported size
@@ -109,39 +127,111 @@ inline __host__ __device__ int fft_tpl_twsize(int n) {
   return 0;
 }
 
-inline __host__ __device__ int fft_tw_slots(int key, int n) { return key > 0 ? (fft_tpl_twsize(key) + 1) & ~1 : n; }
+inline __host__ __device__ int fft_tpl_twstaged(int n) {
+#define ASHRT_TW_CASE(S) \
+  if (n == S) return FftPlan<S>::twoff(FftPlan<S>::npass - 1);
+  ASHRT_TPL_SIZES(ASHRT_TW_CASE)
+#undef ASHRT_TW_CASE
+  return 0;
+}
 
+inline __host__ __device__ int fft_tw_slots(int key, int n) { return key > 0 ? (fft_tpl_twstaged(key) + 1) & ~1 : n; }
 
-template <bool INV>
+// One butterfly's twiddles as (cos, tan) pairs: radix 8 (w^4, w^2, w,
+// w e^(-i pi/4)), radix 4 (w^2, w), radix 2 (w).
+template <int R>
+struct Tw {
+  float2 w[R / 2];
+  __device__ __forceinline__ void load(const float2* tab, int Ns, int jm) {
+    if constexpr (R == 2) {
+      w[0] = tab[jm];
+    } else {
+#pragma unroll
+      for (int q = 0; q < R / 4; ++q) {
+        const float4 v = reinterpret_cast<const float4*>(tab)[q * Ns + jm];
+        w[2 * q] = make_float2(v.x, v.y);
+        w[2 * q + 1] = make_float2(v.z, v.w);
+      }
+    }
+  }
+};
+
+// (a, b) <- (a + z b, a - z b) with z = w (ROT = 0) or -i w (ROT = 1); the
+// inverse transform takes the conjugate of z.
+template <bool INV, int ROT>
+__device__ __forceinline__ void bfly_tw(float2& a, float2& b, float2 w) {
+  const float c = w.x, t = INV ? -w.y : w.y;
+  const float u = fmaf(-t, b.y, b.x), v = fmaf(t, b.x, b.y);
+  float2 p;
+  if constexpr (ROT == 0) p = make_float2(u, v);
+  else p = INV ? make_float2(-v, u) : make_float2(v, -u);
+  b = make_float2(fmaf(-c, p.x, a.x), fmaf(-c, p.y, a.y));
+  a = make_float2(fmaf(c, p.x, a.x), fmaf(c, p.y, a.y));
+}
+// The same for z = 1, -i (conjugated when INV), without multiplications.
+template <bool INV, int ROT>
+__device__ __forceinline__ void bfly_one(float2& a, float2& b) {
+  const float2 p = ROT == 0 ? b : (INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x));
+  b = csub(a, p);
+  a = cadd(a, p);
+}
+
+// In place: v_r -> DFT_R(v_r w^r).
+template <int R, bool INV>
+__device__ __forceinline__ void dft_tw(float2 (&v)[R], const Tw<R>& w) {
+  if constexpr (R == 2) {
+    bfly_tw<INV, 0>(v[0], v[1], w.w[0]);
+  } else if constexpr (R == 4) {
+    bfly_tw<INV, 0>(v[0], v[2], w.w[0]);
+    bfly_tw<INV, 0>(v[1], v[3], w.w[0]);
+    bfly_tw<INV, 0>(v[0], v[1], w.w[1]);  // outputs 0, 2
+    bfly_tw<INV, 1>(v[2], v[3], w.w[1]);  // outputs 1, 3
+    const float2 y2 = v[1];
+    v[1] = v[2];
+    v[2] = y2;
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bfly_tw<INV, 0>(v[r], v[r + 4], w.w[0]);
+    bfly_tw<INV, 0>(v[0], v[2], w.w[1]);  // even inputs: E0 (0), E2 (2)
+    bfly_tw<INV, 1>(v[4], v[6], w.w[1]);  //              E1 (4), E3 (6)
+    bfly_tw<INV, 0>(v[1], v[3], w.w[1]);  // odd inputs:  O0 (1), O2 (3)
+    bfly_tw<INV, 1>(v[5], v[7], w.w[1]);  //              O1 (5), O3 (7)
+    bfly_tw<INV, 0>(v[0], v[1], w.w[2]);  // outputs 0, 4
+    bfly_tw<INV, 1>(v[2], v[3], w.w[2]);  // outputs 2, 6
+    bfly_tw<INV, 0>(v[4], v[5], w.w[3]);  // outputs 1, 5
+    bfly_tw<INV, 1>(v[6], v[7], w.w[3]);  // outputs 3, 7
+    const float2 y4 = v[1], y1 = v[4], y6 = v[3], y3 = v[6];
+    v[1] = y1;
+    v[3] = y3;
+    v[4] = y4;
+    v[6] = y6;
+  }
+}
+
+// DFT of eight inputs, in place; HALF: inputs 4 .. 7 are zero (and not read).
+template <bool INV, bool HALF = false>
 __device__ __forceinline__ void dft8(float2 (&v)[8]) {
   constexpr float h = 0.70710678118654752440f;
-  float2 b[4], c[4];
+  if constexpr (HALF) {
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    b[n] = cadd(v[n], v[n + 4]);
-    c[n] = csub(v[n], v[n + 4]);
+    for (int r = 0; r < 4; ++r) v[r + 4] = v[r];
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bfly_one<INV, 0>(v[r], v[r + 4]);
   }
-  // c_n *= W^n, W = exp(-+2 pi i / 8)
-  {
-    const float2 x = c[1];
-    c[1] = INV ? make_float2(h * (x.x - x.y), h * (x.x + x.y)) : make_float2(h * (x.x + x.y), h * (x.y - x.x));
-    const float2 y = c[2];
-    c[2] = INV ? make_float2(-y.y, y.x) : make_float2(y.y, -y.x);
-    const float2 z = c[3];
-    c[3] = INV ? make_float2(-h * (z.x + z.y), h * (z.x - z.y)) : make_float2(h * (z.y - z.x), -h * (z.x + z.y));
-  }
-  float2 B[4] = {b[0], b[1], b[2], b[3]};
-  float2 C[4] = {c[0], c[1], c[2], c[3]};
-  butterfly<4, INV>(B);
-  butterfly<4, INV>(C);
-  v[0] = B[0];
-  v[2] = B[1];
-  v[4] = B[2];
-  v[6] = B[3];
-  v[1] = C[0];
-  v[3] = C[1];
-  v[5] = C[2];
-  v[7] = C[3];
+  bfly_one<INV, 0>(v[0], v[2]);
+  bfly_one<INV, 1>(v[4], v[6]);
+  bfly_one<INV, 0>(v[1], v[3]);
+  bfly_one<INV, 1>(v[5], v[7]);
+  bfly_one<INV, 0>(v[0], v[1]);
+  bfly_one<INV, 1>(v[2], v[3]);
+  bfly_tw<INV, 0>(v[4], v[5], make_float2(h, -1.f));
+  bfly_tw<INV, 1>(v[6], v[7], make_float2(h, -1.f));
+  const float2 y4 = v[1], y1 = v[4], y6 = v[3], y3 = v[6];
+  v[1] = y1;
+  v[3] = y3;
+  v[4] = y4;
+  v[6] = y6;
 }
 
 template <int R, bool INV>
@@ -149,6 +239,31 @@ __device__ __forceinline__ void dft_r(float2 (&v)[R]) {
   if constexpr (R == 8) dft8<INV>(v);
   else butterfly<R, INV>(v);
 }
+
+// The last pass's twiddles of a batch of NBN / N length-N transforms by NT
+// threads, for the butterflies threadIdx.x + i NT: they depend on the thread
+// alone, so a kernel loads them once and uses them for every transform.
+template <int N, int NT, int NBN = N>
+struct LastTw {
+  static constexpr int L = FftPlan<N>::npass - 1;
+  static constexpr int R = FftPlan<N>::radix(L);
+  static constexpr int B = N / R;
+  static constexpr int MAXB = (NBN / R + NT - 1) / NT;
+  static_assert(L >= 1 && FftPlan<N>::ns(L) == B, "the last pass spans N/R");
+  Tw<R> w[MAXB];
+  __device__ __forceinline__ void load(const float2* __restrict__ tab) {
+#pragma unroll
+    for (int i = 0; i < MAXB; ++i) w[i].load(tab + FftPlan<N>::twoff(L), B, (int)(threadIdx.x + i * NT) % B);
+  }
+  // Waits for the loads and keeps the values in registers: without this the
+  // compiler may load them again at every use.
+  __device__ __forceinline__ void pin() {
+#pragma unroll
+    for (int i = 0; i < MAXB; ++i)
+#pragma unroll
+      for (int q = 0; q < R / 2; ++q) asm volatile("" : "+v"(w[i].w[q].x), "+v"(w[i].w[q].y));
+  }
+};
 
 // Pair layout of a length-N spectrum whose bins 0 and N/2 are not needed:
 // pair k (1 <= k < N/2) holds bin k at float2 slot 2k and bin N-k at slot
@@ -174,8 +289,10 @@ __device__ __forceinline__ void pair_put(float2* buf, int o, float2 v) {
 // never read); IO = 4: outputs at index >= nvalid are dropped; IO = 0:
 // padded layout both ways.  Reads complete before the barrier and writes
 // follow it, so the layouts may share memory.
+// lw: the last pass's twiddles in registers.
 template <int N, int PASS, int NBN, bool INV, int NT = kThreads, int IO = 0>
-__device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const float2* twp, int nvalid = N) {
+__device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
+                                         const LastTw<N, NT, NBN>& lw) {
   using P = FftPlan<N>;
   constexpr int R = P::radix(PASS);
   constexpr int Ns = P::ns(PASS);
@@ -225,17 +342,13 @@ __device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const
         else v[i][r] = src[fft_pad(j + r * B)];
       }
       if constexpr (Ns > 1) {
-        // w^r by recurrence from the tabulated w = exp(-+2 pi i jm / (Ns R))
-        float2 w1 = twp[TW + jm];
-        if (INV) w1.y = -w1.y;
-        float2 w = w1;
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          v[i][r] = cmul(v[i][r], w);
-          if (r + 1 < R) w = cmul(w, w1);
-        }
+        Tw<R> w;
+        if constexpr (PASS == P::npass - 1) w = lw.w[i];
+        else w.load(twp + TW, Ns, jm);
+        dft_tw<R, INV>(v[i], w);
+      } else {
+        dft_r<R, INV>(v[i]);
       }
-      dft_r<R, INV>(v[i]);
       bq[i] = jq * Ns * R + jm;
       // padded layout: dst is the padded address of bq, and bq keeps only
       // its low four bits when the steps r Ns need them
@@ -289,7 +402,8 @@ __device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const
 // pass writes only indices < nvalid.
 template <int N, int PASS, int NBN, bool INV, int NT, bool PAIRS_IN = false, bool PAIRS_OUT = false,
           int END = FftPlan<N>::npass, bool MASK_IN = false, bool MASK_OUT = false>
-__device__ __forceinline__ void tpl_passes(float2* buf, int nb, int bstride, const float2* twp, int nvalid = N) {
+__device__ __forceinline__ void tpl_passes(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
+                                           const LastTw<N, NT, NBN>& lw) {
   if constexpr (PASS < END) {
     constexpr bool last = PASS == FftPlan<N>::npass - 1;
     constexpr int IO = (PAIRS_IN && PASS == 0)   ? 1
@@ -299,29 +413,26 @@ __device__ __forceinline__ void tpl_passes(float2* buf, int nb, int bstride, con
                                                  : 0;
     static_assert(!(PAIRS_IN && PAIRS_OUT && FftPlan<N>::npass == 1), "pair input and output need two passes");
     static_assert(!(MASK_IN && MASK_OUT && FftPlan<N>::npass == 1), "masked input and output need two passes");
-    tpl_pass<N, PASS, NBN, INV, NT, IO>(buf, nb, bstride, twp, nvalid);
-    tpl_passes<N, PASS + 1, NBN, INV, NT, PAIRS_IN, PAIRS_OUT, END, MASK_IN, MASK_OUT>(buf, nb, bstride, twp, nvalid);
+    tpl_pass<N, PASS, NBN, INV, NT, IO>(buf, nb, bstride, twp, nvalid, lw);
+    tpl_passes<N, PASS + 1, NBN, INV, NT, PAIRS_IN, PAIRS_OUT, END, MASK_IN, MASK_OUT>(buf, nb, bstride, twp, nvalid,
+                                                                                      lw);
   }
-}
-
-// Full transform(s); the caller places a barrier after filling buf.
-template <int N, int NBN, bool INV, int NT = kThreads>
-__device__ __forceinline__ void fft_tpl(float2* buf, int nb, int bstride, const float2* twp) {
-  tpl_passes<N, 0, NBN, INV, NT>(buf, nb, bstride, twp);
 }
 
 // Full transform(s) of inputs that are zero at index >= nvalid (MASK_IN:
 // those slots are never read, so they need not be filled) or of which only
 // outputs < nvalid are wanted (MASK_OUT: the others are not written).
 template <int N, int NBN, bool INV, bool MASK_IN, bool MASK_OUT, int NT = kThreads>
-__device__ __forceinline__ void fft_tpl_masked(float2* buf, int nb, int bstride, const float2* twp, int nvalid) {
-  tpl_passes<N, 0, NBN, INV, NT, false, false, FftPlan<N>::npass, MASK_IN, MASK_OUT>(buf, nb, bstride, twp, nvalid);
+__device__ __forceinline__ void fft_tpl_masked(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
+                                               const LastTw<N, NT, NBN>& lw) {
+  tpl_passes<N, 0, NBN, INV, NT, false, false, FftPlan<N>::npass, MASK_IN, MASK_OUT>(buf, nb, bstride, twp, nvalid,
+                                                                                    lw);
 }
 
 // One transform of length N whose output is left in the pair layout.
 template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_to_pairs(float2* buf, const float2* twp) {
-  tpl_passes<N, 0, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp);
+__device__ __forceinline__ void fft_tpl_to_pairs(float2* buf, const float2* twp, const LastTw<N, NT>& lw) {
+  tpl_passes<N, 0, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp, N, lw);
 }
 
 // First-pass inputs of a length-N transform held in registers: the
@@ -333,17 +444,21 @@ struct FftRegsIn {
   static constexpr int B = N / R;
   static constexpr int MAXB = (B + NT - 1) / NT;
   static_assert(FftPlan<N>::npass >= 2, "register input needs a later pass to write the pair layout");
+  // rows at most half as long as the transform (the default padding): inputs
+  // r >= R/2 of a radix-8 butterfly are zero, neither loaded nor added
+  static constexpr bool CAN_HALF = R == 8;
   float2 v[MAXB][R];
-  // x[t] = src[t] for t < nt, zero after
-  __device__ __forceinline__ void load(const float2* __restrict__ src, int nt) {
+  // x[t] = src[t] for t < nt, zero after (half: nt <= N/2, inputs r < R/2 only;
+  // wave-uniform)
+  __device__ __forceinline__ void load(const float2* __restrict__ src, int nt, bool half) {
     const int tid = pass_tid();
 #pragma unroll
-    for (int i = 0; i < MAXB; ++i) {
-      const int id = tid + i * NT;
+    for (int r = 0; r < R; ++r) {
+      if (CAN_HALF && r == R / 2 && half) return;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int t = id + r * B;
-        v[i][r] = ((B % NT == 0 || id < B) && t < nt) ? src[t] : make_float2(0.f, 0.f);
+      for (int i = 0; i < MAXB; ++i) {
+        const int t = tid + i * NT + r * B;
+        v[i][r] = ((B % NT == 0 || tid + i * NT < B) && t < nt) ? src[t] : make_float2(0.f, 0.f);
       }
     }
   }
@@ -353,21 +468,26 @@ struct FftRegsIn {
 // there: its span is 1) and whose output is left in the pair layout, in two
 // calls: regs_pass0 (the caller must have finished every read of buf; the
 // registers are free again when it returns) and rest_to_pairs.
-template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, FftRegsIn<N, NT>& in) {
+template <int N, bool INV, int NT, bool HALF = false>
+__device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, const FftRegsIn<N, NT>& in) {
   using I = FftRegsIn<N, NT>;
   const int tid = pass_tid();
 #pragma unroll
   for (int i = 0; i < I::MAXB; ++i) {
     const int id = tid + i * NT;
     if (I::B % NT == 0 || id < I::B) {
-      dft_r<I::R, INV>(in.v[i]);
+      float2 v[I::R];
+#pragma unroll
+      for (int r = 0; r < I::R; ++r)
+        if (!HALF || r < I::R / 2) v[r] = in.v[i][r];
+      if constexpr (HALF) dft8<INV, true>(v);
+      else dft_r<I::R, INV>(v);
       constexpr bool LIN = pad_linear(1, I::R, I::R, 1);
       const int p0 = fft_pad(id * I::R), lo = (id * I::R) & 15;
 #pragma unroll
       for (int r = 0; r < I::R; ++r) {
-        if constexpr (LIN) buf[p0 + r] = in.v[i][r];
-        else buf[pad_step(p0, lo, r)] = in.v[i][r];
+        if constexpr (LIN) buf[p0 + r] = v[r];
+        else buf[pad_step(p0, lo, r)] = v[r];
       }
     }
   }
@@ -375,8 +495,8 @@ __device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, FftRegsIn<N, NT>
 }
 
 template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_rest_to_pairs(float2* buf, const float2* twp) {
-  tpl_passes<N, 1, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp);
+__device__ __forceinline__ void fft_tpl_rest_to_pairs(float2* buf, const float2* twp, const LastTw<N, NT>& lw) {
+  tpl_passes<N, 1, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp, N, lw);
 }
 
 // Outputs of a length-N transform's last pass held in registers: the
@@ -398,12 +518,11 @@ struct FftRegsOut {
 // registers; buf may be reused once every thread has passed a barrier after
 // this returns.
 template <int N, bool INV, int NT, int FIRST, bool PAIRS_IN>
-__device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2* twp, FftRegsOut<N, NT>& out) {
+__device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2* twp, const LastTw<N, NT>& lw,
+                                                       FftRegsOut<N, NT>& out) {
   using O = FftRegsOut<N, NT>;
-  using P = FftPlan<N>;
   static_assert(!PAIRS_IN || FIRST == 0, "only the first pass reads pairs");
-  tpl_passes<N, FIRST, N, INV, NT, PAIRS_IN, false, O::L>(buf, 1, fft_padlen(N), twp);
-  constexpr int TW = P::twoff(O::L);
+  tpl_passes<N, FIRST, N, INV, NT, PAIRS_IN, false, O::L>(buf, 1, fft_padlen(N), twp, N, lw);
   const int tid = pass_tid();
 #pragma unroll
   for (int i = 0; i < O::MAXB; ++i) {
@@ -413,15 +532,7 @@ __device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2
       const float2* s0 = buf + fft_pad(id);
 #pragma unroll
       for (int r = 0; r < O::R; ++r) out.v[i][r] = LIN ? s0[fft_pad(r * O::B)] : buf[fft_pad(id + r * O::B)];
-      float2 w1 = twp[TW + id];
-      if (INV) w1.y = -w1.y;
-      float2 w = w1;
-#pragma unroll
-      for (int r = 1; r < O::R; ++r) {
-        out.v[i][r] = cmul(out.v[i][r], w);
-        if (r + 1 < O::R) w = cmul(w, w1);
-      }
-      dft_r<O::R, INV>(out.v[i]);
+      dft_tw<O::R, INV>(out.v[i], lw.w[i]);
     }
   }
 }
@@ -429,15 +540,9 @@ __device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2
 // Transform whose input is read from the pair layout (bins 0 and N/2 taken
 // as zero) and whose last pass leaves its outputs in registers.
 template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_from_pairs_to_regs(float2* buf, const float2* twp, FftRegsOut<N, NT>& out) {
-  fft_tpl_passes_to_regs<N, INV, NT, 0, true>(buf, twp, out);
-}
-
-// One transform of length N whose input is read from the pair layout (bins
-// 0 and N/2 taken as zero); the output is in the padded layout.
-template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_from_pairs(float2* buf, const float2* twp) {
-  tpl_passes<N, 0, N, INV, NT, true, false>(buf, 1, fft_padlen(N), twp);
+__device__ __forceinline__ void fft_tpl_from_pairs_to_regs(float2* buf, const float2* twp, const LastTw<N, NT>& lw,
+                                                           FftRegsOut<N, NT>& out) {
+  fft_tpl_passes_to_regs<N, INV, NT, 0, true>(buf, twp, lw, out);
 }
 
 }  // namespace ashrt

@@ -252,18 +252,30 @@ __device__ __forceinline__ float2 bin_factor(const GatherDev& G, const PanelDev&
 }
 
 // ------------------------------------------------------------ FFT dispatch
-// Copy the twiddles an FFT of length n needs into LDS (pass table for the
-// compile-time lengths, plain table otherwise).  No barrier.
+// Copy the twiddles an FFT of length n needs into LDS (pass table without
+// its last pass for the compile-time lengths, plain table otherwise).  No
+// barrier.
 template <int N, int NT = kThreads>
 __device__ __forceinline__ void stage_twiddles(float2* dst, const float2* __restrict__ tw, int plain_off,
                                                int pass_off, int n) {
   if constexpr (N > 0) {
-    constexpr int ntw = FftPlan<N>::twsize();
+    constexpr int ntw = FftPlan<N>::twoff(FftPlan<N>::npass - 1);
     for (int i = threadIdx.x; i < ntw; i += NT) dst[i] = tw[pass_off + i];
   } else {
     for (int i = threadIdx.x; i < n; i += NT) dst[i] = tw[plain_off + i];
   }
 }
+
+// Last-pass twiddles of a row transform or of an x-transform batch (nothing
+// for generic lengths).
+struct NoTw {
+  __device__ __forceinline__ void load(const float2*) {}
+  __device__ __forceinline__ void pin() {}
+};
+template <int N, int NT>
+using RowTw = std::conditional_t<(N > 0), LastTw<(N > 0 ? N : 512), NT>, NoTw>;
+template <int N>
+using XTw = std::conditional_t<(N > 0), LastTw<(N > 0 ? N : 512), kThreads, kXfftBatch>, NoTw>;
 
 // Batched x-axis FFTs of a tile: nb transforms of length n at stride
 // bstride, run in groups of at most kXfftBatch points per call (bounded
@@ -271,12 +283,13 @@ __device__ __forceinline__ void stage_twiddles(float2* dst, const float2* __rest
 // Compile-time lengths: the forward reads only the nx trace slots (the pad
 // to nxp is zero and never filled), the inverse writes only the nx traces.
 template <int N, bool INV>
-__device__ __forceinline__ void xfft_tile(float2* buf, int n, int nb, int bstride, const float2* twl, int nx) {
+__device__ __forceinline__ void xfft_tile(float2* buf, int n, int nb, int bstride, const float2* twl, int nx,
+                                          const XTw<N>& lw) {
   if constexpr (N > 0) {
     static_assert(N <= kXfftBatch, "compile-time x-FFT longer than one batch");
     constexpr int per = kXfftBatch / N;
     for (int b0 = 0; b0 < nb; b0 += per)
-      fft_tpl_masked<N, kXfftBatch, INV, !INV, INV>(buf + b0 * bstride, min(per, nb - b0), bstride, twl, nx);
+      fft_tpl_masked<N, kXfftBatch, INV, !INV, INV>(buf + b0 * bstride, min(per, nb - b0), bstride, twl, nx, lw);
   } else {
     // generic: n <= 4096 = kXfftGenericBatch, so per >= 1
     const int per = max(1, kXfftGenericBatch / n);
@@ -476,7 +489,8 @@ __device__ __forceinline__ int xcd_item(int b, int n) {
 // ------------------------------------------------------------ x-direction RFFT
 template <int NX>
 __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
-  extern __shared__ float2 lds[];
+  extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ float s_alpha;
   __shared__ float s_ab[2];
   __shared__ double s_red[kThreads / 64];
@@ -541,6 +555,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
     float2* twl = lds;                          // x twiddles
     float2* buf = lds + fft_tw_slots(NX, nxp);  // T/2 packed column pairs, odd slot stride bs
     stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
+    XTw<NX> lw;
+    lw.load(A.tw + G.twp_x_off);
     const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
     const float* __restrict__ src = A.src + fbase;
     const float* __restrict__ mul = A.mul ? A.mul + fbase : nullptr;
@@ -684,7 +700,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
       __syncthreads();
       continue;
     }
-    xfft_tile<NX, false>(buf, nxp, half, bs, twl, nx);
+    lw.pin();
+    xfft_tile<NX, false>(buf, nxp, half, bs, twl, nx, lw);
 
     // column pair i holds the packed spectra of columns t0 + 2i (real part)
     // and t0 + 2i + 1 (imaginary part); both outputs of a row are written
@@ -724,7 +741,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
 // ------------------------------------------------------------ x-direction C2R
 template <int NX>
 __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
-  extern __shared__ float2 lds[];
+  extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ double sh[kThreads / 64];
   for (int it0 = blockIdx.x; it0 < A.nitems; it0 += gridDim.x) {
     const int it = (int)gridDim.x == A.nitems ? xcd_item(it0, A.nitems) : it0;
@@ -777,6 +795,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
       continue;
     }
     stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
+    XTw<NX> lw;
+    lw.load(A.tw + G.twp_x_off);
 
     const UDiv dh(half);
     const bool even = (nt & 1) == 0;
@@ -812,7 +832,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
       }
     }
     __syncthreads();
-    xfft_tile<NX, true>(buf, nxp, half, bs, twl, nx);
+    lw.pin();
+    xfft_tile<NX, true>(buf, nxp, half, bs, twl, nx, lw);
 
     const float inv = 1.0f / (float)nxp;
     const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
@@ -976,25 +997,15 @@ __device__ __forceinline__ void pairs_to_natural(float2* buf, int n) {
 // (the +l and -l spectra); row 0 separates the packed kx = 0 / Nyquist
 // spectra so that the same reading gives them.
 template <int N, int NT>
-__device__ __forceinline__ void row_spectrum_lds(float2* buf, int r, int ntp, const float2* twl);
-
-template <int N, int NT>
-__device__ __forceinline__ void row_spectrum(float2* buf, const float2* __restrict__ src, int r, int nt,
-                                             int ntp, const float2* twl) {
-  for (int t = threadIdx.x; t < ntp; t += NT) buf[px<N>(t)] = (t < nt) ? src[t] : make_float2(0.f, 0.f);
-  row_spectrum_lds<N, NT>(buf, r, ntp, twl);
-}
-
-// Forward time FFT of the row held in buf (natural order, zero-padded to
-// ntp), leaving the pair layout described above.
-template <int N, int NT>
 __device__ __forceinline__ void row0_separate(float2* buf, int ntp);
 
 template <int N, int NT>
-__device__ __forceinline__ void row_spectrum_lds(float2* buf, int r, int ntp, const float2* twl) {
+__device__ __forceinline__ void row_spectrum(float2* buf, const float2* __restrict__ src, int r, int nt,
+                                             int ntp, const float2* twl, const RowTw<N, NT>& lw) {
+  for (int t = threadIdx.x; t < ntp; t += NT) buf[px<N>(t)] = (t < nt) ? src[t] : make_float2(0.f, 0.f);
   __syncthreads();
   if constexpr (N > 0) {
-    fft_tpl_to_pairs<N, false, NT>(buf, twl);
+    fft_tpl_to_pairs<N, false, NT>(buf, twl, lw);
   } else {
     fft_lds<NT, kRowMaxN, false>(buf, ntp, 1, ntp, twl);
     natural_to_pairs<NT>(buf, ntp);
@@ -1017,24 +1028,6 @@ __device__ __forceinline__ void row0_separate(float2* buf, int ntp) {
       P[k] = make_float4(m0.x, m0.y, m1.x, -m1.y);
     }
     __syncthreads();
-  }
-}
-
-template <int N, int NT>
-__device__ __forceinline__ void row_inverse(float2* buf, int ntp, const float2* twl) {
-  if constexpr (N > 0) fft_tpl<N, N, true, NT>(buf, 1, fft_padlen(N), twl);
-  else fft_lds<NT, kRowMaxN, true>(buf, ntp, 1, ntp, twl);
-}
-
-// Inverse time FFT of a spectrum held in the pair layout (bins 0 and ntp/2
-// zero); the output is in the transform's usual layout.
-template <int N, int NT>
-__device__ __forceinline__ void row_inverse_from_pairs(float2* buf, int ntp, const float2* twl) {
-  if constexpr (N > 0) {
-    fft_tpl_from_pairs<N, true, NT>(buf, twl);
-  } else {
-    pairs_to_natural<NT>(buf, ntp);
-    fft_lds<NT, kRowMaxN, true>(buf, ntp, 1, ntp, twl);
   }
 }
 
@@ -1065,6 +1058,9 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   // counts are even)
   const float4* P4 = reinterpret_cast<const float4*>(buf);
   stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  RowTw<N, NT> lw;
+  lw.load(A.tw + G.twp_t_off);
+  lw.pin();
   for (int i = threadIdx.x; i < 2 * nband; i += NT) acc[i] = make_float2(0.f, 0.f);
   if constexpr (N > 0) {
     if ((int)threadIdx.x < kMapGuardSlots) buf[(int)threadIdx.x - kMapGuardSlots] = make_float2(0.f, 0.f);
@@ -1080,12 +1076,14 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   // is transformed and mapped (the first FFT pass takes it straight from
   // registers), and the panel constants one panel further ahead, so that the
   // liveness of the row to load is known without a wait
-  FftRegsIn<(N > 0 ? N : kRowMaxN), NT> pf;
+  using In = FftRegsIn<(N > 0 ? N : kRowMaxN), NT>;
+  In pf;
+  const bool half = In::CAN_HALF && 2 * nt <= ntp;
   PanelDev pdc, pdn;  // constants of the panel whose row is in pf, and of the one after
   if constexpr (N > 0) {
     if (chunk < P) {
       pdc = A.panels[G.panel_off + chunk];
-      if (r < pdc.rlive) pf.load(xrow + chunk * pstride, nt);
+      if (r < pdc.rlive) pf.load(xrow + chunk * pstride, nt, half);
       if (chunk + S < P) pdn = A.panels[G.panel_off + chunk + S];
     }
   }
@@ -1095,19 +1093,22 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
     if constexpr (N > 0) {
       PD = pdc;
       const bool live = r < PD.rlive;
-      if (live) fft_tpl_regs_pass0<N, false, NT>(buf, pf);
+      if (live) {
+        if (half) fft_tpl_regs_pass0<N, false, NT, In::CAN_HALF>(buf, pf);
+        else fft_tpl_regs_pass0<N, false, NT>(buf, pf);
+      }
       if (p + S < P) {
         pdc = pdn;
-        if (r < pdc.rlive) pf.load(xrow + (p + S) * pstride, nt);
+        if (r < pdc.rlive) pf.load(xrow + (p + S) * pstride, nt, half);
         if (p + 2 * S < P) pdn = A.panels[G.panel_off + p + 2 * S];
       }
       if (!live) continue;
-      fft_tpl_rest_to_pairs<N, false, NT>(buf, twl);
+      fft_tpl_rest_to_pairs<N, false, NT>(buf, twl, lw);
       if (r == 0) row0_separate<N, NT>(buf, ntp);
     } else {
       PD = A.panels[G.panel_off + p];
       if (r >= PD.rlive) continue;
-      row_spectrum<N, NT>(buf, xrow + p * pstride, r, nt, ntp, twl);
+      row_spectrum<N, NT>(buf, xrow + p * pstride, r, nt, ntp, twl, lw);
     }
     const bool plain = (PD.n0m == 0) && (G.wav_off < 0);
     // rows >= 1 map only bins inside the cone (the rest add zero); row 0's
@@ -1263,6 +1264,8 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
   float2* twl = lds;
   float2* buf = lds + fft_tw_slots(N, ntp);
   stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  RowTw<N, NT> lw;
+  lw.load(A.tw + G.twp_t_off);
   // time-spectrum bin k of the row: the chunk sums, Hermitian completion.
   // Branch-free (bins outside the band read the band's first entry and are
   // zeroed by a select), so the loads of all of a thread's bins can be in
@@ -1341,7 +1344,7 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
     fft_tpl_regs_pass0<N, true, NT>(buf, in);
     using O = FftRegsOut<N, NT>;
     O o;
-    fft_tpl_passes_to_regs<N, true, NT, 1, false>(buf, twl, o);
+    fft_tpl_passes_to_regs<N, true, NT, 1, false>(buf, twl, lw, o);
 #pragma unroll
     for (int i = 0; i < O::MAXB; ++i) {
       const int id = (int)threadIdx.x + i * NT;
@@ -1354,7 +1357,7 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
   } else {
     for (int k = threadIdx.x; k < ntp; k += NT) buf[px<N>(k)] = bin(k);
     __syncthreads();
-    row_inverse<N, NT>(buf, ntp, twl);
+    fft_lds<NT, kRowMaxN, true>(buf, ntp, 1, ntp, twl);
     for (int t = threadIdx.x; t < nt; t += NT) dst[t] = cscale(buf[px<N>(t)], inv);
   }
   __syncthreads();
@@ -1364,7 +1367,8 @@ template <int N>
 // one workgroup per row and a few hundred rows: occupancy is low anyway, so the
 // register budget goes to loads in flight
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_rows_fwd_fin(RowsArgs A) {
-  extern __shared__ float2 lds[];
+  extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
   for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
     const WorkItem w = A.items[it];
     const GatherDev G = A.gd[w.g];
@@ -1506,8 +1510,11 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
   float2* bufD = lds + fft_tw_slots(N, ntp);
   float2* bufM = bufD + plen;
   stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  RowTw<N, NT> lw;
+  lw.load(A.tw + G.twp_t_off);
+  lw.pin();
 
-  row_spectrum<N, NT>(bufD, A.H + G.H_off + (long long)r * nt, r, nt, ntp, twl);
+  row_spectrum<N, NT>(bufD, A.H + G.H_off + (long long)r * nt, r, nt, ntp, twl, lw);
 
   // window rotations cos/sin(pi t / R) in registers (the wave barriers below
   // would otherwise reload them from LDS at every tap)
@@ -1630,7 +1637,7 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
       // the last pass's outputs go from registers to global memory
       using O = FftRegsOut<N, NT>;
       O o;
-      fft_tpl_from_pairs_to_regs<N, true, NT>(bufM, twl, o);
+      fft_tpl_from_pairs_to_regs<N, true, NT>(bufM, twl, lw, o);
 #pragma unroll
       for (int i = 0; i < O::MAXB; ++i) {
         const int id = (int)threadIdx.x + i * NT;
@@ -1641,7 +1648,8 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
         }
       }
     } else {
-      row_inverse_from_pairs<N, NT>(bufM, ntp, twl);
+      pairs_to_natural<NT>(bufM, ntp);
+      fft_lds<NT, kRowMaxN, true>(bufM, ntp, 1, ntp, twl);
       for (int t = threadIdx.x; t < nt; t += NT) dst[t] = cscale(bufM[px<N>(t)], inv_n);
     }
     __syncthreads();
