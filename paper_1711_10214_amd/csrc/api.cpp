@@ -205,8 +205,8 @@ struct PlanImpl {
   PanelDev* d_pan = nullptr;
   float2* d_tw = nullptr;
   float* d_wav = nullptr;
-  WorkItem *d_xm = nullptr, *d_xd = nullptr, *d_rf = nullptr, *d_rfin = nullptr, *d_ra = nullptr;
-  int n_xm = 0, n_xd = 0, n_rf = 0, n_rfin = 0, n_ra = 0;
+  WorkItem *d_xm = nullptr, *d_xd = nullptr, *d_rf = nullptr, *d_rfin = nullptr;
+  int n_xm = 0, n_xd = 0, n_rf = 0, n_rfin = 0;
   // CG reductions of per-tile partials: summed by every consuming workgroup
   // (no extra launch) while that costs little (sum over gathers of items^2
   // below kInKernelSumLimit), else once per gather by k_sum_items
@@ -325,6 +325,46 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost*
     for (int j = 0; j <= z.ntp / 2; ++j) gh->wav[j] = (float)d->wavelet_amp[j];
   }
   return ASHRT_OK;
+}
+
+// Estimated work of a panel chunk of each wavenumber row (all chunks of a row
+// alike): a live panel costs its transform (0.26 per point) plus 0.7 per
+// in-cone bin (row 0 maps two half rows).
+static std::vector<float> row_costs(const GatherHost& gh) {
+  const Resolved& z = gh.z;
+  std::vector<std::pair<int, double>> pan;  // (live rows, cone slope in bins per row)
+  for (const auto& p : gh.panels) pan.push_back({p.rlive, std::sqrt(p.c2)});
+  std::sort(pan.begin(), pan.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  std::vector<double> slope(pan.size() + 1, 0.0);
+  for (size_t i = 0; i < pan.size(); ++i) slope[i + 1] = slope[i] + pan[i].second;
+  std::vector<float> cost(gh.nrows);
+  size_t k = pan.size();
+  for (int r = 0; r < gh.nrows; ++r) {
+    while (k > 0 && pan[k - 1].first <= r) --k;  // the first k panels are live in row r
+    const double bins = std::max(0.0, (double)k * (z.jhi - z.jlo + 1) - r * slope[k]);
+    cost[r] = (float)((0.26 * z.ntp * (double)k + (r == 0 ? 1.4 : 0.7) * bins) / gh.nchunk);
+  }
+  return cost;
+}
+
+// Launch order of the row passes' work items, heavy first: rows differ by
+// more than 3x in work, and a launch of many rounds ends with the light ones
+// (24 uneven gathers: 5 % of the solve).  A launch whose workgroups are all
+// resident at once (4 per CU, 2 of the long rows) is dealt instead so that
+// each CU gets the same sum: the hardware deals consecutive workgroups to the
+// 8 XCDs and their 32 CUs in turn, so items kCus apart meet on one CU, and
+// every second run of kCus items is reversed.  On the 1024 x 256, 32-panel
+// gather the last CU then ends 43.2 instead of 45.4 us after the first
+// starts in the forward pass, 58.6 instead of 60.9 in the adjoint.
+static void order_row_items(std::vector<WorkItem>& items, const PlanImpl::Seg& sg,
+                            const std::vector<std::vector<float>>& cost) {
+  constexpr int kCus = 256;
+  const auto b = items.begin() + sg.first;
+  std::stable_sort(b, b + sg.count,
+                   [&](const WorkItem& x, const WorkItem& y) { return cost[x.g][x.a] > cost[y.g][y.a]; });
+  const int resident = kCus * (sg.key > 0 ? 4 * kRowThreads / row_threads(sg.key) : 2);
+  if (sg.count > resident) return;
+  for (int i = kCus; i < sg.count; i += 2 * kCus) std::reverse(b + i, b + std::min(i + kCus, sg.count));
 }
 
 static void destroy_impl(PlanImpl& P) {
@@ -496,7 +536,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   std::vector<PanelDev> pan;
   std::vector<float> wav;
   std::vector<GatherDev> gd(ngather);
-  std::vector<WorkItem> xm, xd, rf, rfin, ra;
+  std::vector<WorkItem> xm, xd, rf, rfin;
   std::vector<VecItem> vm, vd;
   std::vector<int> key_x(ngather), key_t(ngather);
   for (int gi = 0; gi < ngather; ++gi) {
@@ -613,10 +653,16 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     for (int r = 0; r < P.g[gi].nrows; ++r)
       for (int c = 0; c < P.g[gi].nchunk; ++c) rf.push_back(WorkItem{gi, r, c, 0});
   }, lds_rf_of);
-  build_segments(key_t, P.s_ra, ra, [&](int gi) {
-    for (int r = 0; r < P.g[gi].nrows; ++r)
-      for (int c = 0; c < P.g[gi].nchunk; ++c) ra.push_back(WorkItem{gi, r, c, 0});
-  }, lds_ra_of);
+  std::vector<std::vector<float>> cost;
+  for (const auto& gh : P.g) cost.push_back(row_costs(gh));
+  for (const auto& sg : P.s_rf) order_row_items(rf, sg, cost);
+  // the adjoint runs the same list, with its own LDS size
+  P.s_ra = P.s_rf;
+  for (auto& sg : P.s_ra) {
+    sg.lds = 0;
+    for (int gi = 0; gi < ngather; ++gi)
+      if (key_t[gi] == sg.key) sg.lds = std::max(sg.lds, (size_t)lds_ra_of(P.g[gi]));
+  }
   build_segments(key_t, P.s_rfin, rfin, [&](int gi) {
     for (int r = 0; r < P.g[gi].nrows; ++r) rfin.push_back(WorkItem{gi, r, 0, 0});
   }, lds_fin_of);
@@ -645,7 +691,6 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   }
   P.n_rf = (int)rf.size();
   P.n_rfin = (int)rfin.size();
-  P.n_ra = (int)ra.size();
   P.n_vm = (int)vm.size();
   P.n_vd = (int)vd.size();
   std::vector<Part> parts = {
@@ -657,7 +702,6 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       {xd.data(), xd.size() * sizeof(WorkItem), (void**)&P.d_xd},
       {rf.data(), rf.size() * sizeof(WorkItem), (void**)&P.d_rf},
       {rfin.data(), rfin.size() * sizeof(WorkItem), (void**)&P.d_rfin},
-      {ra.data(), ra.size() * sizeof(WorkItem), (void**)&P.d_ra},
       {vm.data(), vm.size() * sizeof(VecItem), (void**)&P.d_vm},
       {vd.data(), vd.size() * sizeof(VecItem), (void**)&P.d_vd},
   };
@@ -1047,7 +1091,7 @@ hipError_t run_adjoint(const Ctx& c, const float* d, const float* mul_d, const u
   }
   for (const auto& sg : P.s_ra) {
     e = timed(ASHRT_K_ROWS_ADJ, c.s,
-              [&] { return launch_rows_adj(sg.key, rows_args(c, P.d_ra + sg.first, sg.count), sg.lds, c.s); });
+              [&] { return launch_rows_adj(sg.key, rows_args(c, P.d_rf + sg.first, sg.count), sg.lds, c.s); });
     if (e != hipSuccess) return e;
   }
   for (const auto& sg : P.s_xm) {
