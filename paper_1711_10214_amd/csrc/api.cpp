@@ -293,7 +293,8 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost*
   Td = std::max(2, std::min(T, Td));
   if (tn && tn->tile_data > 0) Td = tn->tile_data;
   gh->tileTd = Td;
-  gh->ntilesd = (z.nt + Td - 1) / Td;
+  const int Tx = d->x_pos ? kNudftT : Td;
+  gh->ntilesd = (z.nt + Tx - 1) / Tx;
   gh->panels.resize(z.P);
   const double bin = (double)z.ntp * d->dt / ((double)z.nxp * d->dx);
   for (int p = 0; p < z.P; ++p) {
@@ -538,10 +539,11 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   std::vector<GatherDev> gd(ngather);
   std::vector<WorkItem> xm, xd, rf, rfin;
   std::vector<VecItem> vm, vd;
-  std::vector<int> key_x(ngather), key_t(ngather);
+  std::vector<int> key_x(ngather), key_xd(ngather), key_t(ngather);
   for (int gi = 0; gi < ngather; ++gi) {
     GatherHost& gh = P.g[gi];
     key_x[gi] = x_size_is_tpl(gh.z.nxp) ? gh.z.nxp : 0;
+    key_xd[gi] = gh.xpos.empty() ? key_x[gi] : kNudftKey;
     key_t[gi] = rows_size_is_tpl(gh.z.ntp, gh.z.R) ? gh.z.ntp : 0;
     GatherDev& G = gd[gi];
     std::memset(&G, 0, sizeof(G));
@@ -570,15 +572,19 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     if (!gh.xpos.empty()) {
       // exp(-2 pi i r x / (nxp dx)), r = 0..nrows-1; the phase in turns is
       // reduced in FP64 before the FP32 rounding
-      if (tw.size() + (size_t)gh.nrows * gh.z.nx > (size_t)INT32_MAX)
+      const size_t ne = (size_t)gh.nrows * gh.z.nx;
+      if (tw.size() + ne > (size_t)INT32_MAX)
         return fail(ASHRT_E_UNSUPPORTED_SIZE, "irregular-trace tables too large");
       G.nudft_off = (int)tw.size();
+      tw.resize(tw.size() + 2 * ne);  // [r][x], then transposed
+      float2* E = tw.data() + G.nudft_off;
       const double period = (double)gh.z.nxp * descs[gi].dx;
       for (int r = 0; r < gh.nrows; ++r)
         for (int x = 0; x < gh.z.nx; ++x) {
           double turns = std::fmod((double)r * gh.xpos[x] / period, 1.0);
           const double a = -2.0 * M_PI * turns;
-          tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
+          E[(size_t)r * gh.z.nx + x] = make_float2((float)std::cos(a), (float)std::sin(a));
+          E[ne + (size_t)x * gh.nrows + r] = E[(size_t)r * gh.z.nx + x];
         }
     }
     G.tileT = gh.tileT;
@@ -613,8 +619,14 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   auto lds_x_of = [&](const GatherHost& gh) {
     return twx_of(gh) * 8 + (size_t)(gh.tileT / 2) * xstride(gh) * 8;
   };
-  auto lds_xd_of = [&](const GatherHost& gh) {
+  auto lds_xtile_of = [&](const GatherHost& gh) {
     return twx_of(gh) * 8 + (size_t)(gh.tileTd / 2) * xstride(gh) * 8;
+  };
+  auto lds_xd_of = [&](const GatherHost& gh) {
+    if (gh.xpos.empty()) return lds_xtile_of(gh);
+    // the traces' tile on the way in, the rows' tile on the way out
+    return std::max((size_t)std::min((gh.z.nx + 15) & ~15, kNudftRows) * kNudftStride * sizeof(float),
+                    gh.nrows <= kNudftRows ? (size_t)gh.nrows * kNudftT * sizeof(float2) : 0);
   };
   auto nband_of = [](const GatherHost& gh) { return (size_t)(gh.z.jhi - gh.z.jlo + 1); };
   auto plen_of = [](const GatherHost& gh) { return (size_t)fft_padlen(gh.z.ntp); };
@@ -644,7 +656,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       for (int t = 0; t < P.g[gi].ntiles; ++t) xm.push_back(WorkItem{gi, p, t, 0});
     gd[gi].xm_hi = (int)xm.size();
   }, lds_x_of);
-  build_segments(key_x, P.s_xd, xd, [&](int gi) {
+  build_segments(key_xd, P.s_xd, xd, [&](int gi) {
     gd[gi].xd_lo = (int)xd.size();
     for (int t = 0; t < P.g[gi].ntilesd; ++t) xd.push_back(WorkItem{gi, 0, t, 0});
     gd[gi].xd_hi = (int)xd.size();
@@ -671,6 +683,9 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   for (auto* segs : {&P.s_xm, &P.s_xd, &P.s_rf, &P.s_rfin, &P.s_ra})
     for (auto& sg : *segs)
       if (sg.lds > kMaxDynLds) return fail(ASHRT_E_UNSUPPORTED_SIZE, "LDS requirement exceeds the per-workgroup limit");
+  for (const auto& gh : P.g)  // gathers with trace positions take no data tile, but keep its limit
+    if (lds_xtile_of(gh) > kMaxDynLds)
+      return fail(ASHRT_E_UNSUPPORTED_SIZE, "LDS requirement exceeds the per-workgroup limit");
 
   // one device allocation for all tables
   struct Part {

@@ -28,6 +28,11 @@ constexpr int kXLoadBatch = 4;        // x kernels: tile-loop iterations whose g
 constexpr int kXfftTilePoints = 4096;  // complex points of a model x-FFT tile (T = 2 * this / nxp columns)
 constexpr int kXfftBatch = 2048;       // complex points per compile-time x-FFT call (register bound)
 constexpr int kXfftGenericBatch = 4096;  // complex points per generic x-FFT call (nxp <= 4096)
+constexpr int kNudftKey = -1;          // data x-transform class of gathers with trace positions
+constexpr int kNudftT = 16;            // time columns per workgroup of the non-uniform DFTs
+constexpr int kNudftThreads = 1024;
+constexpr int kNudftRows = 1024;       // traces (rows) staged in LDS at a time
+constexpr int kNudftStride = 20;       // floats per staged trace (16 and 4 of padding against bank conflicts)
 constexpr int kMaxSlots = (kRowMaxN / 2 + kThreads - 1) / kThreads;  // per-thread bins
 constexpr long long kVecChunk = 8192;  // elements per vector-kernel work item
 constexpr long long kDataVecChunk = 2048;  // the same for data vectors (a gather's data is P times smaller)
@@ -49,14 +54,14 @@ struct GatherDev {
   int tileT;        // time columns per x-FFT tile of a model panel (even)
   int ntiles;       // ceil(nt / tileT)
   int tileTd;       // time columns per x-FFT tile of the data (even, smaller: more workgroups)
-  int ntilesd;      // ceil(nt / tileTd)
+  int ntilesd;      // ceil(nt / tileTd) (of kNudftT columns for gathers with trace positions)
   int nchunk;       // panel chunks of the forward row pass
   int mit_lo, mit_hi;   // model-vector work items of this gather
   int dit_lo, dit_hi;   // data-vector work items of this gather
   int xm_lo, xm_hi;     // model x-FFT tile items of this gather (partial sums)
   int xd_lo, xd_hi;     // data x-FFT tile items of this gather
   int nudft_off;        // float2 offset of the irregular-trace table exp(-2 pi i r x_pos / (nxp dx)),
-                        // [nrows][nx], in the twiddle pool; -1 = regular traces
+                        // [nrows][nx] and its transpose, in the twiddle pool; -1 = regular traces
   long long d_off;      // float offset of the gather in packed data arrays
   long long m_off;      // float offset in packed model arrays
   long long mask_off;   // byte offset in packed trace masks

@@ -486,6 +486,35 @@ __device__ __forceinline__ int xcd_item(int b, int n) {
   return x * q + min(x, r) + k;
 }
 
+// Step length of the CG iteration whose data transform this is: alpha =
+// gamma[par] / delta (0 once done), delta summed here from the forward's
+// partials when part_red is set; the gather's first item stores alpha.
+// Called by the whole workgroup.
+__device__ __forceinline__ float cg_alpha(const XfwdArgs& A, int g, const GatherDev& G, int it, float* s_alpha,
+                                          double* s_red) {
+  double dsum = 0.0;
+  if (A.part_red) {
+    double part = 0.0;
+    for (int i = G.xd_lo + (int)threadIdx.x; i < G.xd_hi; i += blockDim.x) part += A.part_red[i];
+    dsum = block_sum(part, s_red);
+  }
+  if (threadIdx.x == 0) {
+    double* sc = A.sc + (long long)g * kNScal;
+    const double delta = A.part_red ? dsum : sc[SC_DELTA];
+    const double gm = sc[SC_GAMMA0 + A.par];
+    const bool stop = sc[SC_DONE] != 0.0 || gm == 0.0 || delta == 0.0 || !isfinite(gm) || !isfinite(delta);
+    const double al = stop ? 0.0 : gm / delta;
+    *s_alpha = (float)al;
+    if (A.item_base + it == G.xd_lo) {
+      sc[SC_ALPHA] = al;
+      if (stop) sc[SC_DONE] = 1.0;
+      else sc[SC_NINNER] += 1.0;
+    }
+  }
+  __syncthreads();
+  return *s_alpha;
+}
+
 // ------------------------------------------------------------ x-direction RFFT
 template <int NX>
 __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
@@ -498,30 +527,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
     const int it = (int)gridDim.x == A.nitems ? xcd_item(it0, A.nitems) : it0;
     const WorkItem w = A.items[it];
     const GatherDev G = A.gd[w.g];
-    float alpha = 0.f;
-    if (A.s_inout) {
-      double dsum = 0.0;
-      if (A.part_red) {
-        double part = 0.0;
-        for (int i = G.xd_lo + (int)threadIdx.x; i < G.xd_hi; i += kThreads) part += A.part_red[i];
-        dsum = block_sum(part, s_red);
-      }
-      if (threadIdx.x == 0) {
-        double* sc = A.sc + (long long)w.g * kNScal;
-        const double delta = A.part_red ? dsum : sc[SC_DELTA];
-        const double gm = sc[SC_GAMMA0 + A.par];
-        const bool stop = sc[SC_DONE] != 0.0 || gm == 0.0 || delta == 0.0 || !isfinite(gm) || !isfinite(delta);
-        const double al = stop ? 0.0 : gm / delta;
-        s_alpha = (float)al;
-        if (A.item_base + it == G.xd_lo) {
-          sc[SC_ALPHA] = al;
-          if (stop) sc[SC_DONE] = 1.0;
-          else sc[SC_NINNER] += 1.0;
-        }
-      }
-      __syncthreads();
-      alpha = s_alpha;
-    }
+    const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
     float cg_a = 0.f, cg_b = 0.f;
     if (A.cg_upd) {
       double gsum = 0.0;
@@ -564,7 +570,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
     const bool even = (nt & 1) == 0;
 
     const UDiv dh(half);
-    if (!A.is_model && even && t0 + T <= nt && G.nudft_off < 0) {
+    if (!A.is_model && even && t0 + T <= nt) {
       // a full data tile (all but a ragged last one)
       float* sv = A.s_inout ? A.s_inout + fbase : nullptr;
       const float* qv = A.s_inout ? A.qv + fbase : nullptr;
@@ -675,31 +681,6 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
       }
     }
     __syncthreads();
-    if (!A.is_model && G.nudft_off >= 0) {
-      // irregular traces: non-uniform DFT over the trace positions,
-      // H_t[r] = sum_x d_t[x] exp(-2 pi i r x_pos / (nxp dx)); row 0 packs
-      // (H_t[0], 0) (no Nyquist wavenumber off the grid)
-      const float2* __restrict__ E = A.tw + G.nudft_off;
-      float2* __restrict__ dst = A.dst + G.H_off;
-      for (int idx = threadIdx.x; idx < nrows * T; idx += kThreads) {
-        const int r = idx / T, c = idx - r * T, t = t0 + c;
-        if (t >= nt) continue;
-        const float2* Z = buf + (c >> 1) * bs;
-        float2 acc = make_float2(0.f, 0.f);
-        if (r == 0) {
-          for (int x = 0; x < nx; ++x) acc.x += (c & 1) ? Z[px<NX>(x)].y : Z[px<NX>(x)].x;
-        } else {
-          const float2* Er = E + (long long)r * nx;
-          for (int x = 0; x < nx; ++x) {
-            const float v = (c & 1) ? Z[px<NX>(x)].y : Z[px<NX>(x)].x;
-            acc = cfma(v, Er[x], acc);
-          }
-        }
-        dst[(long long)r * nt + t] = acc;
-      }
-      __syncthreads();
-      continue;
-    }
     lw.pin();
     xfft_tile<NX, false>(buf, nxp, half, bs, twl, nx, lw);
 
@@ -756,44 +737,6 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
     const float2* __restrict__ src = A.src + uniform64(A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
     float2* twl = lds;
     float2* buf = lds + fft_tw_slots(NX, nxp);
-    if (!A.is_model && G.nudft_off >= 0) {
-      // irregular traces: d_t[x] = (1/nxp) (Re H_t[0] + 2 Re sum_{r>=1} H_t[r]
-      // exp(+2 pi i r x_pos / (nxp dx))), the rows staged column by column
-      for (int idx = threadIdx.x; idx < nrows * T; idx += kThreads) {
-        const int l = idx / T, c = idx - l * T, t = t0 + c;
-        buf[c * nrows + l] = (t < nt) ? src[(long long)l * nt + t] : make_float2(0.f, 0.f);
-      }
-      __syncthreads();
-      const float2* __restrict__ E = A.tw + G.nudft_off;
-      const float inv = 1.0f / (float)nxp;
-      const long long fbase = G.d_off;
-      const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-      double ss = 0.0;
-      for (int idx = threadIdx.x; idx < nx * T; idx += kThreads) {
-        const int x = idx / T, c = idx - x * T, t = t0 + c;
-        if (t >= nt) continue;
-        const float2* hc = buf + c * nrows;
-        float acc = 0.f;
-        for (int r = 1; r < nrows; ++r) {
-          const float2 e = E[(long long)r * nx + x];
-          acc = fmaf(hc[r].x, e.x, fmaf(hc[r].y, e.y, acc));
-        }
-        float v = (hc[0].x + 2.0f * acc) * inv;
-        const long long o = fbase + (long long)x * nt + t;
-        if (A.raw_out) A.raw_out[o] = v;
-        if (A.sub) v = A.sub[o] - v;
-        if (tm && tm[x] == 0) v = 0.f;
-        if (A.wmul) v *= A.wmul[o];
-        A.out[o] = v;
-        ss += (double)v * (double)v;
-      }
-      if (A.part) {
-        const double tot = block_sum(ss, sh);
-        if (threadIdx.x == 0) A.part[A.item_base + it] = tot;
-      }
-      __syncthreads();
-      continue;
-    }
     stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
     XTw<NX> lw;
     lw.load(A.tw + G.twp_x_off);
@@ -933,6 +876,182 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
       if (threadIdx.x == 0) A.part[A.item_base + it] = tot;
     }
     __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------ irregular traces
+//
+// Data side of gathers with trace positions: non-uniform DFTs over them, with
+// the table E[r][x] = exp(-2 pi i r x_pos / (nxp dx)) (no Nyquist wavenumber
+// off the grid),
+//   H_t[r] = sum_x E[r][x] d_t[x]  (row 0: its real part),
+//   d_t[x] = (1/nxp) (H_t[0] + 2 Re sum_{r>=1} conj(E[r][x]) H_t[r]).
+// These are matrix products, [rows x traces] by [traces x times] and back,
+// and run on the FP32 matrix cores (v_mfma_f32_16x16x4_f32: FP32 products
+// and sums): a workgroup of 16 waves owns kNudftT = 16 times, each wave 16
+// rows (traces) at a time.  The fragments of E come straight from L2, each
+// line read whole; 1001 times x 187 traces x 192 rows takes 13 us in and 17 us back, where
+// a loop over the traces (rows) per output took 68 and 137 us.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Traces to rows, with the CG step and the mask of the data input folded in
+// as in k_xfft_fwd.  LDS: traces [kNudftRows][kNudftStride] of the tile.
+__global__ __launch_bounds__(kNudftThreads) void k_nudft_fwd(XfwdArgs A) {
+  extern __shared__ float4 lds_raw[];
+  float* buf = reinterpret_cast<float*>(lds_raw);
+  __shared__ float s_alpha;
+  __shared__ double s_red[kNudftThreads / 64];
+  const int it = blockIdx.x;
+  const WorkItem w = A.items[it];
+  const GatherDev G = A.gd[w.g];
+  const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
+  const int nx = G.nx, nt = G.nt, nrows = G.nrows, t0 = w.b * kNudftT;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  const float2* __restrict__ E = A.tw + G.nudft_off;
+  float2* __restrict__ H = A.dst + G.H_off;
+  const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+  for (int c0 = 0; c0 < nx; c0 += kNudftRows) {
+    const int rows = min(kNudftRows, nx - c0);
+    for (int i = threadIdx.x; i < ((rows + 15) & ~15) * kNudftT; i += kNudftThreads) {
+      const int x = i / kNudftT, t = t0 + i % kNudftT;
+      float v = 0.f;
+      if (x < rows && t < nt) {
+        const long long o = G.d_off + (long long)(c0 + x) * nt + t;
+        if (A.s_inout) {
+          v = fmaf(-alpha, A.qv[o], A.s_inout[o]);
+          A.s_inout[o] = v;
+        } else {
+          v = A.src[o];
+        }
+        if (A.mul) v *= A.mul[o];
+        if (tm && tm[c0 + x] == 0) v = 0.f;
+      }
+      buf[x * kNudftStride + i % kNudftT] = v;
+    }
+    __syncthreads();
+    for (int r0 = 16 * wave; r0 < nrows; r0 += kNudftThreads / 4) {
+      // operand k of step s is trace xb + 4 g + s, so that a lane's four
+      // entries of E are adjacent
+      const float2* __restrict__ Er = E + (long long)min(r0 + n, nrows - 1) * nx + c0;
+      f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
+      if (c0 > 0) {  // the sum over the earlier traces
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = r0 + 4 * g + i;
+          if (r < nrows && t0 + n < nt) {
+            const float2 h = H[(long long)r * nt + t0 + n];
+            re[i] = h.x;
+            im[i] = h.y;
+          }
+        }
+      }
+      int xb = 0;
+#pragma unroll 4
+      for (; xb + 16 <= rows; xb += 16) {
+        float2 e[4];
+        __builtin_memcpy(e, Er + xb + 4 * g, sizeof(e));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float v = buf[(xb + 4 * g + s) * kNudftStride + n];
+          re = mfma4(e[s].x, v, re);
+          im = mfma4(e[s].y, v, im);
+        }
+      }
+      if (xb < rows) {  // the staged traces past the last one are zero
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float2 e = Er[min(xb + 4 * g + s, rows - 1)];
+          const float v = buf[(xb + 4 * g + s) * kNudftStride + n];
+          re = mfma4(e.x, v, re);
+          im = mfma4(e.y, v, im);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = r0 + 4 * g + i;
+        if (r < nrows && t0 + n < nt) H[(long long)r * nt + t0 + n] = make_float2(re[i], r == 0 ? 0.f : im[i]);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Rows to traces, with the data epilogue of k_xfft_inv.  LDS: the tile of up
+// to kNudftRows rows (longer x transforms read it from memory).
+__global__ __launch_bounds__(kNudftThreads) void k_nudft_inv(XinvArgs A) {
+  extern __shared__ float4 lds_raw[];
+  float2* buf = reinterpret_cast<float2*>(lds_raw);
+  __shared__ double sh[kNudftThreads / 64];
+  const int it = blockIdx.x;
+  const WorkItem w = A.items[it];
+  const GatherDev G = A.gd[w.g];
+  const int nx = G.nx, nt = G.nt, nrows = G.nrows, t0 = w.b * kNudftT;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  // the table transposed, [x][r]
+  const float2* __restrict__ E = A.tw + G.nudft_off + (long long)nrows * nx;
+  const float2* __restrict__ Ht = A.src + G.H_off;
+  const bool staged = nrows <= kNudftRows;
+  if (staged) {
+    for (int i = threadIdx.x; i < nrows * kNudftT; i += kNudftThreads)
+      buf[i] = Ht[(unsigned)((i / kNudftT) * nt + min(t0 + i % kNudftT, nt - 1))];
+    __syncthreads();
+  }
+  const float2* __restrict__ H = Ht + min(t0 + n, nt - 1);
+  const float h0 = H[0].x, inv = 1.0f / (float)G.nxp;
+  const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+  double ss = 0.0;
+  for (int x0 = 16 * wave; x0 < nx; x0 += kNudftThreads / 4) {
+    const float2* __restrict__ Ex = E + (long long)min(x0 + n, nx - 1) * nrows;
+    f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
+    auto row = [&](int r) { return staged ? buf[r * kNudftT + n] : H[(unsigned)(r * nt)]; };
+    // operand k of step s is row rb + 4 g + s, so that a lane's four entries
+    // of E are adjacent
+    int rb = 1;
+#pragma unroll 4
+    for (; rb + 16 <= nrows; rb += 16) {
+      float2 e[4];
+      __builtin_memcpy(e, Ex + rb + 4 * g, sizeof(e));
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float2 h = row(rb + 4 * g + s);
+        re = mfma4(e[s].x, h.x, re);
+        im = mfma4(e[s].y, h.y, im);
+      }
+    }
+    if (rb < nrows) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = rb + 4 * g + s;
+        float2 e = make_float2(0.f, 0.f), h = e;
+        if (r < nrows) {
+          e = Ex[r];
+          h = row(r);
+        }
+        re = mfma4(e.x, h.x, re);
+        im = mfma4(e.y, h.y, im);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int x = x0 + 4 * g + i, t = t0 + n;
+      if (x >= nx || t >= nt) continue;
+      float v = (h0 + 2.0f * (re[i] + im[i])) * inv;
+      const long long o = G.d_off + (long long)x * nt + t;
+      if (A.raw_out) A.raw_out[o] = v;
+      if (A.sub) v = A.sub[o] - v;
+      if (tm && tm[x] == 0) v = 0.f;
+      if (A.wmul) v *= A.wmul[o];
+      A.out[o] = v;
+      ss += (double)v * (double)v;
+    }
+  }
+  if (A.part) {
+    const double tot = block_sum(ss, sh);
+    if (threadIdx.x == 0) A.part[A.item_base + it] = tot;
   }
 }
 
@@ -1706,6 +1825,8 @@ hipError_t op_kernels_init(size_t max_lds) {
   ASHRT_X_SIZES(X_)
 #undef X_
   set_lds(k_xfft_fwd<0>, max_lds, e);
+  set_lds(k_nudft_fwd, max_lds, e);
+  set_lds(k_nudft_inv, max_lds, e);
   set_lds(k_xfft_inv<0>, max_lds, e);
 #define R_(S) set_lds(k_rows_fwd<S, 4>, max_lds, e); set_lds(k_rows_adj<S, 4>, max_lds, e); set_lds(k_rows_fwd_fin<S>, max_lds, e);
   ASHRT_ROW_SIZES(R_)
@@ -1720,6 +1841,9 @@ hipError_t launch_xfft_fwd(int key, const XfwdArgs& a, size_t lds, hipStream_t s
   if (a.nitems <= 0) return hipSuccess;
   hipError_t e = hipSuccess;
   switch (key) {
+    case kNudftKey:
+      hipLaunchKernelGGL(k_nudft_fwd, dim3(a.nitems), dim3(kNudftThreads), lds, s, a);
+      break;
 #define L_(S)                                                                               \
   case S:                                                                                   \
     hipLaunchKernelGGL(k_xfft_fwd<S>, dim3(a.nitems), dim3(kThreads), lds, s, a); \
@@ -1736,6 +1860,9 @@ hipError_t launch_xfft_inv(int key, const XinvArgs& a, size_t lds, hipStream_t s
   if (a.nitems <= 0) return hipSuccess;
   hipError_t e = hipSuccess;
   switch (key) {
+    case kNudftKey:
+      hipLaunchKernelGGL(k_nudft_inv, dim3(a.nitems), dim3(kNudftThreads), lds, s, a);
+      break;
 #define L_(S)                                                                               \
   case S:                                                                                   \
     hipLaunchKernelGGL(k_xfft_inv<S>, dim3(a.nitems), dim3(kThreads), lds, s, a); \

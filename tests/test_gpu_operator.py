@@ -95,6 +95,20 @@ def test_forward_adjoint_match_oracle(A, name):
     assert ea <= TOL, ea
 
 
+# The non-uniform DFTs' tiles: 16 times, 16 rows or traces, 1024 staged traces.
+IRREGULAR_EDGES = [(15, 2), (16, 15), (17, 16), (33, 17), (5, 300), (20, 1024), (18, 1041)]
+
+
+@pytest.mark.parametrize("nt,nx", IRREGULAR_EDGES)
+def test_irregular_tile_edges(A, nt, nx):
+    """Same bar as above, with dead traces."""
+    print(f"[gpu] irregular tile edges {nt} x {nx}", flush=True)
+    xpos = np.arange(nx) * 12.5 + np.random.default_rng(nx).uniform(-5, 5, nx)
+    kw = geom_kwargs(nt, nx, 0.004, 12.5, [1500.0, 2700.0], fmax=110.0, xpos=list(xpos))
+    g, m, d, d_gpu, m_gpu, d_ref, m_ref = _run_pair(A, kw, seed=nt + nx, mask_frac=0.2)
+    assert rel_l2(d_gpu, d_ref) <= TOL and rel_l2(m_gpu, m_ref) <= TOL
+
+
 def test_wavelet_weight(A):
     kw = geom_kwargs(200, 40, 0.004, 12.5, [1500.0, 2500.0], fmax=100.0)
     H = oracle.fft_len(200) // 2 + 1
