@@ -63,3 +63,34 @@ def test_survey_separation_matches_oracle(A):
     print(f"  rel-L2 vs oracle {e:.2e}; Q separated {q_sep:.2f} dB, pseudo-deblended {q_pd:.2f} dB", flush=True)
     assert e <= 1e-4
     assert q_sep > q_pd
+
+
+# Edges of the kernels' tiles: 4 samples per thread, 1024 record samples and 8
+# receivers per workgroup, 1024 sources tested at a time; shots that start
+# together, out of order, and past the record.
+SURVEY_EDGES = [(1, 1, 1, 1), (3, 2, 3, 5), (5, 9, 7, 40), (4, 8, 1024, 1023), (6, 3, 130, 1025), (1030, 2, 5, 2051)]
+
+
+@pytest.mark.parametrize("ns,nr,nt,nrec", SURVEY_EDGES)
+def test_survey_tile_edges(A, ns, nr, nt, nrec):
+    """Blending adds the shots in index order in FP32, so it equals numpy's
+    running FP32 sum; pseudo-deblending and re-sorting copy."""
+    import torch
+    from paper_1711_10214_amd import survey as S
+    print(f"[gpu] survey edges {ns} x {nr} x {nt}, {nrec} record samples", flush=True)
+    rng = np.random.default_rng(ns + nt)
+    D = rng.standard_normal((ns, nr, nt)).astype(np.float32)
+    fire = rng.integers(0, max(1, nrec), ns).astype(np.int32)
+    fire[::7] = fire[0]
+    b = np.zeros((nr, nrec), np.float32)
+    for s in range(ns):
+        n = min(nt, nrec - int(fire[s]))
+        b[:, fire[s]:fire[s] + n] += D[s, :, :n]
+    g = S.blend(torch.tensor(D, device="cuda"), fire, nrec)
+    assert np.array_equal(g.cpu().numpy(), b)
+    pad = np.concatenate([b, np.zeros((nr, nt), np.float32)], axis=1)
+    c = np.stack([pad[:, f:f + nt] for f in fire])
+    assert np.array_equal(S.deblend(g, fire, ns, nt, receiver_major=False).cpu().numpy(), c)
+    r = S.deblend(g, fire, ns, nt)
+    assert np.array_equal(r.cpu().numpy(), np.transpose(c, (1, 0, 2)))
+    assert np.array_equal(S.resort(r).cpu().numpy(), c)
