@@ -112,6 +112,24 @@ struct SelState {
   unsigned kk[2];
 };
 
+// A table entry read through the constant address space: the plan's tables do
+// not change while a kernel runs, and at a wave-uniform index the compiler
+// then takes scalar loads into SGPRs (through a plain pointer it cannot rule
+// out that the kernel's own stores change them, and takes vector loads).
+template <class T>
+__device__ __forceinline__ T load_const(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "read in words");
+  typedef const __attribute__((address_space(4))) int* cptr;
+  const cptr q = (cptr)(uintptr_t)p;
+  union {
+    T v;
+    int w[sizeof(T) / 4];
+  } u;
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) u.w[i] = q[i];
+  return u.v;
+}
+
 // Device-side report accumulated per gather (copied to irls_report on the host).
 struct RepDev {
   double misfit[64];

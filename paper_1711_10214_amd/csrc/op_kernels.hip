@@ -523,10 +523,10 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
   __shared__ float s_alpha;
   __shared__ float s_ab[2];
   __shared__ double s_red[kThreads / 64];
-  for (int it0 = blockIdx.x; it0 < A.nitems; it0 += gridDim.x) {
-    const int it = (int)gridDim.x == A.nitems ? xcd_item(it0, A.nitems) : it0;
-    const WorkItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+  {
+    const int it = xcd_item(blockIdx.x, A.nitems);
+    const WorkItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
     float cg_a = 0.f, cg_b = 0.f;
     if (A.cg_upd) {
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
     // together (one 16-byte store when nt is even)
     float2* __restrict__ dst = A.dst + (A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
     // model panels: rows at or above the panel's live-row count are never read
-    const int nrw = A.is_model ? min(nrows, A.panels[G.panel_off + p].rlive) : nrows;
+    const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
     for (int idx = threadIdx.x; idx < nrw * half; idx += kThreads) {
       const int r = dh.div(idx);
       const int i = idx - r * half;
@@ -725,10 +725,10 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ double sh[kThreads / 64];
-  for (int it0 = blockIdx.x; it0 < A.nitems; it0 += gridDim.x) {
-    const int it = (int)gridDim.x == A.nitems ? xcd_item(it0, A.nitems) : it0;
-    const WorkItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+  {
+    const int it = xcd_item(blockIdx.x, A.nitems);
+    const WorkItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     const int p = w.a;
     const int nx = G.nx, nt = G.nt, nxp = G.nxp, nrows = G.nrows;
     const int T = A.is_model ? G.tileT : G.tileTd, half = T >> 1;
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
     const UDiv dh(half);
     const bool even = (nt & 1) == 0;
     // model panels: rows at or above the panel's live-row count are zero (not stored)
-    const int nrw = A.is_model ? min(nrows, A.panels[G.panel_off + p].rlive) : nrows;
+    const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
     if (even && t0 + T <= nt) {
       // a full tile (all but a ragged last one)
       xinv_rows_full_tile<NX>(buf, bs, dh, half, nrows, nrw, nxp, nt, t0, src);
@@ -906,8 +906,8 @@ __global__ __launch_bounds__(kNudftThreads) void k_nudft_fwd(XfwdArgs A) {
   __shared__ float s_alpha;
   __shared__ double s_red[kNudftThreads / 64];
   const int it = blockIdx.x;
-  const WorkItem w = A.items[it];
-  const GatherDev G = A.gd[w.g];
+  const WorkItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
   const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
   const int nx = G.nx, nt = G.nt, nrows = G.nrows, t0 = w.b * kNudftT;
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
@@ -987,8 +987,8 @@ __global__ __launch_bounds__(kNudftThreads) void k_nudft_inv(XinvArgs A) {
   float2* buf = reinterpret_cast<float2*>(lds_raw);
   __shared__ double sh[kNudftThreads / 64];
   const int it = blockIdx.x;
-  const WorkItem w = A.items[it];
-  const GatherDev G = A.gd[w.g];
+  const WorkItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
   const int nx = G.nx, nt = G.nt, nrows = G.nrows, t0 = w.b * kNudftT;
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
   // the table transposed, [x][r]
@@ -1201,9 +1201,9 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   PanelDev pdc, pdn;  // constants of the panel whose row is in pf, and of the one after
   if constexpr (N > 0) {
     if (chunk < P) {
-      pdc = A.panels[G.panel_off + chunk];
+      pdc = load_const(A.panels + G.panel_off + chunk);
       if (r < pdc.rlive) pf.load(xrow + chunk * pstride, nt, half);
-      if (chunk + S < P) pdn = A.panels[G.panel_off + chunk + S];
+      if (chunk + S < P) pdn = load_const(A.panels + G.panel_off + chunk + S);
     }
   }
 
@@ -1219,13 +1219,13 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
       if (p + S < P) {
         pdc = pdn;
         if (r < pdc.rlive) pf.load(xrow + (p + S) * pstride, nt, half);
-        if (p + 2 * S < P) pdn = A.panels[G.panel_off + p + 2 * S];
+        if (p + 2 * S < P) pdn = load_const(A.panels + G.panel_off + p + 2 * S);
       }
       if (!live) continue;
       fft_tpl_rest_to_pairs<N, false, NT>(buf, twl, lw);
       if (r == 0) row0_separate<N, NT>(buf, ntp);
     } else {
-      PD = A.panels[G.panel_off + p];
+      PD = load_const(A.panels + G.panel_off + p);
       if (r >= PD.rlive) continue;
       row_spectrum<N, NT>(buf, xrow + p * pstride, r, nt, ntp, twl, lw);
     }
@@ -1361,13 +1361,11 @@ __global__ __launch_bounds__(row_threads(N)) __attribute__((amdgpu_waves_per_eu(
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: the map reads 16-byte pairs
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ float ctab[2 * kMaxHalfWidth], stab[2 * kMaxHalfWidth];
+  const WorkItem w = load_const(A.items + blockIdx.x);
+  const GatherDev G = load_const(A.gd + w.g);
   init_tap_trig(ctab, stab, RC > 0 ? RC : A.R);
   __syncthreads();
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const WorkItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
-    rows_fwd_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
-  }
+  rows_fwd_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
 }
 
 // Sum the panel-chunk partials of row r, complete the Hermitian time
@@ -1488,11 +1486,9 @@ template <int N>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_rows_fwd_fin(RowsArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const WorkItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
-    rows_fin_item<N, kThreads>(A, w, G, lds);
-  }
+  const WorkItem w = load_const(A.items + blockIdx.x);
+  const GatherDev G = load_const(A.gd + w.g);
+  rows_fin_item<N, kThreads>(A, w, G, lds);
 }
 
 // ------------------------------------------------------------ adjoint rows
@@ -1651,7 +1647,7 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
   // panels chunk, chunk + nchunk, ... as in the forward; rows at or above a
   // panel's live-row count get no taps and their x-spectra are not written
   for (int p = chunk; p < P; p += G.nchunk) {
-    const PanelDev PD = A.panels[G.panel_off + p];
+    const PanelDev PD = load_const(A.panels + G.panel_off + p);
     if (r >= PD.rlive) continue;
     const bool plain = (PD.n0m == 0) && (G.wav_off < 0);
     for (int k = threadIdx.x; k < ntp / 2; k += NT) reinterpret_cast<float4*>(bufM)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1780,13 +1776,11 @@ __global__ __launch_bounds__(row_threads(N)) __attribute__((amdgpu_waves_per_eu(
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: the map reads 16-byte pairs
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ float ctab[2 * kMaxHalfWidth], stab[2 * kMaxHalfWidth];
+  const WorkItem w = load_const(A.items + blockIdx.x);
+  const GatherDev G = load_const(A.gd + w.g);
   init_tap_trig(ctab, stab, RC > 0 ? RC : A.R);
   __syncthreads();
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const WorkItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
-    rows_adj_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
-  }
+  rows_adj_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
 }
 
 // ------------------------------------------------------------ launchers

@@ -16,9 +16,10 @@ namespace ashrt {
 
 __global__ __launch_bounds__(kThreads) void k_reduce_part(RedArgs A) {
   __shared__ double sh[kThreads / 64];
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const VecItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+  {
+    const int it = blockIdx.x;
+    const VecItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     const uint8_t* tm = A.tmask ? A.tmask + G.mask_off : nullptr;
     double a = 0.0, b = 0.0;
     const double eps = A.sc ? A.sc[w.g * kNScal + SC_EPS_R] : 0.0;
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce_fin(FinArgs A) {
   __shared__ double sh[kThreads / 64];
   const int g = blockIdx.x;
   if (g >= A.ngather) return;
-  const GatherDev G = A.gd[g];
+  const GatherDev G = load_const(A.gd + g);
   const int lo = A.is_model ? G.mit_lo : G.dit_lo;
   const int hi = A.is_model ? G.mit_hi : G.dit_hi;
   double a = 0.0, b = 0.0;
@@ -120,9 +121,10 @@ __global__ __launch_bounds__(kThreads) void k_reduce_fin(FinArgs A) {
 
 
 __global__ __launch_bounds__(kThreads) void k_elementwise(EwArgs A) {
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const VecItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+  {
+    const int it = blockIdx.x;
+    const VecItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     float c = 0.f;
     float c2 = 0.f;
     if (A.op == EW_AXPY || A.op == EW_XPBY || A.op == EW_WR_UPDATE || A.op == EW_WM_UPDATE)
@@ -271,12 +273,13 @@ __device__ __forceinline__ float key_float(unsigned k) {
 constexpr int kSelSplit = 2;
 __global__ __launch_bounds__(kThreads) void k_sel_hist(SelArgs A) {
   __shared__ unsigned h[2][kSelBins];
-  for (int b = blockIdx.x; b < A.nitems * kSelSplit; b += gridDim.x) {
+  {
+    const int b = blockIdx.x;
     for (int i = threadIdx.x; i < 2 * kSelBins; i += kThreads) (&h[0][0])[i] = 0u;
     __syncthreads();
     const int it = b / kSelSplit, part = b - it * kSelSplit;
-    const VecItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+    const VecItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     const SelState S = A.st[w.g];
     const unsigned hmask = (A.shift + A.width >= 32) ? 0u : (0xffffffffu << (A.shift + A.width));
     const unsigned dmask = (1u << A.width) - 1u;
@@ -388,7 +391,7 @@ __global__ __launch_bounds__(kThreads) void k_count_live(const GatherDev* gd, in
   __shared__ double sh[kThreads / 64];
   const int g = blockIdx.x;
   if (g >= ngather) return;
-  const GatherDev G = gd[g];
+  const GatherDev G = load_const(gd + g);
   double c = 0.0;
   for (int x = threadIdx.x; x < G.nx; x += kThreads) c += (tmask ? (tmask[G.mask_off + x] != 0) : 1) ? 1.0 : 0.0;
   const double r = block_sum(c, sh);
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_items(const GatherDev* gd, 
   __shared__ double sh[kSumThreads / 64];
   const int g = blockIdx.x;
   if (g >= ngather) return;
-  const GatherDev G = gd[g];
+  const GatherDev G = load_const(gd + g);
   const int lo = is_model ? G.xm_lo : G.xd_lo;
   const int hi = is_model ? G.xm_hi : G.xd_hi;
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
@@ -423,9 +426,10 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_items(const GatherDev* gd, 
 __global__ __launch_bounds__(kThreads) void k_cg(CgArgs A) {
   __shared__ float s_ab[2];
   __shared__ double sh[kThreads / 64];
-  for (int it = blockIdx.x; it < A.nitems; it += gridDim.x) {
-    const VecItem w = A.items[it];
-    const GatherDev G = A.gd[w.g];
+  {
+    const int it = blockIdx.x;
+    const VecItem w = load_const(A.items + it);
+    const GatherDev G = load_const(A.gd + w.g);
     double gsum = 0.0;
     if (A.part_gamma) {
       double part = 0.0;
