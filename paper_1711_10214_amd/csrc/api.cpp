@@ -64,6 +64,11 @@ static long long align_up(long long v, long long a) { return (v + a - 1) / a * a
 // Dynamic LDS a kernel may request (gfx950: 160 KB per workgroup, minus a
 // margin for the kernels' static LDS).
 static constexpr size_t kMaxDynLds = 150 * 1024;
+// Device memory of the allocation-free forward (see scratch below).
+static constexpr size_t kStaticScratchBytes = (size_t)96 << 20;
+// Models above this many bytes do not stay in the 256 MB last-level cache
+// between the passes that touch them.
+static constexpr double kCachedModel = 192e6;
 // Largest sum over gathers of (per-tile partials)^2 that the consuming
 // transform reduces in every workgroup (8 M doubles of cached reads per launch).
 static constexpr double kInKernelSumLimit = 8.0 * 1024 * 1024;
@@ -275,7 +280,19 @@ struct ashrt_batch_plan {
   PlanImpl impl;
 };
 
-static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost* gh) {
+// Time columns per model x-FFT workgroup.  8 columns (32-byte pieces of a
+// trace) give small tiles, so many workgroups and loads in flight: 256 x 64 x 8
+// panels 37 us per operator pair against 45 us at 64 columns, 1024 x 256 x 32
+// 157 against 166 us at 16.  Models that outgrow the last-level cache pay for
+// short pieces in memory traffic and take 16 (1024 x 256 x 384 CG solve 43.7
+// against 46.6 ms; 24 uneven gathers 59.9 against 61.5 ms).  Long transforms
+// take what keeps about 35 KB of LDS per workgroup.
+static int model_tile(int nxp, bool big_model) {
+  const int fit = std::max(2, 2 * (kXfftTilePoints / nxp));
+  return big_model && nxp <= 768 ? 16 : std::max(2, std::min(8, fit) & ~1);
+}
+
+static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, bool big_model, GatherHost* gh) {
   int st = resolve_desc(d, &gh->z);
   if (st) return st;
   const Resolved& z = gh->z;
@@ -283,8 +300,7 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost*
   if (tn && ((tn->tile_model < 0 || (tn->tile_model & 1)) || (tn->tile_data < 0 || (tn->tile_data & 1)) ||
              tn->nchunk < 0))
     return fail(ASHRT_E_INVALID_ARG, "tile sizes must be even (or 0) and nchunk >= 0");
-  int T = std::min(64, 2 * (kXfftTilePoints / z.nxp));
-  T = std::max(2, T & ~1);
+  int T = model_tile(z.nxp, big_model);
   if (tn && tn->tile_model > 0) T = tn->tile_model;
   gh->tileT = T;
   gh->ntiles = (z.nt + T - 1) / T;
@@ -326,6 +342,29 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, GatherHost*
     for (int j = 0; j <= z.ntp / 2; ++j) gh->wav[j] = (float)d->wavelet_amp[j];
   }
   return ASHRT_OK;
+}
+
+// Panel chunks per wavenumber row: the row passes' workgroups should fill a
+// whole number k of rounds of the resident ones (4 per CU, 2 of the long rows).
+// A chunk costs about 0.7 panels by itself (its partial sums, the adjoint's
+// data transform); more rounds balance better (a tenth of the time in one).
+// Measured per operator pair: 192 rows x 24 panels, 5 chunks (0.94 rounds) 149
+// us, 6 (1.1 rounds) 154; 384 long rows x 24, 4 chunks (3 rounds) 337 us, 3 (2.3
+// rounds) 348; 256 rows x 96, 8 chunks (2 rounds) 390 us, 4 (1 round) 405; x 32, 4
+// chunks 158 us, 8 chunks 168.
+static int row_chunks(long long rows, int panels, int resident) {
+  int best = 1;
+  double best_score = 0.0;
+  for (int k = 1; k <= 3; ++k) {
+    const long long c = std::max(1LL, std::min<long long>((long long)k * resident / rows, panels));
+    const double rounds = (double)(c * rows) / resident;
+    const double score = rounds / std::ceil(rounds) / ((1.0 + 0.7 * c / panels) * (1.0 + 0.1 / std::ceil(rounds)));
+    if (score > best_score) {
+      best_score = score;
+      best = (int)c;
+    }
+  }
+  return best;
 }
 
 // Estimated work of a panel chunk of each wavenumber row (all chunks of a row
@@ -394,7 +433,6 @@ static void destroy_impl(PlanImpl& P) {
 // a device address: kernels get the address from hipGetSymbolAddress,
 // resolved once per device (with that device current) when a plan is
 // created there, and kept in g_scratch.
-constexpr size_t kStaticScratchBytes = (size_t)96 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 static std::mutex g_scratch_mu;
@@ -422,8 +460,11 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   P.device = device;
   P.ngather = ngather;
   P.g.resize(ngather);
+  double model_bytes = 0.0;
+  for (int i = 0; i < ngather; ++i) model_bytes += 4.0 * descs[i].npanel * (double)descs[i].nx * descs[i].nt;
+  const bool big_model = model_bytes > kCachedModel;
   for (int i = 0; i < ngather; ++i) {
-    int st = build_gather(&descs[i], tn, &P.g[i]);
+    int st = build_gather(&descs[i], tn, big_model, &P.g[i]);
     if (st) return st;
   }
   P.R = P.g[0].z.R;
@@ -431,13 +472,24 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     if (gh.z.R != P.R) return fail(ASHRT_E_INVALID_ARG, "all gathers of a batch must share half_width");
 
   // panel chunks so that the row passes have enough workgroups
-  long long total_rows = 0;
-  for (auto& gh : P.g) total_rows += gh.nrows;
+  long long total_rows = 0, dp1 = 0, x_h = 0;
+  bool all_long = true;
+  int max_panels = 1;
   for (auto& gh : P.g) {
-    long long want = (1024 + total_rows - 1) / total_rows;
-    if (tn && tn->nchunk > 0) want = tn->nchunk;
-    gh.nchunk = (int)std::max(1LL, std::min<long long>(want, gh.z.P));
+    total_rows += gh.nrows;
+    all_long = all_long && rows_size_is_tpl(gh.z.ntp, gh.z.R) && row_threads(gh.z.ntp) > kRowThreads;
+    max_panels = std::max(max_panels, gh.z.P);
+    dp1 += (long long)gh.nrows * 2 * (gh.z.jhi - gh.z.jlo + 1) * 8;
+    x_h += ((long long)gh.z.P + 1) * gh.nrows * gh.z.nt * 8;
   }
+  long long want = row_chunks(total_rows, max_panels, all_long ? 512 : 1024);
+  const long long least = (1024 + total_rows - 1) / total_rows;
+  // (a forward that fits the static scratch with the smaller count keeps fitting)
+  if (want > least && x_h + want * dp1 + 1024 > (long long)kStaticScratchBytes &&
+      x_h + least * dp1 <= (long long)kStaticScratchBytes)
+    want = least;
+  if (tn && tn->nchunk > 0) want = tn->nchunk;
+  for (auto& gh : P.g) gh.nchunk = (int)std::max(1LL, std::min<long long>(want, gh.z.P));
 
   // packed offsets
   long long od = 0, om = 0, omask = 0, oX = 0, oH = 0, oDp = 0;

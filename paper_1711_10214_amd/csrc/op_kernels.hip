@@ -1383,85 +1383,63 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
   stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
   RowTw<N, NT> lw;
   lw.load(A.tw + G.twp_t_off);
-  // time-spectrum bin k of the row: the chunk sums, Hermitian completion.
-  // Branch-free (bins outside the band read the band's first entry and are
-  // zeroed by a select), so the loads of all of a thread's bins can be in
-  // flight together.
+  // The band's bins, one thread each: sum the chunks (all loads of a group of
+  // kFinChunks chunks and kFinBins bins in flight together) and write the
+  // bin and its mirror; the bins outside the band are zero.
+  const int nchunk = G.nchunk;
   const float2* __restrict__ dp0 = A.Dp + uniform64(G.Dp_off + (long long)r * 2 * nband);
   const long long cstride = uniform64((long long)nrows * 2 * nband);
-  auto bin = [&](int k) {
-    const bool up = k >= jlo && k <= jhi;
-    const bool dn = !up && ntp - k >= jlo && ntp - k <= jhi;
-    const int jj = (up ? k : (dn ? ntp - k : jlo)) - jlo;
-    float2 su = make_float2(0.f, 0.f), sl = make_float2(0.f, 0.f);
-    for (int c = 0; c < G.nchunk; ++c) {
-      su = cadd(su, dp0[c * cstride + jj]);
-      sl = cadd(sl, dp0[c * cstride + nband + jj]);
+  auto zero = [&](int k) { buf[px<N>(k)] = make_float2(0.f, 0.f); };
+  for (int k = threadIdx.x; k < jlo; k += NT) {
+    zero(k);
+    if (k > 0) zero(ntp - k);
+  }
+  for (int k = jhi + 1 + (int)threadIdx.x; k <= ntp - jhi - 1; k += NT) zero(k);
+  constexpr int kFinBins = 4, kFinChunks = 4;
+  for (int i0 = threadIdx.x; i0 < nband; i0 += kFinBins * NT) {
+    float2 su[kFinBins], sl[kFinBins];
+#pragma unroll
+    for (int u = 0; u < kFinBins; ++u) su[u] = sl[u] = make_float2(0.f, 0.f);
+    for (int c = 0; c < nchunk; c += kFinChunks) {
+      float2 lu[kFinChunks][kFinBins], ld[kFinChunks][kFinBins];
+#pragma unroll
+      for (int cc = 0; cc < kFinChunks; ++cc) {
+        const float2* __restrict__ dpc = dp0 + min(c + cc, nchunk - 1) * cstride;
+#pragma unroll
+        for (int u = 0; u < kFinBins; ++u) {
+          const unsigned o = 8u * (unsigned)min(i0 + u * NT, nband - 1);
+          lu[cc][u] = at_byte<float2>(dpc, o);
+          ld[cc][u] = at_byte<float2>(dpc + nband, o);
+        }
+      }
+#pragma unroll
+      for (int cc = 0; cc < kFinChunks; ++cc) {
+        if (c + cc < nchunk) {
+#pragma unroll
+          for (int u = 0; u < kFinBins; ++u) {
+            su[u] = cadd(su[u], lu[cc][u]);
+            sl[u] = cadd(sl[u], ld[cc][u]);
+          }
+        }
+      }
     }
-    const float2 vu = (r == 0) ? make_float2(su.x - sl.y, su.y + sl.x) : su;
-    const float2 vd = (r == 0) ? make_float2(su.x + sl.y, -su.y + sl.x) : cconj(sl);
-    return up ? vu : (dn ? vd : make_float2(0.f, 0.f));
-  };
+#pragma unroll
+    for (int u = 0; u < kFinBins; ++u) {
+      const int k = jlo + i0 + u * NT;
+      if (k > jhi) break;
+      const float2 vu = (r == 0) ? make_float2(su[u].x - sl[u].y, su[u].y + sl[u].x) : su[u];
+      const float2 vd = (r == 0) ? make_float2(su[u].x + sl[u].y, -su[u].y + sl[u].x) : cconj(sl[u]);
+      buf[px<N>(k)] = vu;
+      buf[px<N>(ntp - k)] = vd;
+    }
+  }
+  __syncthreads();
   const float inv = 1.0f / (float)ntp;
   float2* __restrict__ dst = A.H + G.H_off + (long long)r * nt;
   if constexpr (N > 0) {
-    // first pass from registers, last pass to global memory
-    // the chunk loop outside, the thread's bins inside: all of a chunk's
-    // loads are issued together
-    using I = FftRegsIn<N, NT>;
-    I in;
-    float2 sl[I::MAXB][I::R];
-    int jj[I::MAXB][I::R];
-#pragma unroll
-    for (int i = 0; i < I::MAXB; ++i) {
-#pragma unroll
-      for (int q = 0; q < I::R; ++q) {
-        const int k = min((int)threadIdx.x + i * NT, I::B - 1) + q * I::B;
-        const bool up = k >= jlo && k <= jhi;
-        const bool dn = !up && ntp - k >= jlo && ntp - k <= jhi;
-        jj[i][q] = 8 * ((up ? k : (dn ? ntp - k : jlo)) - jlo);  // byte offset
-        in.v[i][q] = make_float2(0.f, 0.f);
-        sl[i][q] = make_float2(0.f, 0.f);
-      }
-    }
-    for (int c = 0; c < G.nchunk; ++c) {
-      const float2* __restrict__ dpc = dp0 + c * cstride;
-      float2 lu[I::MAXB][I::R], ld[I::MAXB][I::R];
-#pragma unroll
-      for (int i = 0; i < I::MAXB; ++i) {
-#pragma unroll
-        for (int q = 0; q < I::R; ++q) {
-          lu[i][q] = at_byte<float2>(dpc, (unsigned)jj[i][q]);
-          ld[i][q] = at_byte<float2>(dpc + nband, (unsigned)jj[i][q]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < I::MAXB; ++i) {
-#pragma unroll
-        for (int q = 0; q < I::R; ++q) {
-          in.v[i][q] = cadd(in.v[i][q], lu[i][q]);
-          sl[i][q] = cadd(sl[i][q], ld[i][q]);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < I::MAXB; ++i) {
-      const int id = (int)threadIdx.x + i * NT;
-#pragma unroll
-      for (int q = 0; q < I::R; ++q) {
-        const int k = id + q * I::B;
-        const bool up = k >= jlo && k <= jhi;
-        const bool dn = !up && ntp - k >= jlo && ntp - k <= jhi;
-        const float2 su = in.v[i][q], sd = sl[i][q];
-        const float2 vu = (r == 0) ? make_float2(su.x - sd.y, su.y + sd.x) : su;
-        const float2 vd = (r == 0) ? make_float2(su.x + sd.y, -su.y + sd.x) : cconj(sd);
-        in.v[i][q] = (id < I::B && up) ? vu : ((id < I::B && dn) ? vd : make_float2(0.f, 0.f));
-      }
-    }
-    fft_tpl_regs_pass0<N, true, NT>(buf, in);
     using O = FftRegsOut<N, NT>;
     O o;
-    fft_tpl_passes_to_regs<N, true, NT, 1, false>(buf, twl, lw, o);
+    fft_tpl_passes_to_regs<N, true, NT, 0, false>(buf, twl, lw, o);
 #pragma unroll
     for (int i = 0; i < O::MAXB; ++i) {
       const int id = (int)threadIdx.x + i * NT;
@@ -1472,12 +1450,9 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
       }
     }
   } else {
-    for (int k = threadIdx.x; k < ntp; k += NT) buf[px<N>(k)] = bin(k);
-    __syncthreads();
     fft_lds<NT, kRowMaxN, true>(buf, ntp, 1, ntp, twl);
     for (int t = threadIdx.x; t < nt; t += NT) dst[t] = cscale(buf[px<N>(t)], inv);
   }
-  __syncthreads();
 }
 
 template <int N>
