@@ -25,7 +25,7 @@ namespace ashrt {
 
 constexpr int kBlendTile = 4 * kThreads;  // record samples per workgroup
 constexpr int kBlendList = 1024;          // sources tested at a time
-constexpr int kBlendRows = 8;             // receivers per workgroup
+constexpr int kBlendRows = 8;             // most receivers per workgroup
 
 __device__ __forceinline__ float4 load4(const float* p) {
   float4 v;
@@ -35,7 +35,8 @@ __device__ __forceinline__ float4 load4(const float* p) {
 __device__ __forceinline__ void store4(float* p, float4 v) { __builtin_memcpy(p, &v, 16); }
 
 __global__ __launch_bounds__(kThreads) void k_blend(const float* __restrict__ D, int ns, int nr, int nt,
-                                                   const int* __restrict__ fire, float* __restrict__ b, int nrec) {
+                                                   const int* __restrict__ fire, float* __restrict__ b, int nrec,
+                                                   int rows) {
   __shared__ int src[kBlendList], at[kBlendList];
   __shared__ int wsum[kThreads / 64];
   const int lo = (int)blockIdx.x * kBlendTile, hi = min(nrec - lo, kBlendTile);  // samples lo .. lo + hi - 1
@@ -66,8 +67,8 @@ __global__ __launch_bounds__(kThreads) void k_blend(const float* __restrict__ D,
       n += all;
       __syncthreads();
     }
-    for (int rb = (int)blockIdx.y; left > 0 && rb * kBlendRows < nr; rb += gridDim.y)
-    for (int r = rb * kBlendRows; r < min(nr, (rb + 1) * kBlendRows); ++r) {
+    for (int rb = (int)blockIdx.y; left > 0 && rb * rows < nr; rb += gridDim.y)
+    for (int r = rb * rows; r < min(nr, (rb + 1) * rows); ++r) {
       float* __restrict__ out = b + (long long)r * nrec + tau;
       if (left >= 4) {
         float4 acc = s0 ? load4(out) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -161,9 +162,11 @@ static hipError_t quad_launch(int nj, int nt, int no, F&& f) {
 }
 
 hipError_t launch_blend(const float* D, int ns, int nr, int nt, const int* fire, float* b, int nrec, hipStream_t s) {
-  const dim3 g((unsigned)((nrec + (long long)kBlendTile - 1) / kBlendTile),
-               (unsigned)std::min((nr - 1) / kBlendRows + 1, 65535));
-  hipLaunchKernelGGL(k_blend, g, dim3(kThreads), 0, s, D, ns, nr, nt, fire, b, nrec);
+  // receivers share a workgroup's source list while enough workgroups remain
+  const long long tiles = (nrec + (long long)kBlendTile - 1) / kBlendTile;
+  const int rows = (int)std::max(1LL, std::min<long long>(kBlendRows, tiles * nr / 1024));
+  hipLaunchKernelGGL(k_blend, dim3((unsigned)tiles, (unsigned)std::min((nr - 1) / rows + 1, 65535)), dim3(kThreads), 0, s,
+                     D, ns, nr, nt, fire, b, nrec, rows);
   return hipGetLastError();
 }
 
