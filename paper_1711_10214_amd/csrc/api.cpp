@@ -221,6 +221,7 @@ struct PlanImpl {
   struct Seg {
     int key, first, count;
     size_t lds;
+    bool half;  // rows: every gather's rows are at most half as long as their transform
   };
   std::vector<Seg> s_xm, s_xd, s_rf, s_rfin, s_ra;
   VecItem *d_vm = nullptr, *d_vd = nullptr;
@@ -666,7 +667,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     return (size_t)fft_tw_slots(x_size_is_tpl(gh.z.nxp) ? gh.z.nxp : 0, gh.z.nxp);
   };
   auto twt_of = [](const GatherHost& gh) {
-    return (size_t)fft_tw_slots(rows_size_is_tpl(gh.z.ntp, gh.z.R) ? gh.z.ntp : 0, gh.z.ntp);
+    return (size_t)fft_row_tw_slots(rows_size_is_tpl(gh.z.ntp, gh.z.R) ? gh.z.ntp : 0, gh.z.ntp);
   };
   auto lds_x_of = [&](const GatherHost& gh) {
     return twx_of(gh) * 8 + (size_t)(gh.tileT / 2) * xstride(gh) * 8;
@@ -686,17 +687,20 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     return (twt_of(gh) + kMapGuardSlots + plen_of(gh)) * 8 + nband_of(gh) * 16;
   };
   auto lds_fin_of = [&](const GatherHost& gh) { return (twt_of(gh) + plen_of(gh)) * 8; };
-  auto lds_ra_of = [&](const GatherHost& gh) { return (twt_of(gh) + 2 * plen_of(gh)) * 8; };
+  auto lds_ra_of = [&](const GatherHost& gh) {
+    return (twt_of(gh) + plen_of(gh)) * 8 + (nband_of(gh) + kMapGuardPairs) * 16;
+  };
   // work lists grouped by kernel instantiation; a gather's items stay contiguous
   auto build_segments = [&](const std::vector<int>& keys, std::vector<PlanImpl::Seg>& segs,
                             std::vector<WorkItem>& items, auto&& add_items, auto&& lds_of) {
     std::map<int, std::vector<int>> by_key;
     for (int gi = 0; gi < ngather; ++gi) by_key[keys[gi]].push_back(gi);
     for (auto& kv : by_key) {
-      PlanImpl::Seg sg{kv.first, (int)items.size(), 0, 0};
+      PlanImpl::Seg sg{kv.first, (int)items.size(), 0, 0, true};
       for (int gi : kv.second) {
         add_items(gi);
         sg.lds = std::max(sg.lds, (size_t)lds_of(P.g[gi]));
+        sg.half = sg.half && 2 * P.g[gi].z.nt <= P.g[gi].z.ntp;
       }
       sg.count = (int)items.size() - sg.first;
       if (sg.count > 0) segs.push_back(sg);
@@ -1083,7 +1087,7 @@ hipError_t run_forward(const Ctx& c, const float* m, const float* mul_m, float* 
   }
   for (const auto& sg : P.s_rf) {
     e = timed(ASHRT_K_ROWS_FWD, c.s,
-              [&] { return launch_rows_fwd(sg.key, rows_args(c, P.d_rf + sg.first, sg.count), sg.lds, c.s); });
+              [&] { return launch_rows_fwd(sg.key, sg.half, rows_args(c, P.d_rf + sg.first, sg.count), sg.lds, c.s); });
     if (e != hipSuccess) return e;
   }
   for (const auto& sg : P.s_rfin) {

@@ -17,12 +17,14 @@ constexpr int kRowThreads = 256;       // threads per workgroup of the forward/a
 // workgroup (two per CU): they run 512 threads (8 waves) so that each SIMD
 // still holds four waves; shorter lengths run kRowThreads.
 constexpr int row_threads(int n) { return n >= 3072 ? 512 : kRowThreads; }
-// Compile-time row kernels fit four waves per SIMD in LDS (four 256-thread or
-// two 512-thread workgroups per CU); they are held to the 128 VGPRs that
-// allows.  Generic lengths keep their registers.
-constexpr int row_waves_per_eu(int n) { return n > 0 ? 4 : 1; }
+// Compile-time row kernels of 256 threads are held to the 96 VGPRs that let
+// five waves per SIMD run (their LDS, up to 31 KB at 2048 points and a 100 Hz
+// band at 4 ms, lets five workgroups share a CU); the 512-thread ones to the 128
+// of four.  Generic lengths keep their registers.
+constexpr int row_waves_per_eu(int n) { return n == 0 ? 1 : (row_threads(n) > kRowThreads ? 4 : 5); }
 constexpr int kMaxHalfWidth = 8;       // interpolation half-width R supported
 constexpr int kMapGuardSlots = 6;      // zero float2 slots in front of the forward map's spectrum (taps k >= -3)
+constexpr int kMapGuardPairs = 8;      // zero-weight pairs in front of the adjoint map's spectrum (taps k >= -3; sink)
 constexpr int kRowMaxN = 4096;         // longest time FFT (ntp) the row kernels take
 constexpr int kXLoadBatch = 4;        // x kernels: tile-loop iterations whose global loads are issued together
 constexpr int kXfftTilePoints = 4096;  // complex points of a model x-FFT tile (T = 2 * this / nxp columns)

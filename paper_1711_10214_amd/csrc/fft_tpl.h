@@ -109,10 +109,12 @@ struct FftPlan {
 constexpr double kTwMinCos = 1.0 / 268435456.0;
 
 // LDS slots of the staged twiddles in front of an FFT buffer, an even count
-// (what follows stays 16-byte aligned): the pass table without its last pass
-// (whose twiddles depend on the thread alone and stay in registers), or the
-// plain n-entry table of the generic runtime FFT (key 0).
+// (what follows stays 16-byte aligned): the pass table without the last pass
+// (the x transforms) or the last two (the row transforms), whose twiddles
+// depend on the thread alone and stay in registers, or the plain n-entry
+// table of the generic runtime FFT (key 0).
 inline __host__ __device__ int fft_tw_slots(int key, int n);
+inline __host__ __device__ int fft_row_tw_slots(int key, int n);
 
 // Host and device: pass-table length for a runtime N of a supported size
 // (0 for lengths handled by the generic runtime FFT).
@@ -136,6 +138,13 @@ inline __host__ __device__ int fft_tpl_twstaged(int n) {
 }
 
 inline __host__ __device__ int fft_tw_slots(int key, int n) { return key > 0 ? (fft_tpl_twstaged(key) + 1) & ~1 : n; }
+inline __host__ __device__ int fft_row_tw_slots(int key, int n) {
+#define ASHRT_TW_CASE(S) \
+  if (key == S) return (FftPlan<S>::twoff(FftPlan<S>::npass - 2) + 1) & ~1;
+  ASHRT_TPL_SIZES(ASHRT_TW_CASE)
+#undef ASHRT_TW_CASE
+  return n;
+}
 
 // One butterfly's twiddles as (cos, tan) pairs: radix 8 (w^4, w^2, w,
 // w e^(-i pi/4)), radix 4 (w^2, w), radix 2 (w).
@@ -240,20 +249,19 @@ __device__ __forceinline__ void dft_r(float2 (&v)[R]) {
   else butterfly<R, INV>(v);
 }
 
-// The last pass's twiddles of a batch of NBN / N length-N transforms by NT
+// One pass's twiddles of a batch of NBN / N length-N transforms by NT
 // threads, for the butterflies threadIdx.x + i NT: they depend on the thread
 // alone, so a kernel loads them once and uses them for every transform.
-template <int N, int NT, int NBN = N>
-struct LastTw {
-  static constexpr int L = FftPlan<N>::npass - 1;
-  static constexpr int R = FftPlan<N>::radix(L);
-  static constexpr int B = N / R;
+template <int N, int NT, int NBN, int PASS>
+struct PassTw {
+  static constexpr int R = FftPlan<N>::radix(PASS);
+  static constexpr int Ns = FftPlan<N>::ns(PASS);
   static constexpr int MAXB = (NBN / R + NT - 1) / NT;
-  static_assert(L >= 1 && FftPlan<N>::ns(L) == B, "the last pass spans N/R");
   Tw<R> w[MAXB];
   __device__ __forceinline__ void load(const float2* __restrict__ tab) {
 #pragma unroll
-    for (int i = 0; i < MAXB; ++i) w[i].load(tab + FftPlan<N>::twoff(L), B, (int)(threadIdx.x + i * NT) % B);
+    for (int i = 0; i < MAXB; ++i)
+      w[i].load(tab + FftPlan<N>::twoff(PASS), Ns, (int)((threadIdx.x + i * NT) % (N / R)) % Ns);
   }
   // Waits for the loads and keeps the values in registers: without this the
   // compiler may load them again at every use.
@@ -262,6 +270,26 @@ struct LastTw {
     for (int i = 0; i < MAXB; ++i)
 #pragma unroll
       for (int q = 0; q < R / 2; ++q) asm volatile("" : "+v"(w[i].w[q].x), "+v"(w[i].w[q].y));
+  }
+};
+
+// The register twiddles of a transform: its last pass (FIRST = npass - 1) or
+// its last two (FIRST = npass - 2), the earlier passes reading LDS.
+template <int N, int NT, int NBN = N, int REGS = 1>
+struct RegTw {
+  static constexpr int L = FftPlan<N>::npass - 1;
+  static constexpr int FIRST = L + 1 - REGS;
+  static_assert(FIRST >= 1, "the first pass has no twiddles");
+  static_assert(FftPlan<N>::ns(L) * FftPlan<N>::radix(L) == N, "the last pass spans N");
+  PassTw<N, NT, NBN, L> last;
+  PassTw<N, NT, NBN, FIRST> prev;  // FIRST == L: unused
+  __device__ __forceinline__ void load(const float2* __restrict__ tab) {
+    last.load(tab);
+    if constexpr (REGS == 2) prev.load(tab);
+  }
+  __device__ __forceinline__ void pin() {
+    last.pin();
+    if constexpr (REGS == 2) prev.pin();
   }
 };
 
@@ -289,10 +317,10 @@ __device__ __forceinline__ void pair_put(float2* buf, int o, float2 v) {
 // never read); IO = 4: outputs at index >= nvalid are dropped; IO = 0:
 // padded layout both ways.  Reads complete before the barrier and writes
 // follow it, so the layouts may share memory.
-// lw: the last pass's twiddles in registers.
-template <int N, int PASS, int NBN, bool INV, int NT = kThreads, int IO = 0>
+// lw: the last passes' twiddles in registers (RegTw).
+template <int N, int PASS, int NBN, bool INV, int NT, int IO, class LW>
 __device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
-                                         const LastTw<N, NT, NBN>& lw) {
+                                         const LW& lw) {
   using P = FftPlan<N>;
   constexpr int R = P::radix(PASS);
   constexpr int Ns = P::ns(PASS);
@@ -343,7 +371,8 @@ __device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const
       }
       if constexpr (Ns > 1) {
         Tw<R> w;
-        if constexpr (PASS == P::npass - 1) w = lw.w[i];
+        if constexpr (PASS == P::npass - 1) w = lw.last.w[i];
+        else if constexpr (PASS >= LW::FIRST) w = lw.prev.w[i];
         else w.load(twp + TW, Ns, jm);
         dft_tw<R, INV>(v[i], w);
       } else {
@@ -401,9 +430,9 @@ __device__ __forceinline__ void tpl_pass(float2* buf, int nb, int bstride, const
 // pass reads only indices < nvalid (the rest is zero); MASK_OUT: the last
 // pass writes only indices < nvalid.
 template <int N, int PASS, int NBN, bool INV, int NT, bool PAIRS_IN = false, bool PAIRS_OUT = false,
-          int END = FftPlan<N>::npass, bool MASK_IN = false, bool MASK_OUT = false>
+          int END = FftPlan<N>::npass, bool MASK_IN = false, bool MASK_OUT = false, class LW>
 __device__ __forceinline__ void tpl_passes(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
-                                           const LastTw<N, NT, NBN>& lw) {
+                                           const LW& lw) {
   if constexpr (PASS < END) {
     constexpr bool last = PASS == FftPlan<N>::npass - 1;
     constexpr int IO = (PAIRS_IN && PASS == 0)   ? 1
@@ -422,43 +451,43 @@ __device__ __forceinline__ void tpl_passes(float2* buf, int nb, int bstride, con
 // Full transform(s) of inputs that are zero at index >= nvalid (MASK_IN:
 // those slots are never read, so they need not be filled) or of which only
 // outputs < nvalid are wanted (MASK_OUT: the others are not written).
-template <int N, int NBN, bool INV, bool MASK_IN, bool MASK_OUT, int NT = kThreads>
+template <int N, int NBN, bool INV, bool MASK_IN, bool MASK_OUT, int NT = kThreads, class LW>
 __device__ __forceinline__ void fft_tpl_masked(float2* buf, int nb, int bstride, const float2* twp, int nvalid,
-                                               const LastTw<N, NT, NBN>& lw) {
+                                               const LW& lw) {
   tpl_passes<N, 0, NBN, INV, NT, false, false, FftPlan<N>::npass, MASK_IN, MASK_OUT>(buf, nb, bstride, twp, nvalid,
                                                                                     lw);
 }
 
 // One transform of length N whose output is left in the pair layout.
-template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_to_pairs(float2* buf, const float2* twp, const LastTw<N, NT>& lw) {
+template <int N, bool INV, int NT, class LW>
+__device__ __forceinline__ void fft_tpl_to_pairs(float2* buf, const float2* twp, const LW& lw) {
   tpl_passes<N, 0, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp, N, lw);
 }
 
 // First-pass inputs of a length-N transform held in registers: the
 // butterfly with id = threadIdx.x + i NT takes x[id + r N/R0], r < R0 (R0 the
 // first radix), so a caller can load them straight from global memory.
-template <int N, int NT>
+// HALF (radix-8 first passes): rows at most N/2 long, the default padding;
+// the inputs r >= R0/2 are zero, and neither held, loaded nor added.
+template <int N, int NT, bool HALF>
 struct FftRegsIn {
   static constexpr int R = FftPlan<N>::radix(0);
   static constexpr int B = N / R;
   static constexpr int MAXB = (B + NT - 1) / NT;
+  static constexpr int RIN = HALF ? R / 2 : R;
   static_assert(FftPlan<N>::npass >= 2, "register input needs a later pass to write the pair layout");
-  // rows at most half as long as the transform (the default padding): inputs
-  // r >= R/2 of a radix-8 butterfly are zero, neither loaded nor added
-  static constexpr bool CAN_HALF = R == 8;
-  float2 v[MAXB][R];
-  // x[t] = src[t] for t < nt, zero after (half: nt <= N/2, inputs r < R/2 only;
-  // wave-uniform)
-  __device__ __forceinline__ void load(const float2* __restrict__ src, int nt, bool half) {
+  static_assert(!HALF || R == 8, "half inputs need a radix-8 first pass");
+  float2 v[MAXB][RIN];
+  // x[t] = src[t] for t < nt, zero after (HALF: nt <= N/2)
+  __device__ __forceinline__ void load(const float2* __restrict__ src, int nt) {
     const int tid = pass_tid();
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (CAN_HALF && r == R / 2 && half) return;
+    for (int i = 0; i < MAXB; ++i) {
+      const int id = tid + i * NT;
 #pragma unroll
-      for (int i = 0; i < MAXB; ++i) {
-        const int t = tid + i * NT + r * B;
-        v[i][r] = ((B % NT == 0 || tid + i * NT < B) && t < nt) ? src[t] : make_float2(0.f, 0.f);
+      for (int r = 0; r < RIN; ++r) {
+        const int t = id + r * B;
+        v[i][r] = ((B % NT == 0 || id < B) && t < nt) ? src[t] : make_float2(0.f, 0.f);
       }
     }
   }
@@ -468,9 +497,9 @@ struct FftRegsIn {
 // there: its span is 1) and whose output is left in the pair layout, in two
 // calls: regs_pass0 (the caller must have finished every read of buf; the
 // registers are free again when it returns) and rest_to_pairs.
-template <int N, bool INV, int NT, bool HALF = false>
-__device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, const FftRegsIn<N, NT>& in) {
-  using I = FftRegsIn<N, NT>;
+template <int N, bool INV, int NT, bool HALF>
+__device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, const FftRegsIn<N, NT, HALF>& in) {
+  using I = FftRegsIn<N, NT, HALF>;
   const int tid = pass_tid();
 #pragma unroll
   for (int i = 0; i < I::MAXB; ++i) {
@@ -478,8 +507,7 @@ __device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, const FftRegsIn<
     if (I::B % NT == 0 || id < I::B) {
       float2 v[I::R];
 #pragma unroll
-      for (int r = 0; r < I::R; ++r)
-        if (!HALF || r < I::R / 2) v[r] = in.v[i][r];
+      for (int r = 0; r < I::RIN; ++r) v[r] = in.v[i][r];
       if constexpr (HALF) dft8<INV, true>(v);
       else dft_r<I::R, INV>(v);
       constexpr bool LIN = pad_linear(1, I::R, I::R, 1);
@@ -494,8 +522,8 @@ __device__ __forceinline__ void fft_tpl_regs_pass0(float2* buf, const FftRegsIn<
   __syncthreads();
 }
 
-template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_rest_to_pairs(float2* buf, const float2* twp, const LastTw<N, NT>& lw) {
+template <int N, bool INV, int NT, class LW>
+__device__ __forceinline__ void fft_tpl_rest_to_pairs(float2* buf, const float2* twp, const LW& lw) {
   tpl_passes<N, 1, N, INV, NT, false, true>(buf, 1, fft_padlen(N), twp, N, lw);
 }
 
@@ -517,8 +545,8 @@ struct FftRegsOut {
 // PAIRS_IN, for FIRST == 0) whose last pass leaves its outputs in
 // registers; buf may be reused once every thread has passed a barrier after
 // this returns.
-template <int N, bool INV, int NT, int FIRST, bool PAIRS_IN>
-__device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2* twp, const LastTw<N, NT>& lw,
+template <int N, bool INV, int NT, int FIRST, bool PAIRS_IN, class LW>
+__device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2* twp, const LW& lw,
                                                        FftRegsOut<N, NT>& out) {
   using O = FftRegsOut<N, NT>;
   static_assert(!PAIRS_IN || FIRST == 0, "only the first pass reads pairs");
@@ -532,15 +560,15 @@ __device__ __forceinline__ void fft_tpl_passes_to_regs(float2* buf, const float2
       const float2* s0 = buf + fft_pad(id);
 #pragma unroll
       for (int r = 0; r < O::R; ++r) out.v[i][r] = LIN ? s0[fft_pad(r * O::B)] : buf[fft_pad(id + r * O::B)];
-      dft_tw<O::R, INV>(out.v[i], lw.w[i]);
+      dft_tw<O::R, INV>(out.v[i], lw.last.w[i]);
     }
   }
 }
 
 // Transform whose input is read from the pair layout (bins 0 and N/2 taken
 // as zero) and whose last pass leaves its outputs in registers.
-template <int N, bool INV, int NT>
-__device__ __forceinline__ void fft_tpl_from_pairs_to_regs(float2* buf, const float2* twp, const LastTw<N, NT>& lw,
+template <int N, bool INV, int NT, class LW>
+__device__ __forceinline__ void fft_tpl_from_pairs_to_regs(float2* buf, const float2* twp, const LW& lw,
                                                            FftRegsOut<N, NT>& out) {
   fft_tpl_passes_to_regs<N, INV, NT, 0, true>(buf, twp, lw, out);
 }

@@ -209,7 +209,8 @@ hipError_t launch_resort(const float* in, int na, int nb, int nt, float* out, hi
 bool x_size_is_tpl(int n);
 hipError_t launch_xfft_fwd(int key, const XfwdArgs& a, size_t lds, hipStream_t s);
 hipError_t launch_xfft_inv(int key, const XinvArgs& a, size_t lds, hipStream_t s);
-hipError_t launch_rows_fwd(int key, const RowsArgs& a, size_t lds, hipStream_t s);
+// half: every gather's rows are at most half as long as their transform
+hipError_t launch_rows_fwd(int key, bool half, const RowsArgs& a, size_t lds, hipStream_t s);
 hipError_t launch_rows_fwd_fin(int key, const RowsArgs& a, size_t lds, hipStream_t s);
 hipError_t launch_rows_adj(int key, const RowsArgs& a, size_t lds, hipStream_t s);
 hipError_t op_kernels_init(size_t max_lds);

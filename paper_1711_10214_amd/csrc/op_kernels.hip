@@ -253,29 +253,29 @@ __device__ __forceinline__ float2 bin_factor(const GatherDev& G, const PanelDev&
 
 // ------------------------------------------------------------ FFT dispatch
 // Copy the twiddles an FFT of length n needs into LDS (pass table without
-// its last pass for the compile-time lengths, plain table otherwise).  No
-// barrier.
-template <int N, int NT = kThreads>
+// its last REGS passes for the compile-time lengths, plain table otherwise).
+// No barrier.
+template <int N, int NT = kThreads, int REGS = 1>
 __device__ __forceinline__ void stage_twiddles(float2* dst, const float2* __restrict__ tw, int plain_off,
                                                int pass_off, int n) {
   if constexpr (N > 0) {
-    constexpr int ntw = FftPlan<N>::twoff(FftPlan<N>::npass - 1);
+    constexpr int ntw = FftPlan<N>::twoff(FftPlan<N>::npass - REGS);
     for (int i = threadIdx.x; i < ntw; i += NT) dst[i] = tw[pass_off + i];
   } else {
     for (int i = threadIdx.x; i < n; i += NT) dst[i] = tw[plain_off + i];
   }
 }
 
-// Last-pass twiddles of a row transform or of an x-transform batch (nothing
-// for generic lengths).
+// Register twiddles of a row transform (the last two passes) or of an
+// x-transform batch (the last; nothing for generic lengths).
 struct NoTw {
   __device__ __forceinline__ void load(const float2*) {}
   __device__ __forceinline__ void pin() {}
 };
 template <int N, int NT>
-using RowTw = std::conditional_t<(N > 0), LastTw<(N > 0 ? N : 512), NT>, NoTw>;
+using RowTw = std::conditional_t<(N > 0), RegTw<(N > 0 ? N : 512), NT, (N > 0 ? N : 512), 2>, NoTw>;
 template <int N>
-using XTw = std::conditional_t<(N > 0), LastTw<(N > 0 ? N : 512), kThreads, kXfftBatch>, NoTw>;
+using XTw = std::conditional_t<(N > 0), RegTw<(N > 0 ? N : 512), kThreads, kXfftBatch>, NoTw>;
 
 // Batched x-axis FFTs of a tile: nb transforms of length n at stride
 // bstride, run in groups of at most kXfftBatch points per call (bounded
@@ -1153,7 +1153,7 @@ __device__ __forceinline__ void row0_separate(float2* buf, int ntp) {
 // ------------------------------------------------------------ forward rows
 //
 // LDS: twiddles [ntp], row spectrum [ntp], accumulators D(+l), D(-l) [2 nband].
-template <int N, int RC, int NT>
+template <int N, int RC, int NT, bool HALF>
 __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem& w, const GatherDev& G,
                                               float2* lds, const float* ctab, const float* stab) {
   const int R = RC > 0 ? RC : A.R;
@@ -1171,12 +1171,12 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   // N/2 + 3 zero, so taps k = -3 .. 0 and past N/2 - 1 read zeros and the
   // map needs no bounds test
   float2* twl = lds;
-  float2* buf = lds + fft_tw_slots(N, ntp) + (N > 0 ? kMapGuardSlots : 0);
+  float2* buf = lds + fft_row_tw_slots(N, ntp) + (N > 0 ? kMapGuardSlots : 0);
   float2* acc = buf + plen;
   // row spectrum, pair layout (16-byte aligned: the twiddle and guard slot
   // counts are even)
   const float4* P4 = reinterpret_cast<const float4*>(buf);
-  stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  stage_twiddles<N, NT, 2>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
   RowTw<N, NT> lw;
   lw.load(A.tw + G.twp_t_off);
   lw.pin();
@@ -1195,14 +1195,12 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   // is transformed and mapped (the first FFT pass takes it straight from
   // registers), and the panel constants one panel further ahead, so that the
   // liveness of the row to load is known without a wait
-  using In = FftRegsIn<(N > 0 ? N : kRowMaxN), NT>;
-  In pf;
-  const bool half = In::CAN_HALF && 2 * nt <= ntp;
+  FftRegsIn<(N > 0 ? N : kRowMaxN), NT, HALF> pf;
   PanelDev pdc, pdn;  // constants of the panel whose row is in pf, and of the one after
   if constexpr (N > 0) {
     if (chunk < P) {
       pdc = load_const(A.panels + G.panel_off + chunk);
-      if (r < pdc.rlive) pf.load(xrow + chunk * pstride, nt, half);
+      if (r < pdc.rlive) pf.load(xrow + chunk * pstride, nt);
       if (chunk + S < P) pdn = load_const(A.panels + G.panel_off + chunk + S);
     }
   }
@@ -1212,13 +1210,10 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
     if constexpr (N > 0) {
       PD = pdc;
       const bool live = r < PD.rlive;
-      if (live) {
-        if (half) fft_tpl_regs_pass0<N, false, NT, In::CAN_HALF>(buf, pf);
-        else fft_tpl_regs_pass0<N, false, NT>(buf, pf);
-      }
+      if (live) fft_tpl_regs_pass0<N, false, NT, HALF>(buf, pf);
       if (p + S < P) {
         pdc = pdn;
-        if (r < pdc.rlive) pf.load(xrow + (p + S) * pstride, nt, half);
+        if (r < pdc.rlive) pf.load(xrow + (p + S) * pstride, nt);
         if (p + 2 * S < P) pdn = load_const(A.panels + G.panel_off + p + 2 * S);
       }
       if (!live) continue;
@@ -1356,16 +1351,26 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   __syncthreads();
 }
 
-template <int N, int RC>
+// Rotations of the window (generic kernels only).
+struct TapTrig {
+  float c[2 * kMaxHalfWidth], s[2 * kMaxHalfWidth];
+};
+
+// HALF: every gather's rows are at most N/2 long and N's first radix is 8.
+template <int N, int RC, bool HALF>
 __global__ __launch_bounds__(row_threads(N)) __attribute__((amdgpu_waves_per_eu(row_waves_per_eu(N)))) void k_rows_fwd(RowsArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: the map reads 16-byte pairs
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  __shared__ float ctab[2 * kMaxHalfWidth], stab[2 * kMaxHalfWidth];
   const WorkItem w = load_const(A.items + blockIdx.x);
   const GatherDev G = load_const(A.gd + w.g);
-  init_tap_trig(ctab, stab, RC > 0 ? RC : A.R);
-  __syncthreads();
-  rows_fwd_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
+  if constexpr (RC > 0) {
+    rows_fwd_item<N, RC, row_threads(N), HALF>(A, w, G, lds, nullptr, nullptr);
+  } else {
+    __shared__ TapTrig trig;
+    init_tap_trig(trig.c, trig.s, A.R);
+    __syncthreads();
+    rows_fwd_item<N, RC, row_threads(N), HALF>(A, w, G, lds, trig.c, trig.s);
+  }
 }
 
 // Sum the panel-chunk partials of row r, complete the Hermitian time
@@ -1379,8 +1384,8 @@ __device__ __forceinline__ void rows_fin_item(const RowsArgs& A, const WorkItem&
   const int nt = G.nt, ntp = N > 0 ? N : G.ntp, nrows = G.nrows;
   const int jlo = G.jlo, jhi = G.jhi, nband = jhi - jlo + 1;
   float2* twl = lds;
-  float2* buf = lds + fft_tw_slots(N, ntp);
-  stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  float2* buf = lds + fft_row_tw_slots(N, ntp);
+  stage_twiddles<N, NT, 2>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
   RowTw<N, NT> lw;
   lw.load(A.tw + G.twp_t_off);
   // The band's bins, one thread each: sum the chunks (all loads of a group of
@@ -1486,8 +1491,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 4))
 //
 // No atomics: each model bin sums its contributions in a fixed order.
 //
-// LDS: twiddles [ntp], data row spectrum bufD and model spectrum bufM
-// (padded lengths).
+// LDS: twiddles, the data row spectrum's band (one 16-byte pair per bin),
+// kMapGuardPairs pairs, and the model spectrum bufM, in which the data row is
+// transformed first.
 // One data bin of the adjoint scatter: its taps and the two values it adds
 // (k0 = kNoTap when j is past jmax or outside the cone).  The tap adds
 // wgt * e1 at k and wgt * e2 at ntp - k of the model spectrum:
@@ -1501,7 +1507,7 @@ struct ScatterBin {
 
 template <int N, int RC>
 __device__ __forceinline__ ScatterBin scatter_bin(const RowsArgs& A, const GatherDev& G, const PanelDev& PD,
-                                                  bool plain, const float2* bufD, int r, int pass, double a2, int R,
+                                                  bool plain, const float4* band, int r, int pass, double a2, int R,
                                                   int j, int jmax) {
   ScatterBin b;
   b.k0 = kNoTap;
@@ -1513,7 +1519,7 @@ __device__ __forceinline__ ScatterBin scatter_bin(const RowsArgs& A, const Gathe
   b.k0 = T.k0;
   b.trig = T.trig;
   // spectrum values of bin j, ramped and scaled
-  const float4 dq = reinterpret_cast<const float4*>(bufD)[j];
+  const float4 dq = band[j];
   float2 du = make_float2(dq.x, dq.y);
   float2 dl = make_float2(dq.z, -dq.w);
   if (plain) {
@@ -1549,7 +1555,7 @@ struct ScatterBin4 {
 // scattered values out of the bin loop.
 template <int N, int MODE>
 __device__ __forceinline__ ScatterBin4 scatter_bin4(const RowsArgs& A, const GatherDev& G, const PanelDev& PD,
-                                                    bool plain, const float2* bufD, RowA2 a, int j, int jmax) {
+                                                    bool plain, const float4* band, RowA2 a, int j, int jmax) {
   ScatterBin4 b;
   b.k0 = kNoTap;
   b.e1 = b.e2 = make_float2(0.f, 0.f);
@@ -1562,7 +1568,7 @@ __device__ __forceinline__ ScatterBin4 scatter_bin4(const RowsArgs& A, const Gat
   b.k0 = T.k0;
 #pragma unroll
   for (int t = 0; t < 8; ++t) b.w[t] = T.w[t];
-  const float4 dq = reinterpret_cast<const float4*>(bufD)[j];
+  const float4 dq = band[j];
   float2 du = make_float2(dq.x, dq.y);
   float2 dl = make_float2(dq.z, -dq.w);
   if (plain) {
@@ -1595,28 +1601,19 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
   const int jlo = G.jlo, jhi = G.jhi;
   const int hmax = ntp / 2 - 1;
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-  const int plen = N > 0 ? fft_padlen(N) : ntp;
+  const int nband = jhi - jlo + 1;
   float2* twl = lds;
-  float2* bufD = lds + fft_tw_slots(N, ntp);
-  float2* bufM = bufD + plen;
-  stage_twiddles<N, NT>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
+  float4* const band0 = reinterpret_cast<float4*>(lds + fft_row_tw_slots(N, ntp));
+  float2* bufM = reinterpret_cast<float2*>(band0 + nband + kMapGuardPairs);
+  const float4* const band = band0 - jlo;  // pair of data bin j
+  stage_twiddles<N, NT, 2>(twl, A.tw, G.tw_t_off, G.twp_t_off, ntp);
   RowTw<N, NT> lw;
   lw.load(A.tw + G.twp_t_off);
   lw.pin();
 
-  row_spectrum<N, NT>(bufD, A.H + G.H_off + (long long)r * nt, r, nt, ntp, twl, lw);
-
-  // window rotations cos/sin(pi t / R) in registers (the wave barriers below
-  // would otherwise reload them from LDS at every tap)
-  constexpr int RT = RC > 0 ? RC : 1;
-  float cr[2 * RT], sr[2 * RT];
-  if constexpr (RC > 0) {
-#pragma unroll
-    for (int i = 0; i < 2 * RC; ++i) {
-      cr[i] = ctab[i];
-      sr[i] = stab[i];
-    }
-  }
+  row_spectrum<N, NT>(bufM, A.H + G.H_off + (long long)r * nt, r, nt, ntp, twl, lw);
+  for (int j = threadIdx.x; j < nband; j += NT) band0[j] = reinterpret_cast<const float4*>(bufM)[jlo + j];
+  __syncthreads();
 
   const int npass = (r == 0) ? 2 : 1;
   // panels chunk, chunk + nchunk, ... as in the forward; rows at or above a
@@ -1636,11 +1633,10 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
       if constexpr (RC > 0) {
         static_assert(RC == 4, "compile-time row kernels use the half-width-4 weight polynomials");
         const RowA2 a = split_a2(a2);
-        // Lanes without taps (bins past jhi) scatter zeros into the last
-        // eight 16-byte slots of bufD's padding (never read after its
-        // transform, N / 16 >= 32 slots), so every lane of a segment runs the
-        // same branch-free read-modify-write sequence.
-        float4* const sink = reinterpret_cast<float4*>(bufM) - 8;
+        // Lanes without taps (bins past jhi) scatter zeros into the guard
+        // pairs in front of bufM (never read), so every lane of a segment
+        // runs the same branch-free read-modify-write sequence.
+        float4* const sink = reinterpret_cast<float4*>(bufM) - kMapGuardPairs;
         auto add = [](float4 v, const ScatterBin4& b, int t) {
           v.x = fmaf(b.w[t], b.e1.x, v.x);
           v.y = fmaf(b.w[t], b.e1.y, v.y);
@@ -1656,15 +1652,14 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
             // read-modify-write chains overlap their LDS latencies
 #pragma unroll 1
             for (int sg = 2 * wave + ph; sg < nseg; sg += 4 * NW) {
-              // taps below bin 1 land in the padding that ends bufD (never
-              // read after its transform), taps past N/2-1 in bufM's own
-              // padding (overwritten by its transform), and pair 0 is never
-              // read by the inverse transform
-              const ScatterBin4 sa = scatter_bin4<N, MODE>(A, G, PD, plain, bufD, a, jb + sg * 64 + lane, jhi);
+              // taps below bin 1 land in the guard pairs, taps past N/2-1 in
+              // bufM's own padding (overwritten by its transform), and pair 0
+              // is never read by the inverse transform
+              const ScatterBin4 sa = scatter_bin4<N, MODE>(A, G, PD, plain, band, a, jb + sg * 64 + lane, jhi);
               float4* qa = sa.k0 != kNoTap ? reinterpret_cast<float4*>(bufM) + (sa.k0 - 3) : sink;
               const int sg2 = sg + 2 * NW;
               if (sg2 < nseg) {
-                const ScatterBin4 sb = scatter_bin4<N, MODE>(A, G, PD, plain, bufD, a, jb + sg2 * 64 + lane, jhi);
+                const ScatterBin4 sb = scatter_bin4<N, MODE>(A, G, PD, plain, band, a, jb + sg2 * 64 + lane, jhi);
                 float4* qb = sb.k0 != kNoTap ? reinterpret_cast<float4*>(bufM) + (sb.k0 - 3) : sink;
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
@@ -1694,18 +1689,13 @@ __device__ __forceinline__ void rows_adj_item(const RowsArgs& A, const WorkItem&
       for (int ph = 0; ph < 2; ++ph) {
 #pragma unroll 1
         for (int sg = 2 * wave + ph; sg < nseg; sg += 2 * NW) {
-          const ScatterBin sb = scatter_bin<N, RC>(A, G, PD, plain, bufD, r, pass, a2, R, jb + sg * 64 + lane, jhi);
+          const ScatterBin sb = scatter_bin<N, RC>(A, G, PD, plain, band, r, pass, a2, R, jb + sg * 64 + lane, jhi);
           if (sb.k0 != kNoTap) {
 #pragma unroll
             for (int t = -R + 1; t <= R; ++t) {
               const int k = sb.k0 + t;
-              // compile-time lengths skip the test: taps below bin 1 land in
-              // the padding that ends bufD (never read after its transform),
-              // taps past N/2-1 in bufM's own padding (overwritten by its
-              // transform), and pair 0 is never read by the inverse transform
-              if (N > 0 || (k >= 1 && k <= hmax)) {
-                const float wt = RC > 0 ? tap_weight(sb.trig, t, cr[(t + R - 1) % (2 * RT)], sr[(t + R - 1) % (2 * RT)])
-                                        : tap_weight(sb.trig, t, ctab[t + R - 1], stab[t + R - 1]);
+              if (k >= 1 && k <= hmax) {
+                const float wt = tap_weight(sb.trig, t, ctab[t + R - 1], stab[t + R - 1]);
                 float4* q = reinterpret_cast<float4*>(bufM) + k;
                 float4 v = *q;
                 v.x = fmaf(wt, sb.e1.x, v.x);
@@ -1750,12 +1740,16 @@ template <int N, int RC>
 __global__ __launch_bounds__(row_threads(N)) __attribute__((amdgpu_waves_per_eu(row_waves_per_eu(N)))) void k_rows_adj(RowsArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: the map reads 16-byte pairs
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  __shared__ float ctab[2 * kMaxHalfWidth], stab[2 * kMaxHalfWidth];
   const WorkItem w = load_const(A.items + blockIdx.x);
   const GatherDev G = load_const(A.gd + w.g);
-  init_tap_trig(ctab, stab, RC > 0 ? RC : A.R);
-  __syncthreads();
-  rows_adj_item<N, RC, row_threads(N)>(A, w, G, lds, ctab, stab);
+  if constexpr (RC > 0) {
+    rows_adj_item<N, RC, row_threads(N)>(A, w, G, lds, nullptr, nullptr);
+  } else {
+    __shared__ TapTrig trig;
+    init_tap_trig(trig.c, trig.s, A.R);
+    __syncthreads();
+    rows_adj_item<N, RC, row_threads(N)>(A, w, G, lds, trig.c, trig.s);
+  }
 }
 
 // ------------------------------------------------------------ launchers
@@ -1781,6 +1775,9 @@ bool x_size_is_tpl(int n) {
   return false;
 }
 
+// Lengths whose row kernel has the half-row form (a radix-8 first pass).
+constexpr bool row_half(int n) { return n % 3 != 0; }
+
 template <class F>
 static void set_lds(F* k, size_t b, hipError_t& e) {
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b);
@@ -1797,10 +1794,10 @@ hipError_t op_kernels_init(size_t max_lds) {
   set_lds(k_nudft_fwd, max_lds, e);
   set_lds(k_nudft_inv, max_lds, e);
   set_lds(k_xfft_inv<0>, max_lds, e);
-#define R_(S) set_lds(k_rows_fwd<S, 4>, max_lds, e); set_lds(k_rows_adj<S, 4>, max_lds, e); set_lds(k_rows_fwd_fin<S>, max_lds, e);
+#define R_(S) set_lds(k_rows_fwd<S, 4, false>, max_lds, e); set_lds(k_rows_fwd<S, 4, row_half(S)>, max_lds, e); set_lds(k_rows_adj<S, 4>, max_lds, e); set_lds(k_rows_fwd_fin<S>, max_lds, e);
   ASHRT_ROW_SIZES(R_)
 #undef R_
-  set_lds(k_rows_fwd<0, 0>, max_lds, e);
+  set_lds(k_rows_fwd<0, 0, false>, max_lds, e);
   set_lds(k_rows_adj<0, 0>, max_lds, e);
   set_lds(k_rows_fwd_fin<0>, max_lds, e);
   return e;
@@ -1844,18 +1841,21 @@ hipError_t launch_xfft_inv(int key, const XinvArgs& a, size_t lds, hipStream_t s
   return e != hipSuccess ? e : hipGetLastError();
 }
 
-hipError_t launch_rows_fwd(int key, const RowsArgs& a, size_t lds, hipStream_t s) {
+hipError_t launch_rows_fwd(int key, bool half, const RowsArgs& a, size_t lds, hipStream_t s) {
   if (a.nitems <= 0) return hipSuccess;
   hipError_t e = hipSuccess;
   switch (key) {
 #define L_(S)                                                                                  \
   case S:                                                                                      \
-    hipLaunchKernelGGL((k_rows_fwd<S, 4>), dim3(a.nitems), dim3(row_threads(S)), lds, s, a); \
+    if (half)                                                                                  \
+      hipLaunchKernelGGL((k_rows_fwd<S, 4, row_half(S)>), dim3(a.nitems), dim3(row_threads(S)), lds, s, a); \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_rows_fwd<S, 4, false>), dim3(a.nitems), dim3(row_threads(S)), lds, s, a); \
     break;
     ASHRT_ROW_SIZES(L_)
 #undef L_
     default:
-      hipLaunchKernelGGL((k_rows_fwd<0, 0>), dim3(a.nitems), dim3(kRowThreads), lds, s, a);
+      hipLaunchKernelGGL((k_rows_fwd<0, 0, false>), dim3(a.nitems), dim3(kRowThreads), lds, s, a);
   }
   return e != hipSuccess ? e : hipGetLastError();
 }
