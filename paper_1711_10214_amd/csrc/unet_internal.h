@@ -14,7 +14,6 @@
 
 namespace unet {
 
-constexpr int kConvTH = 4;    // output rows per conv workgroup (one per wave)
 constexpr int kWgTH = 4;      // pixel tile of the weight-gradient kernel (rows)
 constexpr int kWgTW = 32;     //                                      (columns)
 
@@ -77,6 +76,7 @@ struct WgradArgs {
   const float* gY;          // FP32 NHWC [B][H][W][Cout]: gradient of the conv output before its ReLU
   int Cout, Cin;            // real counts
   int CCw, nccw, Cipw;      // channel chunk of the reduction tile (16 or 32), chunks, padded count
+  int cc0;                  // first chunk of this launch (launch_wgrad)
   float* part;              // [nsplit][Cout][9][Cipw]
   float* bpart;             // [nsplit][Cout] bias partials (from channel chunk 0)
   int nsplit, B;

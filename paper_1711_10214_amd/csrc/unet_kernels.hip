@@ -22,6 +22,8 @@
 // a fixed order.
 #include "unet_internal.h"
 
+#include <type_traits>
+
 namespace unet {
 
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
@@ -29,19 +31,15 @@ typedef float f32x4 __attribute__((__vector_size__(4 * sizeof(float))));
 
 __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
 
-// FP32 -> BF16 bits, round to nearest even (finite inputs).
-__device__ __forceinline__ uint32_t f2bf(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+// Two FP32 -> BF16 bit pairs, round to nearest even (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
 }
 
 __device__ __forceinline__ uint4 pack8(const float v[8]) {
-  uint4 r;
-  r.x = f2bf(v[0]) | (f2bf(v[1]) << 16);
-  r.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-  r.z = f2bf(v[4]) | (f2bf(v[5]) << 16);
-  r.w = f2bf(v[6]) | (f2bf(v[7]) << 16);
-  return r;
+  return make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
 }
 
 __device__ __forceinline__ void unpack8(uint4 q, float v[8]) {
@@ -62,139 +60,129 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Channels [c, c + 8) of conv-input pixel (b, y, x); zero outside the image
-// and beyond the real channels.  c is a multiple of 8, and so are Ca and Cb
-// unless Ca == 1 (the FP32 network input).
-template <bool AF32>
-__device__ __forceinline__ void load_in8(const ConvIn& I, int b, int y, int x, int c, float v[8]) {
+// Stages a ROWS x COLS pixel tile of 8 NG channels of a convolution's input
+// into LDS as [pixel][channel], pixel stride PS BF16 values, in two calls:
+// fetch issues the global loads into registers (so that they fly under the
+// multiplies of the tile before) and store rounds and writes them.  A task is
+// one pixel's group of 8 channels; a thread's tasks all have the same channel
+// group and lie 256 / NG pixels apart, so their indices are found once per
+// workgroup (init) and their LDS places are constants apart: with the indices
+// recomputed per chunk by run-time divisions the convolutions were bound by
+// integer arithmetic (24 M VALU instructions in 22 M CU cycles at 4 x 1024 x 256
+// pixels, 16 channels).  Outside the image and beyond the real channels the
+// tile is zero.  MODE: ConvIn::modeA (a pooled A has no skip); FP32 inputs are
+// at the same resolution and alone.  Ca and Cb are multiples of 8 unless Ca == 1
+// (the FP32 network input).
+template <bool AF32, int MODE, int NG, int ROWS, int COLS, int PS>
+struct TileStage {
+  static constexpr int N = ROWS * COLS * NG;
+  static constexpr int S = (N + 255) / 256;
+  static_assert(256 % NG == 0 && S <= 32, "tasks of a thread share a channel group; one bit each");
+  static_assert(!AF32 || MODE == 0, "FP32 inputs are at the same resolution");
+  int po[S];              // pixel offset of each task from the tile's first pixel
+  int ph[MODE == 1 ? S : 1];  // the same in the half-resolution A
+  long long org, orgA;    // the tile's first pixel and its A pixel (of the batch's pixels in order)
+  unsigned ok;            // bit u: task u lies in the image
+  float4 f0[AF32 ? S : 1], f1[AF32 ? S : 1];
+  uint4 q[AF32 ? 1 : S];
+
+  __device__ __forceinline__ void init(const ConvIn& I, int b, int y0, int x0) {
+    const int pix0 = (int)threadIdx.x / NG;
+    ok = 0;
+    org = ((long long)b * I.H + y0) * I.W + x0;
+    if constexpr (MODE == 0) orgA = org;
+    if constexpr (MODE == 1) orgA = ((long long)b * (I.H >> 1) + (y0 >> 1)) * (I.W >> 1) + (x0 >> 1);
+    if constexpr (MODE == 2) orgA = ((long long)b * (2 * I.H) + 2 * y0) * (2 * I.W) + 2 * x0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = 0.f;
-  if (y < 0 || y >= I.H || x < 0 || x >= I.W) return;
-  if (c < I.Ca) {
+    for (int u = 0; u < S; ++u) {
+      const int pix = pix0 + u * (256 / NG);
+      const int r = pix / COLS, x = pix - r * COLS;
+      const int yy = y0 + r, xx = x0 + x;
+      const bool in = pix < ROWS * COLS && yy >= 0 && yy < I.H && xx >= 0 && xx < I.W;
+      ok |= in ? 1u << u : 0u;
+      po[u] = (MODE == 2 ? 4 * r * I.W + 2 * x : r * I.W + x);
+      if constexpr (MODE == 1) ph[u] = ((yy >> 1) - (y0 >> 1)) * (I.W >> 1) + ((xx >> 1) - (x0 >> 1));
+    }
+  }
+
+  // channels [c0, c0 + 8 NG)
+  __device__ __forceinline__ void fetch(const ConvIn& I, int c0) {
+    const int c = c0 + ((int)threadIdx.x % NG) * 8;
+    const bool inA = c < I.Ca;
     if constexpr (AF32) {
-      const float* A = static_cast<const float*>(I.A);
-      if (I.Ca == 1) {
-        v[0] = A[((long long)b * I.H + y) * I.W + x];
-      } else {
-        const long long o = (((long long)b * I.H + y) * I.W + x) * I.Ca + c;
-        const float4 p = *reinterpret_cast<const float4*>(A + o);
-        const float4 q = *reinterpret_cast<const float4*>(A + o + 4);
-        v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w;
-        v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
-      }
-    } else {
-      const uint16_t* A = static_cast<const uint16_t*>(I.A);
-      if (I.modeA == 0) {
-        unpack8(*reinterpret_cast<const uint4*>(A + (((long long)b * I.H + y) * I.W + x) * I.Ca + c), v);
-      } else if (I.modeA == 1) {
-        const int Ha = I.H >> 1, Wa = I.W >> 1;
-        unpack8(*reinterpret_cast<const uint4*>(A + (((long long)b * Ha + (y >> 1)) * Wa + (x >> 1)) * I.Ca + c),
-                v);
-      } else {
-        const int Ha = I.H * 2, Wa = I.W * 2;
-        float t[8];
+      const float* p = static_cast<const float*>(I.A) + orgA * I.Ca + c;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ya = 2 * y + (q >> 1), xa = 2 * x + (q & 1);
-          unpack8(*reinterpret_cast<const uint4*>(A + (((long long)b * Ha + ya) * Wa + xa) * I.Ca + c), t);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] += t[i];
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] *= 0.25f;
-      }
-    }
-  } else if (c < I.Ca + I.Cb) {
-    unpack8(*reinterpret_cast<const uint4*>(I.Bs + (((long long)b * I.H + y) * I.W + x) * I.Cb + (c - I.Ca)), v);
-  }
-}
-
-// Source of channels [c, c + 8) of conv-input pixel (b, y, x) for a BF16
-// loader without pooling (A at the same or at half resolution, and the
-// skip): one 16-byte load, or null where the channels are zero.
-__device__ __forceinline__ const uint4* in8_src(const ConvIn& I, int b, int y, int x, int c) {
-  if (y < 0 || y >= I.H || x < 0 || x >= I.W) return nullptr;
-  if (c < I.Ca) {
-    const uint16_t* A = static_cast<const uint16_t*>(I.A);
-    if (I.modeA == 0) return reinterpret_cast<const uint4*>(A + (((long long)b * I.H + y) * I.W + x) * I.Ca + c);
-    const int Ha = I.H >> 1, Wa = I.W >> 1;
-    return reinterpret_cast<const uint4*>(A + (((long long)b * Ha + (y >> 1)) * Wa + (x >> 1)) * I.Ca + c);
-  }
-  if (c < I.Ca + I.Cb)
-    return reinterpret_cast<const uint4*>(I.Bs + (((long long)b * I.H + y) * I.W + x) * I.Cb + (c - I.Ca));
-  return nullptr;
-}
-
-// Stage the (rows x cols) input tile of channel chunk [c0, c0 + 8 ng) into
-// LDS as [pixel][channel] with pixel stride PS, pixel (r, q) of the tile
-// being input pixel (y0 + r, x0 + q).  Loaders without pooling (BF16
-// activations, the FP32 gradient) issue the loads of several tasks before
-// storing any, so that a thread waits on one memory latency per group of
-// tasks rather than per task.
-template <bool AF32>
-__device__ __forceinline__ void stage_tile(const ConvIn& I, int b, int y0, int x0, int rows, int cols, int c0,
-                                           int ng, uint16_t* dst, int PS) {
-  const int ntask = rows * cols * ng;
-  if (!AF32 && I.modeA != 2) {
-    constexpr int U = 4;
-    for (int t0 = threadIdx.x; t0 < ntask; t0 += U * 256) {
-      uint4 q[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int task = t0 + u * 256;
-        q[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (task < ntask) {
-          const int g = task % ng, pix = task / ng;
-          const int r = pix / cols, x = pix - r * cols;
-          const uint4* src = in8_src(I, b, y0 + r, x0 + x, c0 + g * 8);
-          if (src) q[u] = *src;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int task = t0 + u * 256;
-        if (task < ntask) *reinterpret_cast<uint4*>(dst + (task / ng) * PS + (task % ng) * 8) = q[u];
-      }
-    }
-  } else if (AF32 && I.Ca > 1 && I.Cb == 0 && I.modeA == 0) {
-    constexpr int U = 4;
-    const float* A = static_cast<const float*>(I.A);
-    for (int t0 = threadIdx.x; t0 < ntask; t0 += U * 256) {
-      float4 p[U], q[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int task = t0 + u * 256;
-        p[u] = q[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (task < ntask) {
-          const int g = task % ng, pix = task / ng;
-          const int r = pix / cols, x = pix - r * cols;
-          const int y = y0 + r, xx = x0 + x, c = c0 + g * 8;
-          if (y >= 0 && y < I.H && xx >= 0 && xx < I.W && c < I.Ca) {
-            const long long o = (((long long)b * I.H + y) * I.W + xx) * I.Ca + c;
-            p[u] = *reinterpret_cast<const float4*>(A + o);
-            q[u] = *reinterpret_cast<const float4*>(A + o + 4);
+      for (int u = 0; u < S; ++u) {
+        f0[u] = f1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if ((ok >> u & 1u) && inA) {
+          const float* t = p + (long long)po[u] * I.Ca;
+          if (I.Ca == 1) {
+            f0[u].x = *t;
+          } else {
+            f0[u] = *reinterpret_cast<const float4*>(t);
+            f1[u] = *reinterpret_cast<const float4*>(t + 4);
           }
         }
       }
+    } else if constexpr (MODE == 2) {
+      const uint16_t* p = static_cast<const uint16_t*>(I.A) + orgA * I.Ca + c;
+      const long long row = 2LL * I.W * I.Ca;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int task = t0 + u * 256;
-        if (task < ntask) {
-          const float v[8] = {p[u].x, p[u].y, p[u].z, p[u].w, q[u].x, q[u].y, q[u].z, q[u].w};
-          *reinterpret_cast<uint4*>(dst + (task / ng) * PS + (task % ng) * 8) = pack8(v);
+      for (int u = 0; u < S; ++u) {
+        q[u] = make_uint4(0u, 0u, 0u, 0u);
+        if ((ok >> u & 1u) && inA) {
+          float v[8], t[8];
+          const uint16_t* s = p + (long long)po[u] * I.Ca;
+          const uint4 h[4] = {*reinterpret_cast<const uint4*>(s), *reinterpret_cast<const uint4*>(s + I.Ca),
+                              *reinterpret_cast<const uint4*>(s + row),
+                              *reinterpret_cast<const uint4*>(s + row + I.Ca)};
+          unpack8(h[0], v);
+#pragma unroll
+          for (int k = 1; k < 4; ++k) {
+            unpack8(h[k], t);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] += t[i];
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] *= 0.25f;
+          q[u] = pack8(v);
+        }
+      }
+    } else {
+      const uint16_t* p = inA ? static_cast<const uint16_t*>(I.A) + orgA * I.Ca + c : I.Bs + org * I.Cb + (c - I.Ca);
+      const int C = inA ? I.Ca : I.Cb;
+      const bool live = c < I.Ca + I.Cb;
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        q[u] = make_uint4(0u, 0u, 0u, 0u);
+        if ((ok >> u & 1u) && live) {
+          int o = po[u];
+          if constexpr (MODE == 1) {
+            const int h = ph[u];
+            o = inA ? h : o;
+          }
+          q[u] = *reinterpret_cast<const uint4*>(p + (long long)o * C);
         }
       }
     }
-  } else {
-    for (int task = threadIdx.x; task < ntask; task += 256) {
-      const int g = task % ng, pix = task / ng;
-      const int r = pix / cols, x = pix - r * cols;
-      float v[8];
-      load_in8<AF32>(I, b, y0 + r, x0 + x, c0 + g * 8, v);
-      *reinterpret_cast<uint4*>(dst + pix * PS + g * 8) = pack8(v);
+  }
+
+  __device__ __forceinline__ void store(uint16_t* dst) const {
+    uint16_t* d = dst + ((int)threadIdx.x / NG) * PS + ((int)threadIdx.x % NG) * 8;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      if (N % 256 != 0 && u == S - 1 && (int)threadIdx.x + u * 256 >= N) continue;
+      uint4 w;
+      if constexpr (AF32) {
+        const float v[8] = {f0[u].x, f0[u].y, f0[u].z, f0[u].w, f1[u].x, f1[u].y, f1[u].z, f1[u].w};
+        w = pack8(v);
+      } else {
+        w = q[u];
+      }
+      *reinterpret_cast<uint4*>(d + u * (256 / NG) * PS) = w;
     }
   }
-}
+};
 
 // ------------------------------------------------------------ routed epilogue
 // float4 store or accumulate of four consecutive channels, each zeroed where
@@ -224,226 +212,236 @@ __device__ __forceinline__ float lane_pair_swap(float v) {
 }
 
 // Epilogue of an input-gradient convolution (see ConvRoute): lane (sub, n16)
-// of wave w holds channels co0 + 16 mi + 4 sub + [0, 4) of pixel (ty0 + w,
-// tx0 + 16 ni + n16).  An upsampled A (UP, mode 1) sums each 2 x 2 pixel
-// block: the two columns by a lane exchange, then the two rows (waves 2k and
-// 2k + 1) through LDS, (g00 + g01) + (g10 + g11); every wave reaches that
-// barrier.  UP is a template parameter so that the other input gradients do
-// not carry its registers.
-template <int MT, int NTL, bool UP>
-__device__ __forceinline__ void route_store(const ConvArgs& a, f32x4 (&acc)[MT][NTL], int b, int ty0, int tx0,
-                                            int co0, int MI, float* red) {
+// holds channels co0 + 16 mi + 4 sub + [0, 4) of the pixels (y0 + rr, tx0 + 16
+// ni + n16).  An upsampled A (UP, mode 1) sums each 2 x 2 pixel block, (g00 +
+// g01) + (g10 + g11): the two columns by a lane exchange, then the wave's two
+// rows; the even lanes store the first column tile's sums and the odd lanes
+// the second's (16-channel tiles lie wholly in A or in B there, Ca being a
+// multiple of 16).  UP is a template parameter so that the other input
+// gradients do not carry its registers.
+template <int MT, int NTL, int RW, bool UP>
+__device__ __forceinline__ void route_store(const ConvArgs& a, f32x4 (&acc)[RW][MT][NTL], int b, int y0, int tx0,
+                                            int co0) {
   const ConvRoute& R = a.rt;
   const int H = a.in.H, W = a.in.W;
-  const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+  const int lane = (int)threadIdx.x & 63;
   const int sub = lane >> 4, n16 = lane & 15;
-  const int y = ty0 + wave;
   if constexpr (UP) {
-    // column-pair sums (DPP lane swap) of the A tiles, written by the even
-    // lanes of every wave to LDS as [row][A column][channel of the tile]
-    // (16-channel tiles lie wholly in A or in B, Ca being a multiple of 16);
-    // then every thread adds the two rows of an A pixel and stores four of
-    // its channels, consecutive threads taking consecutive channels, then
-    // A columns, so that the stores are contiguous
-    constexpr int XA = 8 * NTL;        // A columns of the tile
-    constexpr int CS = 16 * MT + 4;    // LDS floats per A column of a row
-    const int MA = max(0, min(MI, (R.Ca - co0) >> 4));  // A tiles of this workgroup
+    static_assert(RW == 2 && NTL == 2, "a wave holds whole 2 x 2 blocks of two column tiles");
+    const int Hh = H >> 1, Wh = W >> 1;
+    const bool odd = n16 & 1;
+    const int yh = y0 >> 1, xh = (tx0 + (odd ? 16 : 0) + n16) >> 1;
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi) {
-      if (mi >= MA) continue;
+      const int co = co0 + mi * 16 + sub * 4;
+      if (co0 + mi * 16 >= R.Ca) continue;
+      float t[NTL][4];
 #pragma unroll
-      for (int ni = 0; ni < NTL; ++ni) {
+      for (int ni = 0; ni < NTL; ++ni)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[mi][ni][i] += lane_pair_swap(acc[mi][ni][i]);
-        if (!(n16 & 1))
-          *reinterpret_cast<float4*>(red + (wave * XA + ((ni * 16 + n16) >> 1)) * CS + mi * 16 + sub * 4) =
-              make_float4(acc[mi][ni][0], acc[mi][ni][1], acc[mi][ni][2], acc[mi][ni][3]);
+        for (int i = 0; i < 4; ++i) {
+          const float r0 = acc[0][mi][ni][i] + lane_pair_swap(acc[0][mi][ni][i]);
+          const float r1 = acc[1][mi][ni][i] + lane_pair_swap(acc[1][mi][ni][i]);
+          t[ni][i] = r0 + r1;
+        }
+      if (yh < Hh && xh < Wh) {
+        const long long oa = (((long long)b * Hh + yh) * Wh + xh) * R.Ca + co;
+        put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, odd ? t[1][0] : t[0][0], odd ? t[1][1] : t[0][1],
+             odd ? t[1][2] : t[0][2], odd ? t[1][3] : t[0][3], R.accA != 0);
       }
     }
-    __syncthreads();
-    const int ng = MA * 4, Hh = H >> 1, Wh = W >> 1;
-    for (int idx = (int)threadIdx.x; idx < 2 * XA * ng; idx += 256) {
-      const int g = idx % ng, rest = idx / ng;
-      const int xa = rest % XA, ya = rest / XA;
-      const int yh = (ty0 >> 1) + ya, xh = (tx0 >> 1) + xa;
-      if (yh >= Hh || xh >= Wh) continue;
-      // (g00 + g01) + (g10 + g11): row 2 ya, then row 2 ya + 1
-      const float4 r0 = *reinterpret_cast<const float4*>(red + ((2 * ya) * XA + xa) * CS + 4 * g);
-      const float4 r1 = *reinterpret_cast<const float4*>(red + ((2 * ya + 1) * XA + xa) * CS + 4 * g);
-      const long long oa = (((long long)b * Hh + yh) * Wh + xh) * R.Ca + co0 + 4 * g;
-      put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, r0.x + r1.x, r0.y + r1.y, r0.z + r1.z, r0.w + r1.w,
-           R.accA != 0);
-    }
   }
-  if (y >= H) return;
 #pragma unroll
   for (int mi = 0; mi < MT; ++mi) {
     const int co = co0 + mi * 16 + sub * 4;
-    if (mi >= MI || co >= R.Ca + R.Cb) continue;
+    if (co >= R.Ca + R.Cb) continue;
     if (UP && co < R.Ca) continue;  // stored above
 #pragma unroll
-    for (int ni = 0; ni < NTL; ++ni) {
-      const int x = tx0 + ni * 16 + n16;
-      if (x >= W) continue;
-      const f32x4 o = acc[mi][ni];
-      if (co >= R.Ca) {
-        const long long ob = (((long long)b * H + y) * W + x) * R.Cb + (co - R.Ca);
-        put4(R.gB + ob, R.mB ? R.mB + ob : nullptr, o[0], o[1], o[2], o[3], R.accB != 0);
-      } else if (R.modeA == 0) {
-        const long long oa = (((long long)b * H + y) * W + x) * R.Ca + co;
-        put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, o[0], o[1], o[2], o[3], R.accA != 0);
-      } else {
-        // mode 2 (pooled A): an upsampled A (mode 1) always launches with UP
-        // set, or split with the route left to k_conv_finish
-        const int H2 = 2 * H, W2 = 2 * W;
+    for (int rr = 0; rr < RW; ++rr) {
+      const int y = y0 + rr;
+      if (y >= H) continue;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const long long oa = (((long long)b * H2 + 2 * y + (q >> 1)) * W2 + 2 * x + (q & 1)) * R.Ca + co;
-          put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, 0.25f * o[0], 0.25f * o[1], 0.25f * o[2], 0.25f * o[3],
-               R.accA != 0);
+      for (int ni = 0; ni < NTL; ++ni) {
+        const int x = tx0 + ni * 16 + n16;
+        if (x >= W) continue;
+        const f32x4 o = acc[rr][mi][ni];
+        if (co >= R.Ca) {
+          const long long ob = (((long long)b * H + y) * W + x) * R.Cb + (co - R.Ca);
+          put4(R.gB + ob, R.mB ? R.mB + ob : nullptr, o[0], o[1], o[2], o[3], R.accB != 0);
+        } else if (R.modeA == 0) {
+          const long long oa = (((long long)b * H + y) * W + x) * R.Ca + co;
+          put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, o[0], o[1], o[2], o[3], R.accA != 0);
+        } else {
+          // mode 2 (pooled A): an upsampled A (mode 1) always launches with UP
+          // set, or split with the route left to k_conv_finish
+          const int H2 = 2 * H, W2 = 2 * W;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const long long oa = (((long long)b * H2 + 2 * y + (q >> 1)) * W2 + 2 * x + (q & 1)) * R.Ca + co;
+            put4(R.gA + oa, R.mA ? R.mA + oa : nullptr, 0.25f * o[0], 0.25f * o[1], 0.25f * o[2], 0.25f * o[3],
+                 R.accA != 0);
+          }
         }
       }
     }
   }
 }
 
+// LDS pixel stride of a conv tile in BF16 values.  A fragment read takes 16
+// consecutive pixels' 16-byte groups, and the hardware serves lanes 0-3, 12-15
+// of one group together with lanes 4-11 of the next: strides of 2 mod 4 groups
+// keep the 16 of them on different banks for any first pixel.
+constexpr int conv_ps(int CC) { return CC == 32 ? 48 : CC; }
+
 // ------------------------------------------------------------ 3x3 convolution
 // Grid: (row tiles x column tiles, output-channel tiles of 16 MT, batch x
-// ksplit).  Wave w computes output row w of the tile: up to MT x NTL MFMA tiles
-// (16 MT channels x 16 NTL columns).  MT = 4, NTL = 2 in general; layers
-// with at most 16 output channels take MT = 1, NTL = 4 (64 columns).
-template <bool AF32, bool OUTF32, int MT = 4, int NTL = 2, bool UP = false>
+// ksplit).  Wave w computes output rows RW w .. RW w + RW - 1 of the tile: MT x
+// NTL MFMA tiles (16 MT channels x 16 NTL columns) of each.  The taps are
+// unrolled, every LDS offset a constant, and the next chunk's tile is loaded
+// while this one multiplies.  Whatever the tile, an output value adds the same
+// products in the same order (chunks, then taps, 32 at a time), so the rounded
+// activations do not depend on it.
+// Level-0 and level-1 input gradients are bound by their FP32 tensors (16 -> 16
+// channels at 4 x 1024 x 256 pixels: 167 MB in 35 us), the others by the LDS and
+// L1 reads of the fragments (64 -> 64 at 4 x 256 x 64: 15 us for 4 us of products).
+template <bool AF32, bool OUTF32, int MODE, int CC, int MT, int NTL, int RW, bool UP>
 __global__ __launch_bounds__(256) void k_conv3(ConvArgs a) {
-  static_assert((MT == 4 && NTL == 2) || (MT == 1 && NTL == 4), "4 x 2 or 1 x 4 accumulator tiles per wave");
-  constexpr int TW = 16 * NTL;
-  constexpr int TW2 = TW + 2;
-  // input tile [row][col][channel], (kConvTH + 2) x TW2 pixels of CC + 8
-  // channel slots (dynamic: conv3_launch)
-  extern __shared__ __attribute__((aligned(16))) uint16_t sX[];
+  constexpr int TW = 16 * NTL, TW2 = TW + 2, TH = 4 * RW, PS = conv_ps(CC), NG = CC / 8;
+  constexpr int TPK = 32 / CC, KS = (9 + TPK - 1) / TPK;  // taps per k-step, k-steps per chunk
+  constexpr int PF = 3;                                   // weight fragments held: this k-step's and the next two
+  static_assert(TPK > 1 || KS % PF == 0, "the fragment rotation restarts with each chunk");
+  __shared__ __attribute__((aligned(16))) uint16_t sX[(TH + 2) * TW2 * PS];
   const int H = a.in.H, W = a.in.W;
   const int tiles_x = (W + TW - 1) / TW;
-  const int ty0 = ((int)blockIdx.x / tiles_x) * kConvTH;
+  const int ty0 = ((int)blockIdx.x / tiles_x) * TH;
   const int tx0 = ((int)blockIdx.x % tiles_x) * TW;
   const int co0 = (int)blockIdx.y * 16 * MT, b = (int)blockIdx.z % a.B, ks = (int)blockIdx.z / a.B;
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
   const int sub = lane >> 4, n16 = lane & 15;
   const ConvPack& P = a.pk;
-  const int MI = min(MT, (P.Coutp - co0) >> 4);
-  const int CC = P.CC, PS = CC + 8, ng = CC >> 3;
-  const int kl = sub * 8, tap_l = kl / CC, coff = kl - tap_l * CC;
-  const int nkc = P.KKp / P.TPK;
+  const int y0 = ty0 + RW * wave;
 
-  f32x4 acc[MT][NTL];
+  f32x4 acc[RW][MT][NTL];
 #pragma unroll
-  for (int mi = 0; mi < MT; ++mi)
+  for (int rr = 0; rr < RW; ++rr)
 #pragma unroll
-    for (int ni = 0; ni < NTL; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NTL; ++ni) acc[rr][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // packed weights of output channel co0 + mi 16 + n16, k-step s of the
-  // whole reduction (s = cc nkc + kc): consecutive k-steps are consecutive
-  // KKp-CC blocks, 32 BF16 apart
+  // LDS offset of this lane's tap of k-step kc from its first pixel; tap past the ninth: no product
+  const uint16_t* const bx = sX + (RW * wave * TW2 + n16) * PS + (sub * 8) % CC;
+  auto tap_off = [&](int kc) {
+    if constexpr (TPK == 1) {
+      return ((kc / 3) * TW2 + kc % 3) * PS;
+    } else {
+      const int t = kc * TPK + (sub * 8) / CC, tt = t < 9 ? t : 0;
+      return ((tt / 3) * TW2 + tt % 3) * PS;
+    }
+  };
+
+  // packed weights of output channel co0 + 16 mi + n16: the k-steps of the
+  // whole reduction are consecutive blocks of 32
   const uint16_t* wrow[MT];
+  const int cc_lo = ks * P.ncc / a.ksplit, cc_hi = (ks + 1) * P.ncc / a.ksplit;
 #pragma unroll
   for (int mi = 0; mi < MT; ++mi)
-    wrow[mi] = a.Wp + ((long long)min(co0 + mi * 16 + n16, P.Coutp - 1) * P.ncc * P.KKp + tap_l) * CC + coff;
-  // the A fragments of the next two k-steps are in flight while this one
-  // multiplies (wq: step s + 1, wq2: step s + 2)
-  uint4 wq[MT], wq2[MT];
-  // this split's channel chunks (all of them without a split)
-  const int cc_lo = ks * P.ncc / a.ksplit, cc_hi = (ks + 1) * P.ncc / a.ksplit;
-  const int nks = cc_hi * nkc, sb = cc_lo * nkc;
+    wrow[mi] = a.Wp + ((long long)(co0 + mi * 16 + n16) * P.ncc + cc_lo) * (KS * 32) + sub * 8;
+  uint4 wq[PF][MT];
 #pragma unroll
-  for (int mi = 0; mi < MT; ++mi) {
-    wq[mi] = mi < MI ? *reinterpret_cast<const uint4*>(wrow[mi] + (long long)sb * P.TPK * CC) : make_uint4(0u, 0u, 0u, 0u);
-    wq2[mi] = (mi < MI && sb + 1 < nks) ? *reinterpret_cast<const uint4*>(wrow[mi] + (long long)(sb + 1) * P.TPK * CC)
-                                          : make_uint4(0u, 0u, 0u, 0u);
-  }
+  for (int s = 0; s < PF - 1; ++s)
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi) wq[s][mi] = *reinterpret_cast<const uint4*>(wrow[mi] + s * 32);
 
+  TileStage<AF32, MODE, NG, TH + 2, TW2, PS> st;
+  st.init(a.in, b, ty0 - 1, tx0 - 1);
+  st.fetch(a.in, cc_lo * CC);
   for (int cc = cc_lo; cc < cc_hi; ++cc) {
-    stage_tile<AF32>(a.in, b, ty0 - 1, tx0 - 1, kConvTH + 2, TW2, cc * CC, ng, sX, PS);
+    st.store(sX);
     __syncthreads();
-    for (int kc = 0; kc < nkc; ++kc) {
-      const int kk = kc * P.TPK + tap_l;
-      const bool valid = kk < 9;
-      const int dy = valid ? kk / 3 : 0, dx = valid ? kk - (kk / 3) * 3 : 0;
-      bf16x8 bfrag[NTL];
+    const bool more = TPK == 1 && cc + 1 < cc_hi;  // channel counts below 32 are one chunk
+    if (more) st.fetch(a.in, (cc + 1) * CC);
 #pragma unroll
-      for (int ni = 0; ni < NTL; ++ni) {
-        const int px = ni * 16 + n16;
-        uint4 q = *reinterpret_cast<const uint4*>(sX + ((wave + dy) * TW2 + px + dx) * PS + coff);
-        if (!valid) q = make_uint4(0u, 0u, 0u, 0u);
-        bfrag[ni] = __builtin_bit_cast(bf16x8, q);
-      }
-      bf16x8 afrag[MT];
-#pragma unroll
-      for (int mi = 0; mi < MT; ++mi) {
-        afrag[mi] = __builtin_bit_cast(bf16x8, wq[mi]);
-        wq[mi] = wq2[mi];
-      }
-      const int sn = cc * nkc + kc + 2;
-      if (sn < nks) {
+    for (int kc = 0; kc < KS; ++kc) {
+      if (kc + PF - 1 < KS || more) {
 #pragma unroll
         for (int mi = 0; mi < MT; ++mi)
-          if (mi < MI) wq2[mi] = *reinterpret_cast<const uint4*>(wrow[mi] + (long long)sn * P.TPK * CC);
+          wq[(kc + PF - 1) % PF][mi] = *reinterpret_cast<const uint4*>(wrow[mi] + (kc + PF - 1) * 32);
       }
+      const int to = tap_off(kc);
+      const bool none = kc * TPK + (sub * 8) / CC >= 9;
 #pragma unroll
-      for (int mi = 0; mi < MT; ++mi) {
-        if (mi < MI) {
+      for (int rr = 0; rr < RW; ++rr) {
+        bf16x8 bf[NTL];
 #pragma unroll
-          for (int ni = 0; ni < NTL; ++ni) acc[mi][ni] = mfma(afrag[mi], bfrag[ni], acc[mi][ni]);
+        for (int ni = 0; ni < NTL; ++ni) {
+          uint4 q = *reinterpret_cast<const uint4*>(bx + to + (rr * TW2 + ni * 16) * PS);
+          if (TPK > 1 && kc == KS - 1 && none) q = make_uint4(0u, 0u, 0u, 0u);
+          bf[ni] = __builtin_bit_cast(bf16x8, q);
         }
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NTL; ++ni)
+            acc[rr][mi][ni] = mfma(__builtin_bit_cast(bf16x8, wq[kc % PF][mi]), bf[ni], acc[rr][mi][ni]);
       }
     }
-    __syncthreads();
+    if (more) {
+#pragma unroll
+      for (int mi = 0; mi < MT; ++mi) wrow[mi] += KS * 32;
+      __syncthreads();
+    }
   }
 
-  const int y = ty0 + wave;
   if (!UP && a.ksplit > 1) {  // the upsampled route is launched unsplit
     // raw partial sums of this split; the finishing kernel applies the epilogue
-    if (y >= H) return;
 #pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-      if (mi >= MI) continue;
-      const int co = co0 + mi * 16 + sub * 4;
+    for (int rr = 0; rr < RW; ++rr) {
+      const int y = y0 + rr;
+      if (y >= H) continue;
 #pragma unroll
-      for (int ni = 0; ni < NTL; ++ni) {
-        const int x = tx0 + ni * 16 + n16;
-        if (x >= W) continue;
-        const long long off = ((((long long)ks * a.B + b) * H + y) * W + x) * P.Coutp + co;
-        *reinterpret_cast<float4*>(a.kpart + off) =
-            make_float4(acc[mi][ni][0], acc[mi][ni][1], acc[mi][ni][2], acc[mi][ni][3]);
+      for (int mi = 0; mi < MT; ++mi) {
+        const int co = co0 + mi * 16 + sub * 4;
+#pragma unroll
+        for (int ni = 0; ni < NTL; ++ni) {
+          const int x = tx0 + ni * 16 + n16;
+          if (x >= W) continue;
+          const long long off = ((((long long)ks * a.B + b) * H + y) * W + x) * P.Coutp + co;
+          *reinterpret_cast<float4*>(a.kpart + off) =
+              make_float4(acc[rr][mi][ni][0], acc[rr][mi][ni][1], acc[rr][mi][ni][2], acc[rr][mi][ni][3]);
+        }
       }
     }
     return;
   }
   if constexpr (OUTF32) {
-    if (a.rt.gA) {
-      route_store<MT, NTL, UP>(a, acc, b, ty0, tx0, co0, MI, reinterpret_cast<float*>(sX));
-      return;
-    }
-  }
-  if (y >= H) return;
+    // FP32 outputs are input gradients, always routed (launch_conv3)
+    route_store<MT, NTL, RW, UP>(a, acc, b, y0, tx0, co0);
+  } else {
 #pragma unroll
-  for (int mi = 0; mi < MT; ++mi) {
-    if (mi >= MI) continue;
-    const int co = co0 + mi * 16 + sub * 4;
-    if (co >= P.Cout) continue;
+    for (int mi = 0; mi < MT; ++mi) {
+      const int co = co0 + mi * 16 + sub * 4;
+      if (co >= P.Cout) continue;
+      float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (a.bias) bias = make_float4(a.bias[co], a.bias[co + 1], a.bias[co + 2], a.bias[co + 3]);
 #pragma unroll
-    for (int ni = 0; ni < NTL; ++ni) {
-      const int x = tx0 + ni * 16 + n16;
-      if (x >= W) continue;
-      float o[4];
+      for (int rr = 0; rr < RW; ++rr) {
+        const int y = y0 + rr;
+        if (y >= H) continue;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        o[i] = acc[mi][ni][i] + (a.bias ? a.bias[co + i] : 0.f);
-        if (a.relu) o[i] = fmaxf(o[i], 0.f);
-      }
-      const long long off = (((long long)b * H + y) * W + x) * P.Cout + co;
-      if constexpr (OUTF32) {
-        *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) = make_float4(o[0], o[1], o[2], o[3]);
-      } else {
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + off) =
-            make_uint2(f2bf(o[0]) | (f2bf(o[1]) << 16), f2bf(o[2]) | (f2bf(o[3]) << 16));
+        for (int ni = 0; ni < NTL; ++ni) {
+          const int x = tx0 + ni * 16 + n16;
+          if (x >= W) continue;
+          float o[4] = {acc[rr][mi][ni][0] + bias.x, acc[rr][mi][ni][1] + bias.y, acc[rr][mi][ni][2] + bias.z,
+                        acc[rr][mi][ni][3] + bias.w};
+          if (a.relu) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = fmaxf(o[i], 0.f);
+          }
+          const long long off = (((long long)b * H + y) * W + x) * P.Cout + co;
+          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + off) =
+              make_uint2(f2bf2(o[0], o[1]), f2bf2(o[2], o[3]));
+        }
       }
     }
   }
@@ -497,7 +495,7 @@ __global__ __launch_bounds__(256) void k_conv_finish(ConvArgs a) {
           *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) = make_float4(o[0], o[1], o[2], o[3]);
         } else {
           *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + off) =
-              make_uint2(f2bf(o[0]) | (f2bf(o[1]) << 16), f2bf(o[2]) | (f2bf(o[3]) << 16));
+              make_uint2(f2bf2(o[0], o[1]), f2bf2(o[2], o[3]));
         }
       } else if (co >= R.Ca) {
         const long long ob = pix * R.Cb + (co - R.Ca);
@@ -555,36 +553,31 @@ __device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p, int step) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <bool AF32, int COT>
+template <bool AF32, int MODE, int COT, int NI>
 __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
   constexpr int MT = COT / 16;
   constexpr int NG = COT / 8;            // 8-channel groups of the output gradient
   constexpr int ZP = COT + 8;            // LDS pixel stride of the output gradient
   constexpr int XW = kWgTW + 2, XR = kWgTH + 2;
-  constexpr int XP = 32 + 8;             // LDS pixel stride of the input (chunks of up to 32 channels)
+  constexpr int XP = 16 * NI + 8;        // LDS pixel stride of the input
   __shared__ __attribute__((aligned(16))) uint16_t sZ[kWgTH * kWgTW * ZP];
   __shared__ __attribute__((aligned(16))) uint16_t sX[XR * XW * XP];
   const int H = a.in.H, W = a.in.W;
-  const int cc = (int)blockIdx.x, co0 = (int)blockIdx.y * COT, split = (int)blockIdx.z;
+  const int cc = a.cc0 + (int)blockIdx.x, co0 = (int)blockIdx.y * COT, split = (int)blockIdx.z;
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
   const int sub = lane >> 4, n16 = lane & 15;
-  const int MI = min(MT, (a.Cout - co0 + 15) >> 4);
-  // 16-channel input tiles of this chunk holding real channels (the last
-  // chunk of a padded count stages and multiplies only those)
-  const int NI = min(a.CCw, a.Cin - cc * a.CCw + 15) >> 4;
-  const int ngx = 2 * NI;
   const int tiles_x = (W + kWgTW - 1) / kWgTW, tiles_y = (H + kWgTH - 1) / kWgTH;
   const int T = a.B * tiles_x * tiles_y;
   // this lane's transpose-read offsets: pixel n16 / 4 of its k-group, channel quad n16 % 4
   const int kp = 8 * sub + (n16 >> 2), cq = 4 * (n16 & 3);
 
-  f32x4 acc[3][MT][2];
+  f32x4 acc[3][MT][NI];
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) acc[s][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int ni = 0; ni < NI; ++ni) acc[s][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
   // bias partial: thread t always stages channel group t % NG
   float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -593,127 +586,58 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
     for (int row = 0; row < kWgTH; ++row) {
       bf16x8 af[MT];
 #pragma unroll
-      for (int mi = 0; mi < MT; ++mi)
-        af[mi] = mi < MI ? tr_frag(sZ + (row * kWgTW + kp) * ZP + mi * 16 + cq, 4 * ZP) : bf16x8{};
+      for (int mi = 0; mi < MT; ++mi) af[mi] = tr_frag(sZ + (row * kWgTW + kp) * ZP + mi * 16 + cq, 4 * ZP);
 #pragma unroll
       for (int s = 0; s < 3; ++s) {
         const int kk = wave + 4 * s;
         if (kk >= 9) continue;
         const int dy = kk / 3, dx = kk - dy * 3;
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-          if (ni >= NI) continue;
+        for (int ni = 0; ni < NI; ++ni) {
           const bf16x8 bf = tr_frag(sX + ((row + dy) * XW + kp + dx) * XP + ni * 16 + cq, 4 * XP);
 #pragma unroll
-          for (int mi = 0; mi < MT; ++mi)
-            if (mi < MI) acc[s][mi][ni] = mfma(af[mi], bf, acc[s][mi][ni]);
+          for (int mi = 0; mi < MT; ++mi) acc[s][mi][ni] = mfma(af[mi], bf, acc[s][mi][ni]);
         }
       }
     }
   };
 
-  // Light loaders (BF16 without pooling) and 16-channel output tiles: the
-  // next tile's loads are issued before this tile's multiplies, so a
-  // workgroup walking many tiles waits on one memory latency per tile less
-  // (wider tiles measured slower with the extra registers).
-  constexpr int UZ = kWgTH * kWgTW * NG / 256;  // output-gradient tasks per thread
-  constexpr int UX = 4;                           // input tasks per thread (XR XW ngx <= 816)
-  if (COT == 16 && !AF32 && a.in.modeA != 2) {
-    const int ntx = XR * XW * ngx;
-    float4 zp[UZ], zq[UZ];
-    uint4 xq[UX];
-    auto fetch = [&](int t) {
-      const int b = t / (tiles_x * tiles_y);
-      const int rem = t - b * tiles_x * tiles_y;
-      const int ty0 = (rem / tiles_x) * kWgTH, tx0 = (rem % tiles_x) * kWgTW;
+  // the next tile's loads are issued before this tile's multiplies
+  TileStage<true, 0, NG, kWgTH, kWgTW, ZP> sz;   // output gradient (of the pre-activation), [pixel][co]
+  TileStage<AF32, MODE, 2 * NI, XR, XW, XP> sx;     // input tile with a one-pixel halo, [pixel][ci]
+  ConvIn gz{};
+  gz.A = a.gY;
+  gz.Ca = a.Cout;
+  gz.H = H;
+  gz.W = W;
+  auto fetch = [&](int t) {
+    const int b = t / (tiles_x * tiles_y);
+    const int rem = t - b * tiles_x * tiles_y;
+    const int ty0 = (rem / tiles_x) * kWgTH, tx0 = (rem % tiles_x) * kWgTW;
+    sz.init(gz, b, ty0, tx0);
+    sz.fetch(gz, co0);
+    sx.init(a.in, b, ty0 - 1, tx0 - 1);
+    sx.fetch(a.in, cc * a.CCw);
+  };
+  fetch(split);  // split < T: the host takes at most T splits
+  for (int t = split; t < T; t += a.nsplit) {
 #pragma unroll
-      for (int u = 0; u < UZ; ++u) {
-        const int task = (int)threadIdx.x + u * 256;
-        const int g = task % NG, pix = task / NG;
-        const int row = pix / kWgTW, px = pix - row * kWgTW;
-        const int y = ty0 + row, x = tx0 + px, co = co0 + g * 8;
-        zp[u] = zq[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (y < H && x < W && co < a.Cout) {
-          const long long o = (((long long)b * H + y) * W + x) * a.Cout + co;
-          zp[u] = *reinterpret_cast<const float4*>(a.gY + o);
-          zq[u] = *reinterpret_cast<const float4*>(a.gY + o + 4);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UX; ++u) {
-        const int task = (int)threadIdx.x + u * 256;
-        xq[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (task < ntx) {
-          const int g = task % ngx, pix = task / ngx;
-          const int r = pix / XW, xx = pix - r * XW;
-          const uint4* src = in8_src(a.in, b, ty0 - 1 + r, tx0 - 1 + xx, cc * a.CCw + g * 8);
-          if (src) xq[u] = *src;
-        }
-      }
-    };
-    fetch(split);  // split < T: the host takes at most T splits
-    for (int t = split; t < T; t += a.nsplit) {
-#pragma unroll
-      for (int u = 0; u < UZ; ++u) {
-        const int task = (int)threadIdx.x + u * 256;
-        const float v[8] = {zp[u].x, zp[u].y, zp[u].z, zp[u].w, zq[u].x, zq[u].y, zq[u].z, zq[u].w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) bsum[i] += v[i];
-        *reinterpret_cast<uint4*>(sZ + (task / NG) * ZP + (task % NG) * 8) = pack8(v);
-      }
-#pragma unroll
-      for (int u = 0; u < UX; ++u) {
-        const int task = (int)threadIdx.x + u * 256;
-        if (task < ntx) *reinterpret_cast<uint4*>(sX + (task / ngx) * XP + (task % ngx) * 8) = xq[u];
-      }
-      __syncthreads();
-      if (t + a.nsplit < T) fetch(t + a.nsplit);
-      tile_mfma();
-      __syncthreads();
+    for (int u = 0; u < sz.S; ++u) {
+      bsum[0] += sz.f0[u].x;
+      bsum[1] += sz.f0[u].y;
+      bsum[2] += sz.f0[u].z;
+      bsum[3] += sz.f0[u].w;
+      bsum[4] += sz.f1[u].x;
+      bsum[5] += sz.f1[u].y;
+      bsum[6] += sz.f1[u].z;
+      bsum[7] += sz.f1[u].w;
     }
-  } else {
-    for (int t = split; t < T; t += a.nsplit) {
-      const int b = t / (tiles_x * tiles_y);
-      const int rem = t - b * tiles_x * tiles_y;
-      const int ty0 = (rem / tiles_x) * kWgTH, tx0 = (rem % tiles_x) * kWgTW;
-      // output gradient (of the pre-activation), [pixel][co]; the loads of
-      // U tasks are issued before any is stored
-      {
-        constexpr int U = 4;
-        constexpr int NTASK = kWgTH * kWgTW * NG;
-        for (int t0 = threadIdx.x; t0 < NTASK; t0 += U * 256) {
-          float4 p[U], q[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int task = t0 + u * 256;
-            p[u] = q[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int g = task % NG, pix = task / NG;
-            const int row = pix / kWgTW, px = pix - row * kWgTW;
-            const int y = ty0 + row, x = tx0 + px, co = co0 + g * 8;
-            if (task < NTASK && y < H && x < W && co < a.Cout) {
-              const long long o = (((long long)b * H + y) * W + x) * a.Cout + co;
-              p[u] = *reinterpret_cast<const float4*>(a.gY + o);
-              q[u] = *reinterpret_cast<const float4*>(a.gY + o + 4);
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int task = t0 + u * 256;
-            if (task < NTASK) {
-              const float v[8] = {p[u].x, p[u].y, p[u].z, p[u].w, q[u].x, q[u].y, q[u].z, q[u].w};
-#pragma unroll
-              for (int i = 0; i < 8; ++i) bsum[i] += v[i];
-              *reinterpret_cast<uint4*>(sZ + (task / NG) * ZP + (task % NG) * 8) = pack8(v);
-            }
-          }
-        }
-      }
-      // input tile with a one-pixel halo, [pixel][ci]
-      stage_tile<AF32>(a.in, b, ty0 - 1, tx0 - 1, XR, XW, cc * a.CCw, ngx, sX, XP);
-      __syncthreads();
-      tile_mfma();
-      __syncthreads();
-    }
+    sz.store(sZ);
+    sx.store(sX);
+    __syncthreads();
+    if (t + a.nsplit < T) fetch(t + a.nsplit);
+    tile_mfma();
+    __syncthreads();
   }
 
 #pragma unroll
@@ -722,10 +646,8 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
     if (kk >= 9) continue;
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi) {
-      if (mi >= MI) continue;
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        if (ni >= NI) continue;
+      for (int ni = 0; ni < NI; ++ni) {
         const int ci = cc * a.CCw + ni * 16 + n16;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1074,7 +996,7 @@ __global__ __launch_bounds__(256) void k_pack(PackAll a) {
       // co, input = forward output channel ci, taps flipped
       v = fw ? L.W[((long long)co * P.Cin + ci) * 9 + kk] : L.W[((long long)ci * P.Cout + co) * 9 + (8 - kk)];
     }
-    (fw ? L.Wp : L.Wtp)[i] = (uint16_t)f2bf(v);
+    (fw ? L.Wp : L.Wtp)[i] = (uint16_t)f2bf2(v, 0.f);
   }
 }
 
@@ -1103,60 +1025,68 @@ static inline unsigned grid_for(long long n, int per = 256, int cap = 8192) {
 // (such launches leave CUs idle while each workgroup walks every chunk).
 constexpr long long kConvSplitGroups = 512;
 
-// MFMA tile of a launch: MT 16-channel output tiles by NTL 16-column tiles
-// per wave.  4 x 2 in general and for the upsampled route; 16-channel
-// outputs take 1 x 4 (64 columns: wider tiles' input staging, 37-62 KB of
-// LDS, held a CU to two to four workgroups and measured slower).
-static void conv_tile(const ConvPack& pk, bool up, int& MT, int& NTL) {
-  MT = 4;
-  NTL = 2;
-  if (!up && pk.Coutp <= 16) {
-    MT = 1;
-    NTL = 4;
-  }
-}
-
-// Channel-chunk split of a launch (1: none); the host sizes the partial
-// buffer with this same function.
+// Channel-chunk split of a launch (1: none), by the workgroups of 4 rows x 32
+// columns x 64 channels (64 x 16 for at most 16 channels) that it has without.
+// The split decides the order in which an output's products are added, so it
+// goes by the sizes alone and not by the tile that is launched.  The host sizes
+// the partial buffer with this same function.
 int conv_ksplit(const ConvPack& pk, int B, int H, int W, bool up) {
-  int MT, NTL;
-  conv_tile(pk, up, MT, NTL);
-  const long long groups = (long long)((H + kConvTH - 1) / kConvTH) * ((W + 16 * NTL - 1) / (16 * NTL)) *
-                           ((pk.Coutp + 16 * MT - 1) / (16 * MT)) * B;
+  const bool narrow = !up && pk.Coutp <= 16;
+  const long long groups = (long long)((H + 3) / 4) * ((W + (narrow ? 63 : 31)) / (narrow ? 64 : 32)) *
+                           ((pk.Coutp + 63) / 64) * B;
   if (groups >= kConvSplitGroups) return 1;
   return (int)std::min<long long>(pk.ncc, (kConvSplitGroups + groups - 1) / groups);
 }
 
-template <int MT, int NTL>
-static void conv3_launch(const ConvArgs& a, bool af32, bool outf32, hipStream_t s) {
-  const int tiles = ((a.in.H + kConvTH - 1) / kConvTH) * ((a.in.W + 16 * NTL - 1) / (16 * NTL));
-  const int ks = a.ksplit;
-  const dim3 grid(tiles, (a.pk.Coutp + 16 * MT - 1) / (16 * MT), a.B * ks);
-  size_t lds = (size_t)(kConvTH + 2) * (16 * NTL + 2) * (a.pk.CC + 8) * sizeof(uint16_t);
-  if constexpr (MT == 4) {
-    if (ks == 1 && outf32 && a.rt.gA && a.rt.modeA == 1) {
-      // an upsampled route stages every wave's column-pair sums of its A tiles
-      lds = std::max(lds, (size_t)4 * (8 * NTL) * (16 * MT + 4) * sizeof(float));
-      hipLaunchKernelGGL((k_conv3<true, true, MT, NTL, true>), grid, dim3(256), lds, s, a);
-      return;
-    }
-  }
-  if (af32 && outf32) hipLaunchKernelGGL((k_conv3<true, true, MT, NTL>), grid, dim3(256), lds, s, a);
-  else if (af32) hipLaunchKernelGGL((k_conv3<true, false, MT, NTL>), grid, dim3(256), lds, s, a);
-  else hipLaunchKernelGGL((k_conv3<false, false, MT, NTL>), grid, dim3(256), lds, s, a);
+// MFMA tile of a launch: waves of 2 rows by 32 columns by 32 output channels
+// (64 columns where 16 channels are all).  Each weight fragment that comes
+// through the L1 then serves four products; one row halves that, and 64
+// channels cost the registers of a third wave per SIMD.  All convolutions of a
+// gradient step at 4 x 1024 x 256 pixels, base 16: 860 us, one row 1010, 64
+// channels 920; the 32 x 16-channel tiles 54 us with 64 columns, 56 with 32.
+template <bool AF32, bool OUTF32, int MODE, int CC, bool UP>
+static hipError_t conv3_pick(const ConvArgs& a, hipStream_t s) {
+  constexpr int RW = 2;
+  auto go = [&](auto mt) {
+    constexpr int MT = decltype(mt)::value, NTL = MT == 1 && !UP ? 4 : 2;
+    const int tiles = ((a.in.H + 4 * RW - 1) / (4 * RW)) * ((a.in.W + 16 * NTL - 1) / (16 * NTL));
+    const dim3 grid(tiles, a.pk.Coutp / (16 * MT), a.B * a.ksplit);
+    hipLaunchKernelGGL((k_conv3<AF32, OUTF32, MODE, CC, MT, NTL, RW, UP>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+  };
+  const int m16 = a.pk.Coutp / 16;
+  if (m16 % 2 == 0) return go(std::integral_constant<int, 2>{});
+  if (m16 % 3 == 0) return go(std::integral_constant<int, 3>{});
+  return go(std::integral_constant<int, 1>{});
 }
 
 hipError_t launch_conv3(const ConvArgs& args, bool af32, bool outf32, hipStream_t s) {
   ConvArgs a = args;
   a.ksplit = std::max(1, a.ksplit);  // the kernel divides by it
   const bool up = outf32 && a.rt.gA && a.rt.modeA == 1;
-  // FP32 outputs are input gradients: FP32 input, routed or not
-  if (outf32 && !af32) return hipErrorInvalidValue;
+  // FP32 outputs are input gradients: FP32 input, routed; an FP32 forward
+  // input is the network's single channel
+  if (outf32 && (!af32 || !a.rt.gA)) return hipErrorInvalidValue;
+  if (af32 && !outf32 && a.pk.CC != 8) return hipErrorInvalidValue;
   if (a.ksplit > 1 && (!a.kpart || a.ksplit > a.pk.ncc)) return hipErrorInvalidValue;
-  int MT, NTL;
-  conv_tile(a.pk, up, MT, NTL);
-  if (MT == 1) conv3_launch<1, 4>(a, af32, outf32, s);
-  else conv3_launch<4, 2>(a, af32, outf32, s);
+  const bool unsplit_up = up && a.ksplit == 1;
+  const int mode = a.in.modeA;
+  hipError_t e = hipErrorInvalidValue;
+#define UNET_CONV_CC(C)                                                                   \
+  if (a.pk.CC == C) {                                                                     \
+    if (unsplit_up) e = conv3_pick<true, true, 0, C, true>(a, s);                         \
+    else if (outf32) e = conv3_pick<true, true, 0, C, false>(a, s);                       \
+    else if (!af32 && mode == 0) e = conv3_pick<false, false, 0, C, false>(a, s);         \
+    else if (!af32 && mode == 2) e = conv3_pick<false, false, 2, C, false>(a, s);         \
+  }
+  UNET_CONV_CC(8)
+  UNET_CONV_CC(16)
+  UNET_CONV_CC(32)
+#undef UNET_CONV_CC
+  // an upsampled A comes with its skip, at least 24 channels together
+  if (!af32 && mode == 1 && a.pk.CC == 32) e = conv3_pick<false, false, 1, 32, false>(a, s);
+  if (af32 && !outf32) e = conv3_pick<true, false, 0, 8, false>(a, s);
+  if (e != hipSuccess) return e;
   if (a.ksplit > 1) {
     const long long npix = (long long)a.B * a.in.H * a.in.W;
     const long long n = npix * (a.pk.Cout >> 2);  // an upper bound of both index ranges
@@ -1170,19 +1100,38 @@ hipError_t launch_conv3(const ConvArgs& args, bool af32, bool outf32, hipStream_
 // for 16- and 32-channel layers)
 int wgrad_cot(int Cout) { return Cout <= 16 ? 16 : (Cout <= 32 ? 32 : 64); }
 
-hipError_t launch_wgrad(const WgradArgs& a, bool af32, hipStream_t s) {
+// The last channel chunk of a padded count with at most 16 real channels
+// stages and multiplies only those, in a launch of its own.
+hipError_t launch_wgrad(const WgradArgs& args, bool af32, hipStream_t s) {
+  WgradArgs a = args;
   const int cot = wgrad_cot(a.Cout);
-  const dim3 grid(a.nccw, (a.Cout + cot - 1) / cot, a.nsplit);
-  if (cot == 16) {
-    if (af32) hipLaunchKernelGGL((k_wgrad<true, 16>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_wgrad<false, 16>), grid, dim3(256), 0, s, a);
-  } else if (cot == 32) {
-    if (af32) hipLaunchKernelGGL((k_wgrad<true, 32>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_wgrad<false, 32>), grid, dim3(256), 0, s, a);
-  } else {
-    if (af32) hipLaunchKernelGGL((k_wgrad<true, 64>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_wgrad<false, 64>), grid, dim3(256), 0, s, a);
+  const int rest = a.Cin - (a.nccw - 1) * a.CCw;  // real channels of the last chunk
+  const int nhalf = rest <= 16 ? 1 : 0, nfull = a.nccw - nhalf;
+#define UNET_WGRAD_CASE(F, M, C)                                                                  \
+  if (af32 == F && a.in.modeA == M && cot == C) {                                                 \
+    const unsigned gy = (unsigned)((a.Cout + C - 1) / C), gz = (unsigned)a.nsplit;                \
+    if (nfull > 0) {                                                                              \
+      a.cc0 = 0;                                                                                  \
+      hipLaunchKernelGGL((k_wgrad<F, M, C, 2>), dim3((unsigned)nfull, gy, gz), dim3(256), 0, s, a); \
+    }                                                                                             \
+    if (nhalf > 0) {                                                                              \
+      a.cc0 = nfull;                                                                              \
+      hipLaunchKernelGGL((k_wgrad<F, M, C, 1>), dim3(1, gy, gz), dim3(256), 0, s, a);             \
+    }                                                                                             \
   }
+  UNET_WGRAD_CASE(true, 0, 16)
+  UNET_WGRAD_CASE(true, 0, 32)
+  UNET_WGRAD_CASE(true, 0, 64)
+  UNET_WGRAD_CASE(false, 0, 16)
+  UNET_WGRAD_CASE(false, 0, 32)
+  UNET_WGRAD_CASE(false, 0, 64)
+  UNET_WGRAD_CASE(false, 1, 16)
+  UNET_WGRAD_CASE(false, 1, 32)
+  UNET_WGRAD_CASE(false, 1, 64)
+  UNET_WGRAD_CASE(false, 2, 16)
+  UNET_WGRAD_CASE(false, 2, 32)
+  UNET_WGRAD_CASE(false, 2, 64)
+#undef UNET_WGRAD_CASE
   return hipGetLastError();
 }
 

@@ -239,3 +239,61 @@ def test_rejects_bad_shapes(A):
         net.forward(torch.zeros((1, 24, 64), device="cuda"))
     with pytest.raises(A.AshrtError):
         A.UNet(200, base=16)
+
+
+def _integers(A, shape):
+    """A network of small integers: inputs, targets, biases and three weights
+    of +-1 per output channel, so that sums are exact in FP32 in any order."""
+    import torch
+    B, H, W, P, base = shape
+    print(f"[gpu] unet integers B={B} H={H} W={W} P={P} base={base}", flush=True)
+    spec = U.UNetSpec(cin=1, pout=P, base=base)
+    rng = np.random.default_rng(3)
+    parts = []
+    for _, ci, co, k in spec.convs():
+        w = np.zeros((co, ci * k * k))
+        for o in range(co):
+            w[o, rng.choice(ci * k * k, size=3, replace=False)] = rng.choice([-1.0, 1.0, 1.0], size=3)
+        parts += [w.ravel(), rng.integers(0, 2, co).astype(float)]
+    theta = np.concatenate(parts)
+    x = rng.integers(-4, 5, (B, 1, H, W)).astype(float)
+    t_m = rng.integers(-3, 4, (B, P, H, W)).astype(float)
+    t_w = np.full((B, H, W), 0.5)
+    net = A.UNet(P, base=base)
+    net.set_params(theta)
+    dev = [torch.tensor(v, dtype=torch.float32, device="cuda") for v in (x[:, 0], t_m, t_w)]
+    return spec, theta, (x, t_m, t_w), net, dev
+
+
+# Tiles of 8 rows by 32 or 64 columns: heights of 3 and 6 of them and widths
+# with a remainder at every level; 8, 16 and 32 base channels reach each
+# channel chunk (8, 16, 32), output tile (16, 32, 48 channels) and loader
+# (same resolution, pooled, upsampled with its skip).  The outputs are those
+# of the BF16-operand reference to the last bit.
+@pytest.mark.parametrize("shape", [(1, 48, 80, 2, 16), (2, 48, 80, 4, 8), (1, 32, 96, 3, 32)])
+def test_forward_tile_edges_exact(A, shape):
+    spec, theta, (x, _, _), net, dev = _integers(A, shape)
+    y_m = net.forward(dev[0])[0].cpu().numpy()
+    with np.errstate(over="ignore"):  # the weight head's logits are large
+        ref = U.forward(spec, theta, x, bf16=True)[0]
+    assert np.array_equal(y_m, ref.astype(np.float32))
+
+
+# Powers of two: 1 / (pixels x channels) and with it every gradient is a dyadic
+# number (at other sizes BF16 ties of the exact gradient fall either way in
+# FP32), and the input gradients are those of the reference.  What is left is
+# the FP32 sums of the weight gradients, up to 3.4e-7 from the FP64 ones in a
+# layer when the reference sums in FP32; seven times that.
+@pytest.mark.parametrize("shape", [(1, 16, 16, 2, 16), (2, 32, 64, 4, 8), (1, 64, 128, 1, 16), (4, 16, 32, 2, 32)])
+def test_gradient_tile_edges_exact(A, shape):
+    spec, theta, (x, t_m, t_w), net, dev = _integers(A, shape)
+    loss, g = net.loss_grad(*dev, lam_w=0.0)
+    g = g.cpu().numpy()
+    with np.errstate(over="ignore"):
+        L_ref, g_ref = U.loss_and_grad(spec, theta, x, t_m, t_w, lam_w=0.0, bf16=True)
+    assert abs(loss - L_ref) <= 1e-6 * L_ref
+    o = 0
+    for name, ci, co, k in spec.convs():
+        sl = slice(o, o + co * ci * k * k + co)
+        assert rel_l2(g[sl], g_ref[sl]) <= 2.5e-6, name
+        o += co * ci * k * k + co
