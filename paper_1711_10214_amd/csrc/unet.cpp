@@ -5,10 +5,11 @@
 // Each convolution reads its input through a loader that fuses the 2x2 mean
 // pool (encoder), the nearest 2x upsample and the skip concatenation
 // (decoder), so pooled, upsampled and concatenated tensors never exist in
-// memory.  The backward pass walks the graph in reverse: bias gradient,
-// weight gradient (split over pixels, fixed-order reduction) and input
-// gradient (the same convolution kernel with transposed, tap-flipped
-// weights), whose result is routed back to the tensors the loader read.
+// memory.  The backward pass walks the graph in reverse with the input
+// gradients (the same convolution kernel with transposed, tap-flipped weights),
+// whose results are routed back to the tensors the loader read; then come the
+// weight and bias gradients of all layers (split over pixels, fixed-order
+// reduction).
 #include "ashrt.h"
 #include "unet.h"
 #include "unet_internal.h"
@@ -27,7 +28,7 @@ int set_error(int code, const std::string& msg);
 namespace unet {
 hipError_t launch_conv3(const ConvArgs& a, bool af32, bool outf32, hipStream_t s);
 int conv_ksplit(const ConvPack& pk, int B, int H, int W, bool up);
-hipError_t launch_wgrad(const WgradArgs& a, bool af32, hipStream_t s);
+hipError_t launch_wgrad(const WgradAll& a, int cot, hipStream_t s);
 hipError_t launch_wgrad_reduce(const RedAll& a, hipStream_t s);
 int wgrad_cot(int Cout);
 hipError_t launch_head_fwd(const HeadArgs& a, hipStream_t s);
@@ -52,14 +53,12 @@ int fail(int code, const std::string& m) { return ashrt::set_error(code, m); }
   } while (0)
 
 constexpr int kNConv = 18;
-// Pixel splits of a weight gradient: at most kWgradTargetGroups workgroups,
-// and no more splits than balance the FP32 partials each split writes (and
-// the reduction reads back) against the tiles each workgroup walks in
-// sequence: with P partial bytes per split and T pixel tiles, about
-// sqrt(T kWgradTileBytes / P) splits, kWgradTileBytes being the partial
-// traffic that costs about as long as one tile's load latency.
-constexpr int kWgradTargetGroups = 1024;
-constexpr double kWgradTileBytes = 6e6;
+// Workgroups of a weight-gradient launch (all layers of one output-channel
+// tile).  A workgroup's partials are written and read back once however many
+// pixel tiles it walks, so the launch takes two rounds of the 512 that are
+// resident (two on each CU).  At 4 x 1024 x 256 pixels, base 16, the three
+// launches and the reduction take 343 us; 768 groups 385, 512 355, 384 425.
+constexpr int kWgradGroups = 1024;
 
 ConvPack make_pack(int Cin, int Cout) {
   ConvPack p{};
@@ -169,7 +168,7 @@ void build_graph(unet_net& n) {
 struct WsLayout {
   std::vector<size_t> act, gact;
   std::vector<size_t> wpart, bpart;  // per layer: its weight-gradient partials stay until the reduction
-  size_t y_m = 0, y_w = 0, hpart = 0, lpart = 0, kpart = 0, total = 0;
+  size_t hpart = 0, lpart = 0, kpart = 0, total = 0;
   std::vector<int> ks_f, ks_d;  // channel-chunk splits of the forward and input-gradient convolutions
   std::vector<int> nsplit;
   int nblk_h = 0;
@@ -177,6 +176,7 @@ struct WsLayout {
 
 int wgrad_cipw(const Layer& l) { return std::max(16, l.f.Cip); }
 int wgrad_ccw(const Layer& l) { return std::min(wgrad_cipw(l), 32); }
+int cot_index(int Cout) { return wgrad_cot(Cout) / 32; }  // tiles of 16, 32, 64: 0, 1, 2
 
 WsLayout layout(const unet_net& n, int B, int H, int W, bool train) {
   WsLayout w;
@@ -192,8 +192,6 @@ WsLayout layout(const unet_net& n, int B, int H, int W, bool train) {
     const Layer& l = n.L[i];
     w.act[i] = take((long long)B * (H >> l.level) * (W >> l.level) * l.co * 2);
   }
-  w.y_m = take(npix0 * n.pout * 4);
-  w.y_w = take(npix0 * 4);
   // FP32 partials of the convolutions split over their channel chunks
   long long kp = 0;
   w.ks_f.resize(kNConv);
@@ -210,20 +208,27 @@ WsLayout layout(const unet_net& n, int B, int H, int W, bool train) {
   if (train) {
     w.gact.resize(kNConv);
     w.nsplit.resize(kNConv);
+    // pixel splits: every workgroup of a launch walks about as many pixel
+    // tiles (chunks of 16 channels count for 0.6)
+    auto tiles = [&](const Layer& l) {
+      const int Hl = H >> l.level, Wl = W >> l.level;
+      return (long long)B * ((Hl + kWgTH - 1) / kWgTH) * ((Wl + kWgTW - 1) / kWgTW);
+    };
+    double work[3] = {0.0, 0.0, 0.0};  // tile visits by output-channel tile
+    for (int i = 0; i < kNConv; ++i) {
+      const Layer& l = n.L[i];
+      const int cot = wgrad_cot(l.co), ccw = wgrad_ccw(l), nccw = wgrad_cipw(l) / ccw;
+      const double chunks = l.ci - (nccw - 1) * ccw <= 16 ? nccw - 0.4 : nccw;
+      work[cot_index(l.co)] += (double)tiles(l) * chunks * ((l.co + cot - 1) / cot);
+    }
     for (int i = 0; i < kNConv; ++i) {
       const Layer& l = n.L[i];
       const int Hl = H >> l.level, Wl = W >> l.level;
       w.gact[i] = take((long long)B * Hl * Wl * l.co * 4);
-      const int cipw = wgrad_cipw(l), ccw = wgrad_ccw(l);
-      const long long T = (long long)B * ((Hl + kWgTH - 1) / kWgTH) * ((Wl + kWgTW - 1) / kWgTW);
-      const int cot = wgrad_cot(l.co);
-      const long long groups = (long long)(cipw / ccw) * ((l.co + cot - 1) / cot);
-      const double pbytes = (double)l.co * 9 * cipw * 4;
-      const long long nbal = std::max(1LL, (long long)std::sqrt((double)T * kWgradTileBytes / pbytes));
-      const int ns = (int)std::max(
-          1LL, std::min({T, (long long)kWgradTargetGroups / std::max(1LL, groups), nbal}));
+      const double walk = std::max(1.0, work[cot_index(l.co)] / kWgradGroups);
+      const int ns = (int)std::max(1.0, std::min((double)tiles(l), (double)tiles(l) / walk + 0.5));
       w.nsplit[i] = ns;
-      w.wpart.push_back(take((long long)ns * l.co * 9 * cipw * 4));
+      w.wpart.push_back(take((long long)ns * l.co * 9 * wgrad_cipw(l) * 4));
       w.bpart.push_back(take((long long)ns * l.co * 4));
     }
     w.nblk_h = (int)((npix0 + 255) / 256);  // head-backward workgroups, one per 256 pixels
@@ -284,6 +289,7 @@ int run_forward(const unet_net& n, const WsLayout& w, unsigned char* ws, const f
     a.kpart = (float*)(ws + w.kpart);
     U_TRY(launch_conv3(a, l.srcA < 0, false, s));
   }
+  if (!y_m) return ASHRT_OK;  // training: the backward pass has the heads
   HeadArgs h{};
   h.h = (const uint16_t*)(ws + w.act[kNConv - 1]);
   h.Wm = n.theta + n.L[kNConv].woff;
@@ -311,8 +317,6 @@ int run_backward(const unet_net& n, const WsLayout& w, unsigned char* ws, const 
   la.hd.h = (const uint16_t*)(ws + w.act[kNConv - 1]);
   la.hd.Wm = n.theta + n.L[kNConv].woff;
   la.hd.Ww = n.theta + n.L[kNConv + 1].woff;
-  la.hd.y_m = (float*)(ws + w.y_m);
-  la.hd.y_w = (float*)(ws + w.y_w);
   la.hd.C1 = n.base;
   la.hd.P = n.pout;
   la.hd.B = B;
@@ -327,14 +331,17 @@ int run_backward(const unet_net& n, const WsLayout& w, unsigned char* ws, const 
   la.ne = n.pout * n.base + n.pout + n.base + 1;
   U_TRY(launch_head_bwd(la, w.nblk_h, g + n.L[kNConv].woff, loss, lam_w, s));
 
-  static_assert(kNConv <= kRedMax, "reduction table too small");
+  static_assert(kNConv <= kRedMax && kNConv <= kWgradMax, "layer tables too small");
+  WgradAll wg[3] = {};  // by output-channel tile
   RedAll red{};
   red.n = kNConv;
   for (int i = kNConv - 1; i >= 0; --i) {
     const Layer& l = n.L[i];
     const int Hl = H >> l.level, Wl = W >> l.level;
     const float* gY = (const float*)(ws + w.gact[i]);
-    WgradArgs wa{};
+    const int cot = wgrad_cot(l.co);
+    WgradAll& wl = wg[cot_index(l.co)];
+    WgradArgs& wa = wl.L[wl.n];
     wa.in = conv_input(n, w, ws, x, i, H, W);
     wa.gY = gY;
     wa.Cout = l.co;
@@ -346,7 +353,9 @@ int run_backward(const unet_net& n, const WsLayout& w, unsigned char* ws, const 
     wa.bpart = (float*)(ws + w.bpart[i]);
     wa.nsplit = w.nsplit[i];
     wa.B = B;
-    U_TRY(launch_wgrad(wa, l.srcA < 0, s));
+    wa.af32 = l.srcA < 0;
+    wl.wg[wl.n + 1] = wl.wg[wl.n] + wa.nsplit * wa.nccw * ((l.co + cot - 1) / cot);
+    ++wl.n;
     RedLayer& rl = red.L[i];
     rl.part = wa.part;
     rl.bpart = wa.bpart;
@@ -387,6 +396,7 @@ int run_backward(const unet_net& n, const WsLayout& w, unsigned char* ws, const 
     da.kpart = (float*)(ws + w.kpart);
     U_TRY(launch_conv3(da, true, true, s));
   }
+  for (int c = 0; c < 3; ++c) U_TRY(launch_wgrad(wg[c], 16 << c, s));
   // 16 elements a workgroup (16 thread groups over the splits) where a
   // layer has at least 256 splits, else 64 (4 groups)
   red.wg[0] = 0;
@@ -544,7 +554,7 @@ static int loss_grad_impl(unet_net* n, const float* x, const float* t_m, const f
   st = check_ws(w, ws, wsb);
   if (st) return st;
   unsigned char* W8 = (unsigned char*)ws;
-  st = run_forward(*n, w, W8, x, B, H, W, (float*)(W8 + w.y_m), (float*)(W8 + w.y_w), s);
+  st = run_forward(*n, w, W8, x, B, H, W, nullptr, nullptr, s);
   if (st) return st;
   return run_backward(*n, w, W8, x, t_m, t_w, B, H, W, lam_w, loss, grad, s);
 }

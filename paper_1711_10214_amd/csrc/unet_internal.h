@@ -76,10 +76,19 @@ struct WgradArgs {
   const float* gY;          // FP32 NHWC [B][H][W][Cout]: gradient of the conv output before its ReLU
   int Cout, Cin;            // real counts
   int CCw, nccw, Cipw;      // channel chunk of the reduction tile (16 or 32), chunks, padded count
-  int cc0;                  // first chunk of this launch (launch_wgrad)
   float* part;              // [nsplit][Cout][9][Cipw]
   float* bpart;             // [nsplit][Cout] bias partials (from channel chunk 0)
   int nsplit, B;
+  int af32;                 // the input is the FP32 network input
+};
+// The layers of one weight-gradient launch: layer l has the workgroups wg[l]
+// <= b < wg[l + 1], its pixel splits varying fastest, then its input-channel
+// chunks, then its output-channel tiles.
+constexpr int kWgradMax = 20;
+struct WgradAll {
+  int n;
+  int wg[kWgradMax + 1];
+  WgradArgs L[kWgradMax];
 };
 
 struct PackArgs {

@@ -533,19 +533,26 @@ __global__ __launch_bounds__(256) void k_conv_finish(ConvArgs a) {
 }
 
 // ------------------------------------------------------------ weight gradient
-// Grid: (input-channel chunks, output-channel tiles of COT (16, 32 or 64), pixel splits).
-// Wave w accumulates the taps kk = w, w + 4, w + 8.  Both operands are
-// staged in LDS pixel-major with channels contiguous (one 16-byte store per
-// 8 channels of a pixel, the tap shift being a per-lane address offset) and
-// read as MFMA fragments with the gfx950 LDS transpose read: for each group
-// of 16 lanes, lane 4 r + q loads four consecutive channels 4 q + [0, 4) of
-// pixel r, and lane c receives channel c of pixels 0..3.  Two such reads
-// (pixels 8 s + [0, 4) and 8 s + [4, 8)) give lane (s, c) the eight
-// consecutive pixels of k-group s of channel c.
+// One launch for all layers of an output-channel tile COT (16, 32 or 64): a
+// workgroup takes an input-channel chunk, an output-channel tile and every
+// nsplit-th pixel tile of one layer.  Layer by layer, the small ones needed
+// hundreds of pixel splits to fill the card, and their partials, 342 MB at 4 x
+// 1024 x 256 pixels, base 16, cost as much as the products.
+// The 9 taps x NI input tiles go to the waves in turn (unit u to wave u mod 4).
+// Both operands are staged in LDS pixel-major with channels contiguous (one
+// 16-byte store per 8 channels of a pixel, the tap shift being an address
+// offset) and read as MFMA fragments with the gfx950 LDS transpose read: for
+// each group of 16 lanes, lane 4 r + q loads four consecutive channels 4 q +
+// [0, 4) of pixel r, and lane c receives channel c of pixels 0..3.  k-group s
+// of a row takes its pixels 4 s + [0, 4) and 16 + 4 s + [0, 4) (any bijection
+// does, the same for both operands): 32 lanes then read eight consecutive
+// pixels, which strides of an odd number of 32-byte units keep on different
+// banks.  All layers 303 us and the reduction 42 (485 and 96 layer by layer).
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 
+// The 8 pixels p and p + step of this lane's k-group.
 __device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p, int step) {
   const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)((__attribute__((address_space(3))) uint16_t*)p));
   const v4i16 hi =
@@ -553,58 +560,38 @@ __device__ __forceinline__ bf16x8 tr_frag(const uint16_t* p, int step) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// LDS pixel stride of C channels in BF16 values: an odd number of 32-byte units.
+constexpr int wg_ps(int C) { return C % 32 == 0 ? C + 16 : C; }
+
 template <bool AF32, int MODE, int COT, int NI>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
+__device__ __forceinline__ void wgrad_item(const WgradArgs& a, int cc, int co0, int split, uint16_t* lds) {
   constexpr int MT = COT / 16;
   constexpr int NG = COT / 8;            // 8-channel groups of the output gradient
-  constexpr int ZP = COT + 8;            // LDS pixel stride of the output gradient
+  constexpr int ZP = wg_ps(COT);
   constexpr int XW = kWgTW + 2, XR = kWgTH + 2;
-  constexpr int XP = 16 * NI + 8;        // LDS pixel stride of the input
-  __shared__ __attribute__((aligned(16))) uint16_t sZ[kWgTH * kWgTW * ZP];
-  __shared__ __attribute__((aligned(16))) uint16_t sX[XR * XW * XP];
+  constexpr int XP = wg_ps(16 * NI);
+  constexpr int UNITS = 9 * NI, US = (UNITS + 3) / 4;
+  uint16_t* const sZ = lds;
+  uint16_t* const sX = lds + kWgTH * kWgTW * ZP;
   const int H = a.in.H, W = a.in.W;
-  const int cc = a.cc0 + (int)blockIdx.x, co0 = (int)blockIdx.y * COT, split = (int)blockIdx.z;
-  const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
   const int sub = lane >> 4, n16 = lane & 15;
   const int tiles_x = (W + kWgTW - 1) / kWgTW, tiles_y = (H + kWgTH - 1) / kWgTH;
   const int T = a.B * tiles_x * tiles_y;
   // this lane's transpose-read offsets: pixel n16 / 4 of its k-group, channel quad n16 % 4
-  const int kp = 8 * sub + (n16 >> 2), cq = 4 * (n16 & 3);
+  const int kp = 4 * sub + (n16 >> 2), cq = 4 * (n16 & 3);
 
-  f32x4 acc[3][MT][NI];
+  f32x4 acc[US][MT];
 #pragma unroll
-  for (int s = 0; s < 3; ++s)
+  for (int s = 0; s < US; ++s)
 #pragma unroll
-    for (int mi = 0; mi < MT; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) acc[s][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mi = 0; mi < MT; ++mi) acc[s][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
   // bias partial: thread t always stages channel group t % NG
   float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // the MFMA work of the tile staged in sZ and sX
-  auto tile_mfma = [&]() {
-    for (int row = 0; row < kWgTH; ++row) {
-      bf16x8 af[MT];
-#pragma unroll
-      for (int mi = 0; mi < MT; ++mi) af[mi] = tr_frag(sZ + (row * kWgTW + kp) * ZP + mi * 16 + cq, 4 * ZP);
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const int kk = wave + 4 * s;
-        if (kk >= 9) continue;
-        const int dy = kk / 3, dx = kk - dy * 3;
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-          const bf16x8 bf = tr_frag(sX + ((row + dy) * XW + kp + dx) * XP + ni * 16 + cq, 4 * XP);
-#pragma unroll
-          for (int mi = 0; mi < MT; ++mi) acc[s][mi][ni] = mfma(af[mi], bf, acc[s][mi][ni]);
-        }
-      }
-    }
-  };
-
   // the next tile's loads are issued before this tile's multiplies
   TileStage<true, 0, NG, kWgTH, kWgTW, ZP> sz;   // output gradient (of the pre-activation), [pixel][co]
-  TileStage<AF32, MODE, 2 * NI, XR, XW, XP> sx;     // input tile with a one-pixel halo, [pixel][ci]
+  TileStage<AF32, MODE, 2 * NI, XR, XW, XP> sx;  // input tile with a one-pixel halo, [pixel][ci]
   ConvIn gz{};
   gz.A = a.gY;
   gz.Ca = a.Cout;
@@ -636,32 +623,41 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
     sx.store(sX);
     __syncthreads();
     if (t + a.nsplit < T) fetch(t + a.nsplit);
-    tile_mfma();
+    for (int row = 0; row < kWgTH; ++row) {
+      bf16x8 af[MT];
+#pragma unroll
+      for (int mi = 0; mi < MT; ++mi) af[mi] = tr_frag(sZ + (row * kWgTW + kp) * ZP + mi * 16 + cq, 16 * ZP);
+#pragma unroll
+      for (int s = 0; s < US; ++s) {
+        const int u = wave + 4 * s;
+        if (4 * s + 3 >= UNITS && u >= UNITS) continue;
+        const int kk = u / NI, ni = u - kk * NI, dy = kk / 3, dx = kk - dy * 3;
+        const bf16x8 bf = tr_frag(sX + ((row + dy) * XW + kp + dx) * XP + ni * 16 + cq, 16 * XP);
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) acc[s][mi] = mfma(af[mi], bf, acc[s][mi]);
+      }
+    }
     __syncthreads();
   }
 
 #pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int kk = wave + 4 * s;
-    if (kk >= 9) continue;
+  for (int s = 0; s < US; ++s) {
+    const int u = wave + 4 * s;
+    if (u >= UNITS) continue;
+    const int kk = u / NI, ci = cc * a.CCw + (u - kk * NI) * 16 + n16;
 #pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
+    for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) {
-        const int ci = cc * a.CCw + ni * 16 + n16;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int co = co0 + mi * 16 + sub * 4 + i;
-          if (co < a.Cout && ci < a.Cipw)
-            a.part[(((long long)split * a.Cout + co) * 9 + kk) * a.Cipw + ci] = acc[s][mi][ni][i];
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int co = co0 + mi * 16 + sub * 4 + i;
+        if (co < a.Cout && ci < a.Cipw)
+          a.part[(((long long)split * a.Cout + co) * 9 + kk) * a.Cipw + ci] = acc[s][mi][i];
       }
-    }
   }
   // bias partial of this split (channel chunk 0 only): the threads of one
   // channel group are added in thread order
-  if (a.bpart && cc == 0) {
-    float* red = reinterpret_cast<float*>(sX);  // the loop ended with a barrier
+  if (cc == 0) {
+    float* red = reinterpret_cast<float*>(lds);  // the loop ended with a barrier
 #pragma unroll
     for (int i = 0; i < 8; ++i) red[threadIdx.x * 8 + i] = bsum[i];
     __syncthreads();
@@ -671,6 +667,34 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
       for (int k = c >> 3; k < 256; k += NG) sum += red[k * 8 + (c & 7)];
       a.bpart[(long long)split * a.Cout + co0 + c] = sum;
     }
+  }
+}
+
+template <int COT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad(WgradAll A) {
+  constexpr int SZ = kWgTH * kWgTW * wg_ps(COT) + (kWgTH + 2) * (kWgTW + 2) * wg_ps(32);
+  static_assert(SZ * 2 >= 256 * 8 * 4, "the bias partials reuse the tiles");
+  __shared__ __attribute__((aligned(16))) uint16_t lds[SZ];
+  int l = 0;
+  while ((int)blockIdx.x >= A.wg[l + 1]) ++l;
+  const WgradArgs& a = A.L[l];
+  int i = (int)blockIdx.x - A.wg[l];
+  const int split = i % a.nsplit;
+  i /= a.nsplit;
+  const int cc = i % a.nccw, co0 = (i / a.nccw) * COT;
+  // the last chunk of a padded count with at most 16 real channels stages and multiplies only those
+  const bool half = a.Cin - cc * a.CCw <= 16;
+  if (a.af32) {  // the network's single-channel input
+    wgrad_item<true, 0, COT, 1>(a, cc, co0, split, lds);
+  } else if (a.in.modeA == 0) {
+    if (half) wgrad_item<false, 0, COT, 1>(a, cc, co0, split, lds);
+    else wgrad_item<false, 0, COT, 2>(a, cc, co0, split, lds);
+  } else if (a.in.modeA == 1) {
+    if (half) wgrad_item<false, 1, COT, 1>(a, cc, co0, split, lds);
+    else wgrad_item<false, 1, COT, 2>(a, cc, co0, split, lds);
+  } else {
+    if (half) wgrad_item<false, 2, COT, 1>(a, cc, co0, split, lds);
+    else wgrad_item<false, 2, COT, 2>(a, cc, co0, split, lds);
   }
 }
 
@@ -750,24 +774,29 @@ static void sum_parts(const float* part, int nblk, int ne, float* scratch, float
 // ------------------------------------------------------------ heads
 constexpr int kHeadRowTiles = 5;  // 16-row tiles of the P + 1 <= 65 head-gradient rows
 
-// One pixel per thread: y_m = Wm h + bm (P channels, planar output), y_w =
-// sigmoid(Ww h + bw).  FP32 weights in LDS.
-// C1 (8, 16 or 32) at compile time: the head input stays in registers and
-// every weight row is read as C1 / 4 16-byte LDS broadcasts.
+// Head weights are the same for every thread: read through the constant
+// address space they come as scalar loads and operands (as LDS broadcasts their
+// reads bound the kernel).
+typedef const __attribute__((address_space(4))) float cfloat;
+__device__ __forceinline__ cfloat* as_const(const float* p) { return (cfloat*)(unsigned long long)p; }
+
+// One row of the model head: bias + w . h.
 template <int C1>
-__global__ __launch_bounds__(256) void k_head_fwd(HeadArgs a) {
-  extern __shared__ __attribute__((aligned(16))) float shw[];
-  const int P = a.P;
-  float* sWm = shw;                 // [P][C1], then bm [P]
-  float* sWw = shw + P * C1 + P;    // [C1], then bw
-  for (int i = threadIdx.x; i < P * C1 + P; i += blockDim.x) sWm[i] = a.Wm[i];
-  for (int i = threadIdx.x; i < C1 + 1; i += blockDim.x) sWw[i] = a.Ww[i];
-  __syncthreads();
-  const long long HW = (long long)a.H * a.W, npix = a.B * HW;
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npix) return;
-  float h[C1];
-  const uint16_t* hp = a.h + p * C1;
+__device__ __forceinline__ float head_row(cfloat* w, float bias, const float (&h)[C1]) {
+  float s = bias;
+#pragma unroll
+  for (int c = 0; c < C1; ++c) s = fmaf(w[c], h[c], s);
+  return s;
+}
+
+// The weight head: w [C1], then its bias.
+template <int C1>
+__device__ __forceinline__ float head_sigmoid(cfloat* w, const float (&h)[C1]) {
+  return 1.0f / (1.0f + __expf(-head_row<C1>(w, w[C1], h)));
+}
+
+template <int C1>
+__device__ __forceinline__ void head_input(const uint16_t* hp, float (&h)[C1]) {
 #pragma unroll
   for (int c = 0; c < C1; c += 8) {
     float v[8];
@@ -775,39 +804,40 @@ __global__ __launch_bounds__(256) void k_head_fwd(HeadArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) h[c + i] = v[i];
   }
+}
+
+// One pixel per thread: y_m = Wm h + bm (P channels, planar output), y_w =
+// sigmoid(Ww h + bw), in FP32; C1 = 8, 16 or 32.  Bound by its output.
+template <int C1>
+__global__ __launch_bounds__(256) void k_head_fwd(HeadArgs a) {
+  const int P = a.P;
+  cfloat* const Wm = as_const(a.Wm);
+  const long long HW = (long long)a.H * a.W, npix = a.B * HW;
+  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= npix) return;
+  float h[C1];
+  head_input<C1>(a.h + p * C1, h);
   const long long b = p / HW, yx = p - b * HW;
   float* ym = a.y_m + b * P * HW + yx;
 #pragma unroll 2
-  for (int co = 0; co < P; ++co) {
-    float s = sWm[P * C1 + co];
-    const float4* w = reinterpret_cast<const float4*>(sWm + co * C1);
-#pragma unroll
-    for (int c = 0; c < C1 / 4; ++c) {
-      const float4 q = w[c];
-      s = fmaf(q.x, h[4 * c], s);
-      s = fmaf(q.y, h[4 * c + 1], s);
-      s = fmaf(q.z, h[4 * c + 2], s);
-      s = fmaf(q.w, h[4 * c + 3], s);
-    }
-    ym[co * HW] = s;
-  }
-  float z = sWw[C1];
-#pragma unroll
-  for (int c = 0; c < C1; ++c) z = fmaf(sWw[c], h[c], z);
-  a.y_w[p] = 1.0f / (1.0f + __expf(-z));
+  for (int co = 0; co < P; ++co) ym[co * HW] = head_row<C1>(Wm + co * C1, Wm[P * C1 + co], h);
+  a.y_w[p] = head_sigmoid<C1>(as_const(a.Ww), h);
 }
 
-// Loss terms, gradient of the head input's pre-activation (FP32 NHWC: the
+// The heads' outputs (as k_head_fwd has them; they stay in registers: written
+// and read back they were 268 MB at 4 x 1024 x 256 pixels and 32 channels),
+// loss terms, gradient of the head input's pre-activation (FP32 NHWC: the
 // head input is a ReLU output) and per-block partial sums of the
 // head-parameter gradient and of the two squared errors.
 // One 256-pixel block per workgroup.  Dynamic LDS: gy [256][P+1] (column
 // P: the gradient gz of the weight head's logit), h [256][C1+1] (column C1:
-// 1), Wm [P][C1], Ww [C1]; the waves' partials of the parameter gradient
+// 1); the waves' partials of the parameter gradient
 // reuse it from the start once those are read.  Every head parameter's
 // block gradient is one entry of sum_t gy[t] h[t]^T, a (P+1) x (C1+1)
 // outer-product sum (Wm, bm; Ww, bw), computed on the FP32 matrix cores,
 // each wave over a quarter of the block's pixels, and added over the waves
-// in wave order.
+// in wave order.  110 us at that size (152 with the separate forward pass),
+// about 65 of them vector instructions: the head both ways is 1024 FMAs a pixel.
 template <int C1>
 __global__ __launch_bounds__(256) void k_head_bwd(LossArgs a) {
   extern __shared__ __attribute__((aligned(16))) float sh[];
@@ -817,10 +847,8 @@ __global__ __launch_bounds__(256) void k_head_bwd(LossArgs a) {
   const int GP = P + 1, HC = C1 + 1;
   float* sgy = sh;
   float* shh = sgy + 256 * GP;
-  float* sWm = shh + 256 * HC;
-  float* sWw = sWm + P * C1;
-  for (int i = tid; i < P * C1; i += 256) sWm[i] = d.Wm[i];
-  for (int i = tid; i < C1; i += 256) sWw[i] = d.Ww[i];
+  cfloat* const Wm = as_const(d.Wm);  // [P][C1], then bm [P]
+  cfloat* const Ww = as_const(d.Ww);  // [C1], then bw
   const long long HW = (long long)d.H * d.W, npix = d.B * HW;
   const float inv_m = 1.0f / (float)((double)npix * P), inv_w = 1.0f / (float)npix;
   // parameter-gradient block sums on the FP32 matrix cores
@@ -839,57 +867,50 @@ __global__ __launch_bounds__(256) void k_head_bwd(LossArgs a) {
   double lm = 0.0, lw = 0.0;
   const long long p = (long long)blockIdx.x * 256 + tid;
   if (p < npix) {
-    const uint16_t* hp = d.h + p * C1;
-    for (int c = 0; c < C1; c += 8) {
-      float v[8];
-      unpack8(*reinterpret_cast<const uint4*>(hp + c), v);
+    float h[C1];
+    head_input<C1>(d.h + p * C1, h);
+    const float yw = head_sigmoid<C1>(Ww, h), dw = yw - a.t_w[p];
+    lw = (double)dw * (double)dw;
+    const float gz = 2.0f * a.lam_w * dw * inv_w * yw * (1.0f - yw);
+    sgy[tid * GP + P] = gz;
+    // g_h[c] = Ww[c] gz + sum over co of Wm[co][c] gy[co], co ascending
+    float s[C1];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) shh[tid * HC + c + i] = v[i];
+    for (int c = 0; c < C1; ++c) s[c] = Ww[c] * gz;
+    const long long b = p / HW, yx = p - b * HW;
+    const float* tm = a.t_m + b * P * HW + yx;
+    constexpr int UT = 16;  // targets in flight
+    for (int c0 = 0; c0 < P; c0 += UT) {
+      float t[UT];
+#pragma unroll
+      for (int k = 0; k < UT; ++k) t[k] = c0 + k < P ? tm[(c0 + k) * HW] : 0.f;
+#pragma unroll
+      for (int k = 0; k < UT; ++k) {
+        if (c0 + k >= P) continue;
+        cfloat* const w = Wm + (c0 + k) * C1;
+        const float df = head_row<C1>(w, Wm[P * C1 + c0 + k], h) - t[k];
+        lm += (double)df * (double)df;
+        const float gy = 2.0f * df * inv_m;
+        sgy[tid * GP + c0 + k] = gy;
+#pragma unroll
+        for (int c = 0; c < C1; ++c) s[c] = fmaf(w[c], gy, s[c]);
+      }
+    }
+    // the head input is a ReLU output: store the gradient of its pre-activation
+#pragma unroll
+    for (int c = 0; c < C1; ++c) {
+      if (!(h[c] > 0.f)) s[c] = 0.f;
+      shh[tid * HC + c] = h[c];
     }
     shh[tid * HC + C1] = 1.f;
-    const long long b = p / HW, yx = p - b * HW;
-    for (int co = 0; co < P; ++co) {
-      const long long o = (b * P + co) * HW + yx;
-      const float df = d.y_m[o] - a.t_m[o];
-      lm += (double)df * (double)df;
-      sgy[tid * GP + co] = 2.0f * df * inv_m;
-    }
-    const float yw = d.y_w[p], dw = yw - a.t_w[p];
-    lw = (double)dw * (double)dw;
-    sgy[tid * GP + P] = 2.0f * a.lam_w * dw * inv_w * yw * (1.0f - yw);
+#pragma unroll
+    for (int c = 0; c < C1; c += 4)
+      *reinterpret_cast<float4*>(a.g_h + p * C1 + c) = make_float4(s[c], s[c + 1], s[c + 2], s[c + 3]);
   } else {
     for (int co = 0; co < GP; ++co) sgy[tid * GP + co] = 0.f;
     for (int c = 0; c < HC; ++c) shh[tid * HC + c] = 0.f;
   }
   __syncthreads();
-  if (p < npix) {
-    // g_h[c] = Ww[c] gz + sum over co of Wm[co][c] gy[co], co ascending; all
-    // C1 sums in registers, each gy read once, each Wm row as C1 / 4
-    // 16-byte LDS broadcasts
-    const float gz = sgy[tid * GP + P];
-    float s[C1];
-#pragma unroll
-    for (int c = 0; c < C1; ++c) s[c] = sWw[c] * gz;
-    for (int co = 0; co < P; ++co) {
-      const float gy = sgy[tid * GP + co];
-      const float4* w = reinterpret_cast<const float4*>(sWm + co * C1);
-#pragma unroll
-      for (int c = 0; c < C1 / 4; ++c) {
-        const float4 q = w[c];
-        s[4 * c] = fmaf(q.x, gy, s[4 * c]);
-        s[4 * c + 1] = fmaf(q.y, gy, s[4 * c + 1]);
-        s[4 * c + 2] = fmaf(q.z, gy, s[4 * c + 2]);
-        s[4 * c + 3] = fmaf(q.w, gy, s[4 * c + 3]);
-      }
-    }
-    // the head input is a ReLU output: store the gradient of its pre-activation
-#pragma unroll
-    for (int c = 0; c < C1; ++c)
-      if (!(shh[tid * HC + c] > 0.f)) s[c] = 0.f;
-#pragma unroll
-    for (int c = 0; c < C1; c += 4)
-      *reinterpret_cast<float4*>(a.g_h + p * C1 + c) = make_float4(s[c], s[c + 1], s[c + 2], s[c + 3]);
-  }
   for (int ks = 0; ks < 16; ++ks) {
     const int t = 64 * wave + 4 * ks + kq;
     float hb[TC];
@@ -1100,38 +1121,15 @@ hipError_t launch_conv3(const ConvArgs& args, bool af32, bool outf32, hipStream_
 // for 16- and 32-channel layers)
 int wgrad_cot(int Cout) { return Cout <= 16 ? 16 : (Cout <= 32 ? 32 : 64); }
 
-// The last channel chunk of a padded count with at most 16 real channels
-// stages and multiplies only those, in a launch of its own.
-hipError_t launch_wgrad(const WgradArgs& args, bool af32, hipStream_t s) {
-  WgradArgs a = args;
-  const int cot = wgrad_cot(a.Cout);
-  const int rest = a.Cin - (a.nccw - 1) * a.CCw;  // real channels of the last chunk
-  const int nhalf = rest <= 16 ? 1 : 0, nfull = a.nccw - nhalf;
-#define UNET_WGRAD_CASE(F, M, C)                                                                  \
-  if (af32 == F && a.in.modeA == M && cot == C) {                                                 \
-    const unsigned gy = (unsigned)((a.Cout + C - 1) / C), gz = (unsigned)a.nsplit;                \
-    if (nfull > 0) {                                                                              \
-      a.cc0 = 0;                                                                                  \
-      hipLaunchKernelGGL((k_wgrad<F, M, C, 2>), dim3((unsigned)nfull, gy, gz), dim3(256), 0, s, a); \
-    }                                                                                             \
-    if (nhalf > 0) {                                                                              \
-      a.cc0 = nfull;                                                                              \
-      hipLaunchKernelGGL((k_wgrad<F, M, C, 1>), dim3(1, gy, gz), dim3(256), 0, s, a);             \
-    }                                                                                             \
-  }
-  UNET_WGRAD_CASE(true, 0, 16)
-  UNET_WGRAD_CASE(true, 0, 32)
-  UNET_WGRAD_CASE(true, 0, 64)
-  UNET_WGRAD_CASE(false, 0, 16)
-  UNET_WGRAD_CASE(false, 0, 32)
-  UNET_WGRAD_CASE(false, 0, 64)
-  UNET_WGRAD_CASE(false, 1, 16)
-  UNET_WGRAD_CASE(false, 1, 32)
-  UNET_WGRAD_CASE(false, 1, 64)
-  UNET_WGRAD_CASE(false, 2, 16)
-  UNET_WGRAD_CASE(false, 2, 32)
-  UNET_WGRAD_CASE(false, 2, 64)
-#undef UNET_WGRAD_CASE
+// The layers of one output-channel tile (wgrad_cot of each is cot).
+hipError_t launch_wgrad(const WgradAll& a, int cot, hipStream_t s) {
+  if (a.n < 1) return hipSuccess;
+  for (int l = 0; l < a.n; ++l)
+    if (a.L[l].af32 && a.L[l].Cin > 16) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.wg[a.n]);
+  if (cot == 16) hipLaunchKernelGGL(k_wgrad<16>, grid, dim3(256), 0, s, a);
+  else if (cot == 32) hipLaunchKernelGGL(k_wgrad<32>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_wgrad<64>, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1141,20 +1139,18 @@ hipError_t launch_wgrad_reduce(const RedAll& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-size_t head_fwd_lds(int P, int C1) { return (size_t)(P * C1 + P + C1 + 1) * 4; }
 size_t head_bwd_lds(int P, int C1) {
   // the four waves' 16 x 16 tiles of the (P + 1) x (C1 + 1) entries
   const size_t red = (size_t)4 * ((P + 16) / 16) * ((C1 + 16) / 16) * 256;
-  return std::max((size_t)(256 * (P + 1) + 256 * (C1 + 1) + P * C1 + C1), red) * 4;
+  return std::max((size_t)(256 * (P + 1) + 256 * (C1 + 1)), red) * 4;
 }
 
 hipError_t launch_head_fwd(const HeadArgs& a, hipStream_t s) {
   const long long npix = (long long)a.B * a.H * a.W;
   const dim3 grid((unsigned)((npix + 255) / 256));
-  const size_t lds = head_fwd_lds(a.P, a.C1);
-  if (a.C1 == 8) hipLaunchKernelGGL(k_head_fwd<8>, grid, dim3(256), lds, s, a);
-  else if (a.C1 == 16) hipLaunchKernelGGL(k_head_fwd<16>, grid, dim3(256), lds, s, a);
-  else if (a.C1 == 32) hipLaunchKernelGGL(k_head_fwd<32>, grid, dim3(256), lds, s, a);
+  if (a.C1 == 8) hipLaunchKernelGGL(k_head_fwd<8>, grid, dim3(256), 0, s, a);
+  else if (a.C1 == 16) hipLaunchKernelGGL(k_head_fwd<16>, grid, dim3(256), 0, s, a);
+  else if (a.C1 == 32) hipLaunchKernelGGL(k_head_fwd<32>, grid, dim3(256), 0, s, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
