@@ -1263,7 +1263,6 @@ struct Solver {
     a.nitems = model ? P.n_vm : P.n_vd;
     a.op = op;
     a.sc = sc;
-    a.sign = 1.f;
     return a;
   }
   hipError_t reduce(int op, bool model, const float* x, const uint8_t* tmask, int dst0, int dst1, bool is_max,
@@ -1307,21 +1306,19 @@ struct Solver {
     a.freeze = prm.freeze_eps;
     return launch_scalar(a, c.s);
   }
-  hipError_t cg(int init, int par) const {
+  hipError_t cg(int init) const {
     CgArgs a{};
     a.gd = P.d_gd;
     a.items = P.d_vm;
     a.nitems = P.n_vm;
     a.init = init;
-    a.par = par;
     a.u = u;
     a.pdir = pdir;
-    a.g = g;
     a.part_gamma = P.sum_model_in_kernel ? pgam : nullptr;
     a.sc = sc;
     return timed(ASHRT_K_VECTOR, c.s, [&] { return launch_cg(a, c.s); });
   }
-  hipError_t median(const float* x, const uint8_t* tmask, int stage, int dst) const {
+  hipError_t median_mad(const float* x, const uint8_t* tmask) const {
     SelArgs a{};
     a.gd = P.d_gd;
     a.items = P.d_vd;
@@ -1332,8 +1329,10 @@ struct Solver {
     a.sc = sc;
     a.st = sel;
     a.hist = hist;
-    a.stage = stage;
-    return timed(ASHRT_K_SELECT, c.s, [&] { return launch_select_median(a, sc, dst, c.s); });
+    bool small = true;
+    for (const auto& gh : P.g) small = small && gh.nd() <= kSelSmall;
+    return timed(ASHRT_K_SELECT, c.s,
+                 [&] { return launch_select_median_mad(a, small, sc, SC_MED, SC_MAD, c.s); });
   }
 };
 
@@ -1479,18 +1478,15 @@ int invert_impl(const PlanImpl& P, const irls_params* prm, const float* d, const
       if (q1) {
         E_TRY(S.reduce(RED_ABSMAX, true, m, nullptr, SC_MMAX, -1, true, nullptr, 0));
         E_TRY(S.scalar(ST_EPS_M, k));
-        // W_m^-1 from m (its z_out = W_m m is not needed: pdir, overwritten
-        // by the CG initialisation below, takes it)
         EwArgs w = S.ew(EW_WM_UPDATE, true);
         w.y = S.Wminv;
         w.x = m;
-        w.z_out = S.pdir;
         w.coef = SC_EPS_M;
         E_TRY(timed(ASHRT_K_VECTOR, s, [&] { return launch_elementwise(w, s); }));
       }
     }
     // CGLS on A = W_r S L W_m^-1 from u = W_m m (in model space, see
-    // cg_iteration):  s = W_r r ; g = W_m^-2 L' S s ; pdir = g
+    // cg_iteration):  s = W_r r ; pdir = g = W_m^-2 L' S s
     {
       EwArgs a = S.ew(EW_MUL, false);
       a.y = S.s;
@@ -1498,8 +1494,8 @@ int invert_impl(const PlanImpl& P, const irls_params* prm, const float* d, const
       a.z = S.r;
       E_TRY(timed(ASHRT_K_VECTOR, s, [&] { return launch_elementwise(a, s); }));
     }
-    E_TRY(run_adjoint(c, S.s, S.Wr, mask, S.g, S.Wminv, S.pgam, nullptr, S.sc, q1));
-    E_TRY(S.cg(1, 0));
+    E_TRY(run_adjoint(c, S.s, S.Wr, mask, S.pdir, S.Wminv, S.pgam, nullptr, S.sc, q1));
+    E_TRY(S.cg(1));
     if (prm->n_inner > 0) {
       // iteration 0 starts from pdir = g; iterations 1.. apply their
       // predecessor's update in their model transform; k_cg applies the last
@@ -1508,14 +1504,13 @@ int invert_impl(const PlanImpl& P, const irls_params* prm, const float* d, const
       if (cg_exec)
         for (; i + 1 < prm->n_inner; i += 2) E_TRY(hipGraphLaunch(cg_exec, s));
       for (; i < prm->n_inner; ++i) E_TRY(cg_iteration(S, mask, i & 1, true));
-      E_TRY(S.cg(0, (prm->n_inner - 1) & 1));
+      E_TRY(S.cg(0));
     }
     E_TRY(S.scalar(ST_REPORT_INNER, k));
     // residual, separated gather, clip and misfit
     E_TRY(run_forward(c, m, nullptr, S.r, d, nullptr, d_rec, mask));
     if (p1) {
-      E_TRY(S.median(S.r, mask, 0, SC_MED));
-      E_TRY(S.median(S.r, mask, 1, SC_MAD));
+      E_TRY(S.median_mad(S.r, mask));
       E_TRY(S.scalar(ST_EPS_R, k));
     }
     E_TRY(S.reduce(RED_MISFIT, false, S.r, mask, SC_MISFIT, SC_HUBER, false, S.rep, k));

@@ -100,18 +100,16 @@ struct FinArgs {
 };
 
 enum EwOp {
-  EW_AXPY = 0,        // y += sign * sc[g][coef] * x
-  EW_XPBY = 1,        // y = x + sc[g][coef] * y
-  EW_MUL = 2,         // y = x * z
-  EW_COPY = 3,        // y = x
-  EW_FILL = 4,        // y = value
-  EW_WR_INIT = 5,     // y = live ? (x ? x : 1) : 0           (x = w0 or null)
-  EW_WR_UPDATE = 6,   // y = live ? (eps > 0 ? max(|x|, eps)^-1/2 : 1) : 0   (p = 1)
-  EW_WM_UPDATE = 7,   // y = max(|x|, eps_m)^1/2 (or 1), z_out = x / y        (q = 1)
-  EW_WR_MASK = 8,     // y = live ? 1 : 0                     (p = 2)
-  EW_SCALE_RSQRT = 9, // y = x / sqrt(sc[g][coef])            (power-method normalisation)
-  EW_FISTA = 10       // v = y + sc[coef] x; m' = soft(v, sc[coef + 1]); y = m' + value (m' - m); m = m'
-                      //   (m is z_out, in and out)
+  EW_MUL,         // y = x * z
+  EW_COPY,        // y = x
+  EW_FILL,        // y = value
+  EW_WR_INIT,     // y = live ? (x ? x : 1) : 0           (x = w0 or null)
+  EW_WR_UPDATE,   // y = live ? (eps > 0 ? max(|x|, eps)^-1/2 : 1) : 0   (p = 1)
+  EW_WM_UPDATE,   // y = max(|x|, eps_m)^1/2 (or 1)       (q = 1)
+  EW_WR_MASK,     // y = live ? 1 : 0                     (p = 2)
+  EW_SCALE_RSQRT, // y = x / sqrt(sc[g][coef])            (power-method normalisation)
+  EW_FISTA        // v = y + sc[coef] x; m' = soft(v, sc[coef + 1]); y = m' + value (m' - m); m = m'
+                  //   (m is z_out, in and out)
 };
 
 struct EwArgs {
@@ -125,7 +123,6 @@ struct EwArgs {
   float* z_out;
   const double* sc;
   int coef;
-  float sign;
   float value;
   const uint8_t* tmask;
 };
@@ -148,6 +145,7 @@ struct ScalArgs {
   double safety, mu_abs, mu_rel;  // ST_FISTA
 };
 
+constexpr int kSelSmall = 32768;  // samples of a gather that one workgroup selects from
 struct SelArgs {
   const GatherDev* gd;
   const VecItem* items;
@@ -162,21 +160,18 @@ struct SelArgs {
   int shift, width;        // digit = (key >> shift) & ((1 << width) - 1)
 };
 
-// CG initialisation and update over model-vector items; gamma_new = |g|^2 of
-// the latest adjoint is reduced from its per-tile partials part_gamma when
-// set (every workgroup in the same order), else read from sc[SC_GNEW].
-//   init:   pdir = g ; gamma[0] = gamma_new, done = 0, ninner = 0
-//   update: beta = gamma_new / gamma[par] ; u += alpha pdir ; pdir = g + beta pdir ;
-//           gamma[par ^ 1] = gamma_new
+// What the CG iterations leave to do around them (their model transforms apply
+// the update of the iteration before):
+//   init:   gamma[0] = |g|^2 of the first adjoint, from its per-tile partials
+//           part_gamma when set, else from sc[SC_GNEW]; done = 0, ninner = 0
+//   update: u += alpha pdir of the last iteration
 struct CgArgs {
   const GatherDev* gd;
   const VecItem* items;
   int nitems;
   int init;
-  int par;
   float* u;
-  float* pdir;
-  const float* g;
+  const float* pdir;
   const double* part_gamma;
   double* sc;
 };
@@ -223,7 +218,8 @@ hipError_t launch_scalar(const ScalArgs& a, hipStream_t s);
 hipError_t launch_zero_words(void* p, long long n, hipStream_t s);
 hipError_t launch_count_live(const GatherDev* gd, int ngather, const uint8_t* tmask, double* sc,
                              hipStream_t s);
-hipError_t launch_select_median(SelArgs a, double* sc, int dst, hipStream_t s);
+// small: every gather has at most kSelSmall samples
+hipError_t launch_select_median_mad(SelArgs a, bool small, double* sc, int dst_med, int dst_mad, hipStream_t s);
 hipError_t launch_cg(const CgArgs& a, hipStream_t s);
 // sc[g][dst] = sum of the per-tile partials of gather g's model (xm) or data
 // (xd) x-transform items, in a fixed order (one workgroup per gather).

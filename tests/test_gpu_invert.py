@@ -284,3 +284,28 @@ def test_irregular_traces_solve_matches_oracle(A, pq_missing):
     print(f"  d_rec rel-L2 {e:.2e}", flush=True)
     assert e <= 1e-4
     np.testing.assert_allclose(rep["misfit"], rep_r["misfit"], rtol=1e-4)
+
+
+# Residual clips of one-workgroup selections (at most 32768 samples) and of the
+# histogram passes above: both sides of the limit, sample counts that are no
+# multiple of the 1024 threads, odd and even live counts, dead traces.
+# eps_r after the first outer iteration is b_r MAD / 0.6745 of
+# the residual, which the returned model gives: r = d - d_rec in FP32, the
+# residual of the same forward pass, so the medians agree to FP32 rounding of r
+# (2^-23 of its largest value, times b_r / 0.6745).
+@pytest.mark.parametrize("nt,nx,dead", [(128, 256, 0), (129, 255, 0), (256, 129, 3), (201, 33, 2), (64, 16, 15)])
+def test_residual_clip_is_the_median_of_either_path(A, nt, nx, dead):
+    import torch
+    print(f"[gpu] clip nt={nt} nx={nx} dead={dead}", flush=True)
+    rng = np.random.default_rng(nt + nx)
+    d = (rng.standard_normal((nx, nt)) * rng.choice([0.0, 1.0, 50.0], (nx, nt))).astype(np.float32)
+    mask = np.ones(nx, np.uint8)
+    mask[rng.choice(nx, dead, replace=False)] = 0
+    plan = A.Plan(nt, nx, 0.004, 12.5, [1500.0, 2200.0], fmax=60.0)
+    P = A.Params(p=1, q=2, n_outer=1, n_inner=1, b_r=1.0)
+    dt = torch.tensor(d, device="cuda")
+    m, drec, rep = plan.robust_invert(dt, P, mask=torch.tensor(mask, device="cuda"))
+    r = (d - drec.cpu().numpy())[mask > 0].astype(np.float64)
+    mad = np.median(np.abs(r - np.median(r)))
+    eps = rep["eps_r"][0]
+    assert abs(eps - max(mad / 0.6745, P.eps_floor_rel * np.abs(d[mask > 0]).max())) <= 2.0**-21 * np.abs(d).max()
