@@ -346,7 +346,8 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, bool big_mo
 }
 
 // Panel chunks per wavenumber row: the row passes' workgroups should fill a
-// whole number k of rounds of the resident ones (4 per CU, 2 of the long rows).
+// whole number k of rounds of 4 per CU (2 of the long rows); a fifth fits at
+// 2048 points, but 256 rows x 32 panels take 156 us in 5 chunks and 152 in 4.
 // A chunk costs about 0.7 panels by itself (its partial sums, the adjoint's
 // data transform); more rounds balance better (a tenth of the time in one).
 // Measured per operator pair: 192 rows x 24 panels, 5 chunks (0.94 rounds) 149

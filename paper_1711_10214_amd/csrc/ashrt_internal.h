@@ -13,9 +13,9 @@ namespace ashrt {
 
 constexpr int kThreads = 256;          // threads per workgroup (all kernels but the row passes)
 constexpr int kRowThreads = 256;       // threads per workgroup of the forward/adjoint row passes
-// Compile-time row lengths of 3072 and 4096 need 60-75 KB of LDS per
-// workgroup (two per CU): they run 512 threads (8 waves) so that each SIMD
-// still holds four waves; shorter lengths run kRowThreads.
+// Compile-time row lengths of 3072 and 4096 need 46-62 KB of LDS per
+// workgroup: they run 512 threads (8 waves), two to a CU, so that each SIMD
+// holds four waves; shorter lengths run kRowThreads.
 constexpr int row_threads(int n) { return n >= 3072 ? 512 : kRowThreads; }
 // Compile-time row kernels of 256 threads are held to the 96 VGPRs that let
 // five waves per SIMD run (their LDS, up to 31 KB at 2048 points and a 100 Hz
