@@ -326,7 +326,25 @@ __device__ __forceinline__ const V& at_byte(const T* base, unsigned off) {
   return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
 }
 
-// Input of a full model tile (nt even, t0 + T <= nt): the element pairs
+// Pairs of neighbouring samples, and of x-spectrum values, of a row: rows of
+// odd length start on 4-byte (8-byte) boundaries, which the 8-byte (16-byte)
+// global accesses take on this hardware.  (One sample at a time there, the x
+// kernels of 24 panels x 187 x 1001 took 23 + 23 us; now 19 + 19.)
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(8)));
+__device__ __forceinline__ float2 ld2(const float* base, unsigned off) {
+  const f32x2u v = at_byte<f32x2u>(base, off);
+  return make_float2(v.x, v.y);
+}
+__device__ __forceinline__ void st2(float* base, unsigned off, float2 v) {
+  at_byte<f32x2u>(base, off) = f32x2u{v.x, v.y};
+}
+__device__ __forceinline__ float4 ld4(const float2* base, unsigned off) {
+  const f32x4u v = at_byte<f32x4u>(base, off);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Input of a full model tile (t0 + T <= nt): the element pairs
 // (t, t+1) of the nx columns go to the LDS column pairs.  CG: the previous
 // CG iteration's update of the pair (u += ca p, p = g + cb p) comes first
 // and the new p is the input; MUL: the input is scaled by mul.  The loads
@@ -348,13 +366,13 @@ __device__ __forceinline__ void xfwd_model_full_tile(float2* buf, int bs, const 
       const int x = dh.div(idx);
       off[u] = 4u * (unsigned)(x * nt + t0 + 2 * (idx - x * half));
       if constexpr (CG) {
-        va[u] = at_byte<float2>(pp, off[u]);
-        vg[u] = at_byte<float2>(gg, off[u]);
-        vu[u] = at_byte<float2>(uu, off[u]);
+        va[u] = ld2(pp, off[u]);
+        vg[u] = ld2(gg, off[u]);
+        vu[u] = ld2(uu, off[u]);
       } else {
-        va[u] = at_byte<float2>(src, off[u]);
+        va[u] = ld2(src, off[u]);
       }
-      if constexpr (MUL) vm[u] = at_byte<float2>(mul, off[u]);
+      if constexpr (MUL) vm[u] = ld2(mul, off[u]);
     }
 #pragma unroll
     for (int u = 0; u < kXLoadBatch; ++u) {
@@ -364,9 +382,9 @@ __device__ __forceinline__ void xfwd_model_full_tile(float2* buf, int bs, const 
         const int i = idx - x * half;
         float2 v = va[u];
         if constexpr (CG) {
-          at_byte<float2>(uu, off[u]) = make_float2(fmaf(ca, v.x, vu[u].x), fmaf(ca, v.y, vu[u].y));
+          st2(uu, off[u], make_float2(fmaf(ca, v.x, vu[u].x), fmaf(ca, v.y, vu[u].y)));
           v = make_float2(fmaf(cb, v.x, vg[u].x), fmaf(cb, v.y, vg[u].y));
-          at_byte<float2>(pp, off[u]) = v;
+          st2(pp, off[u], v);
         }
         if constexpr (MUL) v = make_float2(v.x * vm[u].x, v.y * vm[u].y);
         buf[i * bs + px<NX>(x)] = v;
@@ -375,7 +393,7 @@ __device__ __forceinline__ void xfwd_model_full_tile(float2* buf, int bs, const 
   }
 }
 
-// Input of a full data tile (nt even, t0 + T <= nt), loads batched as in
+// Input of a full data tile (t0 + T <= nt), loads batched as in
 // xfwd_model_full_tile.  SCG: the CG step s -= alpha q first (s is written
 // back) and the new s is the input; MUL: times mul; traces with tm[x] == 0
 // (tm non-null) give zero.
@@ -396,12 +414,12 @@ __device__ __forceinline__ void xfwd_data_full_tile(float2* buf, int bs, const U
       const int x = dh.div(idx);
       off[u] = 4u * (unsigned)(x * nt + t0 + 2 * (idx - x * half));
       if constexpr (SCG) {
-        va[u] = at_byte<float2>(sv, off[u]);
-        vq[u] = at_byte<float2>(qv, off[u]);
+        va[u] = ld2(sv, off[u]);
+        vq[u] = ld2(qv, off[u]);
       } else {
-        va[u] = at_byte<float2>(src, off[u]);
+        va[u] = ld2(src, off[u]);
       }
-      if constexpr (MUL) vm[u] = at_byte<float2>(mul, off[u]);
+      if constexpr (MUL) vm[u] = ld2(mul, off[u]);
       live[u] = x;
     }
     // mask bytes after every other load of the batch is issued
@@ -421,7 +439,7 @@ __device__ __forceinline__ void xfwd_data_full_tile(float2* buf, int bs, const U
         float2 v = va[u];
         if constexpr (SCG) {
           v = make_float2(fmaf(-alpha, vq[u].x, v.x), fmaf(-alpha, vq[u].y, v.y));
-          at_byte<float2>(sv, off[u]) = v;
+          st2(sv, off[u], v);
         }
         if constexpr (MUL) v = make_float2(v.x * vm[u].x, v.y * vm[u].y);
         if (live[u] == 0) v = make_float2(0.f, 0.f);
@@ -431,7 +449,7 @@ __device__ __forceinline__ void xfwd_data_full_tile(float2* buf, int bs, const U
   }
 }
 
-// Input of a full tile of the x-spectrum rows (nt even, t0 + T <= nt) into
+// Input of a full tile of the x-spectrum rows (t0 + T <= nt) into
 // the LDS column pairs, Hermitian-completed: rows l >= 1 fill slots l and
 // nxp - l, row 0 packs (DC, Nyquist).  Rows nrw .. nrows-1 are zero and not
 // read.  Loads batched as in xfwd_model_full_tile.
@@ -447,7 +465,7 @@ __device__ __forceinline__ void xinv_rows_full_tile(float2* buf, int bs, const U
       const int idx = min(base + u * kThreads, nin - 1);
       const int l = dh.div(idx);
       // byte offset in the panel's rows (8 nrows nt < 2^32)
-      hv[u] = at_byte<float4>(src, 8u * (unsigned)(l * nt + t0 + 2 * (idx - l * half)));
+      hv[u] = ld4(src, 8u * (unsigned)(l * nt + t0 + 2 * (idx - l * half)));
     }
 #pragma unroll
     for (int u = 0; u < kXLoadBatch; ++u) {
@@ -567,10 +585,9 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
     const float* __restrict__ src = A.src + fbase;
     const float* __restrict__ mul = A.mul ? A.mul + fbase : nullptr;
     const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-    const bool even = (nt & 1) == 0;
 
     const UDiv dh(half);
-    if (!A.is_model && even && t0 + T <= nt) {
+    if (!A.is_model && t0 + T <= nt) {
       // a full data tile (all but a ragged last one)
       float* sv = A.s_inout ? A.s_inout + fbase : nullptr;
       const float* qv = A.s_inout ? A.qv + fbase : nullptr;
@@ -581,7 +598,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
         if (mul) xfwd_data_full_tile<NX, false, true>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
         else xfwd_data_full_tile<NX, false, false>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
       }
-    } else if (A.is_model && even && t0 + T <= nt) {
+    } else if (A.is_model && t0 + T <= nt) {
       // a full model tile (all but a ragged last one)
       float* pp = A.cg_upd ? A.cg_p + fbase : nullptr;
       float* uu = A.cg_upd ? A.cg_u + fbase : nullptr;
@@ -606,27 +623,17 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
         float* pp = A.cg_p + fbase;
         float* uu = A.cg_u + fbase;
         const float* gg = A.cg_g + fbase;
-        if (even && t < nt) {
-          const float2 pv = *reinterpret_cast<const float2*>(pp + o);
-          const float2 gv = *reinterpret_cast<const float2*>(gg + o);
-          const float2 uv = *reinterpret_cast<const float2*>(uu + o);
-          *reinterpret_cast<float2*>(uu + o) = make_float2(fmaf(cg_a, pv.x, uv.x), fmaf(cg_a, pv.y, uv.y));
+        if (t + 1 < nt) {
+          const float2 pv = ld2(pp + o, 0), gv = ld2(gg + o, 0), uv = ld2(uu + o, 0);
+          st2(uu + o, 0, make_float2(fmaf(cg_a, pv.x, uv.x), fmaf(cg_a, pv.y, uv.y)));
           a = fmaf(cg_b, pv.x, gv.x);
           b = fmaf(cg_b, pv.y, gv.y);
-          *reinterpret_cast<float2*>(pp + o) = make_float2(a, b);
-        } else {
-          if (t < nt) {
-            const float pv = pp[o];
-            uu[o] = fmaf(cg_a, pv, uu[o]);
-            a = fmaf(cg_b, pv, gg[o]);
-            pp[o] = a;
-          }
-          if (t + 1 < nt) {
-            const float pv = pp[o + 1];
-            uu[o + 1] = fmaf(cg_a, pv, uu[o + 1]);
-            b = fmaf(cg_b, pv, gg[o + 1]);
-            pp[o + 1] = b;
-          }
+          st2(pp + o, 0, make_float2(a, b));
+        } else if (t < nt) {
+          const float pv = pp[o];
+          uu[o] = fmaf(cg_a, pv, uu[o]);
+          a = fmaf(cg_b, pv, gg[o]);
+          pp[o] = a;
         }
         if (mul) {
           a *= (t < nt) ? mul[o] : 0.f;
@@ -647,25 +654,18 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
           a *= (t < nt) ? mul[o] : 0.f;
           b *= (t + 1 < nt) ? mul[o + 1] : 0.f;
         }
-      } else if (even && t < nt) {
-        // nt even: (t, t+1) is an aligned pair inside the trace
-        const float2 v = *reinterpret_cast<const float2*>(src + o);
+      } else if (t + 1 < nt) {
+        const float2 v = ld2(src + o, 0);
         a = v.x;
         b = v.y;
         if (mul) {
-          const float2 wv = *reinterpret_cast<const float2*>(mul + o);
+          const float2 wv = ld2(mul + o, 0);
           a *= wv.x;
           b *= wv.y;
         }
-      } else {
-        if (t < nt) {
-          a = src[o];
-          if (mul) a *= mul[o];
-        }
-        if (t + 1 < nt) {
-          b = src[o + 1];
-          if (mul) b *= mul[o + 1];
-        }
+      } else if (t < nt) {
+        a = src[o];
+        if (mul) a *= mul[o];
       }
       if (tm && tm[x] == 0) {
         a = 0.f;
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
 
     // column pair i holds the packed spectra of columns t0 + 2i (real part)
     // and t0 + 2i + 1 (imaginary part); both outputs of a row are written
-    // together (one 16-byte store when nt is even)
+    // together (one 16-byte store)
     float2* __restrict__ dst = A.dst + (A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
     // model panels: rows at or above the panel's live-row count are never read
     const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
@@ -708,12 +708,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
         o1 = make_float2(0.5f * (a.y - b.y), -0.5f * (a.x - b.x));
       }
       float2* d = dst + (long long)r * nt + t;
-      if (even) {
-        *reinterpret_cast<float4*>(d) = make_float4(o0.x, o0.y, o1.x, o1.y);
-      } else {
-        d[0] = o0;
-        if (t + 1 < nt) d[1] = o1;
-      }
+      if (t + 1 < nt) *reinterpret_cast<f32x4u*>(d) = f32x4u{o0.x, o0.y, o1.x, o1.y};
+      else d[0] = o0;
     }
     __syncthreads();
   }
@@ -742,10 +738,9 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
     lw.load(A.tw + G.twp_x_off);
 
     const UDiv dh(half);
-    const bool even = (nt & 1) == 0;
     // model panels: rows at or above the panel's live-row count are zero (not stored)
     const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
-    if (even && t0 + T <= nt) {
+    if (t0 + T <= nt) {
       // a full tile (all but a ragged last one)
       xinv_rows_full_tile<NX>(buf, bs, dh, half, nrows, nrw, nxp, nt, t0, src);
     } else
@@ -756,14 +751,12 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
       float2 h1 = make_float2(0.f, 0.f), h2 = make_float2(0.f, 0.f);
       if (l >= nrw) {
         // zero row
-      } else if (even && t < nt) {
-        // nt even: (t, t+1) is an aligned pair inside the row
-        const float4 h = *reinterpret_cast<const float4*>(src + (long long)l * nt + t);
+      } else if (t + 1 < nt) {
+        const float4 h = ld4(src + (long long)l * nt + t, 0);
         h1 = make_float2(h.x, h.y);
         h2 = make_float2(h.z, h.w);
-      } else {
-        if (t < nt) h1 = src[(long long)l * nt + t];
-        if (t + 1 < nt) h2 = src[(long long)l * nt + t + 1];
+      } else if (t < nt) {
+        h1 = src[(long long)l * nt + t];
       }
       float2* Z = buf + i * bs;
       if (l == 0) {
@@ -782,7 +775,7 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
     const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
     const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
     double ss = 0.0;
-    if (even && t0 + T <= nt && (A.wmul || A.sub)) {
+    if (t0 + T <= nt && (A.wmul || A.sub)) {
       // a full tile whose epilogue reads memory (wmul, sub): the loads of
       // kXLoadBatch loop iterations are issued together (indices past the
       // tile clamped)
@@ -801,8 +794,8 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
           const int idx = min(base + u * kThreads, nin - 1);
           const int x = dh.div(idx);
           off[u] = 4u * (unsigned)(x * nt + t0 + 2 * (idx - x * half));
-          if (wm) wv[u] = at_byte<float2>(wm, off[u]);
-          if (sb) sv[u] = at_byte<float2>(sb, off[u]);
+          if (wm) wv[u] = ld2(wm, off[u]);
+          if (sb) sv[u] = ld2(sb, off[u]);
           live[u] = x;
         }
         // mask bytes after every other load of the batch is issued
@@ -821,13 +814,13 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
             const int i = idx - x * half;
             const float2 z = buf[i * bs + px<NX>(x)];
             float2 v = make_float2(z.x * inv, z.y * inv);
-            if (raw) at_byte<float2>(raw, off[u]) = v;
+            if (raw) st2(raw, off[u], v);
             if (sb) v = make_float2(sv[u].x - v.x, sv[u].y - v.y);
             if (live[u] == 0) v = make_float2(0.f, 0.f);
             if (wm) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
             ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
             if (wsq) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
-            at_byte<float2>(out, off[u]) = v;
+            st2(out, off[u], v);
           }
         }
       }
@@ -840,35 +833,32 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
       const float2 z = buf[i * bs + px<NX>(x)];
       const bool live = !(tm && tm[x] == 0);
       const long long o = fbase + (long long)x * nt + t;
-      if (even) {
-        // nt even: columns t, t+1 form an aligned pair inside the trace
+      if (t + 1 < nt) {
         float2 v = make_float2(z.x * inv, z.y * inv);
-        if (A.raw_out) *reinterpret_cast<float2*>(A.raw_out + o) = v;
+        if (A.raw_out) st2(A.raw_out + o, 0, v);
         if (A.sub) {
-          const float2 sv = *reinterpret_cast<const float2*>(A.sub + o);
+          const float2 sv = ld2(A.sub + o, 0);
           v = make_float2(sv.x - v.x, sv.y - v.y);
         }
         if (!live) v = make_float2(0.f, 0.f);
         if (A.wmul) {
-          const float2 wv = *reinterpret_cast<const float2*>(A.wmul + o);
+          const float2 wv = ld2(A.wmul + o, 0);
           v = make_float2(v.x * wv.x, v.y * wv.y);
           ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
           if (A.wmul_sq) v = make_float2(v.x * wv.x, v.y * wv.y);
         } else {
           ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
         }
-        *reinterpret_cast<float2*>(A.out + o) = v;
+        st2(A.out + o, 0, v);
       } else {
-        for (int c = 0; c < 2 && t + c < nt; ++c) {
-          float v = (c ? z.y : z.x) * inv;
-          if (A.raw_out) A.raw_out[o + c] = v;
-          if (A.sub) v = A.sub[o + c] - v;
-          if (!live) v = 0.f;
-          if (A.wmul) v *= A.wmul[o + c];
-          ss += (double)v * (double)v;
-          if (A.wmul && A.wmul_sq) v *= A.wmul[o + c];
-          A.out[o + c] = v;
-        }
+        float v = z.x * inv;
+        if (A.raw_out) A.raw_out[o] = v;
+        if (A.sub) v = A.sub[o] - v;
+        if (!live) v = 0.f;
+        if (A.wmul) v *= A.wmul[o];
+        ss += (double)v * (double)v;
+        if (A.wmul && A.wmul_sq) v *= A.wmul[o];
+        A.out[o] = v;
       }
     }
     if (A.part) {

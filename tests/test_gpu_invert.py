@@ -309,3 +309,20 @@ def test_residual_clip_is_the_median_of_either_path(A, nt, nx, dead):
     mad = np.median(np.abs(r - np.median(r)))
     eps = rep["eps_r"][0]
     assert abs(eps - max(mad / 0.6745, P.eps_floor_rel * np.abs(d[mask > 0]).max())) <= 2.0**-21 * np.abs(d).max()
+
+
+# The x kernels' solver forms (CG update, weights, residual) on rows of odd
+# length with a last tile of one sample; the bar of this file.
+@pytest.mark.parametrize("pq", [(1, 2), (2, 1)])
+def test_odd_record_solve_matches_oracle(A, pq):
+    p, q = pq
+    w, gth, _ = _cfg1()
+    kw = geom_kwargs(129, gth.nx, w.dt, w.dx, list(w.vel)[:4], fmax=w.fmax)
+    print(f"[gpu] odd record solve p={p} q={q}", flush=True)
+    mask = np.ones(gth.nx, np.uint8)
+    mask[5::7] = 0
+    d = f32(np.ascontiguousarray(gth.d_blend[:, :129])) * mask[:, None]
+    prm = IrlsParams(p=p, q=q, n_outer=2, n_inner=5)
+    _, d_g, rep, _, d_r, rep_r = _solve_both(A, kw, d, prm, mask=mask)
+    assert rel_l2(d_g, d_r) <= 1e-4
+    np.testing.assert_allclose(rep["misfit"], rep_r["misfit"], rtol=1e-4)

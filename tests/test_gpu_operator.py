@@ -109,6 +109,17 @@ def test_irregular_tile_edges(A, nt, nx):
     assert rel_l2(d_gpu, d_ref) <= TOL and rel_l2(m_gpu, m_ref) <= TOL
 
 
+# Rows of odd length (pairs of samples on 4-byte boundaries), a last x tile of
+# one, two and three samples, and a record shorter than a tile.
+@pytest.mark.parametrize("nt,nx", [(257, 33), (201, 40), (90, 17), (91, 17), (7, 48)])
+def test_odd_records(A, nt, nx):
+    """Same bar as above, with dead traces."""
+    print(f"[gpu] odd records {nt} x {nx}", flush=True)
+    kw = geom_kwargs(nt, nx, 0.004, 12.5, [1500.0, 2700.0], fmax=110.0)
+    g, m, d, d_gpu, m_gpu, d_ref, m_ref = _run_pair(A, kw, seed=nt + nx, mask_frac=0.2)
+    assert rel_l2(d_gpu, d_ref) <= TOL and rel_l2(m_gpu, m_ref) <= TOL
+
+
 def test_wavelet_weight(A):
     kw = geom_kwargs(200, 40, 0.004, 12.5, [1500.0, 2500.0], fmax=100.0)
     H = oracle.fft_len(200) // 2 + 1
