@@ -1,7 +1,7 @@
 // Host side of the warm-start U-Net behind include/unet.h: parameter
 // storage, workspace layout and the forward / backward launch sequences.
 //
-// The network is a fixed graph of 14 3x3 convolutions and two 1x1 heads.
+// The network is a fixed graph of 18 3x3 convolutions and two 1x1 heads.
 // Each convolution reads its input through a loader that fuses the 2x2 mean
 // pool (encoder), the nearest 2x upsample and the skip concatenation
 // (decoder), so pooled, upsampled and concatenated tensors never exist in

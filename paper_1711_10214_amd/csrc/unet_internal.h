@@ -48,7 +48,7 @@ struct ConvPack {
 // pre-activations, each value zeroed where the activation (mA, mB) is not
 // positive, which is what every consumer of the gradient needs.
 struct ConvRoute {
-  float* gA;                // FP32 NHWC gradient of A, or null: plain output to ConvArgs::out
+  float* gA;                // FP32 NHWC gradient of A
   float* gB;                // FP32 NHWC gradient of the skip, or null
   const uint16_t* mA;       // BF16 activation A (ReLU mask), or null
   const uint16_t* mB;       // BF16 skip activation (ReLU mask), or null
@@ -60,9 +60,9 @@ struct ConvArgs {
   const uint16_t* Wp;       // BF16 [Coutp][ncc][KKp][CC]
   const float* bias;        // [Cout] or null
   int relu;
-  void* out;                // BF16 or FP32 NHWC [B][H][W][Cout]
+  void* out;                // BF16 NHWC [B][H][W][Cout] (no route)
   int B;
-  ConvRoute rt;             // FP32 outputs only
+  ConvRoute rt;             // input gradients only
   // split over the channel chunks: with ksplit > 1, grid.z = ksplit B and
   // split ks sums chunks [ks ncc / ksplit, (ks + 1) ncc / ksplit) into
   // kpart [ksplit][B][H][W][Coutp] (FP32); k_conv_finish adds the splits in
@@ -124,8 +124,6 @@ struct PackAll {
   int start[kPackMax + 1];
   PackArgs L[kPackMax];
 };
-
-
 
 struct HeadArgs {
   const uint16_t* h;        // BF16 NHWC [B][H][W][C1]

@@ -449,8 +449,8 @@ __global__ __launch_bounds__(256) void k_conv3(ConvArgs a) {
 
 // Finish a convolution split over its channel chunks: S(pixel, co) = the
 // ksplit partials added in split order, then the epilogue of k_conv3 for
-// that value: bias, ReLU and a BF16 (or FP32) store, or the route to A and
-// the skip (see ConvRoute).  Four channels a thread.  An upsampled A takes
+// that value: bias, ReLU and a BF16 store, or (OUTF32) the route to A and the
+// skip (see ConvRoute).  Four channels a thread.  An upsampled A takes
 // its 2 x 2 block sums as (S00 + S01) + (S10 + S11) in a second index range
 // over A's pixels.
 __device__ __forceinline__ float4 ksum4(const ConvArgs& a, long long pix, int co) {
@@ -471,8 +471,7 @@ __global__ __launch_bounds__(256) void k_conv_finish(ConvArgs a) {
   const int H = a.in.H, W = a.in.W;
   const long long npix = (long long)a.B * H * W;
   const ConvRoute& R = a.rt;
-  const bool routed = OUTF32 && R.gA;
-  const bool up = routed && R.modeA == 1;
+  const bool up = OUTF32 && R.modeA == 1;
   // range 1: every output pixel's channel groups (without the A channels of
   // an upsampled route); range 2: the A pixels of an upsampled route
   const int c_lo = up ? R.Ca : 0, ng1 = (a.pk.Cout - c_lo) >> 2;
@@ -483,20 +482,15 @@ __global__ __launch_bounds__(256) void k_conv_finish(ConvArgs a) {
       const long long pix = i / ng1;
       const int co = c_lo + 4 * (int)(i - pix * ng1);
       const float4 t = ksum4(a, pix, co);
-      if (!routed) {
+      if constexpr (!OUTF32) {
         float o[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           if (a.bias) o[k] += a.bias[co + k];
           if (a.relu) o[k] = fmaxf(o[k], 0.f);
         }
-        const long long off = pix * a.pk.Cout + co;
-        if constexpr (OUTF32) {
-          *reinterpret_cast<float4*>(static_cast<float*>(a.out) + off) = make_float4(o[0], o[1], o[2], o[3]);
-        } else {
-          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + off) =
-              make_uint2(f2bf2(o[0], o[1]), f2bf2(o[2], o[3]));
-        }
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + pix * a.pk.Cout + co) =
+            make_uint2(f2bf2(o[0], o[1]), f2bf2(o[2], o[3]));
       } else if (co >= R.Ca) {
         const long long ob = pix * R.Cb + (co - R.Ca);
         put4(R.gB + ob, R.mB ? R.mB + ob : nullptr, t.x, t.y, t.z, t.w, R.accB != 0);
