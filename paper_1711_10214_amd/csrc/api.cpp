@@ -533,7 +533,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       const double a = -2.0 * M_PI * (double)m / (double)N;
       tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
     }
-    // pass table of the compile-time FFT (layout in fft_tpl.h): (cos, tan) of
+    // pass table of the compile-time FFT (layout in fft_tpl.h): (cos, sin) of
     // the stage twiddles of every pass but the first
     if (tw.size() & 1) tw.push_back(make_float2(0.f, 0.f));  // 16-byte records
     twp_off[i] = (int)tw.size();
@@ -552,13 +552,9 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       if (L2 % 3 == 2) radices.push_back(4);
       int Ns = radices[0];
       const size_t start = tw.size();
-      // exp(-2 pi i turns) as (cos, tan), the cosine kept off zero
-      auto put = [&](double turns) {
+      auto put = [&](double turns) {  // exp(-2 pi i turns)
         const double a = -2.0 * M_PI * turns;
-        double c = std::cos(a);
-        const double sn = std::sin(a);
-        if (std::fabs(c) < kTwMinCos) c = c < 0.0 ? -kTwMinCos : kTwMinCos;
-        tw.push_back(make_float2((float)c, (float)(sn / c)));
+        tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
       };
       for (size_t k = 1; k < radices.size(); ++k) {
         const int R = radices[k];

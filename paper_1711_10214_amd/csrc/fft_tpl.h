@@ -13,17 +13,19 @@
 //
 // Twiddles.  A radix-8 butterfly of v_r w^r is three radix-2 stages whose
 // twiddles are w^4, then w^2, then w and w e^(-i pi/4), up to a factor -i
-// that only swaps components.  Each is stored as (c, t) = (cos, tan) of its
-// angle, so a + w b and a - w b take six FMAs: u = b.x - t b.y, v = b.y + t b.x,
-// then a +- c (u, v).  That is 72 instructions per twiddled radix-8 butterfly
+// that only swaps components.  Each is stored as (cos, sin), and a + w b and
+// a - w b take six FMAs: two a component for the first, and the second is
+// 2 a minus the first.  That is 72 instructions per twiddled radix-8 butterfly
 // where multiplying the inputs by w .. w^7 formed by recurrence took 112, with
 // fewer roundings on the way (no powers, one FMA where a multiply and an add
 // were).  On the 1024 x 256, 32-panel gather the forward row kernel went from
-// 21.8 to 18.2 M vector instructions and from 48.3 to 45.4 us, the model x
-// kernels from 28.3 to 27.1 and 31.2 to 30.1 us, and the operator's error
-// against FP64 from 3.7e-7 to 2.2e-7.  Only the quarter turn has cos = 0; its cosine is stored as 2^-28
-// (kTwMinCos), 4e-9 off.  A per-length "pass table" built in FP64 on the host
-// holds, for pass i and jm = 0..Ns-1,
+// 48.3 to 45.4 us, the model x kernels from 28.3 to 27.1 and 31.2 to 30.1 us,
+// and the operator's error against FP64 from 3.7e-7 to 2.5e-7.  No value passes
+// |a| + |b|, so the transforms take the whole FP32 range (the same six
+// instructions as c (b.x - tan b.y) with tabulated tangents are as fast and
+// reach 2.1e-7, but their quarter turns overflow from 2^100 on).
+// A per-length "pass table" built in FP64 on the host holds, for pass i and
+// jm = 0..Ns-1,
 //   radix 8: (w^4, w^2)[Ns], (w, w e^(-i pi/4))[Ns];  radix 4: (w^2, w)[Ns];
 //   radix 2: w[Ns]          (16-byte records, w = exp(-2 pi i jm / (Ns R))).
 #pragma once
@@ -106,8 +108,6 @@ struct FftPlan {
   static constexpr int twsize() { return twoff(npass); }
 };
 
-constexpr double kTwMinCos = 1.0 / 268435456.0;
-
 // LDS slots of the staged twiddles in front of an FFT buffer, an even count
 // (what follows stays 16-byte aligned): the pass table without the last pass
 // (the x transforms) or the last two (the row transforms), whose twiddles
@@ -146,7 +146,7 @@ inline __host__ __device__ int fft_row_tw_slots(int key, int n) {
   return n;
 }
 
-// One butterfly's twiddles as (cos, tan) pairs: radix 8 (w^4, w^2, w,
+// One butterfly's twiddles as (cos, sin) pairs: radix 8 (w^4, w^2, w,
 // w e^(-i pi/4)), radix 4 (w^2, w), radix 2 (w).
 template <int R>
 struct Tw {
@@ -169,13 +169,10 @@ struct Tw {
 // inverse transform takes the conjugate of z.
 template <bool INV, int ROT>
 __device__ __forceinline__ void bfly_tw(float2& a, float2& b, float2 w) {
-  const float c = w.x, t = INV ? -w.y : w.y;
-  const float u = fmaf(-t, b.y, b.x), v = fmaf(t, b.x, b.y);
-  float2 p;
-  if constexpr (ROT == 0) p = make_float2(u, v);
-  else p = INV ? make_float2(-v, u) : make_float2(v, -u);
-  b = make_float2(fmaf(-c, p.x, a.x), fmaf(-c, p.y, a.y));
-  a = make_float2(fmaf(c, p.x, a.x), fmaf(c, p.y, a.y));
+  const float zx = ROT == 0 ? w.x : w.y, zi = ROT == 0 ? w.y : -w.x, zy = INV ? -zi : zi;
+  const float2 p = make_float2(fmaf(-zy, b.y, fmaf(zx, b.x, a.x)), fmaf(zy, b.x, fmaf(zx, b.y, a.y)));
+  b = make_float2(fmaf(2.f, a.x, -p.x), fmaf(2.f, a.y, -p.y));
+  a = p;
 }
 // The same for z = 1, -i (conjugated when INV), without multiplications.
 template <bool INV, int ROT>
@@ -234,8 +231,8 @@ __device__ __forceinline__ void dft8(float2 (&v)[8]) {
   bfly_one<INV, 1>(v[5], v[7]);
   bfly_one<INV, 0>(v[0], v[1]);
   bfly_one<INV, 1>(v[2], v[3]);
-  bfly_tw<INV, 0>(v[4], v[5], make_float2(h, -1.f));
-  bfly_tw<INV, 1>(v[6], v[7], make_float2(h, -1.f));
+  bfly_tw<INV, 0>(v[4], v[5], make_float2(h, -h));
+  bfly_tw<INV, 1>(v[6], v[7], make_float2(h, -h));
   const float2 y4 = v[1], y1 = v[4], y6 = v[3], y3 = v[6];
   v[1] = y1;
   v[3] = y3;

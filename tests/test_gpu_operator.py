@@ -120,6 +120,28 @@ def test_odd_records(A, nt, nx):
     assert rel_l2(d_gpu, d_ref) <= TOL and rel_l2(m_gpu, m_ref) <= TOL
 
 
+# The compile-time transforms (time 512 .. 4096, x 128 .. 1024, lengths 3 2^a
+# among them) at amplitudes that leave headroom for their sums only.
+@pytest.mark.parametrize("nt,nx", [(256, 64), (300, 100), (450, 150), (700, 300), (1000, 48), (1500, 16), (1900, 10),
+                                   (200, 500)])
+def test_large_amplitudes(A, nt, nx):
+    """FP32 scales exactly by powers of two while nothing overflows: inputs 2^90
+    and 2^104 times larger give the same outputs as many times larger, bit for
+    bit, and those match the oracle."""
+    import torch
+    print(f"[gpu] large amplitudes {nt} x {nx}", flush=True)
+    kw = geom_kwargs(nt, nx, 0.004, 12.5, [1500.0, 2700.0], tau0=[0, 5], fmax=110.0)
+    g, m, d, d_gpu, m_gpu, d_ref, m_ref = _run_pair(A, kw, seed=nt + nx)
+    plan = A.Plan(**kw)
+    for k in (90, 104):
+        mt = torch.tensor(m * 2.0 ** k, dtype=torch.float32, device="cuda")
+        dt_ = torch.tensor(d * 2.0 ** k, dtype=torch.float32, device="cuda")
+        d_big = plan.forward(mt).cpu().numpy().astype(np.float64) * 2.0 ** -k
+        m_big = plan.adjoint(dt_).cpu().numpy().astype(np.float64) * 2.0 ** -k
+        assert rel_l2(d_big, d_ref) <= TOL and rel_l2(m_big, m_ref) <= TOL
+        assert np.array_equal(d_big, d_gpu) and np.array_equal(m_big, m_gpu)
+
+
 def test_wavelet_weight(A):
     kw = geom_kwargs(200, 40, 0.004, 12.5, [1500.0, 2500.0], fmax=100.0)
     H = oracle.fft_len(200) // 2 + 1
