@@ -40,24 +40,14 @@ constexpr int kTdFwdWaves = 16;  // waves that share a forward tile's panels and
 constexpr int kTdAdjWaves = 4;   // adjoint waves per workgroup
 constexpr int kTdAdjX = 4;       // neighbouring apexes per adjoint wave
 
-// sqrt(T2) as its integer part i and fraction f in [0, 1], from the FP32 root
-// and its exact residual: sqrt(T2) = s + (T2 - s^2) / (2 s) to 1e-8.  T2 is
-// below 2^26 (callers test it against the record first).
-struct TdTime {
-  float i, f;
-};
-__device__ __forceinline__ TdTime td_time(double T2) {
-  const float s = __builtin_amdgcn_sqrtf((float)T2);
-  const double sd = (double)s;
-  const float r = (float)fma(-sd, sd, T2);
-  const float dl = 0.5f * r * __builtin_amdgcn_rcpf(fmaxf(s, 1e-30f));
-  TdTime o;
-  o.i = floorf(s);
-  o.f = (s - o.i) + dl;
-  const float c = o.f < 0.f ? -1.f : (o.f >= 1.f ? 1.f : 0.f);
-  o.i += c;
-  o.f -= c;
-  return o;
+// sqrt(T2) to FP64 rounding: two Newton steps, their residuals in FP64, from an
+// FP32 root (good to 1e-15 for a root below that, and 0 for 0).  T2 is below
+// 2^26 (callers test it against the record first).
+__device__ __forceinline__ double td_root(double T2) {
+  const float t = (float)T2, i = __builtin_amdgcn_rsqf(fmaxf(t, 1e-30f));
+  const double s0 = (double)(t * i), h = (double)(0.5f * i);
+  const double s1 = fma(fma(-s0, s0, T2), h, s0);
+  return fma(fma(-s1, s1, T2), h, s1);
 }
 
 // The pairs of a distance: bit k is trace x0 + k + h, bit K + k is
@@ -107,9 +97,9 @@ __global__ __launch_bounds__(64 * kTdAdjWaves) void k_td_adjoint(TdArgs A) {
       if (!__any(on)) break;                 // T rises with h
       const unsigned ok = td_pairs<K>(x0, h, nx, A.tmask);
       if (!on) continue;
-      const TdTime T = td_time(T2);
-      const int i0 = P.n0 + (int)T.i;
-      const float f = T.f, e = 1.f - T.f;
+      const double T = td_root(T2), fl = floor(T);
+      const int i0 = P.n0 + (int)fl;
+      const float f = (float)(T - fl), e = 1.f - f;
       const float* up = A.d + (long long)(x0 + h) * nt;  // rows x0 + h + k and x0 - h + k
       const float* dn = A.d + (long long)(x0 - h) * nt;
       if (i0 + 1 < nt) {
@@ -176,8 +166,7 @@ __device__ __forceinline__ void td_forward_wave(const TdArgs& A, const GatherDev
     const float* __restrict__ mp = A.m + (long long)p * nx * nt;
     const int ts = t - P.n0;
     const double s0 = (double)ts, s1 = (double)(ts - 1), s2 = (double)(ts + 1);
-    const double s02 = s0 * s0, s12 = s1 * s1, s22 = s2 * s2;
-    const float tf = (float)ts;
+    const double s12 = s1 * s1, s22 = s2 * s2;
     int hh = wave - turn;
     if (hh < 0) hh += kTdFwdWaves;
     for (; 2 * hh <= hmax; hh += kTdFwdWaves) {
@@ -195,21 +184,16 @@ __device__ __forceinline__ void td_forward_wave(const TdArgs& A, const GatherDev
       // both halves' pairs all inside the gather
       const bool inside = hh > 0 && x0 - 2 * hh - 1 >= 0 && x0 + K - 1 + 2 * hh + 1 < nx && nt >= 4;
       const float* row = mp + (long long)x0 * nt;
-      const double base = h2 - s02;
       for (int c = lo; c <= hi; c += 4) {
         const int b = max(0, min(c, nt - 4));  // the load stays in the row (nt >= 4)
         float w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          // D = T - t = (T^2 - t^2) / (T + t), the numerator good to FP64
-          // rounding and the root only in the denominator: within 3e-7
+          // the weight 1 - |T - t| in FP64, rounded once
           const int tau = b + i;
           const double td = (double)tau;
-          const float num = (float)fma(td, td, base);
-          const float T = __builtin_amdgcn_sqrtf(fmaxf(fmaf(tf, tf, num), 0.f));
-          const float D = num * __builtin_amdgcn_rcpf(fmaxf(T + tf, 1e-30f));
-          const float ww = 1.f - fabsf(D);
-          w[i] = (tau >= c && tau <= hi && ww > 0.f) ? ww : 0.f;
+          const float ww = (float)(1.0 - fabs(td_root(fma(td, td, h2)) - s0));
+          w[i] = (tau >= c && tau <= hi) ? fmaxf(ww, 0.f) : 0.f;
         }
         auto add = [&](float& a, const float (&v)[4]) {
 #pragma unroll

@@ -114,3 +114,34 @@ def test_time_domain_tile_edges(A, nt, nx, vel, tau0):
     assert np.isfinite(fg).all() and np.isfinite(ag).all()
     assert np.linalg.norm(fg - fr) <= 1e-5 * max(np.linalg.norm(fr), 1e-3)
     assert np.linalg.norm(ag - ar) <= 1e-5 * max(np.linalg.norm(ar), 1e-3)
+
+
+# Impulses (apex trace, apex time) per velocity and shift: steep and flat parts
+# of the curves, the apex itself, weights near 0 and 1.
+@pytest.mark.parametrize("v,n0", [(1500.0, 0), (2345.0, 7), (700.0, 0), (6000.0, 31)])
+def test_time_domain_weights(A, v, n0):
+    """The interpolation weights themselves: a unit impulse gives each output
+    one weight.  The curve times are FP64 and the weights are rounded to FP32
+    once in the forward (2^-24 of the weight), and at f and again at 1 - f in
+    the adjoint (2^-25 each); 1e-11 for the FP64 roundings of T."""
+    import torch
+    print(f"[gpu] time-domain weights v {v} n0 {n0}", flush=True)
+    nt, nx, dt, dx = 300, 40, 0.004, 12.5
+    plan = A.Plan(nt, nx, dt, dx, [v], tau0=[n0])
+    x, tau = np.arange(nx), np.arange(nt)
+    q = (dx / (v * dt)) ** 2
+    for xa, ta in [(0, 0), (17, 1), (20, 40), (39, 97), (5, 203), (11, 255)]:
+        T = n0 + np.sqrt(ta * ta + (x - xa) ** 2 * q)
+        w = np.maximum(0.0, 1.0 - np.abs(T[:, None] - tau[None, :]))
+        m = torch.zeros((1, nx, nt), device="cuda")
+        m[0, xa, ta] = 1.0
+        e = np.abs(plan.td_forward(m).cpu().numpy() - w)
+        assert np.all(e <= 2.0 ** -24 * w + 1e-11), e.max()
+        i = n0 + ta  # data impulse on trace xa: the times of every apex's curve there
+        T = n0 + np.sqrt(tau[None, :] ** 2 + (x - xa)[:, None] ** 2 * q)
+        w = np.maximum(0.0, 1.0 - np.abs(T - i))
+        d = torch.zeros((nx, nt), device="cuda")
+        d[xa, i] = 1.0
+        e = np.abs(plan.td_adjoint(d).cpu().numpy()[0] - w)
+        assert np.all(e <= 2.0 ** -24 + 1e-11), e.max()
+        assert np.all(e[w == 0.0] == 0.0)
