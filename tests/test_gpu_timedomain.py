@@ -145,3 +145,58 @@ def test_time_domain_weights(A, v, n0):
         e = np.abs(plan.td_adjoint(d).cpu().numpy()[0] - w)
         assert np.all(e <= 2.0 ** -24 + 1e-11), e.max()
         assert np.all(e[w == 0.0] == 0.0)
+
+
+# The forward's wider tiles: 8 traces where 32-time by 8-trace tiles number at
+# least 512, 4 traces where those of 4 do; ragged times and traces.
+@pytest.mark.parametrize("nt,nx,vel,tau0", [(1021, 131, [1500.0], [0]), (509, 131, [1900.0, 0.0], [3, 0]),
+                                            (520, 126, [2500.0], [9])])
+def test_time_domain_wide_tiles(A, nt, nx, vel, tau0):
+    """Same bar as above, with dead traces."""
+    import torch
+    print(f"[gpu] time-domain wide tiles {nt} x {nx}", flush=True)
+    rng = np.random.default_rng(nt)
+    m = f32(rng.standard_normal((len(vel), nx, nt)))
+    mask = np.ones(nx, np.uint8)
+    mask[2::5] = 0
+    plan = A.Plan(nt, nx, 0.004, 12.5, vel, tau0=tau0)
+    fg = plan.td_forward(torch.tensor(m, dtype=torch.float32, device="cuda"),
+                         mask=torch.tensor(mask, device="cuda")).cpu().numpy()
+    fr = TD.forward(m[:1], 0.004, 12.5, vel[:1], tau0[:1])
+    for p in range(1, len(vel)):
+        fr[:, tau0[p]:] += m[p][:, :nt - tau0[p]]  # v = 0
+    fr *= mask[:, None]
+    assert rel_l2(fg, fr) <= 1e-5
+
+
+# One tile width each (2, 4 and 8 traces).
+@pytest.mark.parametrize("nt,nx", [(90, 21), (509, 131), (1021, 131)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_time_domain_non_finite_sample(A, nt, nx, bad):
+    """A model sample that is not finite reaches the outputs on its curve
+    (weight above 0) and no other; the adjoint likewise."""
+    import torch
+    print(f"[gpu] time-domain non-finite sample {nt} x {nx} {bad}", flush=True)
+    rng = np.random.default_rng(nx)
+    v, xa, ta = 1800.0, nx // 3, nt // 4
+    plan = A.Plan(nt, nx, 0.004, 12.5, [v])
+    m = torch.tensor(rng.standard_normal((1, nx, nt)), dtype=torch.float32, device="cuda")
+    m[0, xa, ta] = 0.0
+    f0 = plan.td_forward(m).cpu().numpy()
+    m[0, xa, ta] = float(bad)
+    f1 = plan.td_forward(m).cpu().numpy()
+    T = np.sqrt(ta * ta + (np.arange(nx) - xa) ** 2 * (12.5 / (v * 0.004)) ** 2)
+    hit = np.abs(T[:, None] - np.arange(nt)[None, :]) < 1.0
+    assert hit.any() and not np.isfinite(f1[hit]).any()
+    assert np.array_equal(f1[~hit], f0[~hit])
+    d = torch.tensor(rng.standard_normal((nx, nt)), dtype=torch.float32, device="cuda")
+    i = nt // 2
+    d[xa, i] = 0.0
+    a0 = plan.td_adjoint(d).cpu().numpy()[0]
+    d[xa, i] = float(bad)
+    a1 = plan.td_adjoint(d).cpu().numpy()[0]
+    T = np.sqrt(np.arange(nt)[None, :] ** 2 + (np.arange(nx)[:, None] - xa) ** 2 * (12.5 / (v * 0.004)) ** 2)
+    # (a curve time on a whole sample reads its later neighbour with weight 0)
+    hit = (T >= i - 1) & (T < i + 1)
+    assert not np.isfinite(a1[hit]).any()
+    assert np.array_equal(a1[~hit], a0[~hit])
