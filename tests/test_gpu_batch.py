@@ -57,6 +57,26 @@ def test_batched_operator_matches_oracle(A):
         assert e_f <= 1e-5 and e_a <= 1e-5
 
 
+def test_batch_with_one_record_past_half_its_transform(A):
+    """One launch takes all gathers of a transform length: a record of more than
+    half of it among shorter ones (either order) must keep all its samples."""
+    import torch
+    print("[gpu] batched forward/adjoint, records below and past half their transform", flush=True)
+    for nts in [(200, 400), (400, 256, 257)]:
+        rng = np.random.default_rng(len(nts))
+        geoms = [geom_kwargs(nt, 24, 0.004, 12.5, [1600.0, 2700.0], ntp=512, fmax=100.0) for nt in nts]
+        plan = A.BatchPlan(geoms)
+        gs = [oracle_geometry(kw) for kw in geoms]
+        ms = [f32(rng.standard_normal((g.npanel, g.nx, g.nt))) for g in gs]
+        ds = [f32(rng.standard_normal((g.nx, g.nt))) for g in gs]
+        d_out = plan.forward(plan.pack_model(ms))
+        m_out = plan.adjoint(plan.pack_data(ds))
+        torch.cuda.synchronize()
+        for i, g in enumerate(gs):
+            assert rel_l2(plan.unpack_data(d_out, i).cpu().numpy(), oracle.forward(g, ms[i], None)) <= 1e-5
+            assert rel_l2(plan.unpack_model(m_out, i).cpu().numpy(), oracle.adjoint(g, ds[i], None)) <= 1e-5
+
+
 def test_batched_operator_with_irregular_gather_matches_oracle(A):
     """A gather on jittered trace positions (non-uniform DFTs on the data
     side) packed between two regular ones, with a mask on the irregular one."""

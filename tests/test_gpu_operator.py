@@ -95,6 +95,18 @@ def test_forward_adjoint_match_oracle(A, name):
     assert ea <= TOL, ea
 
 
+# Records around half of their transform: up to it the forward's first pass
+# leaves out its upper inputs (power-of-two lengths), past it it takes them all.
+@pytest.mark.parametrize("nt,ntp", [(256, 512), (257, 512), (300, 512), (512, 512), (513, 1024), (1000, 1024),
+                                    (1024, 2048), (1025, 2048), (1500, 2048), (2049, 4096), (4000, 4096)])
+def test_records_past_half_their_transform(A, nt, ntp):
+    """Same bar as above, with dead traces."""
+    print(f"[gpu] records past half their transform {nt} of {ntp}", flush=True)
+    kw = geom_kwargs(nt, 20, 0.004, 12.5, [1500.0, 2700.0], tau0=[0, 4], ntp=ntp, fmax=110.0)
+    g, m, d, d_gpu, m_gpu, d_ref, m_ref = _run_pair(A, kw, seed=nt, mask_frac=0.2)
+    assert rel_l2(d_gpu, d_ref) <= TOL and rel_l2(m_gpu, m_ref) <= TOL
+
+
 # The non-uniform DFTs' tiles: 16 times, 16 rows or traces, 1024 staged traces.
 IRREGULAR_EDGES = [(15, 2), (16, 15), (17, 16), (33, 17), (5, 300), (20, 1024), (18, 1041)]
 
