@@ -345,25 +345,68 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, bool big_mo
   return ASHRT_OK;
 }
 
-// Panel chunks per wavenumber row: the row passes' workgroups should fill a
-// whole number k of rounds of 4 per CU (2 of the long rows); a fifth fits at
-// 2048 points, but 256 rows x 32 panels take 156 us in 5 chunks and 152 in 4.
-// A chunk costs about 0.7 panels by itself (its partial sums, the adjoint's
-// data transform); more rounds balance better (a tenth of the time in one).
-// Measured per operator pair: 192 rows x 24 panels, 5 chunks (0.94 rounds) 149
-// us, 6 (1.1 rounds) 154; 384 long rows x 24, 4 chunks (3 rounds) 337 us, 3 (2.3
-// rounds) 348; 256 rows x 96, 8 chunks (2 rounds) 390 us, 4 (1 round) 405; x 32, 4
-// chunks 158 us, 8 chunks 168.
-static int row_chunks(long long rows, int panels, int resident) {
+// Row passes: kernel class of a gather (one launch per class) and LDS of its
+// forward and adjoint workgroups.
+static int row_key(const Resolved& z) { return rows_size_is_tpl(z.ntp, z.R) ? z.ntp : 0; }
+static size_t row_tw_slots(const Resolved& z) { return (size_t)fft_row_tw_slots(row_key(z), z.ntp); }
+static size_t row_band(const Resolved& z) { return (size_t)(z.jhi - z.jlo + 1); }
+static size_t row_fwd_lds(const Resolved& z) {
+  return (row_tw_slots(z) + kMapGuardSlots + fft_padlen(z.ntp)) * 8 + row_band(z) * 16;
+}
+static size_t row_adj_lds(const Resolved& z) {
+  return (row_tw_slots(z) + fft_padlen(z.ntp)) * 8 + (row_band(z) + kMapGuardPairs) * 16;
+}
+
+constexpr int kCus = 256;
+
+// A launch class of the row passes: its rows, largest panel count, and the
+// workgroups that are resident at once, by waves (3 per SIMD for the generic
+// lengths' registers) and by LDS (160 KB per CU).  At 2048 points a fifth
+// workgroup on a CU adds nothing: 256 rows x 32 panels take 152 us a pair in 4
+// chunks (1024 workgroups) and 156 in 5; at 1024 points 109 and 105.
+struct RowClass {
+  long long rows = 0;
+  int panels = 1;
+  size_t lds = 0;
+  int resident(int key) const {
+    const int waves = key == 0 ? 3 : (key == 2048 ? 4 : row_waves_per_eu(key));
+    return kCus * std::min(waves * 4 * 64 / row_threads(key), std::max(1, (int)(160000 / lds)));
+  }
+};
+static std::map<int, RowClass> row_classes(const std::vector<GatherHost>& g) {
+  std::map<int, RowClass> c;
+  for (const auto& gh : g) {
+    RowClass& k = c[row_key(gh.z)];
+    k.rows += gh.nrows;
+    k.panels = std::max(k.panels, gh.z.P);
+    k.lds = std::max({k.lds, row_fwd_lds(gh.z), row_adj_lds(gh.z)});
+  }
+  return c;
+}
+
+// Panel chunks per wavenumber row of a launch class (classes run one after the
+// other, so each counts its own workgroups).  In units of a panel's time, a full
+// round of resident workgroups takes a chunk's panels plus 1 (the chunk's own
+// partial sums and data transform); a part f of a round takes 0.2 + 0.8 f of
+// that, CUs with fewer workgroups running them faster; and the last workgroups,
+// rows differing in work, a quarter of a round (0.6 for the generic kernels, one
+// to three to a CU).  Fitted to operator pairs of 64 to 2560 rows x 8 to 32
+// panels, 256 to 2048 samples: within 0.5 % of the best count in the mean, 7 %
+// at most (11 % where the band is cut to 50 Hz), the generic kernels 1 % and
+// 6 %.  One count from the rows of all classes together took 4.86 ms for 7
+// gathers of 60 to 300 traces that take 3.64 in counts of their own.
+static int row_chunks(const RowClass& c, int key) {
+  const int resident = c.resident(key);
+  const double tail = key > 0 ? 0.25 : 0.6;
   int best = 1;
-  double best_score = 0.0;
-  for (int k = 1; k <= 3; ++k) {
-    const long long c = std::max(1LL, std::min<long long>((long long)k * resident / rows, panels));
-    const double rounds = (double)(c * rows) / resident;
-    const double score = rounds / std::ceil(rounds) / ((1.0 + 0.7 * c / panels) * (1.0 + 0.1 / std::ceil(rounds)));
-    if (score > best_score) {
-      best_score = score;
-      best = (int)c;
+  double best_time = 1e300;
+  for (int n = 1; n <= c.panels; ++n) {
+    const double w = (double)n * c.rows / resident, full = std::floor(w), f = w - full;
+    const double panels = 0.25 * ((c.panels + n - 1) / n) + 0.75 * c.panels / n;
+    const double time = (full + (f > 0.0 ? 0.2 + 0.8 * f : 0.0) + tail) * (panels + 1.0);
+    if (time < best_time) {
+      best_time = time;
+      best = n;
     }
   }
   return best;
@@ -392,19 +435,16 @@ static std::vector<float> row_costs(const GatherHost& gh) {
 // Launch order of the row passes' work items, heavy first: rows differ by
 // more than 3x in work, and a launch of many rounds ends with the light ones
 // (24 uneven gathers: 5 % of the solve).  A launch whose workgroups are all
-// resident at once (4 per CU, 2 of the long rows) is dealt instead so that
-// each CU gets the same sum: the hardware deals consecutive workgroups to the
+// resident at once is dealt instead so that each CU gets the same sum: the hardware deals consecutive workgroups to the
 // 8 XCDs and their 32 CUs in turn, so items kCus apart meet on one CU, and
 // every second run of kCus items is reversed.  On the 1024 x 256, 32-panel
 // gather the last CU then ends 43.2 instead of 45.4 us after the first
 // starts in the forward pass, 58.6 instead of 60.9 in the adjoint.
 static void order_row_items(std::vector<WorkItem>& items, const PlanImpl::Seg& sg,
-                            const std::vector<std::vector<float>>& cost) {
-  constexpr int kCus = 256;
+                            const std::vector<std::vector<float>>& cost, int resident) {
   const auto b = items.begin() + sg.first;
   std::stable_sort(b, b + sg.count,
                    [&](const WorkItem& x, const WorkItem& y) { return cost[x.g][x.a] > cost[y.g][y.a]; });
-  const int resident = kCus * (sg.key > 0 ? 4 * kRowThreads / row_threads(sg.key) : 2);
   if (sg.count > resident) return;
   for (int i = kCus; i < sg.count; i += 2 * kCus) std::reverse(b + i, b + std::min(i + kCus, sg.count));
 }
@@ -473,25 +513,29 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   for (auto& gh : P.g)
     if (gh.z.R != P.R) return fail(ASHRT_E_INVALID_ARG, "all gathers of a batch must share half_width");
 
-  // panel chunks so that the row passes have enough workgroups
-  long long total_rows = 0, dp1 = 0, x_h = 0;
-  bool all_long = true;
-  int max_panels = 1;
-  for (auto& gh : P.g) {
-    total_rows += gh.nrows;
-    all_long = all_long && rows_size_is_tpl(gh.z.ntp, gh.z.R) && row_threads(gh.z.ntp) > kRowThreads;
-    max_panels = std::max(max_panels, gh.z.P);
-    dp1 += (long long)gh.nrows * 2 * (gh.z.jhi - gh.z.jlo + 1) * 8;
-    x_h += ((long long)gh.z.P + 1) * gh.nrows * gh.z.nt * 8;
+  // panel chunks so that each row launch has enough workgroups
+  const auto classes = row_classes(P.g);
+  std::map<int, long long> chunks;
+  long long total_rows = 0;
+  for (const auto& kv : classes) {
+    chunks[kv.first] = tn && tn->nchunk > 0 ? tn->nchunk : row_chunks(kv.second, kv.first);
+    total_rows += kv.second.rows;
   }
-  long long want = row_chunks(total_rows, max_panels, all_long ? 512 : 1024);
+  auto set_chunks = [&](auto&& count) {  // returns the bytes of the forward's scratch
+    long long bytes = 0;
+    for (auto& gh : P.g) {
+      gh.nchunk = (int)std::min<long long>(count(gh), gh.z.P);
+      bytes += ((gh.z.P + 1LL) * gh.z.nt + gh.nchunk * 2LL * (gh.z.jhi - gh.z.jlo + 1)) * gh.nrows * 8;
+    }
+    return bytes;
+  };
+  // a forward that fits the static scratch with the count that gives 1024
+  // workgroups in all keeps fitting (1 KB for the layout's alignment)
   const long long least = (1024 + total_rows - 1) / total_rows;
-  // (a forward that fits the static scratch with the smaller count keeps fitting)
-  if (want > least && x_h + want * dp1 + 1024 > (long long)kStaticScratchBytes &&
-      x_h + least * dp1 <= (long long)kStaticScratchBytes)
-    want = least;
-  if (tn && tn->nchunk > 0) want = tn->nchunk;
-  for (auto& gh : P.g) gh.nchunk = (int)std::max(1LL, std::min<long long>(want, gh.z.P));
+  auto few = [&](const GatherHost&) { return least; };
+  auto own = [&](const GatherHost& gh) { return chunks.at(row_key(gh.z)); };
+  const bool fits = set_chunks(few) <= (long long)kStaticScratchBytes;
+  if (set_chunks(own) + 1024 > (long long)kStaticScratchBytes && fits && !(tn && tn->nchunk > 0)) set_chunks(few);
 
   // packed offsets
   long long od = 0, om = 0, omask = 0, oX = 0, oH = 0, oDp = 0;
@@ -594,7 +638,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     GatherHost& gh = P.g[gi];
     key_x[gi] = x_size_is_tpl(gh.z.nxp) ? gh.z.nxp : 0;
     key_xd[gi] = gh.xpos.empty() ? key_x[gi] : kNudftKey;
-    key_t[gi] = rows_size_is_tpl(gh.z.ntp, gh.z.R) ? gh.z.ntp : 0;
+    key_t[gi] = row_key(gh.z);
     GatherDev& G = gd[gi];
     std::memset(&G, 0, sizeof(G));
     G.nt = gh.z.nt;
@@ -663,9 +707,6 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   auto twx_of = [](const GatherHost& gh) {
     return (size_t)fft_tw_slots(x_size_is_tpl(gh.z.nxp) ? gh.z.nxp : 0, gh.z.nxp);
   };
-  auto twt_of = [](const GatherHost& gh) {
-    return (size_t)fft_row_tw_slots(rows_size_is_tpl(gh.z.ntp, gh.z.R) ? gh.z.ntp : 0, gh.z.ntp);
-  };
   auto lds_x_of = [&](const GatherHost& gh) {
     return twx_of(gh) * 8 + (size_t)(gh.tileT / 2) * xstride(gh) * 8;
   };
@@ -678,15 +719,8 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
     return std::max((size_t)std::min((gh.z.nx + 15) & ~15, kNudftRows) * kNudftStride * sizeof(float),
                     gh.nrows <= kNudftRows ? (size_t)gh.nrows * kNudftT * sizeof(float2) : 0);
   };
-  auto nband_of = [](const GatherHost& gh) { return (size_t)(gh.z.jhi - gh.z.jlo + 1); };
-  auto plen_of = [](const GatherHost& gh) { return (size_t)fft_padlen(gh.z.ntp); };
-  auto lds_rf_of = [&](const GatherHost& gh) {
-    return (twt_of(gh) + kMapGuardSlots + plen_of(gh)) * 8 + nband_of(gh) * 16;
-  };
-  auto lds_fin_of = [&](const GatherHost& gh) { return (twt_of(gh) + plen_of(gh)) * 8; };
-  auto lds_ra_of = [&](const GatherHost& gh) {
-    return (twt_of(gh) + plen_of(gh)) * 8 + (nband_of(gh) + kMapGuardPairs) * 16;
-  };
+  auto lds_rf_of = [](const GatherHost& gh) { return row_fwd_lds(gh.z); };
+  auto lds_fin_of = [](const GatherHost& gh) { return (row_tw_slots(gh.z) + fft_padlen(gh.z.ntp)) * 8; };
   // work lists grouped by kernel instantiation; a gather's items stay contiguous
   auto build_segments = [&](const std::vector<int>& keys, std::vector<PlanImpl::Seg>& segs,
                             std::vector<WorkItem>& items, auto&& add_items, auto&& lds_of) {
@@ -720,13 +754,13 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   }, lds_rf_of);
   std::vector<std::vector<float>> cost;
   for (const auto& gh : P.g) cost.push_back(row_costs(gh));
-  for (const auto& sg : P.s_rf) order_row_items(rf, sg, cost);
+  for (const auto& sg : P.s_rf) order_row_items(rf, sg, cost, classes.at(sg.key).resident(sg.key));
   // the adjoint runs the same list, with its own LDS size
   P.s_ra = P.s_rf;
   for (auto& sg : P.s_ra) {
     sg.lds = 0;
     for (int gi = 0; gi < ngather; ++gi)
-      if (key_t[gi] == sg.key) sg.lds = std::max(sg.lds, (size_t)lds_ra_of(P.g[gi]));
+      if (key_t[gi] == sg.key) sg.lds = std::max(sg.lds, row_adj_lds(P.g[gi].z));
   }
   build_segments(key_t, P.s_rfin, rfin, [&](int gi) {
     for (int r = 0; r < P.g[gi].nrows; ++r) rfin.push_back(WorkItem{gi, r, 0, 0});
