@@ -166,10 +166,10 @@ int ashrt_plan_create(const ashrt_desc *desc, int device, ashrt_plan **out);
 int ashrt_plan_create_tuned(const ashrt_desc *desc, const ashrt_tuning *tuning, int device, ashrt_plan **plan);
 
 /* Autotuner: times one forward + adjoint pair (median of `repeats`, >= 1)
- * for every candidate tiling -- model tiles {8, 16, 32}, data tiles
- * {2, 4, 8}, chunks {1, 2, 4, 8} within 1..npanel -- on zero-filled scratch
- * inputs of the descriptor's geometry, and returns the fastest in *best
- * (and its time in *best_ms, may be NULL).  Allocates and frees its own
+ * for every candidate tiling -- the built-in one, and model tiles {8, 16, 32},
+ * data tiles {2, 4, 8}, chunks {1, 2, 4, 8} within 1..npanel -- on zero-filled
+ * scratch inputs of the descriptor's geometry, and returns the fastest in
+ * *best (and its time in *best_ms, may be NULL).  Allocates and frees its own
  * scratch device memory and synchronises `device`; results are cached per
  * geometry for the life of the process.  The time includes the per-gather
  * sums of the CG partials that a tiling with many model tiles moves into

@@ -1901,73 +1901,85 @@ extern "C" int ashrt_autotune(const ashrt_desc* desc, int device, int32_t repeat
   }
   double best_t = 1e300;
   ashrt_tuning bt{0, 0, 0};
+  // the built-in tiling first, so that a tuned plan is not slower than an untuned
+  // one, then a grid around it
+  std::vector<ashrt_tuning> candidates;
+  {
+    PlanImpl P;
+    if (create_impl(desc, 1, device, P) == ASHRT_OK)
+      candidates.push_back({P.g[0].tileT, P.g[0].tileTd, P.g[0].nchunk});
+    destroy_impl(P);
+  }
   for (int tm : {8, 16, 32})
     for (int td : {2, 4, 8})
       for (int ch : {1, 2, 4, 8}) {
-        if (ch > z.P) continue;
-        const ashrt_tuning tn{tm, td, ch};
-        PlanImpl P;
-        if (create_impl(desc, 1, device, P, &tn) != ASHRT_OK) {  // e.g. the tile does not fit in LDS
-          destroy_impl(P);
-          continue;
-        }
-        const size_t need = std::max(P.layout(ASHRT_OP_FORWARD, 2).total, P.layout(ASHRT_OP_ADJOINT, 2).total);
-        if (need > ws_cap) {
-          if (ws) (void)hipFree(ws);
-          ws = nullptr;
-          ws_cap = 0;
-          if (hipMalloc(&ws, need) != hipSuccess) {
-            destroy_impl(P);
-            cleanup();
-            return fail(ASHRT_E_OOM, "autotune workspace allocation failed");
-          }
-          ws_cap = need;
-        }
-        // A CG iteration also sums the per-tile partials of |q|^2 and |g|^2:
-        // inside the consuming transform for small plans, else by one
-        // k_sum_items launch each (sum_*_in_kernel).  Those launches are
-        // timed with the pair, on zeroed partials, so that a tiling whose
-        // tile count moves the sums out of the transforms pays for them.
-        const size_t npart = (size_t)std::max(P.n_xm, P.n_xd);
-        if (npart > part_cap) {
-          if (part) (void)hipFree(part);
-          part = nullptr;
-          part_cap = 0;
-          if (hipMalloc(&part, npart * sizeof(double)) != hipSuccess ||
-              hipMemsetAsync(part, 0, npart * sizeof(double), s) != hipSuccess) {
-            destroy_impl(P);
-            cleanup();
-            return fail(ASHRT_E_OOM, "autotune partial-sum allocation failed");
-          }
-          part_cap = npart;
-        }
-        auto sums = [&]() {
-          hipError_t e = hipSuccess;
-          if (!P.sum_data_in_kernel) e = launch_sum_items(P.d_gd, 1, part, 0, scal, SC_DELTA, s);
-          if (e == hipSuccess && !P.sum_model_in_kernel) e = launch_sum_items(P.d_gd, 1, part, 1, scal, SC_GNEW, s);
-          return e == hipSuccess;
-        };
-        bool ok = forward_impl(P, m, d, nullptr, ws, ws_cap, s) == ASHRT_OK &&
-                  adjoint_impl(P, d, m2, nullptr, ws, ws_cap, s) == ASHRT_OK && sums();
-        std::vector<float> ts;
-        for (int r = 0; ok && r < repeats; ++r) {
-          ok = hipEventRecord(e0, s) == hipSuccess && forward_impl(P, m, d, nullptr, ws, ws_cap, s) == ASHRT_OK &&
-               adjoint_impl(P, d, m2, nullptr, ws, ws_cap, s) == ASHRT_OK && sums() &&
-               hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
-          float ms = 0.f;
-          if (ok) ok = hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
-          ts.push_back(ms);
-        }
-        (void)hipStreamSynchronize(s);
-        destroy_impl(P);
-        if (!ok) continue;
-        std::sort(ts.begin(), ts.end());
-        const double med = ts[ts.size() / 2];
-        if (med < best_t) {
-          best_t = med;
-          bt = tn;
-        }
+        const bool have = !candidates.empty() && candidates[0].tile_model == tm && candidates[0].tile_data == td &&
+                          candidates[0].nchunk == ch;
+        if (ch <= z.P && !have) candidates.push_back({tm, td, ch});
       }
+  for (const ashrt_tuning& tn : candidates) {
+    PlanImpl P;
+    if (create_impl(desc, 1, device, P, &tn) != ASHRT_OK) {  // e.g. the tile does not fit in LDS
+      destroy_impl(P);
+      continue;
+    }
+    const size_t need = std::max(P.layout(ASHRT_OP_FORWARD, 2).total, P.layout(ASHRT_OP_ADJOINT, 2).total);
+    if (need > ws_cap) {
+      if (ws) (void)hipFree(ws);
+      ws = nullptr;
+      ws_cap = 0;
+      if (hipMalloc(&ws, need) != hipSuccess) {
+        destroy_impl(P);
+        cleanup();
+        return fail(ASHRT_E_OOM, "autotune workspace allocation failed");
+      }
+      ws_cap = need;
+    }
+    // A CG iteration also sums the per-tile partials of |q|^2 and |g|^2:
+    // inside the consuming transform for small plans, else by one
+    // k_sum_items launch each (sum_*_in_kernel).  Those launches are
+    // timed with the pair, on zeroed partials, so that a tiling whose
+    // tile count moves the sums out of the transforms pays for them.
+    const size_t npart = (size_t)std::max(P.n_xm, P.n_xd);
+    if (npart > part_cap) {
+      if (part) (void)hipFree(part);
+      part = nullptr;
+      part_cap = 0;
+      if (hipMalloc(&part, npart * sizeof(double)) != hipSuccess ||
+          hipMemsetAsync(part, 0, npart * sizeof(double), s) != hipSuccess) {
+        destroy_impl(P);
+        cleanup();
+        return fail(ASHRT_E_OOM, "autotune partial-sum allocation failed");
+      }
+      part_cap = npart;
+    }
+    auto sums = [&]() {
+      hipError_t e = hipSuccess;
+      if (!P.sum_data_in_kernel) e = launch_sum_items(P.d_gd, 1, part, 0, scal, SC_DELTA, s);
+      if (e == hipSuccess && !P.sum_model_in_kernel) e = launch_sum_items(P.d_gd, 1, part, 1, scal, SC_GNEW, s);
+      return e == hipSuccess;
+    };
+    bool ok = forward_impl(P, m, d, nullptr, ws, ws_cap, s) == ASHRT_OK &&
+              adjoint_impl(P, d, m2, nullptr, ws, ws_cap, s) == ASHRT_OK && sums();
+    std::vector<float> ts;
+    for (int r = 0; ok && r < repeats; ++r) {
+      ok = hipEventRecord(e0, s) == hipSuccess && forward_impl(P, m, d, nullptr, ws, ws_cap, s) == ASHRT_OK &&
+           adjoint_impl(P, d, m2, nullptr, ws, ws_cap, s) == ASHRT_OK && sums() &&
+           hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
+      float ms = 0.f;
+      if (ok) ok = hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+      ts.push_back(ms);
+    }
+    (void)hipStreamSynchronize(s);
+    destroy_impl(P);
+    if (!ok) continue;
+    std::sort(ts.begin(), ts.end());
+    const double med = ts[ts.size() / 2];
+    if (med < best_t) {
+      best_t = med;
+      bt = tn;
+    }
+  }
   cleanup();
   if (best_t >= 1e300) return fail(ASHRT_E_UNSUPPORTED_SIZE, "no candidate tiling could run");
   {

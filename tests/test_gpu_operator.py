@@ -277,6 +277,27 @@ def test_autotune_is_cached_and_usable(A):
     assert plan.info["tile_model"] == t1["tile_model"] and plan.info["nchunk"] == t1["nchunk"]
 
 
+def test_autotune_tries_the_built_in_tiling(A):
+    """The built-in panel chunks of a geometry can lie off the tuner's grid (1, 2,
+    4, 8 chunks, 36 tilings): they are one more candidate, so a tuned plan is
+    not slower than an untuned one.  Each candidate runs 1 + repeats pairs."""
+    import ctypes
+    from paper_1711_10214_amd import _lib as L
+    kw = geom_kwargs(400, 180, 0.004, 12.5, list(np.linspace(1400.0, 3900.0, 24)), fmax=100.0)
+    n = A.Plan(**kw).info["nchunk"]
+    print(f"[gpu] autotune with {n} built-in panel chunks", flush=True)
+    assert n not in (1, 2, 4, 8)
+    rows_fwd = [k for k in range(16) if L.lib().ashrt_kernel_name(k) == b"k_rows_fwd"][0]
+    launches = ctypes.c_int64()
+    L.check(L.lib().ashrt_profile_enable(1 << rows_fwd), "ashrt_profile_enable")
+    try:
+        A.autotune(repeats=2, **kw)
+        L.check(L.lib().ashrt_profile_read(rows_fwd, None, ctypes.byref(launches), 1), "ashrt_profile_read")
+    finally:
+        L.check(L.lib().ashrt_profile_enable(0), "ashrt_profile_enable")
+    assert launches.value == 37 * 3
+
+
 def test_autotune_file_cache(A, tmp_path, monkeypatch):
     """With ASHRT_TUNE_CACHE set, a tuned tiling is appended to the file under
     the device's architecture name, and an entry already in the file is
