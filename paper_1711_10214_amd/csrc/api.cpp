@@ -624,6 +624,13 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
         return fail(ASHRT_E_UNSUPPORTED_SIZE, "internal: FFT pass table mismatch");
     }
   }
+  // irregular-trace tables: at most 2^31 entries (their transposes not counted)
+  size_t table = 0;
+  for (const auto& gh : P.g)
+    if (!gh.xpos.empty()) table += (size_t)gh.nrows * gh.z.nx;
+  if (tw.size() + table > (size_t)INT32_MAX)
+    return fail(ASHRT_E_UNSUPPORTED_SIZE, "irregular-trace tables too large");
+  tw.reserve(tw.size() + 2 * table);
   auto idx_of = [&](int N) { return std::lower_bound(lens.begin(), lens.end(), N) - lens.begin(); };
   auto tw_of = [&](int N) { return tw_off[idx_of(N)]; };
   auto twp_of = [&](int N) { return twp_off[idx_of(N)]; };
@@ -667,9 +674,7 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
       // exp(-2 pi i r x / (nxp dx)), r = 0..nrows-1; the phase in turns is
       // reduced in FP64 before the FP32 rounding
       const size_t ne = (size_t)gh.nrows * gh.z.nx;
-      if (tw.size() + ne > (size_t)INT32_MAX)
-        return fail(ASHRT_E_UNSUPPORTED_SIZE, "irregular-trace tables too large");
-      G.nudft_off = (int)tw.size();
+      G.nudft_off = (long long)tw.size();
       tw.resize(tw.size() + 2 * ne);  // [r][x], then transposed
       float2* E = tw.data() + G.nudft_off;
       const double period = (double)gh.z.nxp * descs[gi].dx;
