@@ -541,177 +541,174 @@ __global__ __launch_bounds__(kThreads) void k_xfft_fwd(XfwdArgs A) {
   __shared__ float s_alpha;
   __shared__ float s_ab[2];
   __shared__ double s_red[kThreads / 64];
-  {
-    const int it = xcd_item(blockIdx.x, A.nitems);
-    const WorkItem w = load_const(A.items + it);
-    const GatherDev G = load_const(A.gd + w.g);
-    const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
-    float cg_a = 0.f, cg_b = 0.f;
+  const int it = xcd_item(blockIdx.x, A.nitems);
+  const WorkItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
+  const float alpha = A.s_inout ? cg_alpha(A, w.g, G, it, &s_alpha, s_red) : 0.f;
+  float cg_a = 0.f, cg_b = 0.f;
+  if (A.cg_upd) {
+    double gsum = 0.0;
+    if (A.part_red) {
+      double part = 0.0;
+      for (int i = G.xm_lo + (int)threadIdx.x; i < G.xm_hi; i += kThreads) part += A.part_red[i];
+      gsum = block_sum(part, s_red);
+    }
+    if (threadIdx.x == 0) {
+      double* sc = A.sc + (long long)w.g * kNScal;
+      const double gnew = A.part_red ? gsum : sc[SC_GNEW];
+      const bool done = sc[SC_DONE] != 0.0;
+      const double gold = sc[SC_GAMMA0 + A.cg_par];
+      const double beta = (done || gold == 0.0) ? 0.0 : gnew / gold;
+      s_ab[0] = done ? 0.f : (float)sc[SC_ALPHA];
+      s_ab[1] = (float)beta;
+      if (A.item_base + it == G.xm_lo) {
+        sc[SC_GAMMA0 + (A.cg_par ^ 1)] = gnew;
+        sc[SC_BETA] = beta;
+      }
+    }
+    __syncthreads();
+    cg_a = s_ab[0];
+    cg_b = s_ab[1];
+  }
+  const int p = w.a;
+  const int nx = G.nx, nt = G.nt, nxp = G.nxp, nrows = G.nrows;
+  const int T = A.is_model ? G.tileT : G.tileTd, half = T >> 1;
+  const int bs = ((NX > 0 ? fft_padlen(nxp) : nxp) | 1);  // odd slot stride between columns
+  const int t0 = w.b * T;
+  float2* twl = lds;                          // x twiddles
+  float2* buf = lds + fft_tw_slots(NX, nxp);  // T/2 packed column pairs, odd slot stride bs
+  stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
+  XTw<NX> lw;
+  lw.load(A.tw + G.twp_x_off);
+  const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
+  const float* __restrict__ src = A.src + fbase;
+  const float* __restrict__ mul = A.mul ? A.mul + fbase : nullptr;
+  const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+
+  const UDiv dh(half);
+  if (!A.is_model && t0 + T <= nt) {
+    // a full data tile (all but a ragged last one)
+    float* sv = A.s_inout ? A.s_inout + fbase : nullptr;
+    const float* qv = A.s_inout ? A.qv + fbase : nullptr;
+    if (A.s_inout) {
+      if (mul) xfwd_data_full_tile<NX, true, true>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
+      else xfwd_data_full_tile<NX, true, false>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
+    } else {
+      if (mul) xfwd_data_full_tile<NX, false, true>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
+      else xfwd_data_full_tile<NX, false, false>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
+    }
+  } else if (A.is_model && t0 + T <= nt) {
+    // a full model tile (all but a ragged last one)
+    float* pp = A.cg_upd ? A.cg_p + fbase : nullptr;
+    float* uu = A.cg_upd ? A.cg_u + fbase : nullptr;
+    const float* gg = A.cg_upd ? A.cg_g + fbase : nullptr;
     if (A.cg_upd) {
-      double gsum = 0.0;
-      if (A.part_red) {
-        double part = 0.0;
-        for (int i = G.xm_lo + (int)threadIdx.x; i < G.xm_hi; i += kThreads) part += A.part_red[i];
-        gsum = block_sum(part, s_red);
-      }
-      if (threadIdx.x == 0) {
-        double* sc = A.sc + (long long)w.g * kNScal;
-        const double gnew = A.part_red ? gsum : sc[SC_GNEW];
-        const bool done = sc[SC_DONE] != 0.0;
-        const double gold = sc[SC_GAMMA0 + A.cg_par];
-        const double beta = (done || gold == 0.0) ? 0.0 : gnew / gold;
-        s_ab[0] = done ? 0.f : (float)sc[SC_ALPHA];
-        s_ab[1] = (float)beta;
-        if (A.item_base + it == G.xm_lo) {
-          sc[SC_GAMMA0 + (A.cg_par ^ 1)] = gnew;
-          sc[SC_BETA] = beta;
-        }
-      }
-      __syncthreads();
-      cg_a = s_ab[0];
-      cg_b = s_ab[1];
+      if (mul) xfwd_model_full_tile<NX, true, true>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, cg_a, cg_b);
+      else xfwd_model_full_tile<NX, true, false>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, cg_a, cg_b);
+    } else {
+      if (mul) xfwd_model_full_tile<NX, false, true>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, 0.f, 0.f);
+      else xfwd_model_full_tile<NX, false, false>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, 0.f, 0.f);
     }
-    const int p = w.a;
-    const int nx = G.nx, nt = G.nt, nxp = G.nxp, nrows = G.nrows;
-    const int T = A.is_model ? G.tileT : G.tileTd, half = T >> 1;
-    const int bs = ((NX > 0 ? fft_padlen(nxp) : nxp) | 1);  // odd slot stride between columns
-    const int t0 = w.b * T;
-    float2* twl = lds;                          // x twiddles
-    float2* buf = lds + fft_tw_slots(NX, nxp);  // T/2 packed column pairs, odd slot stride bs
-    stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
-    XTw<NX> lw;
-    lw.load(A.tw + G.twp_x_off);
-    const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
-    const float* __restrict__ src = A.src + fbase;
-    const float* __restrict__ mul = A.mul ? A.mul + fbase : nullptr;
-    const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-
-    const UDiv dh(half);
-    if (!A.is_model && t0 + T <= nt) {
-      // a full data tile (all but a ragged last one)
-      float* sv = A.s_inout ? A.s_inout + fbase : nullptr;
-      const float* qv = A.s_inout ? A.qv + fbase : nullptr;
-      if (A.s_inout) {
-        if (mul) xfwd_data_full_tile<NX, true, true>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
-        else xfwd_data_full_tile<NX, true, false>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
-      } else {
-        if (mul) xfwd_data_full_tile<NX, false, true>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
-        else xfwd_data_full_tile<NX, false, false>(buf, bs, dh, half, nx, nt, t0, src, mul, tm, sv, qv, alpha);
-      }
-    } else if (A.is_model && t0 + T <= nt) {
-      // a full model tile (all but a ragged last one)
-      float* pp = A.cg_upd ? A.cg_p + fbase : nullptr;
-      float* uu = A.cg_upd ? A.cg_u + fbase : nullptr;
-      const float* gg = A.cg_upd ? A.cg_g + fbase : nullptr;
-      if (A.cg_upd) {
-        if (mul) xfwd_model_full_tile<NX, true, true>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, cg_a, cg_b);
-        else xfwd_model_full_tile<NX, true, false>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, cg_a, cg_b);
-      } else {
-        if (mul) xfwd_model_full_tile<NX, false, true>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, 0.f, 0.f);
-        else xfwd_model_full_tile<NX, false, false>(buf, bs, dh, half, nx, nt, t0, src, mul, pp, uu, gg, 0.f, 0.f);
-      }
-    } else
-    for (int idx = threadIdx.x; idx < nx * half; idx += kThreads) {
-      const int x = dh.div(idx);
-      const int i = idx - x * half;
-      const int t = t0 + 2 * i;
-      const long long o = (long long)x * nt + t;
-      float a = 0.f, b = 0.f;
-      if (A.cg_upd) {
-        // the previous iteration's CG update of this element pair; the new
-        // search direction is the input
-        float* pp = A.cg_p + fbase;
-        float* uu = A.cg_u + fbase;
-        const float* gg = A.cg_g + fbase;
-        if (t + 1 < nt) {
-          const float2 pv = ld2(pp + o, 0), gv = ld2(gg + o, 0), uv = ld2(uu + o, 0);
-          st2(uu + o, 0, make_float2(fmaf(cg_a, pv.x, uv.x), fmaf(cg_a, pv.y, uv.y)));
-          a = fmaf(cg_b, pv.x, gv.x);
-          b = fmaf(cg_b, pv.y, gv.y);
-          st2(pp + o, 0, make_float2(a, b));
-        } else if (t < nt) {
-          const float pv = pp[o];
-          uu[o] = fmaf(cg_a, pv, uu[o]);
-          a = fmaf(cg_b, pv, gg[o]);
-          pp[o] = a;
-        }
-        if (mul) {
-          a *= (t < nt) ? mul[o] : 0.f;
-          b *= (t + 1 < nt) ? mul[o + 1] : 0.f;
-        }
-      } else if (A.s_inout) {
-        float* sv = A.s_inout + fbase;
-        const float* qv = A.qv + fbase;
-        if (t < nt) {
-          a = fmaf(-alpha, qv[o], sv[o]);
-          sv[o] = a;
-        }
-        if (t + 1 < nt) {
-          b = fmaf(-alpha, qv[o + 1], sv[o + 1]);
-          sv[o + 1] = b;
-        }
-        if (mul) {
-          a *= (t < nt) ? mul[o] : 0.f;
-          b *= (t + 1 < nt) ? mul[o + 1] : 0.f;
-        }
-      } else if (t + 1 < nt) {
-        const float2 v = ld2(src + o, 0);
-        a = v.x;
-        b = v.y;
-        if (mul) {
-          const float2 wv = ld2(mul + o, 0);
-          a *= wv.x;
-          b *= wv.y;
-        }
+  } else
+  for (int idx = threadIdx.x; idx < nx * half; idx += kThreads) {
+    const int x = dh.div(idx);
+    const int i = idx - x * half;
+    const int t = t0 + 2 * i;
+    const long long o = (long long)x * nt + t;
+    float a = 0.f, b = 0.f;
+    if (A.cg_upd) {
+      // the previous iteration's CG update of this element pair; the new
+      // search direction is the input
+      float* pp = A.cg_p + fbase;
+      float* uu = A.cg_u + fbase;
+      const float* gg = A.cg_g + fbase;
+      if (t + 1 < nt) {
+        const float2 pv = ld2(pp + o, 0), gv = ld2(gg + o, 0), uv = ld2(uu + o, 0);
+        st2(uu + o, 0, make_float2(fmaf(cg_a, pv.x, uv.x), fmaf(cg_a, pv.y, uv.y)));
+        a = fmaf(cg_b, pv.x, gv.x);
+        b = fmaf(cg_b, pv.y, gv.y);
+        st2(pp + o, 0, make_float2(a, b));
       } else if (t < nt) {
-        a = src[o];
-        if (mul) a *= mul[o];
+        const float pv = pp[o];
+        uu[o] = fmaf(cg_a, pv, uu[o]);
+        a = fmaf(cg_b, pv, gg[o]);
+        pp[o] = a;
       }
-      if (tm && tm[x] == 0) {
-        a = 0.f;
-        b = 0.f;
+      if (mul) {
+        a *= (t < nt) ? mul[o] : 0.f;
+        b *= (t + 1 < nt) ? mul[o + 1] : 0.f;
       }
-      buf[i * bs + px<NX>(x)] = make_float2(a, b);
+    } else if (A.s_inout) {
+      float* sv = A.s_inout + fbase;
+      const float* qv = A.qv + fbase;
+      if (t < nt) {
+        a = fmaf(-alpha, qv[o], sv[o]);
+        sv[o] = a;
+      }
+      if (t + 1 < nt) {
+        b = fmaf(-alpha, qv[o + 1], sv[o + 1]);
+        sv[o + 1] = b;
+      }
+      if (mul) {
+        a *= (t < nt) ? mul[o] : 0.f;
+        b *= (t + 1 < nt) ? mul[o + 1] : 0.f;
+      }
+    } else if (t + 1 < nt) {
+      const float2 v = ld2(src + o, 0);
+      a = v.x;
+      b = v.y;
+      if (mul) {
+        const float2 wv = ld2(mul + o, 0);
+        a *= wv.x;
+        b *= wv.y;
+      }
+    } else if (t < nt) {
+      a = src[o];
+      if (mul) a *= mul[o];
     }
-    if constexpr (NX == 0) {  // the generic FFT reads the pad
-      for (int idx = threadIdx.x; idx < (nxp - nx) * half; idx += kThreads) {
-        const int xx = dh.div(idx);
-        const int i = idx - xx * half;
-        buf[i * bs + px<NX>(nx + xx)] = make_float2(0.f, 0.f);
-      }
+    if (tm && tm[x] == 0) {
+      a = 0.f;
+      b = 0.f;
     }
-    __syncthreads();
-    lw.pin();
-    xfft_tile<NX, false>(buf, nxp, half, bs, twl, nx, lw);
+    buf[i * bs + px<NX>(x)] = make_float2(a, b);
+  }
+  if constexpr (NX == 0) {  // the generic FFT reads the pad
+    for (int idx = threadIdx.x; idx < (nxp - nx) * half; idx += kThreads) {
+      const int xx = dh.div(idx);
+      const int i = idx - xx * half;
+      buf[i * bs + px<NX>(nx + xx)] = make_float2(0.f, 0.f);
+    }
+  }
+  __syncthreads();
+  lw.pin();
+  xfft_tile<NX, false>(buf, nxp, half, bs, twl, nx, lw);
 
-    // column pair i holds the packed spectra of columns t0 + 2i (real part)
-    // and t0 + 2i + 1 (imaginary part); both outputs of a row are written
-    // together (one 16-byte store)
-    float2* __restrict__ dst = A.dst + (A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
-    // model panels: rows at or above the panel's live-row count are never read
-    const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
-    for (int idx = threadIdx.x; idx < nrw * half; idx += kThreads) {
-      const int r = dh.div(idx);
-      const int i = idx - r * half;
-      const int t = t0 + 2 * i;
-      if (t >= nt) continue;
-      const float2* Z = buf + i * bs;
-      float2 o0, o1;
-      if (r == 0) {
-        const float2 z0 = Z[0], zn = Z[px<NX>(nrows)];
-        o0 = make_float2(z0.x, zn.x);
-        o1 = make_float2(z0.y, zn.y);
-      } else {
-        const float2 a = Z[px<NX>(r)];
-        const float2 b = cconj(Z[px<NX>(nxp - r)]);
-        o0 = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y + b.y));
-        o1 = make_float2(0.5f * (a.y - b.y), -0.5f * (a.x - b.x));
-      }
-      float2* d = dst + (long long)r * nt + t;
-      if (t + 1 < nt) *reinterpret_cast<f32x4u*>(d) = f32x4u{o0.x, o0.y, o1.x, o1.y};
-      else d[0] = o0;
+  // column pair i holds the packed spectra of columns t0 + 2i (real part)
+  // and t0 + 2i + 1 (imaginary part); both outputs of a row are written
+  // together (one 16-byte store)
+  float2* __restrict__ dst = A.dst + (A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
+  // model panels: rows at or above the panel's live-row count are never read
+  const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
+  for (int idx = threadIdx.x; idx < nrw * half; idx += kThreads) {
+    const int r = dh.div(idx);
+    const int i = idx - r * half;
+    const int t = t0 + 2 * i;
+    if (t >= nt) continue;
+    const float2* Z = buf + i * bs;
+    float2 o0, o1;
+    if (r == 0) {
+      const float2 z0 = Z[0], zn = Z[px<NX>(nrows)];
+      o0 = make_float2(z0.x, zn.x);
+      o1 = make_float2(z0.y, zn.y);
+    } else {
+      const float2 a = Z[px<NX>(r)];
+      const float2 b = cconj(Z[px<NX>(nxp - r)]);
+      o0 = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y + b.y));
+      o1 = make_float2(0.5f * (a.y - b.y), -0.5f * (a.x - b.x));
     }
-    __syncthreads();
+    float2* d = dst + (long long)r * nt + t;
+    if (t + 1 < nt) *reinterpret_cast<f32x4u*>(d) = f32x4u{o0.x, o0.y, o1.x, o1.y};
+    else d[0] = o0;
   }
 }
 
@@ -721,151 +718,148 @@ __global__ __launch_bounds__(kThreads) void k_xfft_inv(XinvArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: twiddle records
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   __shared__ double sh[kThreads / 64];
-  {
-    const int it = xcd_item(blockIdx.x, A.nitems);
-    const WorkItem w = load_const(A.items + it);
-    const GatherDev G = load_const(A.gd + w.g);
-    const int p = w.a;
-    const int nx = G.nx, nt = G.nt, nxp = G.nxp, nrows = G.nrows;
-    const int T = A.is_model ? G.tileT : G.tileTd, half = T >> 1;
-    const int bs = ((NX > 0 ? fft_padlen(nxp) : nxp) | 1);  // odd slot stride between columns
-    const int t0 = w.b * T;
-    const float2* __restrict__ src = A.src + uniform64(A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
-    float2* twl = lds;
-    float2* buf = lds + fft_tw_slots(NX, nxp);
-    stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
-    XTw<NX> lw;
-    lw.load(A.tw + G.twp_x_off);
+  const int it = xcd_item(blockIdx.x, A.nitems);
+  const WorkItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
+  const int p = w.a;
+  const int nx = G.nx, nt = G.nt, nxp = G.nxp, nrows = G.nrows;
+  const int T = A.is_model ? G.tileT : G.tileTd, half = T >> 1;
+  const int bs = ((NX > 0 ? fft_padlen(nxp) : nxp) | 1);  // odd slot stride between columns
+  const int t0 = w.b * T;
+  const float2* __restrict__ src = A.src + uniform64(A.is_model ? G.X_off + (long long)p * nrows * nt : G.H_off);
+  float2* twl = lds;
+  float2* buf = lds + fft_tw_slots(NX, nxp);
+  stage_twiddles<NX>(twl, A.tw, G.tw_x_off, G.twp_x_off, nxp);
+  XTw<NX> lw;
+  lw.load(A.tw + G.twp_x_off);
 
-    const UDiv dh(half);
-    // model panels: rows at or above the panel's live-row count are zero (not stored)
-    const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
-    if (t0 + T <= nt) {
-      // a full tile (all but a ragged last one)
-      xinv_rows_full_tile<NX>(buf, bs, dh, half, nrows, nrw, nxp, nt, t0, src);
-    } else
-    for (int idx = threadIdx.x; idx < nrows * half; idx += kThreads) {
-      const int l = dh.div(idx);
-      const int i = idx - l * half;
-      const int t = t0 + 2 * i;
-      float2 h1 = make_float2(0.f, 0.f), h2 = make_float2(0.f, 0.f);
-      if (l >= nrw) {
-        // zero row
-      } else if (t + 1 < nt) {
-        const float4 h = ld4(src + (long long)l * nt + t, 0);
-        h1 = make_float2(h.x, h.y);
-        h2 = make_float2(h.z, h.w);
-      } else if (t < nt) {
-        h1 = src[(long long)l * nt + t];
-      }
-      float2* Z = buf + i * bs;
-      if (l == 0) {
-        Z[0] = make_float2(h1.x, h2.x);
-        Z[px<NX>(nrows)] = make_float2(h1.y, h2.y);
-      } else {
-        Z[px<NX>(l)] = make_float2(h1.x - h2.y, h1.y + h2.x);
-        Z[px<NX>(nxp - l)] = make_float2(h1.x + h2.y, -h1.y + h2.x);
-      }
+  const UDiv dh(half);
+  // model panels: rows at or above the panel's live-row count are zero (not stored)
+  const int nrw = A.is_model ? min(nrows, load_const(A.panels + G.panel_off + p).rlive) : nrows;
+  if (t0 + T <= nt) {
+    // a full tile (all but a ragged last one)
+    xinv_rows_full_tile<NX>(buf, bs, dh, half, nrows, nrw, nxp, nt, t0, src);
+  } else
+  for (int idx = threadIdx.x; idx < nrows * half; idx += kThreads) {
+    const int l = dh.div(idx);
+    const int i = idx - l * half;
+    const int t = t0 + 2 * i;
+    float2 h1 = make_float2(0.f, 0.f), h2 = make_float2(0.f, 0.f);
+    if (l >= nrw) {
+      // zero row
+    } else if (t + 1 < nt) {
+      const float4 h = ld4(src + (long long)l * nt + t, 0);
+      h1 = make_float2(h.x, h.y);
+      h2 = make_float2(h.z, h.w);
+    } else if (t < nt) {
+      h1 = src[(long long)l * nt + t];
     }
-    __syncthreads();
-    lw.pin();
-    xfft_tile<NX, true>(buf, nxp, half, bs, twl, nx, lw);
+    float2* Z = buf + i * bs;
+    if (l == 0) {
+      Z[0] = make_float2(h1.x, h2.x);
+      Z[px<NX>(nrows)] = make_float2(h1.y, h2.y);
+    } else {
+      Z[px<NX>(l)] = make_float2(h1.x - h2.y, h1.y + h2.x);
+      Z[px<NX>(nxp - l)] = make_float2(h1.x + h2.y, -h1.y + h2.x);
+    }
+  }
+  __syncthreads();
+  lw.pin();
+  xfft_tile<NX, true>(buf, nxp, half, bs, twl, nx, lw);
 
-    const float inv = 1.0f / (float)nxp;
-    const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
-    const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-    double ss = 0.0;
-    if (t0 + T <= nt && (A.wmul || A.sub)) {
-      // a full tile whose epilogue reads memory (wmul, sub): the loads of
-      // kXLoadBatch loop iterations are issued together (indices past the
-      // tile clamped)
-      const float* __restrict__ wm = A.wmul ? A.wmul + fbase : nullptr;
-      const bool wsq = A.wmul && A.wmul_sq;
-      const float* __restrict__ sb = A.sub ? A.sub + fbase : nullptr;
-      float* __restrict__ raw = A.raw_out ? A.raw_out + fbase : nullptr;
-      float* __restrict__ out = A.out + fbase;
-      const int nin = nx * half;
-      for (int base = threadIdx.x; base < nin; base += kXLoadBatch * kThreads) {
-        float2 wv[kXLoadBatch], sv[kXLoadBatch];
-        int live[kXLoadBatch];  // trace index, then its mask byte
-        unsigned off[kXLoadBatch];  // byte offsets (4 nx nt < 2^32)
+  const float inv = 1.0f / (float)nxp;
+  const long long fbase = uniform64(A.is_model ? (G.m_off + (long long)p * nx * nt) : G.d_off);
+  const uint8_t* __restrict__ tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+  double ss = 0.0;
+  if (t0 + T <= nt && (A.wmul || A.sub)) {
+    // a full tile whose epilogue reads memory (wmul, sub): the loads of
+    // kXLoadBatch loop iterations are issued together (indices past the
+    // tile clamped)
+    const float* __restrict__ wm = A.wmul ? A.wmul + fbase : nullptr;
+    const bool wsq = A.wmul && A.wmul_sq;
+    const float* __restrict__ sb = A.sub ? A.sub + fbase : nullptr;
+    float* __restrict__ raw = A.raw_out ? A.raw_out + fbase : nullptr;
+    float* __restrict__ out = A.out + fbase;
+    const int nin = nx * half;
+    for (int base = threadIdx.x; base < nin; base += kXLoadBatch * kThreads) {
+      float2 wv[kXLoadBatch], sv[kXLoadBatch];
+      int live[kXLoadBatch];  // trace index, then its mask byte
+      unsigned off[kXLoadBatch];  // byte offsets (4 nx nt < 2^32)
 #pragma unroll
-        for (int u = 0; u < kXLoadBatch; ++u) {
-          const int idx = min(base + u * kThreads, nin - 1);
+      for (int u = 0; u < kXLoadBatch; ++u) {
+        const int idx = min(base + u * kThreads, nin - 1);
+        const int x = dh.div(idx);
+        off[u] = 4u * (unsigned)(x * nt + t0 + 2 * (idx - x * half));
+        if (wm) wv[u] = ld2(wm, off[u]);
+        if (sb) sv[u] = ld2(sb, off[u]);
+        live[u] = x;
+      }
+      // mask bytes after every other load of the batch is issued
+      if (tm) {
+#pragma unroll
+        for (int u = 0; u < kXLoadBatch; ++u) live[u] = tm[live[u]];
+      } else {
+#pragma unroll
+        for (int u = 0; u < kXLoadBatch; ++u) live[u] = 1;
+      }
+#pragma unroll
+      for (int u = 0; u < kXLoadBatch; ++u) {
+        const int idx = base + u * kThreads;
+        if (idx < nin) {
           const int x = dh.div(idx);
-          off[u] = 4u * (unsigned)(x * nt + t0 + 2 * (idx - x * half));
-          if (wm) wv[u] = ld2(wm, off[u]);
-          if (sb) sv[u] = ld2(sb, off[u]);
-          live[u] = x;
-        }
-        // mask bytes after every other load of the batch is issued
-        if (tm) {
-#pragma unroll
-          for (int u = 0; u < kXLoadBatch; ++u) live[u] = tm[live[u]];
-        } else {
-#pragma unroll
-          for (int u = 0; u < kXLoadBatch; ++u) live[u] = 1;
-        }
-#pragma unroll
-        for (int u = 0; u < kXLoadBatch; ++u) {
-          const int idx = base + u * kThreads;
-          if (idx < nin) {
-            const int x = dh.div(idx);
-            const int i = idx - x * half;
-            const float2 z = buf[i * bs + px<NX>(x)];
-            float2 v = make_float2(z.x * inv, z.y * inv);
-            if (raw) st2(raw, off[u], v);
-            if (sb) v = make_float2(sv[u].x - v.x, sv[u].y - v.y);
-            if (live[u] == 0) v = make_float2(0.f, 0.f);
-            if (wm) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
-            ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
-            if (wsq) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
-            st2(out, off[u], v);
-          }
+          const int i = idx - x * half;
+          const float2 z = buf[i * bs + px<NX>(x)];
+          float2 v = make_float2(z.x * inv, z.y * inv);
+          if (raw) st2(raw, off[u], v);
+          if (sb) v = make_float2(sv[u].x - v.x, sv[u].y - v.y);
+          if (live[u] == 0) v = make_float2(0.f, 0.f);
+          if (wm) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
+          ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+          if (wsq) v = make_float2(v.x * wv[u].x, v.y * wv[u].y);
+          st2(out, off[u], v);
         }
       }
-    } else
-    for (int idx = threadIdx.x; idx < nx * half; idx += kThreads) {
-      const int x = dh.div(idx);
-      const int i = idx - x * half;
-      const int t = t0 + 2 * i;
-      if (t >= nt) continue;
-      const float2 z = buf[i * bs + px<NX>(x)];
-      const bool live = !(tm && tm[x] == 0);
-      const long long o = fbase + (long long)x * nt + t;
-      if (t + 1 < nt) {
-        float2 v = make_float2(z.x * inv, z.y * inv);
-        if (A.raw_out) st2(A.raw_out + o, 0, v);
-        if (A.sub) {
-          const float2 sv = ld2(A.sub + o, 0);
-          v = make_float2(sv.x - v.x, sv.y - v.y);
-        }
-        if (!live) v = make_float2(0.f, 0.f);
-        if (A.wmul) {
-          const float2 wv = ld2(A.wmul + o, 0);
-          v = make_float2(v.x * wv.x, v.y * wv.y);
-          ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
-          if (A.wmul_sq) v = make_float2(v.x * wv.x, v.y * wv.y);
-        } else {
-          ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
-        }
-        st2(A.out + o, 0, v);
+    }
+  } else
+  for (int idx = threadIdx.x; idx < nx * half; idx += kThreads) {
+    const int x = dh.div(idx);
+    const int i = idx - x * half;
+    const int t = t0 + 2 * i;
+    if (t >= nt) continue;
+    const float2 z = buf[i * bs + px<NX>(x)];
+    const bool live = !(tm && tm[x] == 0);
+    const long long o = fbase + (long long)x * nt + t;
+    if (t + 1 < nt) {
+      float2 v = make_float2(z.x * inv, z.y * inv);
+      if (A.raw_out) st2(A.raw_out + o, 0, v);
+      if (A.sub) {
+        const float2 sv = ld2(A.sub + o, 0);
+        v = make_float2(sv.x - v.x, sv.y - v.y);
+      }
+      if (!live) v = make_float2(0.f, 0.f);
+      if (A.wmul) {
+        const float2 wv = ld2(A.wmul + o, 0);
+        v = make_float2(v.x * wv.x, v.y * wv.y);
+        ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+        if (A.wmul_sq) v = make_float2(v.x * wv.x, v.y * wv.y);
       } else {
-        float v = z.x * inv;
-        if (A.raw_out) A.raw_out[o] = v;
-        if (A.sub) v = A.sub[o] - v;
-        if (!live) v = 0.f;
-        if (A.wmul) v *= A.wmul[o];
-        ss += (double)v * (double)v;
-        if (A.wmul && A.wmul_sq) v *= A.wmul[o];
-        A.out[o] = v;
+        ss += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
       }
+      st2(A.out + o, 0, v);
+    } else {
+      float v = z.x * inv;
+      if (A.raw_out) A.raw_out[o] = v;
+      if (A.sub) v = A.sub[o] - v;
+      if (!live) v = 0.f;
+      if (A.wmul) v *= A.wmul[o];
+      ss += (double)v * (double)v;
+      if (A.wmul && A.wmul_sq) v *= A.wmul[o];
+      A.out[o] = v;
     }
-    if (A.part) {
-      const double tot = block_sum(ss, sh);
-      if (threadIdx.x == 0) A.part[A.item_base + it] = tot;
-    }
-    __syncthreads();
+  }
+  if (A.part) {
+    const double tot = block_sum(ss, sh);
+    if (threadIdx.x == 0) A.part[A.item_base + it] = tot;
   }
 }
 
@@ -1338,7 +1332,6 @@ __device__ __forceinline__ void rows_fwd_item(const RowsArgs& A, const WorkItem&
   }
   float2* __restrict__ dp = A.Dp + G.Dp_off + ((long long)chunk * nrows + r) * 2 * nband;
   for (int i = threadIdx.x; i < 2 * nband; i += NT) dp[i] = acc[i];
-  __syncthreads();
 }
 
 // Rotations of the window (generic kernels only).

@@ -16,77 +16,75 @@ namespace ashrt {
 
 __global__ __launch_bounds__(kThreads) void k_reduce_part(RedArgs A) {
   __shared__ double sh[kThreads / 64];
-  {
-    const int it = blockIdx.x;
-    const VecItem w = load_const(A.items + it);
-    const GatherDev G = load_const(A.gd + w.g);
-    const uint8_t* tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-    double a = 0.0, b = 0.0;
-    const double eps = A.sc ? A.sc[w.g * kNScal + SC_EPS_R] : 0.0;
-    long long i0 = threadIdx.x;
-    if ((A.op == RED_SUMSQ || A.op == RED_ABSMAX) && ((w.start | w.len) & 3) == 0) {
-      const float4* x4 = reinterpret_cast<const float4*>(A.x + w.start);
-      // the loads of kBatch iterations are issued before any is used
-      constexpr int kBatch = 4;
-      const int n4 = (int)(w.len >> 2);
-      for (int base = threadIdx.x; base < n4; base += kBatch * kThreads) {
-        float4 q[kBatch];
+  const int it = blockIdx.x;
+  const VecItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
+  const uint8_t* tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+  double a = 0.0, b = 0.0;
+  const double eps = A.sc ? A.sc[w.g * kNScal + SC_EPS_R] : 0.0;
+  long long i0 = threadIdx.x;
+  if ((A.op == RED_SUMSQ || A.op == RED_ABSMAX) && ((w.start | w.len) & 3) == 0) {
+    const float4* x4 = reinterpret_cast<const float4*>(A.x + w.start);
+    // the loads of kBatch iterations are issued before any is used
+    constexpr int kBatch = 4;
+    const int n4 = (int)(w.len >> 2);
+    for (int base = threadIdx.x; base < n4; base += kBatch * kThreads) {
+      float4 q[kBatch];
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) q[k] = x4[min(base + k * kThreads, n4 - 1)];
+      for (int k = 0; k < kBatch; ++k) q[k] = x4[min(base + k * kThreads, n4 - 1)];
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-          if (base + k * kThreads >= n4) break;
-          const float4 v = q[k];
-          if (A.op == RED_SUMSQ) {
-            a += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
-          } else {
-            a = fmax(a, (double)fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-          }
-        }
-      }
-      i0 = w.len;  // done
-    }
-    for (long long i = i0; i < w.len; i += kThreads) {
-      const long long o = w.start + i;
-      const double v = (double)A.x[o];
-      if (A.op == RED_SUMSQ) {
-        a += v * v;
-      } else if (A.op == RED_ABSMAX) {
-        a = fmax(a, fabs(v));
-      } else if (A.op == RED_ABSSUM) {
-        a += fabs(v);
-      } else {
-        bool live = true;
-        if (tm) {
-          const unsigned x = (unsigned)(o - G.d_off) / (unsigned)G.nt;  // nx nt < 2^31
-          live = tm[x] != 0;
-        }
-        if (!live) continue;
-        if (A.op == RED_ABSMAX_LIVE) {
-          a = fmax(a, fabs(v));
-        } else {  // RED_MISFIT: sum |r|^p and the Huber (p = 1) or LS (p = 2) objective
-          const double av = fabs(v);
-          if (A.p == 1) {
-            a += av;
-            b += (eps > 0.0) ? ((av <= eps) ? av * av / (2.0 * eps) : av - 0.5 * eps) : av;
-          } else {
-            a += v * v;
-            b += 0.5 * v * v;
-          }
+      for (int k = 0; k < kBatch; ++k) {
+        if (base + k * kThreads >= n4) break;
+        const float4 v = q[k];
+        if (A.op == RED_SUMSQ) {
+          a += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
+        } else {
+          a = fmax(a, (double)fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
         }
       }
     }
-    double ra, rb = 0.0;
-    if (A.op == RED_ABSMAX || A.op == RED_ABSMAX_LIVE) {
-      ra = block_max(a, sh);
+    i0 = w.len;  // done
+  }
+  for (long long i = i0; i < w.len; i += kThreads) {
+    const long long o = w.start + i;
+    const double v = (double)A.x[o];
+    if (A.op == RED_SUMSQ) {
+      a += v * v;
+    } else if (A.op == RED_ABSMAX) {
+      a = fmax(a, fabs(v));
+    } else if (A.op == RED_ABSSUM) {
+      a += fabs(v);
     } else {
-      ra = block_sum(a, sh);
-      if (A.op == RED_MISFIT) rb = block_sum(b, sh);
+      bool live = true;
+      if (tm) {
+        const unsigned x = (unsigned)(o - G.d_off) / (unsigned)G.nt;  // nx nt < 2^31
+        live = tm[x] != 0;
+      }
+      if (!live) continue;
+      if (A.op == RED_ABSMAX_LIVE) {
+        a = fmax(a, fabs(v));
+      } else {  // RED_MISFIT: sum |r|^p and the Huber (p = 1) or LS (p = 2) objective
+        const double av = fabs(v);
+        if (A.p == 1) {
+          a += av;
+          b += (eps > 0.0) ? ((av <= eps) ? av * av / (2.0 * eps) : av - 0.5 * eps) : av;
+        } else {
+          a += v * v;
+          b += 0.5 * v * v;
+        }
+      }
     }
-    if (threadIdx.x == 0) {
-      A.part[2 * it] = ra;
-      A.part[2 * it + 1] = rb;
-    }
+  }
+  double ra, rb = 0.0;
+  if (A.op == RED_ABSMAX || A.op == RED_ABSMAX_LIVE) {
+    ra = block_max(a, sh);
+  } else {
+    ra = block_sum(a, sh);
+    if (A.op == RED_MISFIT) rb = block_sum(b, sh);
+  }
+  if (threadIdx.x == 0) {
+    A.part[2 * it] = ra;
+    A.part[2 * it + 1] = rb;
   }
 }
 
@@ -292,51 +290,48 @@ constexpr int kSelWidth[3] = {11, 11, 10};
 constexpr int kSelSplit = 2;
 __global__ __launch_bounds__(kThreads) void k_sel_hist(SelArgs A) {
   __shared__ unsigned h[2][kSelBins];
-  {
-    const int b = blockIdx.x;
-    for (int i = threadIdx.x; i < 2 * kSelBins; i += kThreads) (&h[0][0])[i] = 0u;
-    __syncthreads();
-    const int it = b / kSelSplit, part = b - it * kSelSplit;
-    const VecItem w = load_const(A.items + it);
-    const GatherDev G = load_const(A.gd + w.g);
-    const unsigned hmask = (A.shift + A.width >= 32) ? 0u : (0xffffffffu << (A.shift + A.width));
-    const unsigned p0 = A.st[w.g].prefix[0] & hmask, p1 = A.st[w.g].prefix[1] & hmask;
-    const unsigned dmask = (1u << A.width) - 1u;
-    const uint8_t* tm = A.tmask ? A.tmask + G.mask_off : nullptr;
-    const double med = A.stage ? A.sc[w.g * kNScal + SC_MED] : 0.0;
-    const long long lo = w.start + w.len * part / kSelSplit;
-    const int n = (int)(w.start + w.len * (part + 1) / kSelSplit - lo);
-    const unsigned rel0 = (unsigned)(lo - G.d_off);  // sample index in the gather (nx nt < 2^31)
-    for (int base = threadIdx.x; base < n; base += 4 * kThreads) {
-      float v[4];
-      int live[4];
+  const int b = blockIdx.x;
+  for (int i = threadIdx.x; i < 2 * kSelBins; i += kThreads) (&h[0][0])[i] = 0u;
+  __syncthreads();
+  const int it = b / kSelSplit, part = b - it * kSelSplit;
+  const VecItem w = load_const(A.items + it);
+  const GatherDev G = load_const(A.gd + w.g);
+  const unsigned hmask = (A.shift + A.width >= 32) ? 0u : (0xffffffffu << (A.shift + A.width));
+  const unsigned p0 = A.st[w.g].prefix[0] & hmask, p1 = A.st[w.g].prefix[1] & hmask;
+  const unsigned dmask = (1u << A.width) - 1u;
+  const uint8_t* tm = A.tmask ? A.tmask + G.mask_off : nullptr;
+  const double med = A.stage ? A.sc[w.g * kNScal + SC_MED] : 0.0;
+  const long long lo = w.start + w.len * part / kSelSplit;
+  const int n = (int)(w.start + w.len * (part + 1) / kSelSplit - lo);
+  const unsigned rel0 = (unsigned)(lo - G.d_off);  // sample index in the gather (nx nt < 2^31)
+  for (int base = threadIdx.x; base < n; base += 4 * kThreads) {
+    float v[4];
+    int live[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = A.x[lo + min(base + u * kThreads, n - 1)];
-      if (tm) {
+    for (int u = 0; u < 4; ++u) v[u] = A.x[lo + min(base + u * kThreads, n - 1)];
+    if (tm) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) live[u] = tm[(rel0 + (unsigned)min(base + u * kThreads, n - 1)) / (unsigned)G.nt];
-      } else {
+      for (int u = 0; u < 4; ++u) live[u] = tm[(rel0 + (unsigned)min(base + u * kThreads, n - 1)) / (unsigned)G.nt];
+    } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) live[u] = 1;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (base + u * kThreads >= n || live[u] == 0) continue;
-        float x = v[u];
-        if (A.stage) x = (float)fabs((double)x - med);
-        const unsigned key = float_key(x);
-        const unsigned dg = (key >> A.shift) & dmask;
-        if ((key & hmask) == p0) atomicAdd(&h[0][dg], 1u);
-        else if ((key & hmask) == p1) atomicAdd(&h[1][dg], 1u);
-      }
+      for (int u = 0; u < 4; ++u) live[u] = 1;
     }
-    __syncthreads();
-    unsigned* gh = A.hist + (long long)w.g * 2 * kSelBins;
-    for (int i = threadIdx.x; i < 2 * kSelBins; i += kThreads) {
-      const unsigned c = (&h[0][0])[i];
-      if (c) atomicAdd(&gh[i], c);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (base + u * kThreads >= n || live[u] == 0) continue;
+      float x = v[u];
+      if (A.stage) x = (float)fabs((double)x - med);
+      const unsigned key = float_key(x);
+      const unsigned dg = (key >> A.shift) & dmask;
+      if ((key & hmask) == p0) atomicAdd(&h[0][dg], 1u);
+      else if ((key & hmask) == p1) atomicAdd(&h[1][dg], 1u);
     }
-    __syncthreads();
+  }
+  __syncthreads();
+  unsigned* gh = A.hist + (long long)w.g * 2 * kSelBins;
+  for (int i = threadIdx.x; i < 2 * kSelBins; i += kThreads) {
+    const unsigned c = (&h[0][0])[i];
+    if (c) atomicAdd(&gh[i], c);
   }
 }
 
