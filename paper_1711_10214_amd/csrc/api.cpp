@@ -281,37 +281,38 @@ struct ashrt_batch_plan {
   PlanImpl impl;
 };
 
-// Time columns per model x-FFT workgroup.  8 columns (32-byte pieces of a
-// trace) give small tiles, so many workgroups and loads in flight: 256 x 64 x 8
-// panels 37 us per operator pair against 45 us at 64 columns, 1024 x 256 x 32
-// 157 against 166 us at 16.  Models that outgrow the last-level cache pay for
-// short pieces in memory traffic and take 16 (1024 x 256 x 384 CG solve 43.7
-// against 46.6 ms; 24 uneven gathers 59.9 against 61.5 ms).  Long transforms
-// take what keeps about 35 KB of LDS per workgroup.
-static int model_tile(int nxp, bool big_model) {
-  const int fit = std::max(2, 2 * (kXfftTilePoints / nxp));
-  return big_model && nxp <= 768 ? 16 : std::max(2, std::min(8, fit) & ~1);
+// Time columns per model x-FFT workgroup, for an x launch of `columns` columns
+// (panels x samples of its gathers).  Short columns take wide tiles, so that a
+// workgroup has a few thousand points to transform, long ones 8 columns (32-byte
+// pieces of a trace), so that many workgroups and loads are in flight; and
+// fewer than 512 workgroups take narrower tiles, down to 8 columns.  Operator
+// pairs, us:
+//   x length, samples x panels    8 columns   16     32     64
+//         96      1024 x 32         115       95     88     84
+//        128      1024 x 32          81       76     75     79
+//        192       512 x 12 (64 gathers)  803  698  683    757
+//        256       512 x 12 (64 gathers)  933  841  876   1002
+//        256      1024 x 32         102      100    104    109
+//        384      1024 x 32         142      152    168    209
+//        512      1024 x 32         152      162    176    214
+//         64       256 x 16          40       39     40     42
+//        192       256 x 16          45       45     51     61
+// Models that outgrow the last-level cache pay for short pieces in memory
+// traffic and take 16 at least (1024 x 256 x 384 CG solve 38.2 against 40.9 ms;
+// 24 uneven gathers 58.3 against 59.5 ms).  Transforms from 1024 points on take
+// what keeps about 35 KB of LDS per workgroup.
+static int model_tile(int nxp, long long columns, bool big_model) {
+  if (nxp > 768) return std::max(2, std::min(8, 2 * (kXfftTilePoints / nxp)));
+  int T = nxp < 128 ? 64 : (nxp < 192 ? 32 : (nxp < 384 ? 16 : 8));
+  while (T > 8 && columns / T < 512) T /= 2;
+  return big_model ? std::max(T, 16) : T;
 }
 
-static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, bool big_model, GatherHost* gh) {
+static int build_gather(const ashrt_desc* d, GatherHost* gh) {
   int st = resolve_desc(d, &gh->z);
   if (st) return st;
   const Resolved& z = gh->z;
   gh->nrows = z.nxp / 2;
-  if (tn && ((tn->tile_model < 0 || (tn->tile_model & 1)) || (tn->tile_data < 0 || (tn->tile_data & 1)) ||
-             tn->nchunk < 0))
-    return fail(ASHRT_E_INVALID_ARG, "tile sizes must be even (or 0) and nchunk >= 0");
-  int T = model_tile(z.nxp, big_model);
-  if (tn && tn->tile_model > 0) T = tn->tile_model;
-  gh->tileT = T;
-  gh->ntiles = (z.nt + T - 1) / T;
-  // the data transform is one panel: narrower tiles give it ~256 workgroups
-  int Td = 2 * ((z.nt + 511) / 512);
-  Td = std::max(2, std::min(T, Td));
-  if (tn && tn->tile_data > 0) Td = tn->tile_data;
-  gh->tileTd = Td;
-  const int Tx = d->x_pos ? kNudftT : Td;
-  gh->ntilesd = (z.nt + Tx - 1) / Tx;
   gh->panels.resize(z.P);
   const double bin = (double)z.ntp * d->dt / ((double)z.nxp * d->dx);
   for (int p = 0; p < z.P; ++p) {
@@ -341,6 +342,35 @@ static int build_gather(const ashrt_desc* d, const ashrt_tuning* tn, bool big_mo
   if (d->wavelet_amp) {
     gh->wav.resize(z.ntp / 2 + 1);
     for (int j = 0; j <= z.ntp / 2; ++j) gh->wav[j] = (float)d->wavelet_amp[j];
+  }
+  return ASHRT_OK;
+}
+
+// Tile widths of every gather, built in or given.
+static int set_tiles(std::vector<GatherHost>& g, const ashrt_tuning* tn) {
+  if (tn && ((tn->tile_model < 0 || (tn->tile_model & 1)) || (tn->tile_data < 0 || (tn->tile_data & 1)) ||
+             tn->nchunk < 0))
+    return fail(ASHRT_E_INVALID_ARG, "tile sizes must be even (or 0) and nchunk >= 0");
+  auto x_key = [](const Resolved& z) { return x_size_is_tpl(z.nxp) ? z.nxp : 0; };
+  std::map<int, long long> columns;  // of each x launch
+  double model_bytes = 0.0;
+  for (const auto& gh : g) {
+    columns[x_key(gh.z)] += (long long)gh.z.P * gh.z.nt;
+    model_bytes += 4.0 * (double)gh.nm();
+  }
+  for (auto& gh : g) {
+    const Resolved& z = gh.z;
+    int T = model_tile(z.nxp, columns[x_key(z)], model_bytes > kCachedModel);
+    if (tn && tn->tile_model > 0) T = tn->tile_model;
+    gh.tileT = T;
+    gh.ntiles = (z.nt + T - 1) / T;
+    // the data transform is one panel: narrower tiles give it ~256 workgroups
+    int Td = 2 * ((z.nt + 511) / 512);
+    Td = std::max(2, std::min(T, Td));
+    if (tn && tn->tile_data > 0) Td = tn->tile_data;
+    gh.tileTd = Td;
+    const int Tx = gh.xpos.empty() ? Td : kNudftT;
+    gh.ntilesd = (z.nt + Tx - 1) / Tx;
   }
   return ASHRT_OK;
 }
@@ -502,13 +532,11 @@ static int create_impl(const ashrt_desc* descs, int ngather, int device, PlanImp
   P.device = device;
   P.ngather = ngather;
   P.g.resize(ngather);
-  double model_bytes = 0.0;
-  for (int i = 0; i < ngather; ++i) model_bytes += 4.0 * descs[i].npanel * (double)descs[i].nx * descs[i].nt;
-  const bool big_model = model_bytes > kCachedModel;
   for (int i = 0; i < ngather; ++i) {
-    int st = build_gather(&descs[i], tn, big_model, &P.g[i]);
+    int st = build_gather(&descs[i], &P.g[i]);
     if (st) return st;
   }
+  if (const int st = set_tiles(P.g, tn)) return st;
   P.R = P.g[0].z.R;
   for (auto& gh : P.g)
     if (gh.z.R != P.R) return fail(ASHRT_E_INVALID_ARG, "all gathers of a batch must share half_width");

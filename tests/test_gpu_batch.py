@@ -275,3 +275,33 @@ def test_small_batches_get_enough_workgroups(A, n, lo, hi, nv):
     t = {c: float(np.median(v)) / 4 for c, v in ms.items()}
     print("  " + " ".join(f"{c or 'built-in'}: {v:.3f} ms" for c, v in t.items()), flush=True)
     assert t[0] <= 1.15 * min(v for c, v in t.items() if c)
+
+
+# Narrow gathers, alone and in batches: an x transform of a few dozen points per
+# column must not leave its workgroups with next to nothing to do.
+@pytest.mark.parametrize("n,nt,nx,nv", [(1, 1024, 24, 32), (1, 1024, 48, 32), (1, 2048, 96, 16), (64, 512, 24, 12),
+                                        (64, 512, 96, 12), (256, 128, 16, 6), (1, 1024, 256, 32)])
+def test_narrow_gathers_get_wide_tiles(A, n, nt, nx, nv):
+    """The built-in model tile is not slower than the best of 8, 16, 32 and 64
+    columns; 12 % allowed for (the rule's worst case 8 %, the clock 4 %)."""
+    import torch
+    print(f"[gpu] model tile of {n} gathers {nt} x {nx}, {nv} velocities", flush=True)
+    vel = list(np.linspace(1400.0, 4000.0, nv))
+    geoms = [geom_kwargs(nt, nx, 0.004, 12.5, vel, fmax=100.0)] * n
+    m, d = torch.randn(n * nv * nx * nt, device="cuda"), torch.randn(n * nx * nt, device="cuda")
+    plans = {c: A.BatchPlan(geoms, tuning={"tile_model": c} if c else None) for c in (0, 8, 16, 32, 64)}
+    ms = {c: [] for c in plans}
+    for rep in range(8):
+        for c, plan in plans.items():
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(8):
+                plan.forward(m)
+                plan.adjoint(d)
+            e1.record()
+            e1.synchronize()
+            if rep:
+                ms[c].append(e0.elapsed_time(e1))
+    t = {c: float(np.median(v)) / 8 for c, v in ms.items()}
+    print("  " + " ".join(f"{c or 'built-in'}: {v:.3f} ms" for c, v in t.items()), flush=True)
+    assert t[0] <= 1.12 * min(v for c, v in t.items() if c)
