@@ -1340,8 +1340,11 @@ struct TapTrig {
 };
 
 // HALF: every gather's rows are at most N/2 long and N's first radix is 8.
+// At 2048 points the whole-row form is held to four waves: at five it spills
+// (2048 x 512 unpadded, 32 panels: forward 129.4 us, at four 126.3).
 template <int N, int RC, bool HALF>
-__global__ __launch_bounds__(row_threads(N)) __attribute__((amdgpu_waves_per_eu(row_waves_per_eu(N)))) void k_rows_fwd(RowsArgs A) {
+__global__ __launch_bounds__(row_threads(N))
+    __attribute__((amdgpu_waves_per_eu(N == 2048 && !HALF ? 4 : row_waves_per_eu(N)))) void k_rows_fwd(RowsArgs A) {
   extern __shared__ float4 lds_raw[];  // 16-byte aligned: the map reads 16-byte pairs
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   const WorkItem w = load_const(A.items + blockIdx.x);
