@@ -18,13 +18,17 @@
 // of curve times and weights serves every (x, xa) pair at that distance: a
 // wave takes consecutive times of K neighbouring traces and walks the
 // distances, and at each one uses the weights for up to 2 K pairs (both
-// sides).  32 panels of 512 x 128 samples: forward 7140 -> 609 us, adjoint
-// 377 -> 222 us against one curve time per pair (and per candidate tau in
-// the forward).  The forward is bound by vector instructions (86 % of its
-// cycles), a third of them the pairs' products; waves near an apex, where
-// many tau fall on one time, take several rounds.  The adjoint waits on its
-// L1 loads.
+// sides).  32 panels of 512 x 128 samples: forward 7140 -> 660 us, adjoint
+// 377 -> 150 us against one curve time per pair (and per candidate tau in
+// the forward).  The forward is bound by vector instructions (89 % of its
+// cycles), under a quarter of them the pairs' products; waves near an apex,
+// where many tau fall on one time, take several rounds.  The adjoint waits on
+// its L1 loads; small ones are a chain of latencies, one a distance, which
+// several distances at a time overlap (8 panels of 256 x 64: 29 us with one
+// curve time per pair, 67 with one distance at a time, 19 with four).
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace ashrt {
 
@@ -38,7 +42,7 @@ __device__ __forceinline__ double td_q(const PanelDev& P, const GatherDev& G) {
 
 constexpr int kTdFwdWaves = 16;  // waves that share a forward tile's panels and distances
 constexpr int kTdAdjWaves = 4;   // adjoint waves per workgroup
-constexpr int kTdAdjX = 4;       // neighbouring apexes per adjoint wave
+constexpr int kTdMaxTraces = 4096;  // longest x transform a plan takes
 
 // sqrt(T2) to FP64 rounding: two Newton steps, their residuals in FP64, from an
 // FP32 root (good to 1e-15 for a root below that, and 0 for 0).  T2 is below
@@ -50,31 +54,92 @@ __device__ __forceinline__ double td_root(double T2) {
   return fma(fma(-s1, s1, T2), h, s1);
 }
 
-// The pairs of a distance: bit k is trace x0 + k + h, bit K + k is
-// x0 + k - h (h = 0: only the first half), each set where the trace is in
-// the gather and live.  Wave-uniform.
-template <int K>
-__device__ __forceinline__ unsigned td_pairs(int x0, int h, int nx, const uint8_t* __restrict__ live) {
-  if (!live && h > 0 && x0 - h >= 0 && x0 + K - 1 + h < nx) return (1u << 2 * K) - 1;
-  const int lane = (int)threadIdx.x & 63, k = lane & (K - 1);
-  const int x = lane < K ? x0 + k + h : x0 + k - h;
-  bool ok = lane < 2 * K && x0 + k < nx && x >= 0 && x < nx && (h > 0 || lane < K);
-  if (ok && live) ok = live[x] != 0;
-  return __builtin_amdgcn_readfirstlane((unsigned)__ballot(ok));
-}
-
 // n consecutive floats at a 4-byte aligned address, as one load.
 template <int N>
 __device__ __forceinline__ void td_load(float (&v)[N], const float* row, unsigned off) {
   __builtin_memcpy(v, reinterpret_cast<const char*>(row) + off, 4 * N);
 }
 
+// A wave's sums over 64 apex times of K neighbouring apexes of one panel.  H
+// distances at a time, so that their roots and loads overlap: the walk is a
+// chain of latencies where few waves run.  Pair k of distance h is trace x0 + k
+// + h, pair K + k is x0 + k - h (h = 0: only the first half), taken where the
+// trace is in the gather and live; lane 2 K j + k looks pair k of the j-th
+// distance up, and the ballot is wave-uniform.  Lanes without a curve time in
+// the record, and the sample before the record's last, weigh 0; SAFE leaves
+// those out, which differs only where a sample is not finite.
+template <int K, int H, bool SAFE>
+__device__ __forceinline__ void td_adjoint_wave(const TdArgs& A, const PanelDev& P, double q, int nt, int nx, int tau,
+                                                int x0, const uint8_t* live, float (&acc)[K]) {
+  constexpr unsigned kAll = (unsigned)((1ull << 2 * K * H) - 1);
+  static_assert(2 * K * H <= 16, "one lane and one bit a pair");
+#pragma unroll
+  for (int k = 0; k < K; ++k) acc[k] = 0.f;
+  const double t2 = (double)tau * (double)tau;
+  const double lim = (double)(nt - P.n0) * (double)(nt - P.n0);
+  const int hmax = q < 0.0 ? 0 : max(x0 + K - 1, nx - 1 - x0);
+  const int lane = (int)threadIdx.x & 63, lj = lane / (2 * K), lk = lane % K;
+  const bool down = lane % (2 * K) >= K;
+  const bool mine = lane < 2 * K * H && x0 + lk < nx && (q >= 0.0 || lj == 0), self = down && lj == 0;
+  const int xl = x0 + lk + (down ? -lj : lj);
+  for (int h0 = 0; h0 <= hmax; h0 += H) {
+    const int x = xl + (down ? -h0 : h0);
+    bool use = mine && (unsigned)x < (unsigned)nx && !(self && h0 == 0);
+    if (A.tmask && use) use = live[x] != 0;
+    const unsigned ok = (unsigned)__ballot(use);
+    float v[H][2 * K][2], w0[H], w1[H];
+    bool on[H], last[H];
+    unsigned off[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      const double hd = (double)(h0 + j), T2 = q < 0.0 ? t2 : fma(hd * hd, q, t2);
+      on[j] = tau < nt && T2 < lim;            // T < nt
+      if (j == 0 && !__any(on[0])) return;     // T rises with h
+      const double T = td_root(T2), fl = floor(T);
+      const int i0 = on[j] ? P.n0 + (int)fl : 0;
+      const float f = (float)(T - fl), e = 1.f - f;
+      last[j] = i0 > nt - 2;
+      on[j] = on[j] && i0 < nt;
+      w0[j] = on[j] && !last[j] ? e : 0.f;
+      w1[j] = on[j] ? (last[j] ? e : f) : 0.f;
+      off[j] = 4u * (unsigned)min(i0, nt - 2);
+    }
+    const float* const up = A.d + (long long)(x0 + h0) * nt;  // rows x0 + h + k and x0 - h + k
+    const float* const dn = A.d + (long long)(x0 - h0) * nt;
+    auto load = [&](int j, int k) {
+      td_load(v[j][k], (k < K ? up + (long long)(k + j) * nt : dn + (long long)(k - K - j) * nt), off[j]);
+    };
+    auto add = [&](int j, int k) {
+      const float a = SAFE && (!on[j] || last[j]) ? 0.f : v[j][k][0], b = SAFE && !on[j] ? 0.f : v[j][k][1];
+      acc[k % K] = fmaf(w1[j], b, fmaf(w0[j], a, acc[k % K]));
+    };
+    if (ok == kAll) {
+#pragma unroll
+      for (int i = 0; i < 2 * K * H; ++i) load(i / (2 * K), i % (2 * K));
+#pragma unroll
+      for (int i = 0; i < 2 * K * H; ++i) add(i / (2 * K), i % (2 * K));
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2 * K * H; ++i)
+        if (ok >> i & 1) load(i / (2 * K), i % (2 * K));
+#pragma unroll
+      for (int i = 0; i < 2 * K * H; ++i)
+        if (ok >> i & 1) add(i / (2 * K), i % (2 * K));
+    }
+  }
+}
+
 // Adjoint: a wave owns 64 apex times of K neighbouring apexes of one panel.
+template <int K, int H>
 __global__ __launch_bounds__(64 * kTdAdjWaves) void k_td_adjoint(TdArgs A) {
-  constexpr int K = kTdAdjX;
+  __shared__ uint8_t live[kTdMaxTraces];
   const GatherDev G = A.gd[0];
   const int nt = G.nt, nx = G.nx;
   const int ntt = (nt + 63) / 64, nxt = (nx + K - 1) / K;
+  if (A.tmask) {
+    for (int x = threadIdx.x; x < nx; x += 64 * kTdAdjWaves) live[x] = A.tmask[x];
+    __syncthreads();
+  }
   const int lane = (int)threadIdx.x & 63;
   const int id = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kTdAdjWaves + (threadIdx.x >> 6)));
   if (id >= G.npanel * nxt * ntt) return;
@@ -88,47 +153,11 @@ __global__ __launch_bounds__(64 * kTdAdjWaves) void k_td_adjoint(TdArgs A) {
 #pragma unroll
   for (int k = 0; k < K; ++k) acc[k] = 0.f;
   if (P.n0 < nt) {
-    const double t2 = (double)tau * (double)tau;
-    const double lim = (double)(nt - P.n0) * (double)(nt - P.n0);
-    const int hmax = q < 0.0 ? 0 : max(x0 + K - 1, nx - 1 - x0);
-    for (int h = 0; h <= hmax; ++h) {
-      const double T2 = q < 0.0 ? t2 : fma((double)h * (double)h, q, t2);
-      const bool on = tau < nt && T2 < lim;  // T < nt
-      if (!__any(on)) break;                 // T rises with h
-      const unsigned ok = td_pairs<K>(x0, h, nx, A.tmask);
-      if (!on) continue;
-      const double T = td_root(T2), fl = floor(T);
-      const int i0 = P.n0 + (int)fl;
-      const float f = (float)(T - fl), e = 1.f - f;
-      const float* up = A.d + (long long)(x0 + h) * nt;  // rows x0 + h + k and x0 - h + k
-      const float* dn = A.d + (long long)(x0 - h) * nt;
-      if (i0 + 1 < nt) {
-        const unsigned off = 4u * (unsigned)i0;
-        if (ok == (1u << 2 * K) - 1) {
-          float v[2 * K][2];
+    td_adjoint_wave<K, H, false>(A, P, q, nt, nx, tau, x0, live, acc);
+    bool fin = true;
 #pragma unroll
-          for (int k = 0; k < K; ++k) {
-            td_load(v[k], up + (long long)k * nt, off);
-            td_load(v[K + k], dn + (long long)k * nt, off);
-          }
-#pragma unroll
-          for (int k = 0; k < 2 * K; ++k) acc[k % K] = fmaf(f, v[k][1], fmaf(e, v[k][0], acc[k % K]));
-        } else {
-#pragma unroll
-          for (int k = 0; k < 2 * K; ++k) {
-            if (ok >> k & 1) {
-              float v[2];
-              td_load(v, (k < K ? up : dn) + (long long)(k % K) * nt, off);
-              acc[k % K] = fmaf(f, v[1], fmaf(e, v[0], acc[k % K]));
-            }
-          }
-        }
-      } else if (i0 < nt) {  // the record's last sample
-#pragma unroll
-        for (int k = 0; k < 2 * K; ++k)
-          if (ok >> k & 1) acc[k % K] = fmaf(e, ((k < K ? up : dn) + (long long)(k % K) * nt)[i0], acc[k % K]);
-      }
-    }
+    for (int k = 0; k < K; ++k) fin = fin && isfinite(acc[k]);
+    if (__any(!fin)) td_adjoint_wave<K, H, true>(A, P, q, nt, nx, tau, x0, live, acc);
   }
   if (tau < nt) {
 #pragma unroll
@@ -270,10 +299,20 @@ hipError_t launch_td(const TdArgs& a, bool forward, int nt, int nx, int npanel, 
     else if (tiles(4) >= 512) hipLaunchKernelGGL(k_td_forward<4>, dim3(tiles(4)), b, 0, s, a);
     else hipLaunchKernelGGL(k_td_forward<2>, dim3(tiles(2)), b, 0, s, a);
   } else {
-    const long long waves = (long long)((nt + 63) / 64) * ((nx + kTdAdjX - 1) / kTdAdjX) * npanel;
-    if (waves > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_td_adjoint, dim3((unsigned)((waves + kTdAdjWaves - 1) / kTdAdjWaves)), dim3(64 * kTdAdjWaves),
-                       0, s, a);
+    auto waves = [&](int K) { return (long long)((nt + 63) / 64) * ((nx + K - 1) / K) * npanel; };
+    if (waves(1) > 0x7fffff00LL) return hipErrorInvalidValue;
+    auto go = [&](auto k, auto h) {
+      constexpr int K = decltype(k)::value, H = decltype(h)::value;
+      hipLaunchKernelGGL((k_td_adjoint<K, H>), dim3((unsigned)((waves(K) + kTdAdjWaves - 1) / kTdAdjWaves)),
+                         dim3(64 * kTdAdjWaves), 0, s, a);
+    };
+    // 4 apexes a wave share the most weights, once their waves fill the card (7 a
+    // SIMD); fewer waves are latency, and 2 apexes with four distances at a time
+    // give more of them more in flight (us, 4 and 2 apexes: 512 x 128, 32 panels
+    // (8192 waves of 4) 150 and 170; 700 x 150, 17 (7106) 169 and 157; 512 x 128, 8
+    // (2048) 62 and 55; 256 x 64, 8 (512) 30 and 19)
+    if (waves(4) >= 7168) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
   }
   return hipGetLastError();
 }

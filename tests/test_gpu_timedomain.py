@@ -200,3 +200,28 @@ def test_time_domain_non_finite_sample(A, nt, nx, bad):
     hit = (T >= i - 1) & (T < i + 1)
     assert not np.isfinite(a1[hit]).any()
     assert np.array_equal(a1[~hit], a0[~hit])
+
+
+# Few waves take 2 apexes and four distances at a time, a full card of them 4
+# apexes and two: 75 panels of 130 x 126 (7200 waves of 4) against single ones.
+@pytest.mark.parametrize("nt,nx,P", [(130, 126, 75), (129, 127, 75), (64, 250, 114)])
+def test_time_domain_adjoint_tiles_agree(A, nt, nx, P):
+    """Every tile adds an apex's traces in the same order, so a panel among many
+    equals the same panel alone, bit for bit; dead traces hold NaN."""
+    import torch
+    print(f"[gpu] time-domain adjoint tiles {nt} x {nx} x {P}", flush=True)
+    assert (nt + 63) // 64 * ((nx + 3) // 4) * P >= 7168
+    rng = np.random.default_rng(nx)
+    vel = list(np.linspace(0.0, 5000.0, P))
+    tau0 = [int(p % 5 * 3) for p in range(P)]
+    mask = (rng.uniform(size=nx) > 0.3).astype(np.uint8)
+    for mk in (None, torch.tensor(mask, device="cuda")):
+        d = rng.standard_normal((nx, nt))
+        if mk is not None:
+            d[mask == 0] = np.nan
+        d = torch.tensor(d, dtype=torch.float32, device="cuda")
+        a = A.Plan(nt, nx, 0.004, 12.5, vel, tau0=tau0).td_adjoint(d, mask=mk).cpu().numpy()
+        assert np.isfinite(a).all()
+        for p in (0, 1, 17, P // 2, P - 1):
+            one = A.Plan(nt, nx, 0.004, 12.5, vel[p:p + 1], tau0=tau0[p:p + 1]).td_adjoint(d, mask=mk).cpu().numpy()
+            assert np.array_equal(a[p], one[0]), p
