@@ -14,17 +14,19 @@
 // consecutive samples with one 16-byte access each way (firing times and odd
 // sizes leave them at 4-byte alignment, which the hardware takes), and its
 // indices need one 32-bit division.  Blending first lists the sources whose
-// shots reach the workgroup's stretch of the record, a handful, instead of
-// testing every source at every sample.  128 x 128 x 1024: blending 247 ->
-// 28 us, pseudo-deblending 41 -> 20 us, re-sorting 37 -> 19 us (3.4, 5 and 7 TB/s).
+// shots reach the wave's stretch of the record, a handful, instead of testing
+// every source at every sample, and keeps the loads of several in flight (many
+// shots over every sample, 200 x 200 x 128 fired 5 samples apart: 24 us with every
+// source tested, 76 with one listed source at a time, 12).  128 x 128 x 1024:
+// blending 247 -> 25 us, pseudo-deblending 41 -> 20 us, re-sorting 37 -> 19 us
+// (4, 5 and 7 TB/s).
 #include "kernels.h"
 
 #include <algorithm>
 
 namespace ashrt {
 
-constexpr int kBlendTile = 4 * kThreads;  // record samples per workgroup
-constexpr int kBlendList = 1024;          // sources tested at a time
+constexpr int kBlendList = 512;           // sources tested at a time
 constexpr int kBlendRows = 8;             // most receivers per workgroup
 
 __device__ __forceinline__ float4 load4(const float* p) {
@@ -34,70 +36,84 @@ __device__ __forceinline__ float4 load4(const float* p) {
 }
 __device__ __forceinline__ void store4(float* p, float4 v) { __builtin_memcpy(p, &v, 16); }
 
+// Adds the n listed sources' samples to a thread's Q record samples, in list
+// order, the loads of U sources in flight.  (A source that does not reach a
+// sample adds zero, which leaves the sum as it is.)
+template <int Q, int U>
+__device__ __forceinline__ void blend_add(float (&acc)[Q], const float* __restrict__ D, int r, int nr, int nt, int tau,
+                                          const int* src, const int* at, int n) {
+  for (int i = 0; i < n; i += U) {
+    float v[U][Q];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = min(i + u, n - 1), t = i + u < n ? tau - at[e] : nt;
+      const float* __restrict__ d = D + ((long long)src[e] * nr + r) * nt + t;
+#pragma unroll
+      for (int k = 0; k < Q; ++k) v[u][k] = 0.f;
+      if (Q == 4 && t >= 0 && t + 4 <= nt) {
+        __builtin_memcpy(v[u], d, 4 * Q);
+      } else if (t > -Q && t < nt) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k)
+          if (t + k >= 0 && t + k < nt) v[u][k] = d[k];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < Q; ++k) acc[k] += v[u][k];
+  }
+}
+
+// A wave owns 64 Q record samples of its receivers and lists the sources whose
+// shots reach them.
+template <int Q, int U>
 __global__ __launch_bounds__(kThreads) void k_blend(const float* __restrict__ D, int ns, int nr, int nt,
                                                    const int* __restrict__ fire, float* __restrict__ b, int nrec,
                                                    int rows) {
-  __shared__ int src[kBlendList], at[kBlendList];
-  __shared__ int wsum[kThreads / 64];
-  const int lo = (int)blockIdx.x * kBlendTile, hi = min(nrec - lo, kBlendTile);  // samples lo .. lo + hi - 1
-  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-  const int left = hi - 4 * (int)threadIdx.x;  // of the thread's samples tau, tau + 1, ...
-  const int tau = lo + (left > 0 ? 4 * (int)threadIdx.x : 0);
+  constexpr int kWave = 64 * Q, kWaves = kThreads / 64;
+  __shared__ int lists[kWaves][2][kBlendList];
+  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int *const src = lists[wave][0], *const at = lists[wave][1];
+  const long long lo = ((long long)blockIdx.x * kWaves + wave) * kWave, hi = min(nrec - lo, (long long)kWave);
+  if (hi <= 0) return;                     // samples lo .. lo + hi - 1
+  const int left = (int)hi - Q * lane;     // of the lane's samples tau, tau + 1, ...
+  const int tau = (int)lo + (left > 0 ? Q * lane : 0);
   for (int s0 = 0; s0 < ns; s0 += kBlendList) {
-    // the sources s0 .. s0 + kBlendList - 1 that reach the tile, in index order
-    int n = 0;
-    for (int c = s0; c < min(ns, s0 + kBlendList); c += kThreads) {
-      const int s = c + (int)threadIdx.x;
-      const int f = s < ns ? fire[s] : 0;
-      const bool in = s < min(ns, s0 + kBlendList) &&
-                      (long long)f < (long long)lo + hi && (long long)f + nt > (long long)lo;
+    // of the sources s0 .. s0 + kBlendList - 1, in index order
+    int f[kBlendList / 64], n = 0;
+#pragma unroll
+    for (int u = 0; u < kBlendList / 64; ++u) f[u] = fire[min(s0 + 64 * u + lane, ns - 1)];
+#pragma unroll
+    for (int u = 0; u < kBlendList / 64; ++u) {
+      const int s = s0 + 64 * u + lane;
+      const bool in = s < ns && f[u] < lo + hi && (long long)f[u] + nt > lo;
       const unsigned long long m = __ballot(in);
-      if (lane == 0) wsum[wave] = __popcll(m);
-      __syncthreads();
-      int off = n + __popcll(m & ((1ull << lane) - 1));
-      int all = 0;
-      for (int w = 0; w < kThreads / 64; ++w) {
-        if (w < wave) off += wsum[w];
-        all += wsum[w];
-      }
       if (in) {
+        const int off = n + __popcll(m & ((1ull << lane) - 1));
         src[off] = s;
-        at[off] = f;
+        at[off] = f[u];
       }
-      n += all;
-      __syncthreads();
+      n += __popcll(m);
     }
-    for (int rb = (int)blockIdx.y; left > 0 && rb * rows < nr; rb += gridDim.y)
-    for (int r = rb * rows; r < min(nr, (rb + 1) * rows); ++r) {
-      float* __restrict__ out = b + (long long)r * nrec + tau;
-      if (left >= 4) {
-        float4 acc = s0 ? load4(out) : make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int i = 0; i < n; ++i) {
-          const int t = tau - at[i];
-          const float* __restrict__ d = D + ((long long)src[i] * nr + r) * nt + t;
-          if (t >= 0 && t + 4 <= nt) {
-            const float4 v = load4(d);
-            acc = make_float4(acc.x + v.x, acc.y + v.y, acc.z + v.z, acc.w + v.w);
-          } else if (t > -4 && t < nt) {
-            if (t >= 0) acc.x += d[0];
-            if (t + 1 >= 0 && t + 1 < nt) acc.y += d[1];
-            if (t + 2 >= 0 && t + 2 < nt) acc.z += d[2];
-            if (t + 3 >= 0 && t + 3 < nt) acc.w += d[3];
-          }
-        }
-        store4(out, acc);
-      } else {
-        for (int k = 0; k < left; ++k) {
-          float acc = s0 ? out[k] : 0.f;
-          for (int i = 0; i < n; ++i) {
-            const int t = tau + k - at[i];
-            if (t >= 0 && t < nt) acc += D[((long long)src[i] * nr + r) * nt + t];
-          }
-          out[k] = acc;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int rb = (int)blockIdx.y; left > 0 && rb * rows < nr; rb += gridDim.y) {
+      for (int r = rb * rows; r < min(nr, (rb + 1) * rows); ++r) {
+        float* __restrict__ out = b + (long long)r * nrec + tau;
+        float acc[Q];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) acc[k] = s0 && k < left ? out[k] : 0.f;
+        blend_add<Q, U>(acc, D, r, nr, nt, tau, src, at, n);
+        if (left >= Q) {
+          __builtin_memcpy(out, acc, 4 * Q);
+        } else {
+#pragma unroll
+          for (int k = 0; k < Q; ++k)
+            if (k < left) out[k] = acc[k];
         }
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 
@@ -162,11 +178,15 @@ static hipError_t quad_launch(int nj, int nt, int no, F&& f) {
 }
 
 hipError_t launch_blend(const float* D, int ns, int nr, int nt, const int* fire, float* b, int nrec, hipStream_t s) {
-  // receivers share a workgroup's source list while enough workgroups remain
-  const long long tiles = (nrec + (long long)kBlendTile - 1) / kBlendTile;
-  const int rows = (int)std::max(1LL, std::min<long long>(kBlendRows, tiles * nr / 1024));
-  hipLaunchKernelGGL(k_blend, dim3((unsigned)tiles, (unsigned)std::min((nr - 1) / rows + 1, 65535)), dim3(kThreads), 0, s,
-                     D, ns, nr, nt, fire, b, nrec, rows);
+  // four samples a thread once that gives 1024 workgroups, else one; receivers
+  // share a workgroup's source list while enough workgroups remain
+  auto tiles = [&](int q) { return ((long long)nrec + q * kThreads - 1) / (q * kThreads); };
+  const bool wide = tiles(4) * nr >= 1024;
+  const long long n = tiles(wide ? 4 : 1);
+  const int rows = (int)std::max(1LL, std::min<long long>(kBlendRows, n * nr / 1024));
+  const dim3 grid((unsigned)n, (unsigned)std::min((nr - 1) / rows + 1, 65535));
+  if (wide) hipLaunchKernelGGL((k_blend<4, 4>), grid, dim3(kThreads), 0, s, D, ns, nr, nt, fire, b, nrec, rows);
+  else hipLaunchKernelGGL((k_blend<1, 8>), grid, dim3(kThreads), 0, s, D, ns, nr, nt, fire, b, nrec, rows);
   return hipGetLastError();
 }
 

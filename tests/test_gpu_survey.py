@@ -65,12 +65,14 @@ def test_survey_separation_matches_oracle(A):
     assert q_sep > q_pd
 
 
-# Edges of the kernels' tiles: 4 samples per thread, 1024 record samples per
-# workgroup, 1024 sources tested at a time; shots that start together, out of
-# order, and past the record.
+# Edges of the kernels' tiles: 1 or 4 samples per thread, 256 or 1024 record
+# samples per workgroup, 512 sources tested at a time; shots that start together,
+# out of order, and past the record.
 SURVEY_EDGES = [(1, 1, 1, 1), (3, 2, 3, 5), (5, 9, 7, 40), (4, 8, 1024, 1023), (6, 3, 130, 1025), (1030, 2, 5, 2051)]
+# Many shots over every sample, one and four samples per thread.
+SURVEY_EDGES += [(70, 3, 33, 40), (515, 5, 300, 700), (40, 600, 300, 2048), (3, 1000, 5, 1000)]
 # Several receivers per workgroup (a 1024th of receivers x record tiles, at most
-# 8), the last workgroup short: 2, 3, 4 and 8; 4 with two lists of sources.
+# 8), the last workgroup short: 2, 3, 4 and 8; 4 with three lists of sources.
 SURVEY_EDGES += [(2, 2049, 6, 900), (4, 1601, 9, 1100), (3, 2051, 7, 1025), (2, 4099, 5, 1030), (1025, 2050, 2, 1026)]
 
 
