@@ -21,6 +21,7 @@ import argparse
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -37,29 +38,35 @@ FP32_UNPACKED_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 # HBM bytes per launch of the row kernels on the production gather, by the
 # plan's panel-chunk count (which sets their grid), from rocprofv3 --pmc
 # FETCH_SIZE and --pmc WRITE_SIZE (KiB per dispatch) scaled by what the
-# counters read for a 512 MiB device copy (reads x 2.0, writes x 1.0); valid
-# only for the kernel sources with this digest.
+# counters read for 512 MiB and 4 GiB device copies (reads x 2.0, writes x
+# 1.0); valid only for the kernel code with this digest (recount after any
+# change of it; comments do not count).
 _MIB = 1024.0 * 1024.0
 MEASURED_TRAFFIC = {
-    "digest": "161009b65f243d4a",
+    "digest": "89f8724089e9e2e5",
     "workload": "crg-1024x256-nv32",
     "bytes": {
         # nchunk -> read + write
-        "k_rows_fwd": {1: (56.15 + 3.20) * _MIB, 2: (56.19 + 6.41) * _MIB, 4: (56.27 + 12.81) * _MIB,
-                       8: (56.45 + 25.60) * _MIB},
-        "k_rows_adj": {1: (2.32 + 55.92) * _MIB, 2: (4.36 + 55.92) * _MIB, 4: (8.45 + 55.92) * _MIB,
-                       8: (16.67 + 55.92) * _MIB},
+        "k_rows_fwd": {1: (56.18 + 3.20) * _MIB, 2: (56.21 + 6.41) * _MIB, 4: (56.28 + 12.81) * _MIB,
+                       8: (56.48 + 25.59) * _MIB},
+        "k_rows_adj": {1: (2.33 + 55.92) * _MIB, 2: (4.37 + 55.92) * _MIB, 4: (8.45 + 55.92) * _MIB,
+                       8: (16.66 + 55.92) * _MIB},
     },
 }
 _KERNEL_SOURCES = ["ashrt_internal.h", "block_reduce.h", "fft_lds.h", "fft_tpl.h", "kernels.h", "op_kernels.hip"]
+
+
+def _code_only(text):
+    """C++ source without comments, one space for each run of white space."""
+    return " ".join(re.sub(r"//[^\n]*|/\*.*?\*/", " ", text, flags=re.S).split())
 
 
 def _kernel_digest():
     import hashlib
     h = hashlib.sha256()
     for f in _KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_1711_10214_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
+        with open(os.path.join(ROOT, "paper_1711_10214_amd", "csrc", f), encoding="utf-8") as fh:
+            h.update(_code_only(fh.read()).encode())
     return h.hexdigest()[:16]
 
 

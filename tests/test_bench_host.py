@@ -65,3 +65,19 @@ def test_row_kernel_bytes_match_a_direct_count(bench):
     adj_bytes, _ = nums["k_rows_adj"]
     assert fwd_bytes == pytest.approx(x_live + partials, rel=1e-12)
     assert adj_bytes == pytest.approx(data_spec + x_live, rel=1e-12)
+
+
+def test_traffic_digest_covers_code_and_not_comments(bench, tmp_path, monkeypatch):
+    """Counted traffic belongs to the kernel code it was counted on: a change of
+    code makes the bench report none, a change of comments does not."""
+    csrc = tmp_path / "paper_1711_10214_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    for f in bench._KERNEL_SOURCES:
+        (csrc / f).write_text("int a;  // first\n/* block\n */ int b;\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    d = bench._kernel_digest()
+    (csrc / bench._KERNEL_SOURCES[0]).write_text("int a;\n\n// second\nint b;\n")
+    assert bench._kernel_digest() == d
+    (csrc / bench._KERNEL_SOURCES[0]).write_text("int a;\nint c;\n")
+    assert bench._kernel_digest() != d
+    assert bench._measured_traffic(bench.MEASURED_TRAFFIC["workload"], "k_rows_adj", 4) is None
