@@ -22,9 +22,9 @@
 // 377 -> 150 us against one curve time per pair (and per candidate tau in
 // the forward).  The forward is bound by vector instructions (89 % of its
 // cycles), under a quarter of them the pairs' products; waves near an apex,
-// where many tau fall on one time, take several rounds.  The adjoint waits on
-// its L1 loads; small ones are a chain of latencies, one a distance, which
-// several distances at a time overlap (8 panels of 256 x 64: 29 us with one
+// where many tau fall on one time, take several rounds.  The adjoint has one
+// issued 72 % of its cycles; small ones are a chain of latencies, one a distance,
+// which several distances at a time overlap (8 panels of 256 x 64: 29 us with one
 // curve time per pair, 67 with one distance at a time, 19 with four).
 #include "kernels.h"
 
