@@ -465,11 +465,12 @@ static std::vector<float> row_costs(const GatherHost& gh) {
 // Launch order of the row passes' work items, heavy first: rows differ by
 // more than 3x in work, and a launch of many rounds ends with the light ones
 // (24 uneven gathers: 5 % of the solve).  A launch whose workgroups are all
-// resident at once is dealt instead so that each CU gets the same sum: the hardware deals consecutive workgroups to the
-// 8 XCDs and their 32 CUs in turn, so items kCus apart meet on one CU, and
-// every second run of kCus items is reversed.  On the 1024 x 256, 32-panel
-// gather the last CU then ends 43.2 instead of 45.4 us after the first
-// starts in the forward pass, 58.6 instead of 60.9 in the adjoint.
+// resident at once is dealt instead so that each CU gets the same sum: the
+// hardware deals consecutive workgroups to the 8 XCDs and their 32 CUs in turn,
+// so items kCus apart meet on one CU, and every second run of kCus items is
+// reversed.  On the 1024 x 256, 32-panel gather the last CU then ends 43.2
+// instead of 45.4 us after the first starts in the forward pass, 58.6 instead
+// of 60.9 in the adjoint.
 static void order_row_items(std::vector<WorkItem>& items, const PlanImpl::Seg& sg,
                             const std::vector<std::vector<float>>& cost, int resident) {
   const auto b = items.begin() + sg.first;
